@@ -265,8 +265,8 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void *const *args, double po
 
 /* ------------------------------------------------------------------ prefix scan */
 
-/* Bytes of device workspace hipmr_scan needs (two tables of at most 65536
- * wave totals of the result type); 0 for an elementwise or invalid handle. */
+/* Bytes of device workspace hipmr_scan needs (the totals of at least 64000
+ * tiles, more above 2^30 elements); 0 for an elementwise or invalid handle. */
 size_t hipmr_scan_workspace_bytes(hipmr_handle h, int64_t n);
 
 /* Prefix scan of a map: the parallel prefix sums of section "Further
@@ -280,9 +280,11 @@ size_t hipmr_scan_workspace_bytes(hipmr_handle h, int64_t n);
  *               overlap the inputs.
  *   workspace:  at least hipmr_scan_workspace_bytes(h, n) bytes (caller-owned).
  *   cfg:        NULL or a geometry (block, items_per_thread, vec, flags).
- * Three launches on `stream`: every wave folds a contiguous range, one block
- * scans the wave totals, every wave rescans its range from its prefix.  The
- * order of combination depends only on n, alignment and geometry (bitwise
+ * At most two launches on `stream`, by size: one tile alone; tile totals and
+ * a rescan from them; or a clear of the workspace's counters and one pass in
+ * which tiles publish their totals and wait for their predecessors'.  The
+ * workspace belongs to one call at a time.  The order of combination depends
+ * only on n, alignment and geometry (bitwise
  * repeatable).  Chunked accesses when every array and out share one
  * alignment and the map reads arrays only as name[i] (by default 16 bytes of
  * the narrowest input, but at most 16 bytes of output, per lane); one

@@ -70,7 +70,7 @@ std::string spec_key(const KernelSpec& s) {
            std::to_string(s.block) + "|" + std::to_string(s.ipt) + "|" + std::to_string(s.vec) +
            "|" + std::to_string(s.nt_loads) + std::to_string(s.nt_stores) + "|" +
            std::to_string(s.square) + std::to_string(s.scaled) + std::to_string(s.exact_runs) +
-           std::to_string(s.norm) + "|" + std::to_string(s.lds_segs) + "|" + s.combine + "\x1f" +
+           std::to_string(s.norm) + std::to_string(s.scan_mode) + "|" + std::to_string(s.lds_segs) + "|" + s.combine + "\x1f" +
            s.neutral;
 }
 
@@ -780,21 +780,23 @@ hipmr_status hipmr_selftest_compile(int32_t* count) {
                 }
             }
             if (st == HIPMR_OK) {
-                // prefix scan: wave totals, their scan, the rescan (vector and scalar)
-                for (KernelKind k : {KernelKind::ScanUpVector, KernelKind::ScanUpScalar, KernelKind::ScanMid,
-                                     KernelKind::ScanDownVector, KernelKind::ScanDownScalar}) {
-                    const bool vk = k == KernelKind::ScanUpVector || k == KernelKind::ScanDownVector;
-                    if (vk && !h->prog.info.vectorizable) continue;
-                    KernelSpec q;
-                    q.kind = k;
-                    q.block = k == KernelKind::ScanMid ? 1024 : 256;
-                    q.ipt = k == KernelKind::ScanMid ? 1 : 4;
-                    q.vec = vk ? h->default_vec : 1;
-                    q.combine = c.combine;
-                    q.neutral = c.neutral;
-                    st = get_variant(h, q, &co);
+                // prefix scan: every mode of the tile kernel (vector and scalar)
+                for (KernelKind k : {KernelKind::ScanVector, KernelKind::ScanScalar, KernelKind::ScanClear}) {
+                    if (k == KernelKind::ScanVector && !h->prog.info.vectorizable) continue;
+                    const int modes = k == KernelKind::ScanClear ? 1 : 4;
+                    for (int mode = 0; mode < modes && st == HIPMR_OK; ++mode) {
+                        KernelSpec q;
+                        q.kind = k;
+                        q.scan_mode = mode;
+                        q.vec = k == KernelKind::ScanVector ? h->default_vec : 1;
+                        if (k != KernelKind::ScanClear) {
+                            q.combine = c.combine;
+                            q.neutral = c.neutral;
+                        }
+                        st = get_variant(h, q, &co);
+                        ++built;
+                    }
                     if (st != HIPMR_OK) break;
-                    ++built;
                 }
             }
             if (st == HIPMR_OK && h->prog.sig.result == DT_F32) {

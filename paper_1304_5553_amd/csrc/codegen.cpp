@@ -1197,14 +1197,6 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 }
 )HIP";
 
-// ------------------------------------------------------------ prefix scan
-// Reduce-then-scan over a fixed partition: wave w owns the elements
-// [head + w C, head + (w + 1) C) (wave 0 also the unaligned head [0, head)),
-// C = P passes x U sub-tiles x 64 lanes x V elements; lane l owns the V
-// consecutive elements at 64 V u + V l of each sub-tile.  Pass 1 folds each
-// wave's range; pass 2 (one block) scans the wave totals; pass 3 rescans each
-// range from its wave prefix.  The order of every combination is a fixed
-// function of n and the geometry.
 // Data-parallel-primitive (DPP) lane moves and the inclusive wave scan built
 // from them (shared by the segmented and scan kernels).
 const char* kDppHelpers = R"HIP(
@@ -1241,228 +1233,283 @@ __device__ __forceinline__ T hipmr_dpp_scan(T v, T e, Op op) {
 }
 )HIP";
 
+// ------------------------------------------------------------ prefix scan
+// The array is cut into tiles of B threads x U sub-tiles x V elements; wave w
+// of a tile owns U consecutive sub-tiles of 64 V elements, lane l the V
+// consecutive elements at V l of each.  A tile stays in registers between
+// its load and its stores.  What the tile needs from outside is the fold of
+// everything before it; MODE says where that comes from:
+//   0  nothing precedes it (one tile in all);
+//   1  (no outputs) the tile's total goes to partial[tile];
+//   2  the tile folds partial[0 .. tile) of a MODE 1 launch itself;
+//   3  one launch: tiles publish their totals and read their predecessors'.
+// Every combination's order is a fixed function of n and the geometry in
+// every mode (the tree below does not depend on which tile ran first).
+// Bound: HBM, 8 bytes per element for float -> float (MODE 3).  A
+// reduce-then-scan over wave ranges (four launches, input read twice) took
+// 516 us at n = 2^28 float and 16.4 us per call at 100,003 int32 -> int64;
+// MODE 3 takes 360 us (5.97 TB/s), MODE 1 + 2 10.4 us.
 const char* kScanHelpers = R"HIP(
 // inclusive scan across the wave (lane l receives v_0 (+) ... (+) v_l)
-template <typename T>
-__device__ __forceinline__ T hipmr_wave_scan(T v, int lane, T e) {
-  if constexpr (sizeof(T) == 4 || sizeof(T) == 8) {
-    return hipmr_dpp_scan(v, e, [](T a, T b) { return hipmr_combine(a, b); });
+__device__ __forceinline__ hipmr_acc hipmr_wave_scan(hipmr_acc v, hipmr_acc e) {
+  return hipmr_dpp_scan(v, e, [](hipmr_acc a, hipmr_acc b) { return hipmr_combine(a, b); });
+}
+
+// a 4- or 8-byte value as the low bits of a 64-bit word, and back
+typedef unsigned long long hipmr_u64;
+template <typename T> __device__ __forceinline__ hipmr_u64 hipmr_to_bits(T v) {
+  if constexpr (sizeof(T) == 4) return __builtin_bit_cast(unsigned, v);
+  else return __builtin_bit_cast(hipmr_u64, v);
+}
+template <typename T> __device__ __forceinline__ T hipmr_from_bits(hipmr_u64 b) {
+  if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, (unsigned)b);
+  else return __builtin_bit_cast(T, b);
+}
+
+// lane l's value (l the same in every lane), without an LDS round trip
+__device__ __forceinline__ hipmr_acc hipmr_lane_value(hipmr_acc v, int l) {
+  const hipmr_u64 a = hipmr_to_bits(v);
+  hipmr_u64 r = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)a, l);
+  if constexpr (sizeof(hipmr_acc) == 8)
+    r |= (hipmr_u64)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(a >> 32), l) << 32;
+  return hipmr_from_bits<hipmr_acc>(r);
+}
+
+// Published totals (MODE 3).  A 4-byte total is one 64-bit word, value | 1 << 32;
+// an 8-byte total two such words, so a single 64-bit load tells both whether
+// a word is there and what it holds, and no fence is needed.  Accesses are
+// device-scope (the L2s of the eight dies are not coherent otherwise).  Word 0
+// counts tickets, word 1 is set when a wait has been given up.
+constexpr int HIPMR_S = (int)sizeof(hipmr_acc) / 4, HIPMR_STATE0 = 16;
+
+__device__ __forceinline__ hipmr_u64 hipmr_peek(const hipmr_u64* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void hipmr_publish(hipmr_u64* p, hipmr_acc v) {
+  const hipmr_u64 a = hipmr_to_bits(v);
+  __hip_atomic_store(p, (1ull << 32) | (unsigned)a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if constexpr (HIPMR_S == 2)
+    __hip_atomic_store(p + 1, (1ull << 32) | (a >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+struct hipmr_slot { hipmr_u64 w0, w1; };
+__device__ __forceinline__ hipmr_slot hipmr_first_look(const hipmr_u64* p, bool mine) {
+  hipmr_slot s = {1ull << 32, 1ull << 32};
+  if (mine) {
+    s.w0 = hipmr_peek(p);
+    if constexpr (HIPMR_S == 2) s.w1 = hipmr_peek(p + 1);
+  }
+  return s;
+}
+// The fold, in lane order, of the totals the lanes wait for (lanes with
+// mine = false hold the neutral element); every lane receives it.  The waits
+// end: a total is published by a tile with an earlier ticket, whose block is
+// already running and itself waits for still earlier ones only.  The limit
+// below (10 s, or another wave's expiry) is reached only if something else
+// writes the workspace while the scan runs; the scan then ends with wrong
+// sums instead of hanging the GPU.
+__device__ __forceinline__ hipmr_acc hipmr_await_fold(const hipmr_u64* p, bool mine, hipmr_slot s,
+                                                      hipmr_acc e, hipmr_u64* state) {
+  unsigned polls = 0;
+  const hipmr_u64 t0 = __builtin_amdgcn_s_memrealtime();
+  while (__ballot(!((s.w0 >> 32) && (s.w1 >> 32)))) {
+    if ((++polls & 63u) == 0 &&
+        (hipmr_peek(state + 1) || __builtin_amdgcn_s_memrealtime() - t0 > 1000000000ull)) {
+      __hip_atomic_store(state + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      break;
+    }
+    __builtin_amdgcn_s_sleep(16);                    // 1024 clocks: fewer polls beside the ticket atomics
+    if (!(s.w0 >> 32)) s.w0 = hipmr_peek(p);
+    if constexpr (HIPMR_S == 2) { if (!(s.w1 >> 32)) s.w1 = hipmr_peek(p + 1); }
+  }
+  hipmr_acc v = e;
+  if (mine) v = hipmr_from_bits<hipmr_acc>(HIPMR_S == 1 ? s.w0 & 0xffffffffull : (s.w1 << 32) | (s.w0 & 0xffffffffull));
+  return hipmr_lane_value(hipmr_wave_scan(v, e), 63);
+}
+
+// The fold of every tile before `tile`, by one wave (MODE 3), after it has
+// published the tile's own total.  Tiles form groups of 64 and groups of 64
+// groups; the last tile of a group publishes the group's total, and the last
+// of a supergroup that one's, so three short folds reach any distance:
+// earlier tiles of the group, earlier groups of the supergroup, earlier
+// supergroups (64 per round).
+__device__ __forceinline__ hipmr_acc hipmr_before(int tile, int tiles, hipmr_acc own, hipmr_u64* state,
+                                                  hipmr_acc e, int lane) {
+  const int g = tile >> 6, r = tile & 63, h = g >> 6, q = g & 63;
+  hipmr_u64* const pt = state + HIPMR_STATE0;
+  hipmr_u64* const pg = pt + (long long)tiles * HIPMR_S;
+  hipmr_u64* const ph = pg + (long long)((tiles + 63) >> 6) * HIPMR_S;
+  if (lane == 0) hipmr_publish(pt + (long long)tile * HIPMR_S, own);
+  const hipmr_u64* const at = pt + ((long long)(tile - r) + lane) * HIPMR_S;
+  const hipmr_u64* const ag = pg + ((long long)(g - q) + lane) * HIPMR_S;
+  const hipmr_u64* ah = ph + (long long)lane * HIPMR_S;
+  const hipmr_slot st = hipmr_first_look(at, lane < r);
+  const hipmr_slot sg = hipmr_first_look(ag, lane < q);
+  hipmr_slot sh = hipmr_first_look(ah, lane < h);
+  const hipmr_acc ft = hipmr_await_fold(at, lane < r, st, e, state);
+  if (r == 63 && lane == 0) hipmr_publish(pg + (long long)g * HIPMR_S, hipmr_combine(ft, own));
+  const hipmr_acc fg = hipmr_await_fold(ag, lane < q, sg, e, state);
+  if (r == 63 && q == 63 && lane == 0)
+    hipmr_publish(ph + (long long)h * HIPMR_S, hipmr_combine(fg, hipmr_combine(ft, own)));
+  hipmr_acc fh = hipmr_await_fold(ah, lane < h, sh, e, state);
+  for (int k = 64; k < h; k += 64) {
+    ah += 64 * HIPMR_S;
+    sh = hipmr_first_look(ah, lane < h - k);
+    fh = hipmr_combine(fh, hipmr_await_fold(ah, lane < h - k, sh, e, state));
+  }
+  return hipmr_combine(fh, hipmr_combine(fg, ft));
+}
+)HIP";
+
+// Clears the ticket counter and the published totals of a MODE 3 launch.
+const char* kScanClear = R"HIP(
+extern "C" __global__ void __launch_bounds__(256)
+@@KNAME@@(unsigned long long* __restrict__ hipmr_state, int hipmr_words)
+{
+  const int k = blockIdx.x * 256 + threadIdx.x;
+  if (k < hipmr_words) hipmr_state[k] = 0ull;
+}
+)HIP";
+
+const char* kScanTile = R"HIP(
+extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
+@@KNAME@@(@@PARAMS@@, long long hipmr_n, long long hipmr_base, int hipmr_tiles,
+          void* __restrict__ hipmr_state, hipmr_acc* __restrict__ hipmr_out, int hipmr_exclusive)
+{
+  typedef @@IDX@@ hipmr_idx;
+  constexpr int HIPMR_B = @@BLOCK@@, HIPMR_U = @@IPT@@, HIPMR_V = @@VEC@@, HIPMR_MODE = @@MODE@@;
+  constexpr int HIPMR_W = HIPMR_B / 64;
+  constexpr bool HIPMR_NTL = @@NTL@@, HIPMR_NTS = @@NTS@@;
+  constexpr long long HIPMR_SUB = 64LL * HIPMR_V, HIPMR_TILE = HIPMR_SUB * HIPMR_U * HIPMR_W;
+  const hipmr_idx n = (hipmr_idx)hipmr_n;
+  const hipmr_acc hipmr_neutral = (hipmr_acc)(@@NEUTRAL@@);
+  const int hipmr_lane = threadIdx.x & 63;
+  const int hipmr_w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  int hipmr_tile = blockIdx.x;
+  if constexpr (HIPMR_MODE == 3) {
+    // tiles are taken in ticket order: a tile's predecessors are running or done
+    __shared__ int hipmr_ticket;
+    if (threadIdx.x == 0)
+      hipmr_ticket = (int)__hip_atomic_fetch_add((unsigned*)hipmr_state, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    hipmr_tile = __builtin_amdgcn_readfirstlane(hipmr_ticket);
+    if (hipmr_tile < 0) return;
+  }
+  if (hipmr_tile >= hipmr_tiles) return;
+  // base may be negative (the first aligned chunk starts before element 0):
+  // chunks that are not wholly inside [0, n) go element by element
+  const long long hipmr_b0 = hipmr_base + (long long)hipmr_tile * HIPMR_TILE;
+  const bool hipmr_whole = hipmr_b0 >= 0 && hipmr_b0 + HIPMR_TILE <= hipmr_n;
+  const long long hipmr_l0 = hipmr_b0 + hipmr_w * (HIPMR_SUB * HIPMR_U) + (long long)hipmr_lane * HIPMR_V;
+  hipmr_pack<hipmr_acc, HIPMR_V> hipmr_t[HIPMR_U];   // mapped values, then the lane's inclusive prefixes
+  @@DECL_PACKS@@
+  if (hipmr_whole) {
+#pragma unroll
+    for (int hipmr_u = 0; hipmr_u < HIPMR_U; ++hipmr_u) {
+      const long long hipmr_off = hipmr_l0 + hipmr_u * HIPMR_SUB;
+      @@LOADS@@
+    }
+#pragma unroll
+    for (int hipmr_u = 0; hipmr_u < HIPMR_U; ++hipmr_u) {
+      const long long hipmr_off = hipmr_l0 + hipmr_u * HIPMR_SUB;
+#pragma unroll
+      for (int hipmr_j = 0; hipmr_j < HIPMR_V; ++hipmr_j) {
+        const hipmr_idx i = (hipmr_idx)(hipmr_off + hipmr_j);
+        hipmr_t[hipmr_u].v[hipmr_j] = (hipmr_acc)(@@VMAPX@@);
+      }
+    }
   } else {
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const T y = __shfl_up(v, d, 64);
-      if (lane >= d) v = hipmr_combine(y, v);
-    }
-    return v;
-  }
-}
-)HIP";
-
-const char* kScanUp = R"HIP(
-extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
-@@KNAME@@(@@PARAMS@@, long long hipmr_n, long long hipmr_head, int hipmr_passes,
-          long long hipmr_waves, hipmr_acc* __restrict__ hipmr_partial)
-{
-  typedef @@IDX@@ hipmr_idx;
-  constexpr int HIPMR_B = @@BLOCK@@, HIPMR_U = @@IPT@@, HIPMR_V = @@VEC@@;
-  constexpr bool HIPMR_NTL = @@NTL@@, HIPMR_NTS = @@NTS@@;
-  const hipmr_idx n = (hipmr_idx)hipmr_n;
-  const hipmr_acc hipmr_neutral = (hipmr_acc)(@@NEUTRAL@@);
-  const int hipmr_lane = threadIdx.x & 63;
-  const long long hipmr_w = (long long)blockIdx.x * (HIPMR_B / 64) + (threadIdx.x >> 6);
-  if (hipmr_w >= hipmr_waves) return;           // whole waves; no block barrier below
-  const long long hipmr_h = hipmr_head < hipmr_n ? hipmr_head : hipmr_n;
-  const long long hipmr_sub = 64LL * HIPMR_V;
-  const long long hipmr_c = hipmr_sub * HIPMR_U * hipmr_passes;
-  const long long hipmr_b0 = hipmr_h + hipmr_w * hipmr_c;
-  const long long hipmr_e = hipmr_b0 + hipmr_c < hipmr_n ? hipmr_b0 + hipmr_c : hipmr_n;
-  hipmr_acc hipmr_a[HIPMR_U];
-#pragma unroll
-  for (int u = 0; u < HIPMR_U; ++u) hipmr_a[u] = hipmr_neutral;
-  if (hipmr_w == 0 && hipmr_lane < hipmr_h) {
-    const hipmr_idx i = (hipmr_idx)hipmr_lane;
-    hipmr_a[0] = hipmr_combine(hipmr_a[0], (hipmr_acc)(@@MAP@@));
-  }
-  for (int hipmr_p = 0; hipmr_p < hipmr_passes; ++hipmr_p) {
-    const long long hipmr_pb = hipmr_b0 + (long long)hipmr_p * hipmr_sub * HIPMR_U;
-    if (hipmr_pb >= hipmr_e) break;
-    @@DECL_PACKS@@
-#pragma unroll
     for (int hipmr_u = 0; hipmr_u < HIPMR_U; ++hipmr_u) {
-      const long long hipmr_off = hipmr_pb + hipmr_sub * hipmr_u + (long long)hipmr_lane * HIPMR_V;
-      if (hipmr_off + HIPMR_V <= hipmr_e) {
+      const long long hipmr_off = hipmr_l0 + hipmr_u * HIPMR_SUB;
+      if (hipmr_off >= 0 && hipmr_off + HIPMR_V <= hipmr_n) {
         @@LOADS@@
       }
     }
 #pragma unroll
     for (int hipmr_u = 0; hipmr_u < HIPMR_U; ++hipmr_u) {
-      const long long hipmr_off = hipmr_pb + hipmr_sub * hipmr_u + (long long)hipmr_lane * HIPMR_V;
-      if (hipmr_off + HIPMR_V <= hipmr_e) {
+      const long long hipmr_off = hipmr_l0 + hipmr_u * HIPMR_SUB;
+      const bool hipmr_full = hipmr_off >= 0 && hipmr_off + HIPMR_V <= hipmr_n;
 #pragma unroll
-        for (int hipmr_j = 0; hipmr_j < HIPMR_V; ++hipmr_j) {
-          const hipmr_idx i = (hipmr_idx)(hipmr_off + hipmr_j);
-          hipmr_a[hipmr_u] = hipmr_combine(hipmr_a[hipmr_u], (hipmr_acc)(@@VMAP@@));
-        }
-      } else {
-        for (long long hipmr_k = hipmr_off; hipmr_k < hipmr_e; ++hipmr_k) {
-          const hipmr_idx i = (hipmr_idx)hipmr_k;
-          hipmr_a[hipmr_u] = hipmr_combine(hipmr_a[hipmr_u], (hipmr_acc)(@@MAP@@));
-        }
+      for (int hipmr_j = 0; hipmr_j < HIPMR_V; ++hipmr_j) {
+        hipmr_acc hipmr_m = hipmr_neutral;
+        const hipmr_idx i = (hipmr_idx)(hipmr_off + hipmr_j);
+        if (hipmr_full) hipmr_m = (hipmr_acc)(@@VMAPX@@);
+        else if (hipmr_off + hipmr_j >= 0 && hipmr_off + hipmr_j < hipmr_n) hipmr_m = (hipmr_acc)(@@MAP@@);
+        hipmr_t[hipmr_u].v[hipmr_j] = hipmr_m;
       }
     }
   }
-  hipmr_acc hipmr_r = hipmr_fold<HIPMR_U>(hipmr_a);
-  hipmr_r = hipmr_block_reduce<64>(hipmr_r, hipmr_neutral);
-  if (hipmr_lane == 0) hipmr_partial[hipmr_w] = hipmr_r;
-}
-)HIP";
-
-// Pass 2, in two launches over the wave totals (coalesced, one per thread):
-// every block of 1024 scans its 1024 totals (exclusive, within the block)
-// and writes the block total; then one block scans the block totals.
-const char* kScanMid = R"HIP(
-template <int B>
-__device__ __forceinline__ hipmr_acc hipmr_block_exclusive(hipmr_acc v, hipmr_acc neutral, hipmr_acc* total) {
-  constexpr int W = B / 64;
-  __shared__ hipmr_acc hipmr_wt[W];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const hipmr_acc x = hipmr_wave_scan(v, lane, neutral);
-  if (lane == 63) hipmr_wt[w] = x;
+  // MODE 2: this thread's run of the earlier tiles' totals, in order
+  hipmr_acc hipmr_pp = hipmr_neutral;
+  if constexpr (HIPMR_MODE == 2) {
+    const hipmr_acc* const hipmr_partial = (const hipmr_acc*)hipmr_state;
+    const int hipmr_run = (hipmr_tile + HIPMR_B - 1) / HIPMR_B;
+    for (int k = threadIdx.x * hipmr_run; k < (int)(threadIdx.x + 1) * hipmr_run && k < hipmr_tile; ++k)
+      hipmr_pp = hipmr_combine(hipmr_pp, hipmr_partial[k]);
+    hipmr_pp = hipmr_wave_scan(hipmr_pp, hipmr_neutral);   // lane 63: the wave's runs
+  }
+  // inside the wave: lane prefixes, then each sub-tile's exclusive offset
+  // (the sub-tiles' wave scans are independent; only their totals chain)
+  hipmr_acc hipmr_q[HIPMR_U];
+  hipmr_acc hipmr_carry = hipmr_neutral;
+#pragma unroll
+  for (int hipmr_u = 0; hipmr_u < HIPMR_U; ++hipmr_u) {
+#pragma unroll
+    for (int hipmr_j = 1; hipmr_j < HIPMR_V; ++hipmr_j)
+      hipmr_t[hipmr_u].v[hipmr_j] = hipmr_combine(hipmr_t[hipmr_u].v[hipmr_j - 1], hipmr_t[hipmr_u].v[hipmr_j]);
+    const hipmr_acc hipmr_x = hipmr_wave_scan(hipmr_t[hipmr_u].v[HIPMR_V - 1], hipmr_neutral);
+    const hipmr_acc hipmr_up = hipmr_dpp<0x138, 0xf>(hipmr_x, hipmr_neutral);   // wave_shr:1
+    const hipmr_acc hipmr_sum = hipmr_lane_value(hipmr_x, 63);
+    hipmr_q[hipmr_u] = hipmr_u == 0 ? hipmr_up : hipmr_combine(hipmr_carry, hipmr_up);
+    hipmr_carry = hipmr_u == 0 ? hipmr_sum : hipmr_combine(hipmr_carry, hipmr_sum);
+  }
+  // across the block's waves: every wave scans the wave totals itself
+  __shared__ hipmr_acc hipmr_wt[HIPMR_W], hipmr_wp[HIPMR_W], hipmr_pre_lds;
+  if (hipmr_lane == 63) {
+    hipmr_wt[hipmr_w] = hipmr_carry;
+    hipmr_wp[hipmr_w] = hipmr_pp;
+  }
   __syncthreads();
-  if (w == 0) {
-    hipmr_acc t = lane < W ? hipmr_wt[lane] : neutral;
-    t = hipmr_wave_scan(t, lane, neutral);
-    if (lane < W) hipmr_wt[lane] = t;
+  const hipmr_acc hipmr_ws = hipmr_wave_scan(hipmr_lane < HIPMR_W ? hipmr_wt[hipmr_lane] : hipmr_neutral, hipmr_neutral);
+  if constexpr (HIPMR_MODE == 1) {
+    if (threadIdx.x == HIPMR_W - 1) ((hipmr_acc*)hipmr_state)[hipmr_tile] = hipmr_ws;
+    return;
   }
-  __syncthreads();
-  const hipmr_acc up = __shfl_up(x, 1, 64);
-  hipmr_acc r = lane == 0 ? neutral : up;
-  if (w > 0) r = hipmr_combine(hipmr_wt[w - 1], r);
-  *total = hipmr_wt[W - 1];
-  return r;
-}
-
-extern "C" __global__ void __launch_bounds__(1024)
-@@KNAME@@(const hipmr_acc* __restrict__ hipmr_partial, long long hipmr_waves,
-          hipmr_acc* __restrict__ hipmr_prefix, hipmr_acc* __restrict__ hipmr_btot, int hipmr_top)
-{
-  const hipmr_acc hipmr_neutral = (hipmr_acc)(@@NEUTRAL@@);
-  // hipmr_top == 0: block b scans totals [1024 b, 1024 b + 1024);
-  // hipmr_top == 1: the single block scans the block totals in place
-  const long long k = (long long)blockIdx.x * 1024 + threadIdx.x;
-  const hipmr_acc* src = hipmr_top ? hipmr_btot : hipmr_partial;
-  hipmr_acc* dst = hipmr_top ? hipmr_btot : hipmr_prefix;
-  const long long count = hipmr_top ? (hipmr_waves + 1023) / 1024 : hipmr_waves;
-  const hipmr_acc v = k < count ? src[k] : hipmr_neutral;
-  hipmr_acc total;
-  const hipmr_acc r = hipmr_block_exclusive<1024>(v, hipmr_neutral, &total);
-  __syncthreads();                              // every read of src precedes the writes
-  if (k < count) dst[k] = r;
-  if (!hipmr_top && threadIdx.x == 0) hipmr_btot[blockIdx.x] = total;
-}
-)HIP";
-
-// Pass 3: each wave rescans its range from its prefix and writes the outputs.
-const char* kScanDown = R"HIP(
-extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
-@@KNAME@@(@@PARAMS@@, long long hipmr_n, long long hipmr_head, int hipmr_passes,
-          long long hipmr_waves, const hipmr_acc* __restrict__ hipmr_prefix,
-          const hipmr_acc* __restrict__ hipmr_bpre, hipmr_acc* __restrict__ hipmr_out,
-          int hipmr_exclusive)
-{
-  typedef @@IDX@@ hipmr_idx;
-  constexpr int HIPMR_B = @@BLOCK@@, HIPMR_U = @@IPT@@, HIPMR_V = @@VEC@@;
-  constexpr bool HIPMR_NTL = @@NTL@@, HIPMR_NTS = @@NTS@@;
-  const hipmr_idx n = (hipmr_idx)hipmr_n;
-  const hipmr_acc hipmr_neutral = (hipmr_acc)(@@NEUTRAL@@);
-  const int hipmr_lane = threadIdx.x & 63;
-  const long long hipmr_w = (long long)blockIdx.x * (HIPMR_B / 64) + (threadIdx.x >> 6);
-  if (hipmr_w >= hipmr_waves) return;           // whole waves; no block barrier below
-  const long long hipmr_h = hipmr_head < hipmr_n ? hipmr_head : hipmr_n;
-  const long long hipmr_sub = 64LL * HIPMR_V;
-  const long long hipmr_c = hipmr_sub * HIPMR_U * hipmr_passes;
-  const long long hipmr_b0 = hipmr_h + hipmr_w * hipmr_c;
-  const long long hipmr_e = hipmr_b0 + hipmr_c < hipmr_n ? hipmr_b0 + hipmr_c : hipmr_n;
-  hipmr_acc hipmr_carry = hipmr_combine(hipmr_bpre[hipmr_w >> 10], hipmr_prefix[hipmr_w]);
-  if (hipmr_w == 0 && hipmr_h > 0) {            // the unaligned head, one element per lane
-    hipmr_acc hipmr_v = hipmr_neutral;
-    if (hipmr_lane < hipmr_h) {
-      const hipmr_idx i = (hipmr_idx)hipmr_lane;
-      hipmr_v = (hipmr_acc)(@@MAP@@);
+  hipmr_acc hipmr_pre = hipmr_neutral;               // the fold of every element before the tile
+  if constexpr (HIPMR_MODE == 2)
+    hipmr_pre = hipmr_lane_value(hipmr_wave_scan(hipmr_lane < HIPMR_W ? hipmr_wp[hipmr_lane] : hipmr_neutral,
+                                                 hipmr_neutral), 63);
+  if constexpr (HIPMR_MODE == 3) {
+    if (hipmr_w == 0) {
+      const hipmr_acc hipmr_b = hipmr_before(hipmr_tile, hipmr_tiles, hipmr_lane_value(hipmr_ws, HIPMR_W - 1),
+                                             (hipmr_u64*)hipmr_state, hipmr_neutral, hipmr_lane);
+      if (hipmr_lane == 0) hipmr_pre_lds = hipmr_b;
     }
-    const hipmr_acc hipmr_x = hipmr_wave_scan(hipmr_v, hipmr_lane, hipmr_neutral);
-    const hipmr_acc hipmr_up = __shfl_up(hipmr_x, 1, 64);
-    if (hipmr_lane < hipmr_h)
-      hipmr_out[hipmr_lane] = hipmr_exclusive ? (hipmr_lane == 0 ? hipmr_carry : hipmr_combine(hipmr_carry, hipmr_up))
-                                              : hipmr_combine(hipmr_carry, hipmr_x);
-    hipmr_carry = hipmr_combine(hipmr_carry, __shfl(hipmr_x, 63, 64));
+    __syncthreads();
+    hipmr_pre = hipmr_pre_lds;
   }
-  for (int hipmr_p = 0; hipmr_p < hipmr_passes; ++hipmr_p) {
-    const long long hipmr_pb = hipmr_b0 + (long long)hipmr_p * hipmr_sub * HIPMR_U;
-    if (hipmr_pb >= hipmr_e) break;
-    @@DECL_PACKS@@
+  const hipmr_acc hipmr_wpre = hipmr_w == 0 ? hipmr_neutral : hipmr_lane_value(hipmr_ws, hipmr_w - 1);
 #pragma unroll
-    for (int hipmr_u = 0; hipmr_u < HIPMR_U; ++hipmr_u) {
-      const long long hipmr_off = hipmr_pb + hipmr_sub * hipmr_u + (long long)hipmr_lane * HIPMR_V;
-      if (hipmr_off + HIPMR_V <= hipmr_e) {
-        @@LOADS@@
-      }
+  for (int hipmr_u = 0; hipmr_u < HIPMR_U; ++hipmr_u) {
+    const long long hipmr_off = hipmr_l0 + hipmr_u * HIPMR_SUB;
+    // the offsets inside the tile are combined first: one rounding at the
+    // prefix's magnitude here, one per output
+    const hipmr_acc hipmr_p = hipmr_combine(hipmr_pre, hipmr_combine(hipmr_wpre, hipmr_q[hipmr_u]));
+    hipmr_pack<hipmr_acc, HIPMR_V> hipmr_o;
+#pragma unroll
+    for (int hipmr_j = 0; hipmr_j < HIPMR_V; ++hipmr_j) {
+      if (hipmr_exclusive) hipmr_o.v[hipmr_j] = hipmr_j == 0 ? hipmr_p : hipmr_combine(hipmr_p, hipmr_t[hipmr_u].v[hipmr_j > 0 ? hipmr_j - 1 : 0]);
+      else hipmr_o.v[hipmr_j] = hipmr_combine(hipmr_p, hipmr_t[hipmr_u].v[hipmr_j]);
     }
-    @@PASS_P@@
+    if (hipmr_whole || (hipmr_off >= 0 && hipmr_off + HIPMR_V <= hipmr_n)) {
+      hipmr_store<HIPMR_NTS>(hipmr_out + hipmr_off, hipmr_o);
+    } else {
+#pragma unroll
+      for (int hipmr_j = 0; hipmr_j < HIPMR_V; ++hipmr_j)
+        if (hipmr_off + hipmr_j >= 0 && hipmr_off + hipmr_j < hipmr_n) hipmr_out[hipmr_off + hipmr_j] = hipmr_o.v[hipmr_j];
+    }
   }
 }
-)HIP";
-
-// One pass of pass 3 over the chunks in registers (@@VMAPX@@ reads them):
-// per sub-tile, the lane's inclusive prefixes of its V elements, a wave scan
-// of the lane totals, the outputs, the carry.
-const char* kScanDownPass = R"HIP(
-#pragma unroll
-    for (int hipmr_u = 0; hipmr_u < HIPMR_U; ++hipmr_u) {
-      const long long hipmr_off = hipmr_pb + hipmr_sub * hipmr_u + (long long)hipmr_lane * HIPMR_V;
-      const bool hipmr_full = hipmr_off + HIPMR_V <= hipmr_e;
-      hipmr_pack<hipmr_acc, HIPMR_V> hipmr_t;   // the lane's inclusive prefixes
-      if (hipmr_full) {
-#pragma unroll
-        for (int hipmr_j = 0; hipmr_j < HIPMR_V; ++hipmr_j) {
-          const hipmr_idx i = (hipmr_idx)(hipmr_off + hipmr_j);
-          const hipmr_acc hipmr_m = (hipmr_acc)(@@VMAPX@@);
-          hipmr_t.v[hipmr_j] = hipmr_j == 0 ? hipmr_m : hipmr_combine(hipmr_t.v[hipmr_j - 1], hipmr_m);
-        }
-      } else {
-#pragma unroll
-        for (int hipmr_j = 0; hipmr_j < HIPMR_V; ++hipmr_j) {
-          hipmr_acc hipmr_m = hipmr_neutral;
-          if (hipmr_off + hipmr_j < hipmr_e) {
-            const hipmr_idx i = (hipmr_idx)(hipmr_off + hipmr_j);
-            hipmr_m = (hipmr_acc)(@@MAP@@);
-          }
-          hipmr_t.v[hipmr_j] = hipmr_j == 0 ? hipmr_m : hipmr_combine(hipmr_t.v[hipmr_j - 1], hipmr_m);
-        }
-      }
-      const hipmr_acc hipmr_x = hipmr_wave_scan(hipmr_t.v[HIPMR_V - 1], hipmr_lane, hipmr_neutral);
-      const hipmr_acc hipmr_up = __shfl_up(hipmr_x, 1, 64);
-      const hipmr_acc hipmr_pre = hipmr_lane == 0 ? hipmr_carry : hipmr_combine(hipmr_carry, hipmr_up);
-      hipmr_pack<hipmr_acc, HIPMR_V> hipmr_o;
-      if (hipmr_exclusive) {
-        hipmr_o.v[0] = hipmr_pre;
-#pragma unroll
-        for (int hipmr_j = 1; hipmr_j < HIPMR_V; ++hipmr_j)
-          hipmr_o.v[hipmr_j] = hipmr_combine(hipmr_pre, hipmr_t.v[hipmr_j - 1]);
-      } else {
-#pragma unroll
-        for (int hipmr_j = 0; hipmr_j < HIPMR_V; ++hipmr_j)
-          hipmr_o.v[hipmr_j] = hipmr_combine(hipmr_pre, hipmr_t.v[hipmr_j]);
-      }
-      if (hipmr_full) {
-        hipmr_store<HIPMR_NTS>(hipmr_out + hipmr_off, hipmr_o);
-      } else {
-#pragma unroll
-        for (int hipmr_j = 0; hipmr_j < HIPMR_V; ++hipmr_j)
-          if (hipmr_off + hipmr_j < hipmr_e) hipmr_out[hipmr_off + hipmr_j] = hipmr_o.v[hipmr_j];
-      }
-      hipmr_carry = hipmr_combine(hipmr_carry, __shfl(hipmr_x, 63, 64));
-    }
 )HIP";
 
 void replace_all(std::string& s, const std::string& key, const std::string& val) {
@@ -1472,6 +1519,9 @@ void replace_all(std::string& s, const std::string& key, const std::string& val)
         pos += val.size();
     }
 }
+
+// symbol tags of the scan modes (vector, one-element)
+const char* const kScanTags[4][2] = {{"sc1", "sc1s"}, {"scu", "scus"}, {"scd", "scds"}, {"scl", "scls"}};
 
 std::string combine_body(DType r, const KernelSpec& spec) {
     bool fp = r == DT_F32 || r == DT_F64;
@@ -1519,17 +1569,13 @@ std::string render(const Program& prog, const KernelSpec& spec, std::string* sym
         case KernelKind::SegPlan: tmpl = kSegPlan; tag = "segplan"; break;
         case KernelKind::SegS1: tmpl = kSegS1; tag = "seg1"; reduce = true; break;
         case KernelKind::SegS2: tmpl = kSegS2; tag = "seg2"; reduce = true; break;
-        case KernelKind::ScanUpVector: tmpl = kScanUp; tag = "scu"; reduce = true; break;
-        case KernelKind::ScanUpScalar: tmpl = kScanUp; tag = "scus"; reduce = true; break;
-        case KernelKind::ScanMid: tmpl = kScanMid; tag = "scm"; reduce = true; break;
-        case KernelKind::ScanDownVector: tmpl = kScanDown; tag = "scd"; reduce = true; break;
-        case KernelKind::ScanDownScalar: tmpl = kScanDown; tag = "scds"; reduce = true; break;
+        case KernelKind::ScanVector: tmpl = kScanTile; tag = kScanTags[spec.scan_mode][0]; reduce = true; break;
+        case KernelKind::ScanScalar: tmpl = kScanTile; tag = kScanTags[spec.scan_mode][1]; reduce = true; break;
+        case KernelKind::ScanClear: tmpl = kScanClear; tag = "scz"; break;
     }
-    const bool scan = spec.kind == KernelKind::ScanUpVector || spec.kind == KernelKind::ScanUpScalar ||
-                      spec.kind == KernelKind::ScanMid || spec.kind == KernelKind::ScanDownVector ||
-                      spec.kind == KernelKind::ScanDownScalar;
-    // scalar scan kinds: one-element chunks read through the expression itself
-    const bool scan_scalar = spec.kind == KernelKind::ScanUpScalar || spec.kind == KernelKind::ScanDownScalar;
+    // the scalar scan reads its one-element chunks through the expression itself
+    const bool scan_scalar = spec.kind == KernelKind::ScanScalar;
+    const bool scan = spec.kind == KernelKind::ScanVector || scan_scalar;
     const bool seg = spec.kind == KernelKind::SegPlan || spec.kind == KernelKind::SegS1;
     const bool amax = spec.kind == KernelKind::AmaxS1Vector || spec.kind == KernelKind::AmaxS1Scalar;
     std::string body = tmpl;
@@ -1599,12 +1645,8 @@ std::string render(const Program& prog, const KernelSpec& spec, std::string* sym
         decl_packs.clear();
         loads.clear();
     }
-    if (spec.kind == KernelKind::ScanDownVector || spec.kind == KernelKind::ScanDownScalar) {
-        std::string pass_p = kScanDownPass;
-        replace_all(pass_p, "@@VMAPX@@", vector_text);
-        replace_all(body, "@@PASS_P@@", pass_p);
-    }
-
+    replace_all(body, "@@VMAPX@@", vector_text);
+    replace_all(body, "@@MODE@@", std::to_string(spec.scan_mode));
     replace_all(body, "@@PARAMS@@", params);
     replace_all(body, "@@DECL_PACKS@@", decl_packs);
     replace_all(body, "@@LOADS@@", loads);

@@ -123,7 +123,7 @@ enum class KernelKind : int32_t {
     EwVector = 0, EwScalar = 1, RedS1Vector = 2, RedS1Scalar = 3, RedS2 = 4,
     CompS1Vector = 5, CompS1Scalar = 6, CompS2 = 7, AmaxS1Vector = 8, AmaxS1Scalar = 9,
     SegPlan = 11, SegS1 = 12, SegS2 = 13,
-    ScanUpVector = 14, ScanUpScalar = 15, ScanMid = 16, ScanDownVector = 17, ScanDownScalar = 18,
+    ScanVector = 14, ScanScalar = 15, ScanClear = 16,
 };
 
 struct KernelSpec {
@@ -142,6 +142,7 @@ struct KernelSpec {
     bool exact_runs = false;  // CompS1: map is one FP8 load; sum runs of <= 64 exactly
     bool norm = false;        // CompS2: finish as sqrt(sum) / scale
     // batching extension
+    int scan_mode = 0;        // Scan: 0 one tile, 1 tile totals, 2 from totals, 3 one pass
     int lds_segs = 0;         // SegS1: tile-start table held in LDS (capacity), 0 = global
 };
 

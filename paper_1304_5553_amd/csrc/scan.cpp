@@ -3,14 +3,16 @@
 // the formal index i, a combine in a and b, its neutral element; section
 // "Further Facilities" with section "Map-Reduce").
 //
-// Reduce-then-scan in four launches, deterministic and without atomics:
-//   1. scu / scus: each wave folds its contiguous range into partial[w];
-//   2. scm:        each block of 1024 wave totals is scanned (exclusive), then
-//                  one block scans the block totals (a second scm launch);
-//   3. scd / scds: each wave rescans its range from its prefix and writes out.
-// The partition depends only on n, the alignment head and the geometry, so a
-// result is bitwise repeatable.  The input is read twice and the output
-// written once.
+// The array is cut into tiles (see the tile kernel's comment); a tile stays
+// in registers from its load to its stores.  Three ways to give a tile the
+// fold of everything before it, chosen by size below:
+//   one launch        sc1 / sc1s   one tile holds the whole array
+//   two launches      scu, scd     tile totals, then every tile folds its
+//                                  predecessors' totals itself (input read twice)
+//   clear + one pass  scz, scl     tiles publish totals and wait for their
+//                                  predecessors' (input read once)
+// The order of every combination depends only on n, the alignment head and
+// the geometry, so a result is bitwise repeatable.
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
@@ -22,14 +24,25 @@ using namespace hipmr;
 
 namespace {
 
-// Many short ranges (up to 65536 waves): the waves running together cover a
-// compact address window, which keeps the writes efficient (measured on
-// MI355X: a copy with this partition loses ~20 % when each wave owns 64 KB
-// instead of 4-16 KB).  Passes of 4 sub-tiles per wave; pass 1 takes at most
-// 4 sub-tiles per step whatever the pass-3 geometry.
-constexpr int kScanBlock = 256, kScanIpt = 4, kScanUpIpt = 4;
-constexpr long long kScanMaxWaves = 65536;   // wave totals (pass 2: 64 blocks of 1024)
-constexpr int kScanMidBlock = 1024;
+// Tiles and forms by size, from sweeps on MI355X (us per call; float, and
+// int32 -> int64 with half the elements per tile):
+// - one tile of 1024 threads x 8 sub-tiles: one launch instead of two;
+// - totals then rescan while a pass over the tiles is short and the second
+//   read comes out of the caches: 512 x 8 takes 16.0 / 24.7 at n = 2^23 and
+//   34.3 / 49.0 at 2^24, the one-pass form 17.2 / 27.6 and 30.9 / 50.1; every
+//   tile folds all earlier totals, so many small tiles cost (256 x 8: 63.7
+//   for the 4096 tiles of 2^24 int64), few leave compute units idle (256 x 8:
+//   10.8 at 2^22 float);
+// - one pass above: large tiles, as each takes a ticket from one counter
+//   (about 12 ns per ticket bounds 256 x 4 to 0.80 ms at n = 2^28), and two
+//   blocks of 512 threads x 16 sub-tiles (126 registers) fill a compute unit:
+//   0.365 ms at n = 2^28 float and 0.302 ms at 2^27 int64, against 0.384 and
+//   0.328 for 1024 x 8 and 0.398 / 0.364 for 256 x 16 or 512 x 8.
+constexpr int kScanOneBlock = 1024, kScanSmallBlock = 256, kScanBlock = 512;
+constexpr int kScanIpt = 8, kScanPassIpt = 16;
+constexpr long long kScanSmallTiles = 512, kScanFoldTiles = 768;
+constexpr long long kScanMinTiles = 64000;   // the workspace holds at least this many totals
+constexpr long long kScanBigTile = 16384;    // elements of the largest one-element tile (1024 threads, 16 each)
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
@@ -54,19 +67,27 @@ long long scan_head(const hipmr_kernel* h, void* const* args, const void* out, i
     return -1;
 }
 
-KernelSpec scan_spec(KernelKind kind, const LaunchCfg& cfg, bool idx64, const char* combine,
+KernelSpec scan_spec(bool vector, int mode, const LaunchCfg& cfg, bool idx64, const char* combine,
                      const char* neutral) {
     KernelSpec s;
-    s.kind = kind;
+    s.kind = vector ? KernelKind::ScanVector : KernelKind::ScanScalar;
+    s.scan_mode = mode;
     s.idx64 = idx64;
-    s.block = kind == KernelKind::ScanMid ? kScanMidBlock : cfg.block;
-    s.ipt = kind == KernelKind::ScanMid ? 1 : cfg.ipt;
-    s.vec = kind == KernelKind::ScanMid ? 1 : cfg.vec;
-    s.nt_loads = kind == KernelKind::ScanMid ? true : cfg.nt_loads;
-    s.nt_stores = kind == KernelKind::ScanMid ? true : cfg.nt_stores;
+    s.block = cfg.block;
+    s.ipt = cfg.ipt;
+    s.vec = cfg.vec;
+    s.nt_loads = cfg.nt_loads;
+    s.nt_stores = cfg.nt_stores;
     s.combine = combine;
     s.neutral = neutral;
     return s;
+}
+
+// 64-bit words of the one-pass form's ticket counter and published totals:
+// tiles, groups of 64, groups of 64 groups.
+long long state_words(long long tiles, size_t rs) {
+    const long long groups = (tiles + 63) / 64, supers = (groups + 63) / 64;
+    return 16 + (tiles + groups + supers) * (long long)(rs / 4);
 }
 
 }  // namespace
@@ -76,8 +97,7 @@ extern "C" {
 size_t hipmr_scan_workspace_bytes(hipmr_handle h, int64_t n) {
     if (!h || !h->prog.sig.is_reduce || n < 0) return 0;
     const size_t rs = (size_t)dtype_size(h->prog.sig.result);
-    // wave totals, wave prefixes within their block of 1024, block prefixes
-    return 2 * align256((size_t)kScanMaxWaves * rs) + align256((size_t)(kScanMaxWaves / 1024) * rs);
+    return align256((size_t)state_words(std::max<long long>(kScanMinTiles, n / kScanBigTile + 2), rs) * 8);
 }
 
 hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral, int64_t n,
@@ -95,73 +115,78 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
         return fail(HIPMR_E_WORKSPACE, "workspace smaller than hipmr_scan_workspace_bytes()");
     // Default chunk: 16 bytes of the narrowest input, but at most 16 bytes of
     // output per lane, so that each store instruction of a wave writes one
-    // contiguous run; a narrower chunk takes more sub-tiles per pass (at most
-    // 8) to keep the loads in flight.
-    const int out_size = dtype_size(h->prog.sig.result);
-    const int dvec = std::min(h->default_vec, std::max(1, 16 / out_size));
-    const int dipt = std::min(8, kScanIpt * (h->default_vec / dvec));
+    // contiguous run.
+    const size_t rs = (size_t)dtype_size(h->prog.sig.result);
+    const int dvec = std::min(h->default_vec, std::max(1, 16 / (int)rs));
     LaunchCfg cfg;
-    st = resolve_cfg(cfgp, kScanBlock, dipt, dvec, 1, &cfg);
+    st = resolve_cfg(cfgp, kScanBlock, kScanIpt, dvec, 1, &cfg);
     if (st != HIPMR_OK) return st;
 
-    long long head = h->prog.info.vectorizable && !cfg.force_scalar ? scan_head(h, args, out, cfg.vec) : -1;
-    const bool vector = head >= 0;
-    if (!vector) {
-        cfg.vec = 1;
-        head = 0;
-    }
     const long long n64 = n;
-    head = std::min<long long>(head, n64);
-    const long long body = n64 - head;
-    const long long sub = 64LL * cfg.vec * cfg.ipt;            // one pass of a wave (pass 3)
-    const long long passes = std::max<long long>(1, (body + sub * kScanMaxWaves - 1) / (sub * kScanMaxWaves));
-    const long long waves = std::max<long long>(1, (body + sub * passes - 1) / (sub * passes));
-    int passes32 = (int)passes;
-    // pass 1 covers the same ranges in steps of at most kScanUpIpt sub-tiles
-    LaunchCfg up = cfg;
-    up.ipt = std::min(cfg.ipt, kScanUpIpt);
-    while (cfg.ipt % up.ipt) --up.ipt;
-    int passes_up = (int)(passes * (cfg.ipt / up.ipt));
+    const long long head = h->prog.info.vectorizable && !cfg.force_scalar ? scan_head(h, args, out, cfg.vec) : -1;
+    const bool vector = head >= 0;
+    if (!vector) cfg.vec = 1;
+    long long base = head > 0 ? head - cfg.vec : 0;       // tile 0 starts at an aligned element
+    auto tiles_of = [&](const LaunchCfg& c) {
+        const long long tile = (long long)c.block * c.vec * c.ipt;
+        return (n64 - base + tile - 1) / tile;
+    };
+    const bool own_block = cfgp && cfgp->block, own_ipt = cfgp && cfgp->items_per_thread;
+    auto with = [&](int block, int ipt) {
+        LaunchCfg c = cfg;
+        if (!own_block) c.block = block;
+        if (!own_ipt) c.ipt = ipt;
+        return c;
+    };
+    int mode = 3;
+    const LaunchCfg one = with(kScanOneBlock, kScanIpt), small = with(kScanSmallBlock, kScanIpt);
+    if (tiles_of(one) == 1) {
+        mode = 0;
+        cfg = one;
+    } else if (tiles_of(small) <= kScanSmallTiles) {
+        mode = 2;
+        cfg = small;
+    } else if (tiles_of(cfg) <= kScanFoldTiles) {
+        mode = 2;
+    } else {
+        cfg = with(kScanBlock, kScanPassIpt);
+        // larger tiles where the workspace could not hold every tile's total
+        const auto fits = [&] { return state_words(tiles_of(cfg), rs) * 8 <= (long long)workspace_bytes; };
+        while (!fits() && cfg.ipt < 16) cfg.ipt = std::min(16, 2 * cfg.ipt);
+        while (!fits() && cfg.block < 1024) cfg.block = std::min(1024, 2 * cfg.block);
+        if (!fits()) return fail(HIPMR_E_WORKSPACE, "workspace too small for the scan's tile totals");
+    }
+    const long long tiles64 = tiles_of(cfg);
     const bool idx64 = n64 >= (int64_t(1) << 31);
+    int tiles = (int)tiles64, excl = exclusive, words = (int)state_words(tiles64, rs);
 
     std::string syms;
-    void *f_up = nullptr, *f_mid = nullptr, *f_down = nullptr;
-    st = variant_function(h, scan_spec(vector ? KernelKind::ScanUpVector : KernelKind::ScanUpScalar, up,
-                                       idx64, combine, neutral), &f_up, &syms);
+    void *f_first = nullptr, *f_scan = nullptr;
+    st = variant_function(h, scan_spec(vector, mode, cfg, idx64, combine, neutral), &f_scan, &syms);
     if (st != HIPMR_OK) return st;
-    st = variant_function(h, scan_spec(KernelKind::ScanMid, cfg, false, combine, neutral), &f_mid, &syms);
-    if (st != HIPMR_OK) return st;
-    st = variant_function(h, scan_spec(vector ? KernelKind::ScanDownVector : KernelKind::ScanDownScalar, cfg,
-                                       idx64, combine, neutral), &f_down, &syms);
+    if (mode == 2) {
+        st = variant_function(h, scan_spec(vector, 1, cfg, idx64, combine, neutral), &f_first, &syms);
+    } else if (mode == 3) {
+        KernelSpec z;
+        z.kind = KernelKind::ScanClear;
+        st = variant_function(h, z, &f_first, &syms);
+    }
     if (st != HIPMR_OK) return st;
     set_last_symbols(h, syms);
 
-    const size_t rs = (size_t)dtype_size(h->prog.sig.result);
-    void* partial = workspace;
-    void* prefix = (char*)workspace + align256((size_t)kScanMaxWaves * rs);
-    void* bpre = (char*)prefix + align256((size_t)kScanMaxWaves * rs);
-    const unsigned grid = (unsigned)((waves + cfg.block / 64 - 1) / (cfg.block / 64));
-    long long waves64 = waves;
-    int excl = exclusive;
-
-    std::vector<void*> p1;
-    if (h->prog.sig.args.empty()) p1.push_back(&head);       // hipmr_unused
-    for (size_t k = 0; k < h->prog.sig.args.size(); ++k) p1.push_back(args[k]);
-    std::vector<void*> p3 = p1;
+    std::vector<void*> p;
+    if (h->prog.sig.args.empty()) p.push_back(&base);       // hipmr_unused
+    for (size_t k = 0; k < h->prog.sig.args.size(); ++k) p.push_back(args[k]);
     long long n_arg = n64;
-    p1.insert(p1.end(), {(void*)&n_arg, (void*)&head, (void*)&passes_up, (void*)&waves64, (void*)&partial});
-    st = launch(f_up, grid, (unsigned)cfg.block, p1.data(), stream);
+    p.insert(p.end(), {(void*)&n_arg, (void*)&base, (void*)&tiles, (void*)&workspace, (void*)&out, (void*)&excl});
+    if (mode == 2) {
+        st = launch(f_first, (unsigned)tiles, (unsigned)cfg.block, p.data(), stream);
+    } else if (mode == 3) {
+        void* pz[2] = {&workspace, &words};
+        st = launch(f_first, (unsigned)((words + 255) / 256), 256, pz, stream);
+    }
     if (st != HIPMR_OK) return st;
-    int top0 = 0, top1 = 1;
-    void* p2a[5] = {&partial, &waves64, &prefix, &bpre, &top0};
-    st = launch(f_mid, (unsigned)((waves + 1023) / 1024), kScanMidBlock, p2a, stream);
-    if (st != HIPMR_OK) return st;
-    void* p2b[5] = {&partial, &waves64, &prefix, &bpre, &top1};
-    st = launch(f_mid, 1, kScanMidBlock, p2b, stream);
-    if (st != HIPMR_OK) return st;
-    p3.insert(p3.end(), {(void*)&n_arg, (void*)&head, (void*)&passes32, (void*)&waves64, (void*)&prefix,
-                         (void*)&bpre, (void*)&out, (void*)&excl});
-    return launch(f_down, grid, (unsigned)cfg.block, p3.data(), stream);
+    return launch(f_scan, (unsigned)tiles, (unsigned)cfg.block, p.data(), stream);
 }
 
 }  // extern "C"
