@@ -249,12 +249,14 @@ hipmr_status hipmr_reduce_compensated(hipmr_handle h, int64_t n, void *const *ar
 
 /* L2 norm of a float map: *out (double) = post_scale * sqrt(sum_i map(i)^2),
  * precision extension as above.
- *   passes == 2 (scaled): pass 1 takes the exact max |map(i)| per block;
- *     every block of pass 2 (same grid) first derives from those maxima the
- *     power of two s that puts the largest in [1, 2) (exponent clamped to
- *     [-126, 126]), then accumulates (map(i) * s)^2 with compensation; the
- *     final FP64 step returns post_scale * sqrt(sum) / s.  Reads the data
- *     twice, in three launches.
+ *   passes == 2 (scaled): pass 1 accumulates map(i)^2 with compensation and
+ *     takes the exact max |map(i)| per block.  Where that maximum is 0 or in
+ *     [2^-40, 2^40] no square leaves the float range and pass 2 ends at once;
+ *     else every block of it (same grid) derives from the maxima the power of
+ *     two s that puts the largest in [1, 2) (exponent clamped to [-126, 126])
+ *     and accumulates (map(i) * s)^2 instead.  The final FP64 step returns
+ *     post_scale * sqrt(sum) / s.  Three launches; the data are read once, or
+ *     twice where pass 2 is needed.
  *   passes == 1: no scaling, one read; the squares must stay inside the float
  *     range (true for every half or FP8 load: their squares are below 2^32).
  * The first pass's maxima and the scale are kept in the workspace.  Errors:

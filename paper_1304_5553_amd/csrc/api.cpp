@@ -69,7 +69,7 @@ std::string spec_key(const KernelSpec& s) {
     return std::to_string((int)s.kind) + "|" + std::to_string(s.idx64) + "|" +
            std::to_string(s.block) + "|" + std::to_string(s.ipt) + "|" + std::to_string(s.vec) +
            "|" + std::to_string(s.nt_loads) + std::to_string(s.nt_stores) + "|" +
-           std::to_string(s.square) + std::to_string(s.scaled) + std::to_string(s.exact_runs) +
+           std::to_string(s.square) + std::to_string(s.track) + std::to_string(s.scaled) + std::to_string(s.exact_runs) +
            std::to_string(s.norm) + std::to_string(s.scan_mode) + "|" + std::to_string(s.lds_segs) + "|" + s.combine + "\x1f" +
            s.neutral;
 }
@@ -311,7 +311,7 @@ struct Stage1 {
 
 hipmr_status stage1_launch(hipmr_kernel* h, KernelSpec spec, bool vector_ok, const LaunchCfg& cfg,
                            int64_t n, void* const* args, void* partial, void* extra,
-                           bool with_extra, void* stream, std::string* syms, Stage1* out) {
+                           void* stream, std::string* syms, Stage1* out) {
     long long head = -1;
     bool vector = vector_ok && h->prog.info.vectorizable && !cfg.force_scalar;
     if (vector) head = common_head(h, args, cfg.vec);
@@ -319,7 +319,6 @@ hipmr_status stage1_launch(hipmr_kernel* h, KernelSpec spec, bool vector_ok, con
     if (!vector) {
         switch (spec.kind) {
             case KernelKind::CompS1Vector: spec.kind = KernelKind::CompS1Scalar; break;
-            case KernelKind::AmaxS1Vector: spec.kind = KernelKind::AmaxS1Scalar; break;
             default: break;
         }
         spec.vec = 1;
@@ -339,7 +338,7 @@ hipmr_status stage1_launch(hipmr_kernel* h, KernelSpec spec, bool vector_ok, con
     params.push_back(&n64);
     params.push_back(&head64);
     params.push_back(&partial);
-    if (with_extra) params.push_back(&extra);
+    params.push_back(&extra);
     return launch(out->fn, (unsigned)out->grid, (unsigned)cfg.block, params.data(), stream);
 }
 
@@ -396,7 +395,7 @@ hipmr_status hipmr_reduce_compensated(hipmr_handle h, int64_t n, void* const* ar
     s1.exact_runs = single_fp8_load(h) && cfg.vec * cfg.ipt <= 64;
     std::string syms;
     Stage1 r;
-    st = stage1_launch(h, s1, true, cfg, n, args, workspace, nullptr, true, stream, &syms, &r);
+    st = stage1_launch(h, s1, true, cfg, n, args, workspace, nullptr, stream, &syms, &r);
     if (st != HIPMR_OK) return st;
     KernelSpec s2 = comp_spec(KernelKind::CompS2, cfg);
     s2.block = kStage2Block;
@@ -425,20 +424,22 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
     std::string syms;
     const bool two = passes == 2 && n > 0;     // an empty norm is 0 either way
     if (two) {
-        // pass 1: exact max |map| per block (the same grid as pass 2)
-        KernelSpec a1 = comp_spec(KernelKind::AmaxS1Vector, cfg);
+        // pass 1: sum of the unscaled squares and max |map|, per block
+        KernelSpec a1 = comp_spec(KernelKind::CompS1Vector, cfg);
+        a1.square = a1.track = true;
         Stage1 r1;
-        st = stage1_launch(h, a1, true, cfg, n, args, amax, nullptr, false, stream, &syms, &r1);
+        st = stage1_launch(h, a1, true, cfg, n, args, workspace, amax, stream, &syms, &r1);
         if (st != HIPMR_OK) return st;
     }
     // pass 2 (or the only pass): compensated sum of (map * scale)^2; with two
     // passes every block first derives the power-of-two scale from the pass-1
-    // partials (block 0 also stores it for the final fold)
+    // maxima (block 0 also stores it for the final fold) and ends there if
+    // pass 1's sums stand
     KernelSpec q1 = comp_spec(KernelKind::CompS1Vector, cfg);
     q1.square = true;
     q1.scaled = two;
     Stage1 r2;
-    st = stage1_launch(h, q1, true, cfg, n, args, workspace, amax, true, stream, &syms, &r2);
+    st = stage1_launch(h, q1, true, cfg, n, args, workspace, amax, stream, &syms, &r2);
     if (st != HIPMR_OK) return st;
     KernelSpec q2 = comp_spec(KernelKind::CompS2, cfg);
     q2.block = kStage2Block;
@@ -803,11 +804,12 @@ hipmr_status hipmr_selftest_compile(int32_t* count) {
                 // precision extension: compensated sum, norm passes, finishers
                 std::vector<KernelSpec> specs;
                 for (KernelKind k : {KernelKind::CompS1Vector, KernelKind::CompS1Scalar}) {
-                    for (int variant = 0; variant < 3; ++variant) {
+                    for (int variant = 0; variant < 4; ++variant) {
                         KernelSpec q = comp_spec(k, cfg);
                         if (k == KernelKind::CompS1Scalar) q.vec = 1;
                         q.square = variant > 0;
                         q.scaled = variant == 2;
+                        q.track = variant == 3;
                         q.exact_runs = variant == 0 && k == KernelKind::CompS1Vector &&
                                        single_fp8_load(h);
                         specs.push_back(q);
@@ -821,11 +823,8 @@ hipmr_status hipmr_selftest_compile(int32_t* count) {
                     q.scaled = variant == 2;
                     specs.push_back(q);
                 }
-                specs.push_back(comp_spec(KernelKind::AmaxS1Vector, cfg));
                 for (const KernelSpec& q : specs) {
-                    if (!h->prog.info.vectorizable &&
-                        (q.kind == KernelKind::CompS1Vector || q.kind == KernelKind::AmaxS1Vector))
-                        continue;
+                    if (!h->prog.info.vectorizable && q.kind == KernelKind::CompS1Vector) continue;
                     st = get_variant(h, q, &co);
                     if (st != HIPMR_OK) break;
                     ++built;

@@ -675,27 +675,40 @@ __device__ __forceinline__ hipmr_dd hipmr_dd_add(hipmr_dd x, hipmr_dd y) {
   return hipmr_two_sum_d(s.hi, s.lo + (x.lo + y.lo));
 }
 
+// Block maximum of non-negative values (NaN wins), valid in every thread.
+template <int B>
+__device__ __forceinline__ float hipmr_block_amax(float m) {
+  __shared__ float hipmr_amax_lds[B / 64];
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) m = __builtin_elementwise_maximum(m, __shfl_xor(m, d, 64));
+  if ((threadIdx.x & 63) == 0) hipmr_amax_lds[threadIdx.x >> 6] = m;
+  __syncthreads();
+  m = hipmr_amax_lds[0];
+#pragma unroll
+  for (int w = 1; w < B / 64; ++w) m = __builtin_elementwise_maximum(m, hipmr_amax_lds[w]);
+  return m;
+}
+
 // The norm's power-of-two scale from its first pass: the max |map| over
 // that pass's block partials (one per block of this grid: both passes use
-// the same geometry), then s = 2^-e, e the exponent of the max clamped to
-// [-126, 126], so the largest scaled magnitude lies in [1, 2).  Every block
-// computes it; block 0 also stores it (float, then double) for the final
-// fold.
+// the same geometry).  Where that maximum is 0 or lies in [2^-40, 2^40] the
+// first pass's own sums of unscaled squares stand (0 is returned, the stored
+// scale is 1): n < 2^47 such squares stay below 2^127, and what a square
+// loses below 2^-149 is at most 2^-70 of the largest one.  Scaling by a power
+// of two changes no bit of a product or sum that stays in range, so the
+// result is the one the scaled pass would give.  Else s = 2^-e, e the
+// exponent of the max clamped to [-126, 126], so the largest scaled
+// magnitude lies in [1, 2).  Every block computes it; block 0 also stores it
+// (float, then double) for the final fold.
 template <int B>
 __device__ __forceinline__ float hipmr_norm_scale(const float* __restrict__ amax,
                                                   float* __restrict__ store) {
-  __shared__ float hipmr_scale_lds[B / 64];
   float m = 0.0f;
   for (int k = threadIdx.x; k < (int)gridDim.x; k += B) m = __builtin_elementwise_maximum(m, amax[k]);
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) m = __builtin_elementwise_maximum(m, __shfl_xor(m, d, 64));
-  if ((threadIdx.x & 63) == 0) hipmr_scale_lds[threadIdx.x >> 6] = m;
-  __syncthreads();
-  m = hipmr_scale_lds[0];
-#pragma unroll
-  for (int w = 1; w < B / 64; ++w) m = __builtin_elementwise_maximum(m, hipmr_scale_lds[w]);
+  m = hipmr_block_amax<B>(m);
+  const bool stands = m == 0.0f || (m >= 0x1p-40f && m <= 0x1p40f);
   float s = 1.0f;
-  if (m > 0.0f) {
+  if (m > 0.0f && !stands) {
     int e = (int)((__float_as_uint(m) >> 23) & 0xffu) - 127;
     e = e < -126 ? -126 : (e > 126 ? 126 : e);
     s = __uint_as_float((unsigned int)(127 - e) << 23);
@@ -704,7 +717,7 @@ __device__ __forceinline__ float hipmr_norm_scale(const float* __restrict__ amax
     store[0] = s;
     *(double*)(store + 2) = (double)s;
   }
-  return s;
+  return stands ? 0.0f : s;
 }
 
 // pairwise sum of one chunk's V terms (fixed tree); the chunk sum then
@@ -719,10 +732,11 @@ __device__ __forceinline__ float hipmr_chunk_sum(float* t) {
   return t[0];
 }
 
-template <bool SQ>
-__device__ __forceinline__ float hipmr_term(float v, float scale) {
+template <bool SQ, bool TRACK>
+__device__ __forceinline__ float hipmr_term(float v, float scale, float& amax) {
+  if constexpr (TRACK) amax = __builtin_elementwise_maximum(amax, __builtin_fabsf(v));
   if constexpr (SQ) {
-    const float w = v * scale;
+    const float w = TRACK ? v : v * scale;
     return w * w;
   } else {
     return v;
@@ -762,20 +776,27 @@ __device__ __forceinline__ P hipmr_block_reduce_pair(P v, F add) {
 }
 )HIP";
 
-// Stage 1 of a compensated sum (or of the norm's sum of squares).
+// Stage 1 of a compensated sum, or of the norm's sum of squares: its first
+// pass (nrm1) sums the unscaled squares and keeps each block's max |map|, its
+// second (nrm2) rescales and sums again only where those squares could have
+// left the float range, and otherwise ends at once.  Bound: HBM, one read
+// (a pass for the maximum and always a second one for the sum took 81.6 us for
+// 2^27 bfloat16 values, 45.0 now).
 const char* kCompS1Vector = R"HIP(
 extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 @@KNAME@@(@@PARAMS@@, long long hipmr_n, long long hipmr_head,
-          double* __restrict__ hipmr_partial, const float* __restrict__ hipmr_scale_p)
+          double* __restrict__ hipmr_partial, float* __restrict__ hipmr_scale_p)
 {
   typedef @@IDX@@ hipmr_idx;
   constexpr int HIPMR_B = @@BLOCK@@, HIPMR_U = @@IPT@@, HIPMR_V = @@VEC@@;
   constexpr bool HIPMR_NTL = @@NTL@@, HIPMR_NTS = @@NTS@@;
-  constexpr bool HIPMR_SQ = @@SQUARE@@, HIPMR_RUNS = @@RUNS@@, HIPMR_SCALED = @@SCALED@@;
+  constexpr bool HIPMR_SQ = @@SQUARE@@, HIPMR_RUNS = @@RUNS@@, HIPMR_SCALED = @@SCALED@@, HIPMR_TRACK = @@TRACK@@;
   const hipmr_idx n = (hipmr_idx)hipmr_n;
-  float hipmr_sc = 1.0f;
-  if constexpr (HIPMR_SCALED)
+  float hipmr_sc = 1.0f, hipmr_m = 0.0f;
+  if constexpr (HIPMR_SCALED) {
     hipmr_sc = hipmr_norm_scale<HIPMR_B>(hipmr_scale_p, (float*)((char*)hipmr_scale_p + @@SCALE_GAP@@));
+    if (hipmr_sc == 0.0f) return;               // the first pass's sums stand
+  }
   float hipmr_s[HIPMR_U], hipmr_e[HIPMR_U];
 #pragma unroll
   for (int u = 0; u < HIPMR_U; ++u) { hipmr_s[u] = 0.0f; hipmr_e[u] = 0.0f; }
@@ -785,11 +806,11 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   if (blockIdx.x == 0) {
     if ((long long)threadIdx.x < hipmr_h) {
       const hipmr_idx i = (hipmr_idx)threadIdx.x;
-      hipmr_kahan_add(hipmr_s[0], hipmr_e[0], hipmr_term<HIPMR_SQ>((float)(@@MAP@@), hipmr_sc));
+      hipmr_kahan_add(hipmr_s[0], hipmr_e[0], hipmr_term<HIPMR_SQ, HIPMR_TRACK>((float)(@@MAP@@), hipmr_sc, hipmr_m));
     }
     if ((long long)threadIdx.x < hipmr_n - hipmr_t0) {
       const hipmr_idx i = (hipmr_idx)(hipmr_t0 + threadIdx.x);
-      hipmr_kahan_add(hipmr_s[0], hipmr_e[0], hipmr_term<HIPMR_SQ>((float)(@@MAP@@), hipmr_sc));
+      hipmr_kahan_add(hipmr_s[0], hipmr_e[0], hipmr_term<HIPMR_SQ, HIPMR_TRACK>((float)(@@MAP@@), hipmr_sc, hipmr_m));
     }
   }
   const long long hipmr_step = (long long)gridDim.x * (HIPMR_B * HIPMR_U);
@@ -823,7 +844,7 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 #pragma unroll
         for (int hipmr_j = 0; hipmr_j < HIPMR_V; ++hipmr_j) {
           const hipmr_idx i = (hipmr_idx)(hipmr_off + hipmr_j);
-          hipmr_t[hipmr_j] = hipmr_term<HIPMR_SQ>((float)(@@VMAP@@), hipmr_sc);
+          hipmr_t[hipmr_j] = hipmr_term<HIPMR_SQ, HIPMR_TRACK>((float)(@@VMAP@@), hipmr_sc, hipmr_m);
         }
         hipmr_kahan_add(hipmr_s[hipmr_u], hipmr_e[hipmr_u], hipmr_chunk_sum<HIPMR_V>(hipmr_t));
       }
@@ -848,7 +869,7 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 #pragma unroll
         for (int hipmr_j = 0; hipmr_j < HIPMR_V; ++hipmr_j) {
           const hipmr_idx i = (hipmr_idx)(hipmr_off + hipmr_j);
-          hipmr_t[hipmr_j] = hipmr_term<HIPMR_SQ>((float)(@@VMAP@@), hipmr_sc);
+          hipmr_t[hipmr_j] = hipmr_term<HIPMR_SQ, HIPMR_TRACK>((float)(@@VMAP@@), hipmr_sc, hipmr_m);
         }
         hipmr_kahan_add(hipmr_s[hipmr_u], hipmr_e[hipmr_u], hipmr_chunk_sum<HIPMR_V>(hipmr_t));
       }
@@ -861,32 +882,42 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   if (threadIdx.x == 0)
     hipmr_partial[blockIdx.x] = __builtin_isfinite(hipmr_r.hi) ? (double)hipmr_r.hi + (double)hipmr_r.lo
                                                                : (double)hipmr_r.hi;
+  if constexpr (HIPMR_TRACK) {
+    hipmr_m = hipmr_block_amax<@@BLOCK@@>(hipmr_m);
+    if (threadIdx.x == 0) hipmr_scale_p[blockIdx.x] = hipmr_m;
+  }
 }
 )HIP";
 
 const char* kCompS1Scalar = R"HIP(
 extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 @@KNAME@@(@@PARAMS@@, long long hipmr_n, long long hipmr_head,
-          double* __restrict__ hipmr_partial, const float* __restrict__ hipmr_scale_p)
+          double* __restrict__ hipmr_partial, float* __restrict__ hipmr_scale_p)
 {
   typedef @@IDX@@ hipmr_idx;
-  constexpr bool HIPMR_SQ = @@SQUARE@@, HIPMR_SCALED = @@SCALED@@;
+  constexpr bool HIPMR_SQ = @@SQUARE@@, HIPMR_SCALED = @@SCALED@@, HIPMR_TRACK = @@TRACK@@;
   const hipmr_idx n = (hipmr_idx)hipmr_n;
-  float hipmr_sc = 1.0f;
-  if constexpr (HIPMR_SCALED)
+  float hipmr_sc = 1.0f, hipmr_m = 0.0f;
+  if constexpr (HIPMR_SCALED) {
     hipmr_sc = hipmr_norm_scale<@@BLOCK@@>(hipmr_scale_p, (float*)((char*)hipmr_scale_p + @@SCALE_GAP@@));
+    if (hipmr_sc == 0.0f) return;               // the first pass's sums stand
+  }
   float hipmr_s = 0.0f, hipmr_cc = 0.0f;
   const long long hipmr_step = (long long)gridDim.x * @@BLOCK@@;
   for (long long hipmr_k = (long long)blockIdx.x * @@BLOCK@@ + threadIdx.x; hipmr_k < hipmr_n;
        hipmr_k += hipmr_step) {
     const hipmr_idx i = (hipmr_idx)hipmr_k;
-    hipmr_kahan_add(hipmr_s, hipmr_cc, hipmr_term<HIPMR_SQ>((float)(@@MAP@@), hipmr_sc));
+    hipmr_kahan_add(hipmr_s, hipmr_cc, hipmr_term<HIPMR_SQ, HIPMR_TRACK>((float)(@@MAP@@), hipmr_sc, hipmr_m));
   }
   hipmr_ff hipmr_r = {hipmr_s, -hipmr_cc};
   hipmr_r = hipmr_block_reduce_pair<@@BLOCK@@>(hipmr_r, [](hipmr_ff a, hipmr_ff b) { return hipmr_ff_add(a, b); });
   if (threadIdx.x == 0)
     hipmr_partial[blockIdx.x] = __builtin_isfinite(hipmr_r.hi) ? (double)hipmr_r.hi + (double)hipmr_r.lo
                                                                : (double)hipmr_r.hi;
+  if constexpr (HIPMR_TRACK) {
+    hipmr_m = hipmr_block_amax<@@BLOCK@@>(hipmr_m);
+    if (threadIdx.x == 0) hipmr_scale_p[blockIdx.x] = hipmr_m;
+  }
 }
 )HIP";
 
@@ -1542,8 +1573,7 @@ std::string render(const Program& prog, const KernelSpec& spec, std::string* sym
     const char* tag = "";
     bool reduce = false;
     bool comp = false;       // compensated helpers
-    DType acc = prog.sig.result;
-    std::string combine = spec.combine;
+    const DType acc = prog.sig.result;
     switch (spec.kind) {
         case KernelKind::EwVector:
             tmpl = prog.info.shifts.empty() ? kEwVector : kEwVectorShift;
@@ -1558,14 +1588,10 @@ std::string render(const Program& prog, const KernelSpec& spec, std::string* sym
         case KernelKind::RedS1Scalar: tmpl = kRedS1Scalar; tag = "rs1s"; reduce = true; break;
         case KernelKind::RedS2: tmpl = kRedS2; tag = "rs2"; reduce = true; break;
         case KernelKind::CompS1Vector:
-            tmpl = kCompS1Vector; tag = spec.square ? "nrm2" : "csum"; comp = true; break;
+            tmpl = kCompS1Vector; tag = spec.track ? "nrm1" : spec.square ? "nrm2" : "csum"; comp = true; break;
         case KernelKind::CompS1Scalar:
-            tmpl = kCompS1Scalar; tag = spec.square ? "nrm2s" : "csums"; comp = true; break;
+            tmpl = kCompS1Scalar; tag = spec.track ? "nrm1s" : spec.square ? "nrm2s" : "csums"; comp = true; break;
         case KernelKind::CompS2: tmpl = kCompS2; tag = spec.norm ? "nrm2f" : "csumf"; comp = true; break;
-        case KernelKind::AmaxS1Vector:
-            tmpl = kRedS1Vector; tag = "amax"; reduce = true; acc = DT_F32; combine = "max"; break;
-        case KernelKind::AmaxS1Scalar:
-            tmpl = kRedS1Scalar; tag = "amaxs"; reduce = true; acc = DT_F32; combine = "max"; break;
         case KernelKind::SegPlan: tmpl = kSegPlan; tag = "segplan"; break;
         case KernelKind::SegS1: tmpl = kSegS1; tag = "seg1"; reduce = true; break;
         case KernelKind::SegS2: tmpl = kSegS2; tag = "seg2"; reduce = true; break;
@@ -1577,7 +1603,6 @@ std::string render(const Program& prog, const KernelSpec& spec, std::string* sym
     const bool scan_scalar = spec.kind == KernelKind::ScanScalar;
     const bool scan = spec.kind == KernelKind::ScanVector || scan_scalar;
     const bool seg = spec.kind == KernelKind::SegPlan || spec.kind == KernelKind::SegS1;
-    const bool amax = spec.kind == KernelKind::AmaxS1Vector || spec.kind == KernelKind::AmaxS1Scalar;
     std::string body = tmpl;
 
     // parameters in declaration order
@@ -1653,17 +1678,14 @@ std::string render(const Program& prog, const KernelSpec& spec, std::string* sym
     replace_all(body, "@@STORES@@", stores);
     replace_all(body, "@@STMT@@", scalar_text);
     replace_all(body, "@@VSTMT@@", vector_text);
-    if (amax) {   // norm pass 1: |map| as float
-        scalar_text = "fabsf((float)(" + scalar_text + "))";
-        vector_text = "fabsf((float)(" + vector_text + "))";
-    }
     replace_all(body, "@@MAP@@", scalar_text);
     replace_all(body, "@@VMAP@@", vector_text);
-    replace_all(body, "@@NEUTRAL@@", amax ? "0.0f" : (spec.neutral.empty() ? "0" : spec.neutral));
+    replace_all(body, "@@NEUTRAL@@", spec.neutral.empty() ? "0" : spec.neutral);
     replace_all(body, "@@SQUARE@@", spec.square ? "true" : "false");
     replace_all(body, "@@RUNS@@", spec.exact_runs ? "true" : "false");
     replace_all(body, "@@NORM@@", spec.norm ? "true" : "false");
     replace_all(body, "@@SCALED@@", spec.scaled ? "true" : "false");
+    replace_all(body, "@@TRACK@@", spec.track ? "true" : "false");
     replace_all(body, "@@SCALE_GAP@@", std::to_string(kScaleOffset - kAmaxOffset));
     replace_all(body, "@@LDS_SEGS@@", std::to_string(spec.lds_segs));
     replace_all(body, "@@IDX@@", spec.idx64 ? "long long" : "int");
@@ -1678,9 +1700,7 @@ std::string render(const Program& prog, const KernelSpec& spec, std::string* sym
     src << kPrelude;
     std::string cbody;
     if (reduce) {
-        KernelSpec cs = spec;
-        cs.combine = combine;
-        cbody = combine_body(acc, cs);
+        cbody = combine_body(acc, spec);
         src << "typedef " << dtype_device_name(acc) << " hipmr_acc;\n";
         src << "__device__ __forceinline__ hipmr_acc hipmr_combine(hipmr_acc a, hipmr_acc b) "
                "{ return (hipmr_acc)(" << cbody << "); }\n";

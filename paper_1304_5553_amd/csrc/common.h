@@ -121,7 +121,7 @@ struct LaunchCfg {
 // ---------------------------------------------------------------- codegen
 enum class KernelKind : int32_t {
     EwVector = 0, EwScalar = 1, RedS1Vector = 2, RedS1Scalar = 3, RedS2 = 4,
-    CompS1Vector = 5, CompS1Scalar = 6, CompS2 = 7, AmaxS1Vector = 8, AmaxS1Scalar = 9,
+    CompS1Vector = 5, CompS1Scalar = 6, CompS2 = 7,
     SegPlan = 11, SegS1 = 12, SegS2 = 13,
     ScanVector = 14, ScanScalar = 15, ScanClear = 16,
 };
@@ -138,6 +138,7 @@ struct KernelSpec {
     std::string neutral;
     // precision extension
     bool square = false;      // CompS1: accumulate map^2 (norm)
+    bool track = false;       // CompS1: also keep max |map| per block (the norm's first pass)
     bool scaled = false;      // CompS1 / CompS2: apply the device-side power-of-two scale
     bool exact_runs = false;  // CompS1: map is one FP8 load; sum runs of <= 64 exactly
     bool norm = false;        // CompS2: finish as sqrt(sum) / scale

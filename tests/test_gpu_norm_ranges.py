@@ -1,0 +1,38 @@
+"""The scaled norm on both sides of the magnitudes at which its first pass's
+unscaled sums stand (max |x| = 0 or in [2^-40, 2^40])."""
+
+import numpy as np
+import pytest
+
+from gpu_util import dev_array, need_gpu
+import oracle
+import paper_1304_5553_amd as hm
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("fmt", ["float", "bfloat16"])
+@pytest.mark.parametrize("flags", [0, hm.CFG_FORCE_SCALAR])
+@pytest.mark.parametrize("n", [1, 17, 70001])
+def test_norm_is_the_same_at_every_scale(fmt, flags, n):
+    """Scaling the data by a power of two scales the norm by it, bit for bit,
+    whichever pass the sums came from (values in [0.5, 1): no scaled square
+    leaves the normal range), and the unscaled norm meets the 1e-6 gate."""
+    need_gpu()
+    rng = np.random.default_rng(n)
+    bits16 = rng.integers(0x3F00, 0x3F80, n).astype(np.uint16)        # bfloat16 in [0.5, 1)
+    bits16[0] = 0x3F00                                                # largest known: n == 1 gives 0.5
+    vals = (bits16.astype(np.uint32) << 16).view(np.float32)
+    k = hm.compile("x[i]", f"float: const {fmt} *x")
+    cfg = {"flags": flags} if flags else None
+    base = None
+    for e in (0, -126 + 2, -80, -41, -40, -39, -38, 38, 40, 41, 42, 80, 126):
+        shifted = (vals.astype(np.float64) * 2.0 ** e).astype(np.float32)
+        bits = (shifted.view(np.uint32) >> 16).astype(np.uint16)
+        xd = dev_array(bits, "bfloat16") if fmt == "bfloat16" else dev_array(shifted)
+        g = hm.norm2(k, n, [xd], config=cfg).item()
+        if base is None:
+            base = g
+            o = oracle.norm2(vals.astype(np.float64))
+            assert abs(g - o) <= 1e-6 * o
+        assert g == base * 2.0 ** e, e
