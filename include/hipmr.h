@@ -155,9 +155,10 @@ hipmr_status hipmr_compile_named(const char *expr, const char *dtypes, const cha
  * The vector kernel runs when every array access is name[i], a fixed element,
  * or a shifted read name[i + E] / name[i - E] of an array the statement does
  * not write (E built from literals, scalar arguments, n, + - * / % and
- * parentheses: the same distance for every i), and the name[i] arrays share
+ * parentheses: the same distance for every i), and the arrays it writes share
  * one misalignment: 16-byte chunks for name[i] (unaligned head and ragged tail
- * by scalar code), one unaligned chunk load per distinct shifted read, and,
+ * by scalar code; arrays that are only read and share another misalignment are
+ * loaded unaligned), one unaligned chunk load per distinct shifted read, and,
  * for chunks within the largest distance of either end, the statement one
  * element at a time (its own guards apply there; shifted chunks are read only
  * inside [0, n)).  With shifted reads, workgroups are renumbered so that each
@@ -286,13 +287,13 @@ size_t hipmr_scan_workspace_bytes(hipmr_handle h, int64_t n);
  * a rescan from them; or a clear of the workspace's counters and one pass in
  * which tiles publish their totals and wait for their predecessors'.  The
  * workspace belongs to one call at a time.  The order of combination depends
- * only on n, alignment and geometry (bitwise
- * repeatable).  Chunked accesses when every array and out share one
- * alignment and the map reads arrays only as name[i] (by default 16 bytes of
- * the narrowest input, but at most 16 bytes of output, per lane); one
- * element at a time otherwise.  n == 0 writes nothing.  Errors: E_INVALID (NULL, exclusive not
- * 0/1), E_MISMATCH (elementwise handle), E_WORKSPACE, E_PARSE / E_COMPILE
- * (combine or neutral), E_HIP. */
+ * only on n, alignment and geometry (bitwise repeatable).  Chunked accesses
+ * when the map reads arrays as the vector kernels can (by default 16 bytes of
+ * the narrowest input, but at most 16 bytes of output, per lane; out aligned,
+ * inputs loaded unaligned where they share another misalignment); one
+ * element at a time otherwise.  n == 0 writes nothing.  Errors: E_INVALID
+ * (NULL, exclusive not 0/1), E_MISMATCH (elementwise handle), E_WORKSPACE,
+ * E_PARSE / E_COMPILE (combine or neutral), E_HIP. */
 hipmr_status hipmr_scan(hipmr_handle h, const char *combine_op, const char *neutral, int64_t n,
                         void *const *args, void *out, int32_t exclusive, void *workspace,
                         size_t workspace_bytes, const hipmr_launch_config *cfg, void *stream);

@@ -68,7 +68,7 @@ hipmr_status resolve_cfg(const hipmr_launch_config* c, int block, int ipt, int v
 std::string spec_key(const KernelSpec& s) {
     return std::to_string((int)s.kind) + "|" + std::to_string(s.idx64) + "|" +
            std::to_string(s.block) + "|" + std::to_string(s.ipt) + "|" + std::to_string(s.vec) +
-           "|" + std::to_string(s.nt_loads) + std::to_string(s.nt_stores) + "|" +
+           "|" + std::to_string(s.nt_loads) + std::to_string(s.nt_stores) + std::to_string(s.unaligned) + "|" +
            std::to_string(s.square) + std::to_string(s.track) + std::to_string(s.scaled) + std::to_string(s.exact_runs) +
            std::to_string(s.norm) + std::to_string(s.scan_mode) + "|" + std::to_string(s.lds_segs) + "|" + s.combine + "\x1f" +
            s.neutral;
@@ -116,22 +116,53 @@ void set_last_symbols(hipmr_kernel* h, const std::string& syms) {
     h->last_symbols = syms;
 }
 
-// Element offset "head" at which every accessed array is aligned for the
-// vector chunk loads; -1 if no common offset exists.
-long long common_head(const hipmr_kernel* h, void* const* args, int vec) {
+// Where no offset aligns every array, the arrays that are only read are loaded
+// at element alignment instead of leaving the chunk kernels: the written ones
+// must be aligned (a store that straddles lines costs a partial write of each),
+// the reads need not be.  At the offset chosen, the most bytes per element are
+// aligned.  Measured against the one-element kernels, inputs rotated:
+// x[1:] - x[:-1] of 50,000,004 floats 67.4 us against 87.6; a 2^26 lincomb with
+// one shifted input 126.3 against 152.5 (all aligned: 125.0); a 2^27 dot 155.6
+// against 191.3 (aligned 155.5); quantising 2^26 bfloat16 to FP8 36.0 against
+// 54.9; at 100,003 elements 5.4 against 5.8, so there is no lower limit.
+long long vector_head(const hipmr_kernel* h, void* const* args, LaunchCfg* cfg, const void* out,
+                      int out_size) {
+    cfg->unaligned = false;
+    if (!h->prog.info.vectorizable || cfg->force_scalar) return -1;
+    const int vec = cfg->vec;
+    const auto aligned = [&](uintptr_t p, int s, int head) {
+        return (p + (uintptr_t)head * s) % (uintptr_t)std::min(vec * s, 16) == 0;
+    };
+    if (out_size && (uintptr_t)out % (uintptr_t)out_size != 0) return -1;
+    int all_bytes = 0;               // per element, of every array moved in chunks
+    for (size_t k = 0; k < h->prog.sig.args.size(); ++k) {
+        const ArgDecl& a = h->prog.sig.args[k];
+        if (!chunked(a)) continue;
+        if ((uintptr_t)(*(void* const*)args[k]) % (uintptr_t)dtype_size(a.dtype) != 0) return -1;
+        all_bytes += dtype_size(a.dtype);
+    }
+    long long best = -1;
+    int best_bytes = -1;
     for (int head = 0; head < vec; ++head) {
-        bool ok = true;
+        bool ok = !out_size || aligned((uintptr_t)out, out_size, head);
+        int bytes = 0;               // of the arrays aligned here
         for (size_t k = 0; k < h->prog.sig.args.size() && ok; ++k) {
             const ArgDecl& a = h->prog.sig.args[k];
             if (!chunked(a)) continue;
-            uintptr_t p = (uintptr_t)(*(void* const*)args[k]);
-            int s = dtype_size(a.dtype);
-            uintptr_t align = (uintptr_t)std::min(vec * s, 16);
-            if (p % (uintptr_t)s != 0 || (p + (uintptr_t)head * s) % align != 0) ok = false;
+            const uintptr_t p = (uintptr_t)(*(void* const*)args[k]);
+            const int s = dtype_size(a.dtype);
+            const bool here = aligned(p, s, head);
+            if (a.written && !here) ok = false;
+            bytes += here ? s : 0;
         }
-        if (ok) return head;
+        if (ok && bytes > best_bytes) {
+            best = head;
+            best_bytes = bytes;
+            if (bytes == all_bytes) break;
+        }
     }
-    return -1;
+    cfg->unaligned = best >= 0 && best_bytes < all_bytes;
+    return best;
 }
 
 hipmr_status check_args(hipmr_kernel* h, int64_t n, void* const* args) {
@@ -280,6 +311,7 @@ KernelSpec s1_spec(const hipmr_kernel* h, bool vector, const LaunchCfg& cfg, boo
     s.vec = vector ? cfg.vec : 1;
     s.nt_loads = cfg.nt_loads;
     s.nt_stores = cfg.nt_stores;
+    s.unaligned = cfg.unaligned;
     s.combine = combine;
     s.neutral = neutral;
     return s;
@@ -309,18 +341,14 @@ struct Stage1 {
     long long head = 0;
 };
 
-hipmr_status stage1_launch(hipmr_kernel* h, KernelSpec spec, bool vector_ok, const LaunchCfg& cfg,
+hipmr_status stage1_launch(hipmr_kernel* h, KernelSpec spec, LaunchCfg cfg,
                            int64_t n, void* const* args, void* partial, void* extra,
                            void* stream, std::string* syms, Stage1* out) {
-    long long head = -1;
-    bool vector = vector_ok && h->prog.info.vectorizable && !cfg.force_scalar;
-    if (vector) head = common_head(h, args, cfg.vec);
-    if (head < 0) vector = false;
+    const long long head = vector_head(h, args, &cfg);
+    const bool vector = head >= 0;
+    spec.unaligned = cfg.unaligned;
     if (!vector) {
-        switch (spec.kind) {
-            case KernelKind::CompS1Vector: spec.kind = KernelKind::CompS1Scalar; break;
-            default: break;
-        }
+        spec.kind = KernelKind::CompS1Scalar;
         spec.vec = 1;
         spec.exact_runs = false;
     }
@@ -350,6 +378,7 @@ KernelSpec comp_spec(KernelKind kind, const LaunchCfg& cfg) {
     s.vec = cfg.vec;
     s.nt_loads = cfg.nt_loads;
     s.nt_stores = cfg.nt_stores;
+    s.unaligned = cfg.unaligned;
     return s;
 }
 
@@ -395,7 +424,7 @@ hipmr_status hipmr_reduce_compensated(hipmr_handle h, int64_t n, void* const* ar
     s1.exact_runs = single_fp8_load(h) && cfg.vec * cfg.ipt <= 64;
     std::string syms;
     Stage1 r;
-    st = stage1_launch(h, s1, true, cfg, n, args, workspace, nullptr, stream, &syms, &r);
+    st = stage1_launch(h, s1, cfg, n, args, workspace, nullptr, stream, &syms, &r);
     if (st != HIPMR_OK) return st;
     KernelSpec s2 = comp_spec(KernelKind::CompS2, cfg);
     s2.block = kStage2Block;
@@ -428,7 +457,7 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
         KernelSpec a1 = comp_spec(KernelKind::CompS1Vector, cfg);
         a1.square = a1.track = true;
         Stage1 r1;
-        st = stage1_launch(h, a1, true, cfg, n, args, workspace, amax, stream, &syms, &r1);
+        st = stage1_launch(h, a1, cfg, n, args, workspace, amax, stream, &syms, &r1);
         if (st != HIPMR_OK) return st;
     }
     // pass 2 (or the only pass): compensated sum of (map * scale)^2; with two
@@ -439,7 +468,7 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
     q1.square = true;
     q1.scaled = two;
     Stage1 r2;
-    st = stage1_launch(h, q1, true, cfg, n, args, workspace, amax, stream, &syms, &r2);
+    st = stage1_launch(h, q1, cfg, n, args, workspace, amax, stream, &syms, &r2);
     if (st != HIPMR_OK) return st;
     KernelSpec q2 = comp_spec(KernelKind::CompS2, cfg);
     q2.block = kStage2Block;
@@ -479,10 +508,8 @@ hipmr_status hipmr_elementwise_ex(hipmr_handle h, int64_t n, void* const* args,
     st = resolve_cfg(cfgp, kEwBlock, kEwIpt, h->default_vec, kEwBlocksPerCu, &cfg);
     if (st != HIPMR_OK) return st;
     if (n == 0) return HIPMR_OK;
-    long long head = -1;
-    bool vector = h->prog.info.vectorizable && !cfg.force_scalar;
-    if (vector) head = common_head(h, args, cfg.vec);
-    if (head < 0) vector = false;
+    const long long head = vector_head(h, args, &cfg);
+    const bool vector = head >= 0;
     // the one-element kernel does best as a grid-stride loop over a resident
     // grid (measured on MI355X with a five-point stencil: 30 us against 37 us
     // for one element per thread over a full grid)
@@ -495,6 +522,7 @@ hipmr_status hipmr_elementwise_ex(hipmr_handle h, int64_t n, void* const* args,
     spec.vec = vector ? cfg.vec : 1;
     spec.nt_loads = cfg.nt_loads;
     spec.nt_stores = cfg.nt_stores;
+    spec.unaligned = cfg.unaligned;
     void* fn = nullptr;
     std::string syms;
     st = variant_function(h, spec, &fn, &syms);
@@ -563,10 +591,8 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
     int grid = 0;
     std::string syms;
     if (n > 0) {
-        long long head = -1;
-        bool vector = h->prog.info.vectorizable && !cfg.force_scalar;
-        if (vector) head = common_head(h, args, cfg.vec);
-        if (head < 0) vector = false;
+        const long long head = vector_head(h, args, &cfg);
+        const bool vector = head >= 0;
         head64 = vector ? head : 0;
         void* fn = nullptr;
         st = variant_function(h, s1_spec(h, vector, cfg, n >= (int64_t(1) << 31), combine, neutral), &fn,

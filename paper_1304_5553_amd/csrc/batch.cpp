@@ -86,7 +86,10 @@ KernelSpec seg_spec(KernelKind kind, const LaunchCfg& cfg, bool idx64, const cha
         s.combine = combine;
         s.neutral = neutral;
     }
-    if (kind == KernelKind::SegS1) s.lds_segs = lds;
+    if (kind == KernelKind::SegS1) {
+        s.lds_segs = lds;
+        s.unaligned = cfg.unaligned;
+    }
     if (kind == KernelKind::SegS2) {
         s.block = kSegBlock;
         s.ipt = 1;
@@ -101,8 +104,8 @@ hipmr_status seg_prepare(hipmr_kernel* h, const char* combine, const char* neutr
                          int64_t total_n, void* const* args, const LaunchCfg& cfg_in,
                          std::string* syms, SegLaunch* out) {
     LaunchCfg cfg = cfg_in;
-    long long head = h->prog.info.vectorizable && !cfg.force_scalar ? common_head(h, args, cfg.vec) : -1;
-    if (head < 0) {       // no common alignment (or scalar access): one-element chunks
+    long long head = vector_head(h, args, &cfg);
+    if (head < 0) {       // scalar access: one-element chunks
         cfg.vec = 1;
         head = 0;
     }
@@ -396,8 +399,7 @@ hipmr_status hipmr_autotune_segmented(hipmr_handle h, const char* combine, const
             hipmr_status s2 = resolve_cfg(&cands[c], kSegBlock, kSegIpt, h->default_vec, kSegBlocksPerCu, &cfg);
             if (s2 != HIPMR_OK) return s2;
             // compile only: building variants never touches the GPU
-            long long head = h->prog.info.vectorizable ? common_head(h, args, cfg.vec) : -1;
-            if (head < 0) cfg.vec = 1;
+            if (vector_head(h, args, &cfg) < 0) cfg.vec = 1;
             bool idx64 = total_n >= (int64_t(1) << 31);
             int lds = lds_capacity(nseg);
             std::shared_ptr<CodeObject> co;

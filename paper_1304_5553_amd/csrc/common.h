@@ -115,6 +115,7 @@ struct LaunchCfg {
     bool nt_loads = true;   // streaming (non-temporal) loads
     bool nt_stores = true;  // streaming (non-temporal) stores
     bool force_scalar = false;
+    bool unaligned = false;   // some arrays are read at element alignment (set by vector_head)
     bool seg_global = false;  // segmented: tile table in global memory
 };
 
@@ -134,6 +135,7 @@ struct KernelSpec {
     int vec = 4;
     bool nt_loads = true;
     bool nt_stores = true;
+    bool unaligned = false;   // chunk loads at element alignment
     std::string combine;      // reduce kinds
     std::string neutral;
     // precision extension

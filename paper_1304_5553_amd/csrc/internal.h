@@ -46,9 +46,14 @@ hipmr_status get_variant(hipmr_kernel* h, const KernelSpec& spec, std::shared_pt
 hipmr_status variant_function(hipmr_kernel* h, const KernelSpec& spec, void** fn,
                               std::string* syms);
 void set_last_symbols(hipmr_kernel* h, const std::string& syms);
-// element offset at which every accessed array is aligned for VEC-element
-// chunk loads, or -1
-long long common_head(const hipmr_kernel* h, void* const* args, int vec);
+// Element offset at which the chunks start, or -1 for the one-element kernels
+// (a map or statement that cannot run on chunks, or an array off its element
+// alignment): every written array is aligned for VEC-element chunks there, and
+// so are all read ones, or cfg->unaligned is set and those that are not are
+// loaded at element alignment.  `out` of `out_size` bytes per element (0: none)
+// is written besides the arguments.
+long long vector_head(const hipmr_kernel* h, void* const* args, LaunchCfg* cfg,
+                      const void* out = nullptr, int out_size = 0);
 hipmr_status check_args(hipmr_kernel* h, int64_t n, void* const* args);
 int grid_for(long long work_units, int per_block, const LaunchCfg& cfg, int cap);
 // geometry stored by the autotuner for (op, combine, neutral, size class of n)

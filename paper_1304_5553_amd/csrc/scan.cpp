@@ -46,27 +46,6 @@ constexpr long long kScanBigTile = 16384;    // elements of the largest one-elem
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
-// Element offset at which every accessed array and the output are aligned
-// for VEC-element chunks, or -1.
-long long scan_head(const hipmr_kernel* h, void* const* args, const void* out, int vec) {
-    const int rs = dtype_size(h->prog.sig.result);
-    for (long long head = 0; head < vec; ++head) {
-        bool ok = true;
-        for (size_t k = 0; k < h->prog.sig.args.size() && ok; ++k) {
-            const ArgDecl& a = h->prog.sig.args[k];
-            if (!chunked(a)) continue;
-            uintptr_t p = (uintptr_t)(*(void* const*)args[k]);
-            int s = dtype_size(a.dtype);
-            uintptr_t align = (uintptr_t)std::min(vec * s, 16);
-            if (p % (uintptr_t)s != 0 || (p + (uintptr_t)head * s) % align != 0) ok = false;
-        }
-        uintptr_t o = (uintptr_t)out;
-        if (o % (uintptr_t)rs != 0 || (o + (uintptr_t)head * rs) % 16 != 0) ok = false;
-        if (ok) return head;
-    }
-    return -1;
-}
-
 KernelSpec scan_spec(bool vector, int mode, const LaunchCfg& cfg, bool idx64, const char* combine,
                      const char* neutral) {
     KernelSpec s;
@@ -78,6 +57,7 @@ KernelSpec scan_spec(bool vector, int mode, const LaunchCfg& cfg, bool idx64, co
     s.vec = cfg.vec;
     s.nt_loads = cfg.nt_loads;
     s.nt_stores = cfg.nt_stores;
+    s.unaligned = cfg.unaligned;
     s.combine = combine;
     s.neutral = neutral;
     return s;
@@ -123,7 +103,7 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
     if (st != HIPMR_OK) return st;
 
     const long long n64 = n;
-    const long long head = h->prog.info.vectorizable && !cfg.force_scalar ? scan_head(h, args, out, cfg.vec) : -1;
+    const long long head = vector_head(h, args, &cfg, out, (int)rs);
     const bool vector = head >= 0;
     if (!vector) cfg.vec = 1;
     long long base = head > 0 ? head - cfg.vec : 0;       // tile 0 starts at an aligned element
