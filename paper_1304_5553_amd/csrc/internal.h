@@ -12,7 +12,8 @@ struct hipmr_kernel {
     bool cached = false;          // listed in the handle cache under cache_key
     std::string cache_key;
     hipmr::Program prog;
-    int default_vec = 4;
+    int default_vec = 4;          // elements per chunk, and of the elementwise kernels
+    int ew_vec = 4, ew_ipt = 1;   // (with the chunks per thread)
     std::mutex mu;
     std::map<std::string, std::shared_ptr<hipmr::CodeObject>> variants;
     std::string last_symbols;                        // kernels of the most recent call
@@ -37,6 +38,7 @@ constexpr size_t kWorkspaceBytes = kScaleOffset + 256;
 // in flight per thread and array); elementwise kernels, which mix reads and
 // writes, do best as one pass over a full grid (one chunk per thread).
 constexpr int kEwBlock = 256, kEwIpt = 1, kEwBlocksPerCu = 1 << 20;
+constexpr int kEwMixedIpt = 2;               // arrays of different element sizes (see default_ew_shape)
 constexpr int kEwScalarBlocksPerCu = 32;     // one-element elementwise kernels
 constexpr int kRedBlock = 256, kRedIpt = 4, kRedBlocksPerCu = 2;
 

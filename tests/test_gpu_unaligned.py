@@ -45,7 +45,7 @@ EW = [("z[i] = 2.5f*x[i] - 0.5f*y[i]", "float *z, const float *x, const float *y
 
 
 @pytest.mark.parametrize("case", range(len(EW)))
-@pytest.mark.parametrize("offsets", [(0, 1, 0), (1, 0, 1), (0, 1, 2), (3, 2, 5)])
+@pytest.mark.parametrize("offsets", [(0, 0, 0), (0, 1, 0), (1, 0, 1), (0, 1, 2), (3, 2, 5)])
 def test_elementwise_equals_one_element_kernel(dev, case, offsets):
     stmt, sig, dts = EW[case]
     k = hm.compile(stmt, sig, name="unal_ew")
