@@ -299,6 +299,31 @@ hipmr_status hipmr_scan(hipmr_handle h, const char *combine_op, const char *neut
                         void *const *args, void *out, int32_t exclusive, void *workspace,
                         size_t workspace_bytes, const hipmr_launch_config *cfg, void *stream);
 
+/* ------------------------------------------------------------------ conjugate gradients */
+
+/* Bytes of device workspace hipmr_poisson_cg needs (block partials and a
+ * second buffer of p); 0 for an invalid grid. */
+size_t hipmr_poisson_cg_workspace_bytes(int64_t nx, int64_t ny);
+
+/* Runs `iters` conjugate-gradient iterations on the five-point operator of an
+ * nx by ny grid with zero boundary values (unknown (j, k) at j nx + k;
+ * section "Further Facilities": a CG Krylov solver).
+ *   b:       NULL to continue from x, r, p and s, or the right-hand side: x = 0,
+ *            r = p = b and s[2 parity] = b . b come first.
+ *   x, r, p: device arrays of nx ny floats, updated in place.
+ *   q:       device array of nx ny floats; holds A p of the last iteration.
+ *   s:       four device floats, two (r . r, p . A p) pairs: iteration k reads
+ *            r . r from pair (parity + k) mod 2, writes its p . A p there and
+ *            the next r . r into the other pair.
+ * 2 iters + 1 launches (one more with b), asynchronous on `stream`, nothing
+ * allocated.  Sums in FP64; the result depends only on the arguments (not on
+ * how a run of iterations is divided into calls).  iters == 0: only the
+ * start runs, if b is given.  Errors: E_INVALID, E_WORKSPACE, E_UNSUPPORTED
+ * (2^31 tiles), E_COMPILE, E_HIP. */
+hipmr_status hipmr_poisson_cg(int64_t nx, int64_t ny, const void *b, int32_t iters, void *x, void *r,
+                              void *p, void *q, void *s, int32_t parity, void *workspace,
+                              size_t workspace_bytes, void *stream);
+
 /* ------------------------------------------------------------------ batching extension */
 
 /* Bytes of device workspace hipmr_reduce_segmented / hipmr_autotune_segmented

@@ -1,29 +1,25 @@
-"""Conjugate gradients on the five-point model problem, built from run-time
-generated elementwise and map-reduce kernels.
+"""Conjugate gradients on the five-point model problem, in fused run-time
+compiled kernels.
 
 The paper lists a conjugate-gradient Krylov solver for large sparse systems
 among the facilities shipped beside the elementwise and map-reduce kernels
 (section "Further Facilities").  Here A is the symmetric positive definite
 five-point operator on an nx-by-ny grid with zero boundary values (unknown
-(j, k) at index j * nx + k), applied matrix-free by an elementwise kernel.
-Every step of an iteration runs in the library's kernels; the scalars stay
-in a small device array, so an iteration needs no host synchronisation and
-can be captured into one HIP graph.  The array holds two (r . r, p . Ap)
-pairs, c (this iteration's) and d (the next one's), which swap roles every
-iteration, so no kernel has to copy r . r forward:
+(j, k) at index j * nx + k), applied matrix-free.
+The textbook iteration, as statements of the library's elementwise and
+map-reduce kernels (the constants below; two (r . r, p . Ap) pairs, c of this
+iteration and d of the next, swap roles every iteration):
 
-    q = A p                           elementwise (shifted reads p[i +/- 1], p[i +/- nx])
-    c[1] = p . q                      map-reduce
-    d[0] = sum (r - alpha q)^2        map-reduce (the next r . r), alpha = c[0] / c[1]
-    x += alpha p;  r -= alpha q;  p = r + beta p      one fused elementwise,
-                                                      beta = d[0] / c[0]
+    q = A p                           SPMV (shifted reads p[i +/- 1], p[i +/- nx])
+    c[1] = p . q                      DOT
+    d[0] = sum (r - alpha q)^2        RR_NEXT (the next r . r), alpha = c[0] / c[1]
+    x += alpha p;  r -= alpha q;  p = r + beta p      UPDATE, beta = d[0] / c[0]
 
-alpha and beta are the same float quotients the textbook iteration forms
-once per step; each kernel reads the two scalars as fixed elements.
-
-Per unknown and iteration the kernels move 52 bytes: A p reads p and writes
-q (8), the two reductions read two vectors each (16), the update reads x, r,
-p, q and writes x, r, p (28).
+PoissonCG runs the same iteration in the library's fused kernels
+(hipmr_poisson_cg): two launches per iteration inside a run, one native call
+for the whole run, no host synchronisation, so a run can also be captured into
+one HIP graph.  Sums are kept in FP64; vectors and scalars between kernels are
+float, each rounded once.
 """
 
 from __future__ import annotations
@@ -41,14 +37,12 @@ UPDATE = ("float *x, float *r, float *p, const float *q, const float *c, const f
           "x[i] += (c[0]/c[1])*p[i]; r[i] -= (c[0]/c[1])*q[i]; p[i] = r[i] + (d[0]/c[0])*p[i]")
 START = ("float *x, float *r, float *p, const float *b", "x[i] = 0.0f; r[i] = b[i]; p[i] = b[i]")
 
-BYTES_PER_UNKNOWN = 52
+BYTES_PER_UNKNOWN = 52       # of the four statements (the fused kernels move 32)
 
-# The solver rereads its vectors every iteration (x, r, p, q: 256 MB at a
-# 4096 x 4096 grid, the size of MI355X's last-level cache).  The reductions
-# and the update therefore use temporal loads and stores, which keep the
-# vectors cached for the next kernel; the streaming (non-temporal) default
-# suits single passes over data larger than the cache.  Measured at 4096^2:
-# 136 us per iteration against 165 us with streaming accesses throughout.
+# Launch configuration for the statements above when they are run one by one:
+# they reread their vectors every iteration, so temporal accesses, which keep
+# them in the last-level cache, suit grids up to its size (4096 x 4096 in one
+# process: 136 us per iteration against 165 us with streaming accesses).
 CACHED = _hm.LaunchConfig(flags=_hm.CFG_TEMPORAL)
 
 
@@ -65,10 +59,15 @@ class PoissonCG:
         self.x, self.r, self.p, self.q = (torch.empty(self.n, **f) for _ in range(4))
         self.s = torch.zeros(4, **f)          # two (r . r, p . Ap) pairs
         self.parity = 0                       # which pair holds this iteration's r . r
-        self.k = {name: _hm.compile(expr, sig, name=f"cg_{name}") for name, (sig, expr) in
-                  dict(spmv=SPMV, dot=DOT, rrn=RR_NEXT, update=UPDATE, start=START).items()}
-        sp = stream.cuda_stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
-        self._ws = _hm.workspace(_hm.reduce_workspace_bytes(self.k["dot"], self.n), dev, sp)
+        # block partials and a second buffer of p, this solver's own
+        nbytes = _hm.lib().hipmr_poisson_cg_workspace_bytes(self.nx, self.ny)
+        self._ws = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=dev)
+
+    @property
+    def k(self):
+        """Handles of the iteration's statements (compiled when asked for)."""
+        return {name: _hm.compile(expr, sig, name=f"cg_{name}") for name, (sig, expr) in
+                dict(spmv=SPMV, dot=DOT, rrn=RR_NEXT, update=UPDATE, start=START).items()}
 
     def _pairs(self):
         a, b = self.s[0:2], self.s[2:4]
@@ -79,25 +78,28 @@ class PoissonCG:
         """This iteration's r . r (a one-element device tensor)."""
         return self._pairs()[0][0:1]
 
+    def _run(self, b, iters):
+        if b is not None:
+            if hasattr(b, "numel") and b.numel() < self.n:
+                raise _hm.InvalidError(f"array 'b' has {b.numel()} elements, fewer than n = {self.n}")
+            self.parity = 0
+            b = b if isinstance(b, int) else b.data_ptr()
+            if self.n == 0:
+                self.s[0:1].zero_()
+        iters = max(0, int(iters))
+        _hm._check(_hm.lib().hipmr_poisson_cg(
+            self.nx, self.ny, b, iters, self.x.data_ptr(), self.r.data_ptr(), self.p.data_ptr(),
+            self.q.data_ptr(), self.s.data_ptr(), self.parity, self._ws.data_ptr(),
+            self._ws.numel(), _hm._stream_ptr(self.stream)))
+        self.parity ^= iters & 1
+
     def start(self, b):
         """x = 0, r = p = b, r . r = b . b."""
-        self.parity = 0
-        _hm.elementwise(self.k["start"], self.n, [self.x, self.r, self.p, b], stream=self.stream)
-        _hm.reduce(self.k["dot"], None, "a+b", "0", self.n, [b, b], self.s[0:1],
-                   workspace_buf=self._ws, stream=self.stream)
+        self._run(b, 0)
 
     def step(self):
-        """One CG iteration (four kernels, six launches, no host sync)."""
-        c, d = self._pairs()
-        n, st = self.n, self.stream
-        _hm.elementwise(self.k["spmv"], n, [self.q, self.p, self.nx], stream=st)
-        _hm.reduce(self.k["dot"], None, "a+b", "0", n, [self.p, self.q], c[1:2],
-                   workspace_buf=self._ws, stream=st, config=CACHED)
-        _hm.reduce(self.k["rrn"], None, "a+b", "0", n, [self.r, self.q, c], d[0:1],
-                   workspace_buf=self._ws, stream=st, config=CACHED)
-        _hm.elementwise(self.k["update"], n, [self.x, self.r, self.p, self.q, c, d], stream=st,
-                        config=CACHED)
-        self.parity ^= 1
+        """One CG iteration (three launches, no host sync)."""
+        self._run(None, 1)
 
     def capture(self, iters):
         """A HIP graph of `iters` iterations (an even count, so that every
@@ -112,16 +114,14 @@ class PoissonCG:
         g = _hm.Graph()
         try:
             with g.capture(self.stream):
-                for _ in range(iters):
-                    self.step()
+                self._run(None, iters)
         finally:
             self.parity = saved
         return g
 
     def solve(self, b, iters):
-        self.start(b)
-        for _ in range(iters):
-            self.step()
+        """start(b), then `iters` iterations in one native call (2 iters + 2 launches)."""
+        self._run(b, iters)
         return self.x
 
 

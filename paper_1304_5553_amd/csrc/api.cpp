@@ -896,6 +896,8 @@ hipmr_status hipmr_selftest_compile(int32_t* count) {
         if (!co) return st2;
         ++built;
     }
+    hipmr_status stc = cg_selftest(&built);
+    if (stc != HIPMR_OK) return stc;
     if (count) *count = built;
     return HIPMR_OK;
 }

@@ -76,6 +76,9 @@ hipmr_status reduce_segmented_on(hipmr_kernel* h, const char* combine, const cha
                                  size_t workspace_bytes, const hipmr_launch_config* cfgp,
                                  void* stream);
 
+// builds the conjugate-gradient kernels (no GPU needed), counting them in *built
+hipmr_status cg_selftest(int32_t* built);
+
 // device source of the serving loop's kernels
 std::string serve_source(const std::string& prefix);
 

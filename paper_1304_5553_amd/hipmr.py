@@ -120,6 +120,8 @@ _SIGS = {
     "hipmr_scan_workspace_bytes": (_SZ, [_VP, _I64]),
     "hipmr_scan": (_I32, [_VP, _CP, _CP, _I64, _VP, _VP, _I32, _VP, _SZ,
                           ctypes.POINTER(LaunchConfig), _VP]),
+    "hipmr_poisson_cg_workspace_bytes": (_SZ, [_I64, _I64]),
+    "hipmr_poisson_cg": (_I32, [_I64, _I64, _VP, _I32] + [_VP] * 5 + [_I32, _VP, _SZ, _VP]),
     "hipmr_segmented_workspace_bytes": (_SZ, [_VP, _I32, _I64]),
     "hipmr_reduce_segmented": (_I32, [_VP, _CP, _CP, _I32, _VP, _I64, _VP, _VP, _VP, _SZ,
                                       ctypes.POINTER(LaunchConfig), _VP]),
