@@ -191,7 +191,8 @@ size_t hipmr_reduce_workspace_bytes(hipmr_handle h, int64_t n);
  *   out:        device pointer to one element of the result type.
  *   workspace:  device buffer of at least hipmr_reduce_workspace_bytes(h, n)
  *               bytes (E_WORKSPACE otherwise); it is scratch for block partials.
- * Two launches on stream (block partials, then one block folding them), no
+ * Two launches on stream (block partials, then one block folding them), or one
+ * where one block takes the whole reduction (small n), no
  * atomics; for a given device, n and launch configuration the result is
  * bitwise reproducible.  n == 0 writes neutral.  The map reads arrays in
  * chunks as described for hipmr_elementwise, shifted reads name[i +/- E]

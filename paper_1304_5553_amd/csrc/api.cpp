@@ -27,6 +27,28 @@ void chunk_sizes(const Signature& sig, int* narrow, int* wide) {
         }
 }
 
+// Bytes per index of the arrays moved in chunks (at least 1).
+long long chunk_bytes(const Signature& sig) {
+    long long b = 0;
+    for (auto& a : sig.args)
+        if (chunked(a) || a.shifted) b += dtype_size(a.dtype);
+    return std::max(b, 1LL);
+}
+
+// Elements one block may take by itself where that saves a launch: its 16
+// waves evaluate a map of c instructions on n elements in n c / 256 clocks, so
+// 65536 elements of a map of plain arithmetic (c of about 10) cost 1 us more
+// than spread over the chip; a map that calls other functions than the
+// cheapest may be thirty times as long.
+long long one_block_elements(const hipmr_kernel* h) {
+    static const std::set<std::string> cheap = {"conj", "real", "imag", "fabsf", "fabs", "sqrtf",
+                                                "fmaf", "fmaxf", "fminf"};
+    const auto& t = h->prog.toks;
+    for (size_t k = 0; k + 1 < t.size(); ++k)
+        if (t[k].kind == Token::Ident && t[k + 1].text == "(" && !cheap.count(t[k].text)) return 4096;
+    return 65536;
+}
+
 // Elements per chunk: 16 bytes of the narrowest array, but 16 bytes of the
 // widest where elementwise kernels mix element sizes.  There a wider chunk moves in several
 // instructions of which each covers every other 16 bytes of its lines, which
@@ -95,19 +117,19 @@ std::string spec_key(const KernelSpec& s) {
            s.neutral;
 }
 
+// The handle's variant, if it has been built.
+std::shared_ptr<CodeObject> find_variant(hipmr_kernel* h, const std::string& key) {
+    std::lock_guard<std::mutex> lk(h->mu);
+    auto it = h->variants.find(key);
+    return it == h->variants.end() ? nullptr : it->second;
+}
+
 hipmr_status get_variant(hipmr_kernel* h, const KernelSpec& spec, std::shared_ptr<CodeObject>* out) {
     if (h->prog.sig.result == DT_C64 && !spec.combine.empty() &&
         canonical_combine(spec.combine) != Combine::Sum && canonical_combine(spec.combine) != Combine::Generic)
         return fail(HIPMR_E_UNSUPPORTED, "complex values have no order: reduce them with a sum");
     std::string k = spec_key(spec);
-    {
-        std::lock_guard<std::mutex> lk(h->mu);
-        auto it = h->variants.find(k);
-        if (it != h->variants.end()) {
-            *out = it->second;
-            return HIPMR_OK;
-        }
-    }
+    if ((*out = find_variant(h, k))) return HIPMR_OK;
     if (no_alloc_now())
         return fail(HIPMR_E_INVALID, "this kernel variant has not been built for the handle: run the "
                                      "allocating entry point once with the same arguments first");
@@ -122,6 +144,17 @@ hipmr_status get_variant(hipmr_kernel* h, const KernelSpec& spec, std::shared_pt
     return HIPMR_OK;
 }
 
+// Variants of several specs; those not built yet are built concurrently.
+hipmr_status build_variants(hipmr_kernel* h, const std::vector<KernelSpec>& specs,
+                            std::vector<std::shared_ptr<CodeObject>>* out) {
+    out->resize(specs.size());
+    std::vector<std::function<hipmr_status()>> jobs;
+    for (size_t k = 0; k < specs.size(); ++k)
+        if (!((*out)[k] = find_variant(h, spec_key(specs[k]))))
+            jobs.push_back([&, k] { return get_variant(h, specs[k], &(*out)[k]); });
+    return run_concurrently(jobs);
+}
+
 // Function of a variant on the current device; appends its symbol to *syms.
 hipmr_status variant_function(hipmr_kernel* h, const KernelSpec& spec, void** fn,
                               std::string* syms) {
@@ -130,6 +163,33 @@ hipmr_status variant_function(hipmr_kernel* h, const KernelSpec& spec, void** fn
     if (st != HIPMR_OK) return st;
     if (syms) *syms += (syms->empty() ? "" : ",") + code_object_symbol(*co);
     return get_function(*co, fn);
+}
+
+hipmr_status load_family(hipmr_kernel* h, char op, bool vector, bool idx64, const LaunchCfg& cfg,
+                         const char* combine, const char* neutral,
+                         const std::function<std::vector<KernelSpec>()>& specs) {
+    if (capturing_now() || no_alloc_now()) return HIPMR_OK;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return HIPMR_OK;      // the launch will say why
+    const char shape[] = {op, (char)dev, (char)(vector | idx64 << 1 | cfg.unaligned << 2 | cfg.nt_loads << 3 | cfg.nt_stores << 4),
+                          (char)cfg.vec, (char)(cfg.block / 64), (char)cfg.ipt};
+    std::string key(shape, sizeof shape);
+    ((key += combine) += '\x1f') += neutral;
+    {
+        std::lock_guard<std::mutex> lk(h->mu);
+        if (h->families.count(key)) return HIPMR_OK;
+    }
+    const std::vector<KernelSpec> all = specs();
+    std::vector<std::shared_ptr<CodeObject>> built;
+    hipmr_status st = build_variants(h, all, &built);
+    for (size_t k = 0; k < all.size() && st == HIPMR_OK; ++k) {
+        void* fn;
+        st = get_function(*built[k], &fn);
+    }
+    if (st != HIPMR_OK) return st;
+    std::lock_guard<std::mutex> lk(h->mu);
+    h->families.insert(key);
+    return HIPMR_OK;
 }
 
 void set_last_symbols(hipmr_kernel* h, const std::string& syms) {
@@ -579,10 +639,14 @@ hipmr_status hipmr_prepare_reduce_ex(hipmr_handle h, const char* combine, const 
     LaunchCfg cfg;
     hipmr_status rs = resolve_cfg(cfgp, kRedBlock, kRedIpt, h->default_vec, kRedBlocksPerCu, &cfg);
     if (rs != HIPMR_OK) return rs;
-    std::shared_ptr<CodeObject> co;
-    hipmr_status st = get_variant(h, s1_spec(h, h->prog.info.vectorizable, cfg, false, combine, neutral), &co);
-    if (st != HIPMR_OK) return st;
-    return get_variant(h, s2_spec(combine, neutral), &co);
+    std::vector<KernelSpec> specs = {s1_spec(h, h->prog.info.vectorizable, cfg, false, combine, neutral),
+                                     s2_spec(combine, neutral)};
+    if (!cfgp) {
+        specs.push_back(specs[0]);
+        specs.back().block = kRedOneBlock;
+    }
+    std::vector<std::shared_ptr<CodeObject>> built;
+    return build_variants(h, specs, &built);
 }
 
 hipmr_status hipmr_prepare_reduce(hipmr_handle h, const char* combine, const char* neutral) {
@@ -609,12 +673,32 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
     st = resolve_cfg(cfgp, kRedBlock, kRedIpt, h->default_vec, kRedBlocksPerCu, &cfg);
     if (st != HIPMR_OK) return st;
 
+    // one block, unless the call chose a geometry
+    const bool own_shape = cfgp && (cfgp->block || cfgp->items_per_thread || cfgp->grid || cfgp->blocks_per_cu);
     long long n64 = n, head64 = 0;
     int grid = 0;
     std::string syms;
     if (n > 0) {
         const long long head = vector_head(h, args, &cfg);
         const bool vector = head >= 0;
+        if (!own_shape) {
+            const bool idx64 = n >= (int64_t(1) << 31);
+            st = load_family(h, 'r', vector, idx64, cfg, combine, neutral, [&] {
+                std::vector<KernelSpec> v;
+                LaunchCfg c = cfg;
+                for (int block : {kRedBlock, kRedOneBlock}) {
+                    c.block = block;
+                    v.push_back(s1_spec(h, vector, c, idx64, combine, neutral));
+                }
+                v.push_back(s2_spec(combine, neutral));
+                return v;
+            });
+            if (st != HIPMR_OK) return st;
+            if (n <= one_block_elements(h) && n * chunk_bytes(h->prog.sig) <= kRedOneBytes) {
+                cfg.block = kRedOneBlock;
+                cfg.grid = 1;
+            }
+        }
         head64 = vector ? head : 0;
         void* fn = nullptr;
         st = variant_function(h, s1_spec(h, vector, cfg, n >= (int64_t(1) << 31), combine, neutral), &fn,
@@ -627,9 +711,11 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
         for (size_t k = 0; k < h->prog.sig.args.size(); ++k) params.push_back(args[k]);
         params.push_back(&n64);
         params.push_back(&head64);
-        params.push_back(&workspace);
+        // one block's partial is the result
+        params.push_back(grid == 1 ? (void*)&out : (void*)&workspace);
+        if (grid == 1) set_last_symbols(h, syms);
         st = launch(fn, (unsigned)grid, (unsigned)cfg.block, params.data(), stream);
-        if (st != HIPMR_OK) return st;
+        if (st != HIPMR_OK || grid == 1) return st;
     }
     void* fn2 = nullptr;
     st = variant_function(h, s2_spec(combine, neutral), &fn2, &syms);

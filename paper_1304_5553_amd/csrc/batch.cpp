@@ -254,30 +254,6 @@ std::vector<hipmr_launch_config> candidates(bool segmented) {
     return v;
 }
 
-// Compiles the variants of every candidate concurrently (hipRTC programs are
-// independent; the code-object cache is thread-safe).
-hipmr_status compile_all(const std::vector<std::function<hipmr_status()>>& jobs) {
-    std::atomic<size_t> next{0};
-    std::atomic<int> status{HIPMR_OK};
-    std::mutex err_mu;
-    std::string err;
-    unsigned nt = std::max(1u, std::min<unsigned>(std::thread::hardware_concurrency(), 16));
-    std::vector<std::thread> pool;
-    for (unsigned k = 0; k < nt; ++k)
-        pool.emplace_back([&] {
-            for (size_t j; (j = next++) < jobs.size();) {
-                hipmr_status st = jobs[j]();
-                if (st != HIPMR_OK) {
-                    std::lock_guard<std::mutex> lk(err_mu);
-                    if (status == HIPMR_OK) { status = st; err = last_error(); }
-                }
-            }
-        });
-    for (auto& t : pool) t.join();
-    if (status != HIPMR_OK) return fail(status, err);
-    return HIPMR_OK;
-}
-
 template <typename Run>
 hipmr_status time_config(Run run, int reps, void* stream, float* ms) {
     hipEvent_t a, b;
@@ -306,6 +282,31 @@ thread_local bool g_capturing = false;
 thread_local bool g_no_alloc = false;
 
 }  // namespace
+
+// (hipRTC programs are independent; the code-object cache is thread-safe)
+hipmr_status run_concurrently(const std::vector<std::function<hipmr_status()>>& jobs) {
+    if (jobs.empty()) return HIPMR_OK;
+    std::atomic<size_t> next{0};
+    std::atomic<int> status{HIPMR_OK};
+    std::mutex err_mu;
+    std::string err;
+    unsigned nt = std::max(1u, std::min<unsigned>(std::thread::hardware_concurrency(), 16));
+    nt = (unsigned)std::min<size_t>(nt, jobs.size());
+    std::vector<std::thread> pool;
+    for (unsigned k = 0; k < nt; ++k)
+        pool.emplace_back([&] {
+            for (size_t j; (j = next++) < jobs.size();) {
+                hipmr_status st = jobs[j]();
+                if (st != HIPMR_OK) {
+                    std::lock_guard<std::mutex> lk(err_mu);
+                    if (status == HIPMR_OK) { status = st; err = last_error(); }
+                }
+            }
+        });
+    for (auto& t : pool) t.join();
+    if (status != HIPMR_OK) return fail(status, err);
+    return HIPMR_OK;
+}
 
 bool capturing_now() { return g_capturing; }
 bool no_alloc_now() { return g_no_alloc; }
@@ -409,7 +410,7 @@ hipmr_status hipmr_autotune_segmented(hipmr_handle h, const char* combine, const
             }
             return HIPMR_OK;
         });
-    st = compile_all(jobs);
+    st = run_concurrently(jobs);
     if (st != HIPMR_OK) return st;
     float best_ms = 1e30f;
     hipmr_launch_config best_cfg{};
@@ -454,7 +455,7 @@ hipmr_status hipmr_autotune_reduce(hipmr_handle h, const char* combine, const ch
             cc.grid = 0;
             return hipmr_prepare_reduce_ex(h, combine, neutral, &cc);
         });
-    st = compile_all(jobs);
+    st = run_concurrently(jobs);
     if (st != HIPMR_OK) return st;
     float best_ms = 1e30f;
     hipmr_launch_config best_cfg{};

@@ -3,7 +3,9 @@
 #pragma once
 
 #include <atomic>
+#include <functional>
 #include <map>
+#include <set>
 
 #include "common.h"
 
@@ -18,6 +20,7 @@ struct hipmr_kernel {
     std::map<std::string, std::shared_ptr<hipmr::CodeObject>> variants;
     std::string last_symbols;                        // kernels of the most recent call
     std::map<std::string, hipmr_launch_config> tuned;  // autotuned geometry per operation
+    std::set<std::string> families;                  // operations whose kernels are all loaded (load_family)
 };
 
 namespace hipmr {
@@ -41,6 +44,13 @@ constexpr int kEwBlock = 256, kEwIpt = 1, kEwBlocksPerCu = 1 << 20;
 constexpr int kEwMixedIpt = 2;               // arrays of different element sizes (see default_ew_shape)
 constexpr int kEwScalarBlocksPerCu = 32;     // one-element elementwise kernels
 constexpr int kRedBlock = 256, kRedIpt = 4, kRedBlocksPerCu = 2;
+// A reduction over at most this many bytes is one block's work, in one launch:
+// a dot of 2 x 4096 floats takes 7.8 us per call and 18.0 waited for, against
+// 10.7 and 21.5 in two launches (3.3 us of host time each); of 2 x 65536 floats
+// 8.0 and 20.4 against 10.5 and 20.6; of twice that 9.0 and 23.8 against 10.7
+// and 20.6.
+constexpr int kRedOneBlock = 1024;
+constexpr long long kRedOneBytes = 512 << 10;
 
 hipmr_status resolve_cfg(const hipmr_launch_config* c, int block, int ipt, int vec,
                          int blocks_per_cu, LaunchCfg* out);
@@ -48,6 +58,16 @@ hipmr_status get_variant(hipmr_kernel* h, const KernelSpec& spec, std::shared_pt
 hipmr_status variant_function(hipmr_kernel* h, const KernelSpec& spec, void** fn,
                               std::string* syms);
 void set_last_symbols(hipmr_kernel* h, const std::string& syms);
+// Builds (concurrently) and loads every kernel that `op` may use on this
+// device at any size, the first time it runs there, so that a later capture
+// finds them whatever its size.  Nothing is loaded during a capture.
+hipmr_status load_family(hipmr_kernel* h, char op, bool vector, bool idx64, const LaunchCfg& cfg,
+                         const char* combine, const char* neutral,
+                         const std::function<std::vector<KernelSpec>()>& specs);
+// elements of the handle's map that one block may take by itself
+long long one_block_elements(const hipmr_kernel* h);
+// runs the jobs on a thread pool; the first failure's status and message
+hipmr_status run_concurrently(const std::vector<std::function<hipmr_status()>>& jobs);
 // Element offset at which the chunks start, or -1 for the one-element kernels
 // (a map or statement that cannot run on chunks, or an array off its element
 // alignment): every written array is aligned for VEC-element chunks there, and

@@ -118,9 +118,22 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
         if (!own_ipt) c.ipt = ipt;
         return c;
     };
+    const bool idx64 = n64 >= (int64_t(1) << 31);
+    KernelSpec clear;
+    clear.kind = KernelKind::ScanClear;
+    st = load_family(h, 's', vector, idx64, cfg, combine, neutral, [&] {
+        const LaunchCfg one = with(kScanOneBlock, kScanIpt), small = with(kScanSmallBlock, kScanIpt);
+        const LaunchCfg pass = with(kScanBlock, kScanPassIpt);
+        std::vector<KernelSpec> v = {scan_spec(vector, 0, one, idx64, combine, neutral),
+                                     scan_spec(vector, 3, pass, idx64, combine, neutral), clear};
+        for (int mode : {1, 2})
+            for (const LaunchCfg& c : {small, cfg}) v.push_back(scan_spec(vector, mode, c, idx64, combine, neutral));
+        return v;
+    });
+    if (st != HIPMR_OK) return st;
     int mode = 3;
     const LaunchCfg one = with(kScanOneBlock, kScanIpt), small = with(kScanSmallBlock, kScanIpt);
-    if (tiles_of(one) == 1) {
+    if (tiles_of(one) == 1 && (own_block || own_ipt || n64 <= one_block_elements(h))) {
         mode = 0;
         cfg = one;
     } else if (tiles_of(small) <= kScanSmallTiles) {
@@ -137,7 +150,6 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
         if (!fits()) return fail(HIPMR_E_WORKSPACE, "workspace too small for the scan's tile totals");
     }
     const long long tiles64 = tiles_of(cfg);
-    const bool idx64 = n64 >= (int64_t(1) << 31);
     int tiles = (int)tiles64, excl = exclusive, words = (int)state_words(tiles64, rs);
 
     std::string syms;
@@ -147,9 +159,7 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
     if (mode == 2) {
         st = variant_function(h, scan_spec(vector, 1, cfg, idx64, combine, neutral), &f_first, &syms);
     } else if (mode == 3) {
-        KernelSpec z;
-        z.kind = KernelKind::ScanClear;
-        st = variant_function(h, z, &f_first, &syms);
+        st = variant_function(h, clear, &f_first, &syms);
     }
     if (st != HIPMR_OK) return st;
     set_last_symbols(h, syms);
