@@ -108,19 +108,10 @@ hipmr_status resolve_cfg(const hipmr_launch_config* c, int block, int ipt, int v
     return HIPMR_OK;
 }
 
-std::string spec_key(const KernelSpec& s) {
-    return std::to_string((int)s.kind) + "|" + std::to_string(s.idx64) + "|" +
-           std::to_string(s.block) + "|" + std::to_string(s.ipt) + "|" + std::to_string(s.vec) +
-           "|" + std::to_string(s.nt_loads) + std::to_string(s.nt_stores) + std::to_string(s.unaligned) + "|" +
-           std::to_string(s.square) + std::to_string(s.track) + std::to_string(s.scaled) + std::to_string(s.exact_runs) +
-           std::to_string(s.norm) + std::to_string(s.scan_mode) + "|" + std::to_string(s.lds_segs) + "|" + s.combine + "\x1f" +
-           s.neutral;
-}
-
 // The handle's variant, if it has been built.
-std::shared_ptr<CodeObject> find_variant(hipmr_kernel* h, const std::string& key) {
+std::shared_ptr<CodeObject> find_variant(hipmr_kernel* h, const KernelSpec& spec) {
     std::lock_guard<std::mutex> lk(h->mu);
-    auto it = h->variants.find(key);
+    auto it = h->variants.find(spec);
     return it == h->variants.end() ? nullptr : it->second;
 }
 
@@ -128,8 +119,7 @@ hipmr_status get_variant(hipmr_kernel* h, const KernelSpec& spec, std::shared_pt
     if (h->prog.sig.result == DT_C64 && !spec.combine.empty() &&
         canonical_combine(spec.combine) != Combine::Sum && canonical_combine(spec.combine) != Combine::Generic)
         return fail(HIPMR_E_UNSUPPORTED, "complex values have no order: reduce them with a sum");
-    std::string k = spec_key(spec);
-    if ((*out = find_variant(h, k))) return HIPMR_OK;
+    if ((*out = find_variant(h, spec))) return HIPMR_OK;
     if (no_alloc_now())
         return fail(HIPMR_E_INVALID, "this kernel variant has not been built for the handle: run the "
                                      "allocating entry point once with the same arguments first");
@@ -139,8 +129,7 @@ hipmr_status get_variant(hipmr_kernel* h, const KernelSpec& spec, std::shared_pt
     auto co = get_or_build(src, symbol, &st);
     if (!co) return st;
     std::lock_guard<std::mutex> lk(h->mu);
-    h->variants[k] = co;
-    *out = co;
+    *out = h->variants.emplace(spec, co).first->second;    // another thread's, if it was first
     return HIPMR_OK;
 }
 
@@ -150,18 +139,18 @@ hipmr_status build_variants(hipmr_kernel* h, const std::vector<KernelSpec>& spec
     out->resize(specs.size());
     std::vector<std::function<hipmr_status()>> jobs;
     for (size_t k = 0; k < specs.size(); ++k)
-        if (!((*out)[k] = find_variant(h, spec_key(specs[k]))))
+        if (!((*out)[k] = find_variant(h, specs[k])))
             jobs.push_back([&, k] { return get_variant(h, specs[k], &(*out)[k]); });
     return run_concurrently(jobs);
 }
 
-// Function of a variant on the current device; appends its symbol to *syms.
+// Function of a variant on the current device; adds it to *used.
 hipmr_status variant_function(hipmr_kernel* h, const KernelSpec& spec, void** fn,
-                              std::string* syms) {
+                              CallKernels* used) {
     std::shared_ptr<CodeObject> co;
     hipmr_status st = get_variant(h, spec, &co);
     if (st != HIPMR_OK) return st;
-    if (syms) *syms += (syms->empty() ? "" : ",") + code_object_symbol(*co);
+    if (used && used->n < 4) used->co[used->n++] = co.get();
     return get_function(*co, fn);
 }
 
@@ -192,9 +181,9 @@ hipmr_status load_family(hipmr_kernel* h, char op, bool vector, bool idx64, cons
     return HIPMR_OK;
 }
 
-void set_last_symbols(hipmr_kernel* h, const std::string& syms) {
+void set_last_kernels(hipmr_kernel* h, const CallKernels& used) {
     std::lock_guard<std::mutex> lk(h->mu);
-    h->last_symbols = syms;
+    h->last = used;
 }
 
 // Where no offset aligns every array, the arrays that are only read are loaded
@@ -425,7 +414,7 @@ struct Stage1 {
 
 hipmr_status stage1_launch(hipmr_kernel* h, KernelSpec spec, LaunchCfg cfg,
                            int64_t n, void* const* args, void* partial, void* extra,
-                           void* stream, std::string* syms, Stage1* out) {
+                           void* stream, CallKernels* used, Stage1* out) {
     const long long head = vector_head(h, args, &cfg);
     const bool vector = head >= 0;
     spec.unaligned = cfg.unaligned;
@@ -435,7 +424,7 @@ hipmr_status stage1_launch(hipmr_kernel* h, KernelSpec spec, LaunchCfg cfg,
         spec.exact_runs = false;
     }
     spec.idx64 = n >= (int64_t(1) << 31);
-    hipmr_status st = variant_function(h, spec, &out->fn, syms);
+    hipmr_status st = variant_function(h, spec, &out->fn, used);
     if (st != HIPMR_OK) return st;
     long long n64 = n, head64 = vector ? head : 0;
     long long units = vector ? (n64 > head64 ? (n64 - head64) / cfg.vec : 0) : n64;
@@ -504,17 +493,17 @@ hipmr_status hipmr_reduce_compensated(hipmr_handle h, int64_t n, void* const* ar
     if (st != HIPMR_OK) return st;
     KernelSpec s1 = comp_spec(KernelKind::CompS1Vector, cfg);
     s1.exact_runs = single_fp8_load(h) && cfg.vec * cfg.ipt <= 64;
-    std::string syms;
+    CallKernels used;
     Stage1 r;
-    st = stage1_launch(h, s1, cfg, n, args, workspace, nullptr, stream, &syms, &r);
+    st = stage1_launch(h, s1, cfg, n, args, workspace, nullptr, stream, &used, &r);
     if (st != HIPMR_OK) return st;
     KernelSpec s2 = comp_spec(KernelKind::CompS2, cfg);
     s2.block = kStage2Block;
     s2.ipt = s2.vec = 1;
     void* fn2 = nullptr;
-    st = variant_function(h, s2, &fn2, &syms);
+    st = variant_function(h, s2, &fn2, &used);
     if (st != HIPMR_OK) return st;
-    set_last_symbols(h, syms);
+    set_last_kernels(h, used);
     void* scale64 = (char*)workspace + kScaleOffset + 8;
     void* params2[5] = {&workspace, &r.grid, &post_scale, &scale64, &out};
     return launch(fn2, 1, kStage2Block, params2, stream);
@@ -532,14 +521,14 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
     if (st != HIPMR_OK) return st;
     void* amax = (char*)workspace + kAmaxOffset;
     void* scale_d = (char*)workspace + kScaleOffset + 8;
-    std::string syms;
+    CallKernels used;
     const bool two = passes == 2 && n > 0;     // an empty norm is 0 either way
     if (two) {
         // pass 1: sum of the unscaled squares and max |map|, per block
         KernelSpec a1 = comp_spec(KernelKind::CompS1Vector, cfg);
         a1.square = a1.track = true;
         Stage1 r1;
-        st = stage1_launch(h, a1, cfg, n, args, workspace, amax, stream, &syms, &r1);
+        st = stage1_launch(h, a1, cfg, n, args, workspace, amax, stream, &used, &r1);
         if (st != HIPMR_OK) return st;
     }
     // pass 2 (or the only pass): compensated sum of (map * scale)^2; with two
@@ -550,7 +539,7 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
     q1.square = true;
     q1.scaled = two;
     Stage1 r2;
-    st = stage1_launch(h, q1, cfg, n, args, workspace, amax, stream, &syms, &r2);
+    st = stage1_launch(h, q1, cfg, n, args, workspace, amax, stream, &used, &r2);
     if (st != HIPMR_OK) return st;
     KernelSpec q2 = comp_spec(KernelKind::CompS2, cfg);
     q2.block = kStage2Block;
@@ -558,9 +547,9 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
     q2.norm = true;
     q2.scaled = two;
     void* fn2 = nullptr;
-    st = variant_function(h, q2, &fn2, &syms);
+    st = variant_function(h, q2, &fn2, &used);
     if (st != HIPMR_OK) return st;
-    set_last_symbols(h, syms);
+    set_last_kernels(h, used);
     void* params2[5] = {&workspace, &r2.grid, &post_scale, &scale_d, &out};
     return launch(fn2, 1, kStage2Block, params2, stream);
 }
@@ -606,10 +595,10 @@ hipmr_status hipmr_elementwise_ex(hipmr_handle h, int64_t n, void* const* args,
     spec.nt_stores = cfg.nt_stores;
     spec.unaligned = cfg.unaligned;
     void* fn = nullptr;
-    std::string syms;
-    st = variant_function(h, spec, &fn, &syms);
+    CallKernels used;
+    st = variant_function(h, spec, &fn, &used);
     if (st != HIPMR_OK) return st;
-    set_last_symbols(h, syms);
+    set_last_kernels(h, used);
     long long n64 = n, head64 = vector ? head : 0;
     long long units = vector ? (n64 > head64 ? (n64 - head64) / cfg.vec : 0) : n64;
     int grid = grid_for(units, cfg.block * (vector ? cfg.ipt : 1), cfg, 1 << 30);
@@ -677,7 +666,7 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
     const bool own_shape = cfgp && (cfgp->block || cfgp->items_per_thread || cfgp->grid || cfgp->blocks_per_cu);
     long long n64 = n, head64 = 0;
     int grid = 0;
-    std::string syms;
+    CallKernels used;
     if (n > 0) {
         const long long head = vector_head(h, args, &cfg);
         const bool vector = head >= 0;
@@ -702,7 +691,7 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
         head64 = vector ? head : 0;
         void* fn = nullptr;
         st = variant_function(h, s1_spec(h, vector, cfg, n >= (int64_t(1) << 31), combine, neutral), &fn,
-                              &syms);
+                              &used);
         if (st != HIPMR_OK) return st;
         long long units = vector ? (n64 > head64 ? (n64 - head64) / cfg.vec : 0) : n64;
         grid = grid_for(units, cfg.block * (vector ? cfg.ipt : 1), cfg, kMaxPartials);
@@ -713,14 +702,14 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
         params.push_back(&head64);
         // one block's partial is the result
         params.push_back(grid == 1 ? (void*)&out : (void*)&workspace);
-        if (grid == 1) set_last_symbols(h, syms);
+        if (grid == 1) set_last_kernels(h, used);
         st = launch(fn, (unsigned)grid, (unsigned)cfg.block, params.data(), stream);
         if (st != HIPMR_OK || grid == 1) return st;
     }
     void* fn2 = nullptr;
-    st = variant_function(h, s2_spec(combine, neutral), &fn2, &syms);
+    st = variant_function(h, s2_spec(combine, neutral), &fn2, &used);
     if (st != HIPMR_OK) return st;
-    set_last_symbols(h, syms);
+    set_last_kernels(h, used);
     void* params2[3] = {&workspace, &grid, &out};
     return launch(fn2, 1, kStage2Block, params2, stream);
 }
@@ -816,7 +805,7 @@ hipmr_status hipmr_get_last_symbols(hipmr_handle h, char* buf, size_t cap, size_
     std::string syms;
     {
         std::lock_guard<std::mutex> lk(h->mu);
-        syms = h->last_symbols;
+        for (int k = 0; k < h->last.n; ++k) syms += (k ? "," : "") + code_object_symbol(*h->last.co[k]);
     }
     if (len) *len = syms.size();
     if (buf && cap) {

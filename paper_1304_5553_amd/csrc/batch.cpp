@@ -102,7 +102,7 @@ KernelSpec seg_spec(KernelKind kind, const LaunchCfg& cfg, bool idx64, const cha
 
 hipmr_status seg_prepare(hipmr_kernel* h, const char* combine, const char* neutral, int32_t nseg,
                          int64_t total_n, void* const* args, const LaunchCfg& cfg_in,
-                         std::string* syms, SegLaunch* out) {
+                         CallKernels* used, SegLaunch* out) {
     LaunchCfg cfg = cfg_in;
     long long head = vector_head(h, args, &cfg);
     if (head < 0) {       // scalar access: one-element chunks
@@ -115,12 +115,12 @@ hipmr_status seg_prepare(hipmr_kernel* h, const char* combine, const char* neutr
     out->plan = nullptr;
     if (lds == 0) {       // the table does not fit LDS: a planning launch writes it to global memory
         st = variant_function(h, seg_spec(KernelKind::SegPlan, cfg, idx64, combine, neutral, lds),
-                              &out->plan, syms);
+                              &out->plan, used);
         if (st != HIPMR_OK) return st;
     }
-    st = variant_function(h, seg_spec(KernelKind::SegS1, cfg, idx64, combine, neutral, lds), &out->s1, syms);
+    st = variant_function(h, seg_spec(KernelKind::SegS1, cfg, idx64, combine, neutral, lds), &out->s1, used);
     if (st != HIPMR_OK) return st;
-    st = variant_function(h, seg_spec(KernelKind::SegS2, cfg, idx64, combine, neutral, lds), &out->s2, syms);
+    st = variant_function(h, seg_spec(KernelKind::SegS2, cfg, idx64, combine, neutral, lds), &out->s2, used);
     if (st != HIPMR_OK) return st;
     long long tiles = max_tiles(nseg, total_n, cfg.vec);
     int waves_per_block = cfg.block / 64;
@@ -330,11 +330,11 @@ hipmr_status reduce_segmented_on(hipmr_kernel* h, const char* combine, const cha
     LaunchCfg cfg;
     st = resolve_cfg(cfgp, kSegBlock, kSegIpt, h->default_vec, kSegBlocksPerCu, &cfg);
     if (st != HIPMR_OK) return st;
-    std::string syms;
+    CallKernels used;
     SegLaunch L;
-    st = seg_prepare(h, combine, neutral, nseg, total_n, args, cfg, &syms, &L);
+    st = seg_prepare(h, combine, neutral, nseg, total_n, args, cfg, &used, &L);
     if (st != HIPMR_OK) return st;
-    set_last_symbols(h, syms);
+    set_last_kernels(h, used);
     return seg_launch(h, L, nseg, d_offsets, total_n, args, d_out, workspace, stream);
 }
 
@@ -418,9 +418,9 @@ hipmr_status hipmr_autotune_segmented(hipmr_handle h, const char* combine, const
         LaunchCfg cfg;
         st = resolve_cfg(&cands[c], kSegBlock, kSegIpt, h->default_vec, kSegBlocksPerCu, &cfg);
         if (st != HIPMR_OK) return st;
-        std::string syms;
+        CallKernels used;
         SegLaunch L;
-        st = seg_prepare(h, combine, neutral, nseg, total_n, args, cfg, &syms, &L);
+        st = seg_prepare(h, combine, neutral, nseg, total_n, args, cfg, &used, &L);
         if (st != HIPMR_OK) return st;
         float ms = 0;
         st = time_config([&] { return seg_launch(h, L, nseg, d_offsets, total_n, args, d_out, workspace, stream); },

@@ -8,6 +8,7 @@
 #include <memory>
 #include <mutex>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "hipmr.h"
@@ -147,6 +148,22 @@ struct KernelSpec {
     // batching extension
     int scan_mode = 0;        // Scan: 0 one tile, 1 tile totals, 2 from totals, 3 one pass
     int lds_segs = 0;         // SegS1: tile-start table held in LDS (capacity), 0 = global
+};
+inline auto spec_fields(const KernelSpec& s) {
+    return std::tie(s.kind, s.idx64, s.block, s.ipt, s.vec, s.nt_loads, s.nt_stores, s.unaligned, s.square,
+                    s.track, s.scaled, s.exact_runs, s.norm, s.scan_mode, s.lds_segs, s.combine, s.neutral);
+}
+inline bool operator==(const KernelSpec& a, const KernelSpec& b) { return spec_fields(a) == spec_fields(b); }
+struct KernelSpecHash {
+    size_t operator()(const KernelSpec& s) const {
+        const uint64_t shape = (uint64_t)s.kind | (uint64_t)s.block << 5 | (uint64_t)s.ipt << 16 |
+                               (uint64_t)s.vec << 21 | (uint64_t)s.lds_segs << 26 | (uint64_t)s.scan_mode << 40 |
+                               (uint64_t)(s.idx64 | s.nt_loads << 1 | s.nt_stores << 2 | s.unaligned << 3 |
+                                          s.square << 4 | s.track << 5 | s.scaled << 6 | s.exact_runs << 7 |
+                                          s.norm << 8) << 44;
+        const std::hash<std::string> text;
+        return std::hash<uint64_t>()(shape * 0x9E3779B97F4A7C15ull) ^ text(s.combine) ^ text(s.neutral) * 31;
+    }
 };
 
 struct Program {                 // everything codegen needs about one handle

@@ -6,8 +6,17 @@
 #include <functional>
 #include <map>
 #include <set>
+#include <unordered_map>
 
 #include "common.h"
+
+namespace hipmr {
+// The kernels of one call, in the order looked up (the handle keeps them alive).
+struct CallKernels {
+    const CodeObject* co[4] = {};
+    int n = 0;
+};
+}  // namespace hipmr
 
 struct hipmr_kernel {
     int refs = 1;                 // changed only under the handle cache's lock
@@ -17,8 +26,8 @@ struct hipmr_kernel {
     int default_vec = 4;          // elements per chunk, and of the elementwise kernels
     int ew_vec = 4, ew_ipt = 1;   // (with the chunks per thread)
     std::mutex mu;
-    std::map<std::string, std::shared_ptr<hipmr::CodeObject>> variants;
-    std::string last_symbols;                        // kernels of the most recent call
+    std::unordered_map<hipmr::KernelSpec, std::shared_ptr<hipmr::CodeObject>, hipmr::KernelSpecHash> variants;
+    hipmr::CallKernels last;                         // kernels of the most recent call
     std::map<std::string, hipmr_launch_config> tuned;  // autotuned geometry per operation
     std::set<std::string> families;                  // operations whose kernels are all loaded (load_family)
 };
@@ -56,8 +65,8 @@ hipmr_status resolve_cfg(const hipmr_launch_config* c, int block, int ipt, int v
                          int blocks_per_cu, LaunchCfg* out);
 hipmr_status get_variant(hipmr_kernel* h, const KernelSpec& spec, std::shared_ptr<CodeObject>* out);
 hipmr_status variant_function(hipmr_kernel* h, const KernelSpec& spec, void** fn,
-                              std::string* syms);
-void set_last_symbols(hipmr_kernel* h, const std::string& syms);
+                              CallKernels* used);
+void set_last_kernels(hipmr_kernel* h, const CallKernels& used);
 // Builds (concurrently) and loads every kernel that `op` may use on this
 // device at any size, the first time it runs there, so that a later capture
 // finds them whatever its size.  Nothing is loaded during a capture.

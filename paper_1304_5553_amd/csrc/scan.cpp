@@ -152,17 +152,17 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
     const long long tiles64 = tiles_of(cfg);
     int tiles = (int)tiles64, excl = exclusive, words = (int)state_words(tiles64, rs);
 
-    std::string syms;
+    CallKernels used;
     void *f_first = nullptr, *f_scan = nullptr;
-    st = variant_function(h, scan_spec(vector, mode, cfg, idx64, combine, neutral), &f_scan, &syms);
+    st = variant_function(h, scan_spec(vector, mode, cfg, idx64, combine, neutral), &f_scan, &used);
     if (st != HIPMR_OK) return st;
     if (mode == 2) {
-        st = variant_function(h, scan_spec(vector, 1, cfg, idx64, combine, neutral), &f_first, &syms);
+        st = variant_function(h, scan_spec(vector, 1, cfg, idx64, combine, neutral), &f_first, &used);
     } else if (mode == 3) {
-        st = variant_function(h, clear, &f_first, &syms);
+        st = variant_function(h, clear, &f_first, &used);
     }
     if (st != HIPMR_OK) return st;
-    set_last_symbols(h, syms);
+    set_last_kernels(h, used);
 
     std::vector<void*> p;
     if (h->prog.sig.args.empty()) p.push_back(&base);       // hipmr_unused

@@ -182,19 +182,51 @@ def lib():
     return _lib
 
 
+_fast = None                       # the call marshalling extension, once a call has needed it
+_FN = {}                           # C ABI function name -> address
+
+
+def _load_fast():
+    global _fast
+    import torch
+    try:
+        from . import _fastcall
+    except ImportError as e:
+        raise RuntimeError("_fastcall.so is missing: build it with __graft_entry__.build() "
+                           "(make -C paper_1304_5553_amd/csrc)") from e
+    for name in ("hipmr_elementwise_ex", "hipmr_reduce_ex", "hipmr_scan"):
+        _FN[name] = ctypes.cast(getattr(lib(), name), ctypes.c_void_p).value
+    _fastcall.init(torch.Tensor)
+    torch_dtype(F32)                 # fills the table
+    _fast = _fastcall
+    return _fast
+
+
 def _check(status):
     if status != OK:
         msg = lib().hipmr_last_error().decode(errors="replace")
         raise _ERRORS.get(status, HipmrError)(msg, status)
 
 
+_torch_calls = None
+
+
+def _torch_stream_calls():
+    """(device index, raw current stream of a device), looked up once."""
+    global _torch_calls
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:              # the handle through a Stream object
+        def raw(device):
+            return torch.cuda.current_stream(device).cuda_stream
+    _torch_calls = (torch.cuda.current_device, raw)
+    return _torch_calls
+
+
 def _stream_ptr(stream):
     if stream is None:
-        import torch
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw is not None:      # the current stream's handle without a Stream object
-            return raw(torch.cuda.current_device())
-        return torch.cuda.current_stream().cuda_stream
+        device, raw = _torch_calls or _torch_stream_calls()
+        return raw(device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -222,12 +254,18 @@ _CTYPE = {F32: ctypes.c_float, F64: ctypes.c_double, I8: ctypes.c_int8, U8: ctyp
           C64: ctypes.c_float * 2}
 
 
+_TORCH_DTYPES = {}
+
+
 def torch_dtype(code):
-    import torch
-    return {F32: torch.float32, F64: torch.float64, I8: torch.int8, U8: torch.uint8,
+    if not _TORCH_DTYPES:
+        import torch
+        _TORCH_DTYPES.update({
+            F32: torch.float32, F64: torch.float64, I8: torch.int8, U8: torch.uint8,
             I16: torch.int16, U16: torch.uint16, I32: torch.int32, U32: torch.uint32,
             I64: torch.int64, BF16: torch.bfloat16, F16: torch.float16,
-            FP8: torch.float8_e4m3fn, C64: torch.complex64}[code]
+            FP8: torch.float8_e4m3fn, C64: torch.complex64})
+    return _TORCH_DTYPES[code]
 
 
 def _lowp_bits(code, value):
@@ -237,6 +275,9 @@ def _lowp_bits(code, value):
     if code == FP8:
         return int(t.clamp(-448, 448).to(torch.float8_e4m3fn).view(torch.uint8).item())
     return int(t.to(torch_dtype(code)).view(torch.int16).item()) & 0xFFFF
+
+
+_KINDS = {F32: "f", F64: "d", I32: "i", U32: "i", I64: "l"}
 
 
 class Arg:
@@ -277,6 +318,12 @@ class Kernel:
         self._h = h
         (self.is_reduce, self.result_dtype, self.vectorizable, self.vec, self.args,
          self._sized, _) = meta
+        self._slots = range(len(self.args))
+        self._hv = h.value                # the handle as an integer, and the arguments' kinds
+        self._kinds = bytes(              # (as the marshalling extension names them)
+            ord(("A" if k in self._sized else "a") if a.pointer else _KINDS.get(a.dtype, "?"))
+            for k, a in enumerate(self.args))
+        self._ws_bytes = None             # of a reduction (the same for every n), asked for once
         self._tls = None                  # per-thread argument buffers, made by the first marshal
 
     @staticmethod
@@ -324,14 +371,9 @@ class Kernel:
                 raise InvalidError(f"array '{self.args[k].name}' has {val.numel()} elements, "
                                    f"fewer than n = {n}")
 
-    def marshal(self, args):
-        """(storage, ctypes array of pointers) for the C ABI's args: every
-        value sits in its own 8-byte slot of one buffer (a device pointer, or
-        the scalar's bytes in its C type), and args[k] points at slot k.  The
-        library copies the values during the call, so each thread reuses one
-        pair of buffers per handle, rewritten by its next call."""
-        if len(args) != len(self.args):
-            raise InvalidError(f"expected {len(self.args)} arguments, got {len(args)}")
+    def _buffers(self):
+        """This thread's argument buffers: the values' 8-byte slots, the array
+        of pointers to them (right behind, in one allocation) and their address."""
         tls = self._tls
         if tls is None:
             with _META_LOCK:
@@ -340,12 +382,26 @@ class Kernel:
             tls = self._tls
         bufs = getattr(tls, "bufs", None)
         if bufs is None:
-            nargs = max(1, len(args))
-            store = (ctypes.c_uint64 * nargs)()
-            base = ctypes.addressof(store)
-            bufs = tls.bufs = (store, (ctypes.c_void_p * nargs)(*range(base, base + 8 * nargs, 8)))
-        store, ptrs = bufs
-        for k, (decl, val) in enumerate(zip(self.args, args)):
+            nargs = max(1, len(self.args))
+            raw = (ctypes.c_uint64 * (2 * nargs))()
+            base = ctypes.addressof(raw)
+            store = (ctypes.c_uint64 * nargs).from_buffer(raw)
+            ptrs = (ctypes.c_void_p * nargs).from_buffer(raw, 8 * nargs)
+            for k in range(nargs):
+                ptrs[k] = base + 8 * k
+            bufs = tls.bufs = (store, ptrs, base)
+        return bufs
+
+    def marshal(self, args):
+        """(storage, ctypes array of pointers) for the C ABI's args: every
+        value sits in its own 8-byte slot of one buffer (a device pointer, or
+        the scalar's bytes in its C type), and args[k] points at slot k.  The
+        library copies the values during the call, so each thread reuses one
+        pair of buffers per handle, rewritten by its next call."""
+        if len(args) != len(self.args):
+            raise InvalidError(f"expected {len(self.args)} arguments, got {len(args)}")
+        store, ptrs, _ = self._buffers()
+        for k, decl, val in zip(self._slots, self.args, args):
             if decl.pointer:
                 store[k] = val if isinstance(val, int) else (0 if val is None else val.data_ptr())
             elif decl.dtype in (BF16, F16, FP8):
@@ -416,6 +472,15 @@ def compile(expr, dtypes, name=None) -> Kernel:   # noqa: A001 - the C ABI's nam
 
 
 def elementwise(handle: Kernel, n, args, stream=None, config=None):
+    if config is None:
+        fast = _fast or _load_fast()
+        keep, _, base = handle._buffers()
+        st = fast.elementwise(_FN["hipmr_elementwise_ex"], handle._hv, handle._kinds, args, n, base,
+                              _stream_ptr(stream))
+        if st is not None:
+            if st != OK:
+                _check(st)
+            return keep
     handle.check_lengths(int(n), args)
     keep, ptrs = handle.marshal(args)
     _check(lib().hipmr_elementwise_ex(handle.handle, int(n), ptrs, _config(config),
@@ -429,8 +494,11 @@ _ws_lock = threading.Lock()
 
 def workspace(nbytes, device, stream_ptr):
     """A device workspace of at least nbytes, cached per (device, stream)."""
+    key = (device if isinstance(device, str) else (device.type, device.index), stream_ptr)
+    buf = _ws_cache.get(key)
+    if buf is not None and buf.numel() >= nbytes:
+        return buf
     import torch
-    key = (str(device), stream_ptr)
     with _ws_lock:
         buf = _ws_cache.get(key)
         if buf is None or buf.numel() < nbytes:
@@ -440,21 +508,33 @@ def workspace(nbytes, device, stream_ptr):
 
 
 def reduce_workspace_bytes(handle: Kernel, n):
-    return lib().hipmr_reduce_workspace_bytes(handle.handle, int(n))
+    need = handle._ws_bytes
+    if need is None:
+        need = handle._ws_bytes = lib().hipmr_reduce_workspace_bytes(handle.handle, int(n))
+    return need
 
 
 def reduce(handle: Kernel, map_expr, combine_op, neutral, n, args, out, workspace_buf=None,
            stream=None, config=None):   # noqa: A001 - the C ABI's name
-    _check_out(out, handle.result_dtype, 1, "reduce")
+    fast = _fast or _load_fast()
+    ptr = fast.out_pointer(out, _TORCH_DTYPES.get(handle.result_dtype), 1)
+    if ptr is None:
+        _check_out(out, handle.result_dtype, 1, "reduce")
     s = _stream_ptr(stream)
-    need = reduce_workspace_bytes(handle, n)
     if workspace_buf is None:
-        workspace_buf = workspace(need, out.device, s)
+        workspace_buf = workspace(reduce_workspace_bytes(handle, n), out.device, s)
+    if config is None:
+        st = fast.reduce(_FN["hipmr_reduce_ex"], handle._hv, handle._kinds, args, n, handle._buffers()[2], s,
+                         _enc(map_expr), _enc(combine_op), _enc(neutral), ptr, workspace_buf)
+        if st is not None:
+            if st != OK:
+                _check(st)
+            return out
     handle.check_lengths(int(n), args)
     keep, ptrs = handle.marshal(args)
     _check(lib().hipmr_reduce_ex(handle.handle, _enc(map_expr), _enc(combine_op), _enc(neutral),
-                                 int(n), ptrs, ctypes.c_void_p(out.data_ptr()),
-                                 ctypes.c_void_p(workspace_buf.data_ptr()),
+                                 int(n), ptrs, out.data_ptr(),
+                                 workspace_buf.data_ptr(),
                                  _nbytes(workspace_buf),
                                  _config(config), s))
     return out
@@ -479,8 +559,8 @@ def reduce_compensated(handle: Kernel, n, args, post_scale=1.0, out=None, worksp
     handle.check_lengths(int(n), args)
     keep, ptrs = handle.marshal(args)
     _check(lib().hipmr_reduce_compensated(handle.handle, int(n), ptrs, float(post_scale),
-                                          ctypes.c_void_p(out.data_ptr()),
-                                          ctypes.c_void_p(workspace_buf.data_ptr()),
+                                          out.data_ptr(),
+                                          workspace_buf.data_ptr(),
                                           _nbytes(workspace_buf), _config(config), s))
     return out
 
@@ -495,8 +575,8 @@ def norm2(handle: Kernel, n, args, post_scale=1.0, passes=2, out=None, workspace
     handle.check_lengths(int(n), args)
     keep, ptrs = handle.marshal(args)
     _check(lib().hipmr_norm2(handle.handle, int(n), ptrs, float(post_scale), int(passes),
-                             ctypes.c_void_p(out.data_ptr()),
-                             ctypes.c_void_p(workspace_buf.data_ptr()), _nbytes(workspace_buf),
+                             out.data_ptr(),
+                             workspace_buf.data_ptr(), _nbytes(workspace_buf),
                              _config(config), s))
     return out
 
@@ -509,15 +589,25 @@ def scan(handle: Kernel, combine_op, neutral, n, args, out, exclusive=False, wor
          stream=None, config=None):
     """out[i] = neutral (+) map(0) (+) ... (+) map(i) (inclusive) or up to
     map(i - 1) (exclusive); `out` is a device tensor of n result values."""
-    _check_out(out, handle.result_dtype, int(n), "scan")
+    fast = _fast or _load_fast()
+    ptr = fast.out_pointer(out, _TORCH_DTYPES.get(handle.result_dtype), n)
+    if ptr is None:
+        _check_out(out, handle.result_dtype, int(n), "scan")
     s = _stream_ptr(stream)
     if workspace_buf is None:
         workspace_buf = workspace(scan_workspace_bytes(handle, n), out.device, s)
+    if config is None:
+        st = fast.scan(_FN["hipmr_scan"], handle._hv, handle._kinds, args, n, handle._buffers()[2], s,
+                       combine_op.encode(), neutral.encode(), ptr, bool(exclusive), workspace_buf)
+        if st is not None:
+            if st != OK:
+                _check(st)
+            return out
     handle.check_lengths(int(n), args)
     keep, ptrs = handle.marshal(args)
     _check(lib().hipmr_scan(handle.handle, combine_op.encode(), neutral.encode(), int(n), ptrs,
-                            ctypes.c_void_p(out.data_ptr()), 1 if exclusive else 0,
-                            ctypes.c_void_p(workspace_buf.data_ptr()), _nbytes(workspace_buf),
+                            out.data_ptr(), 1 if exclusive else 0,
+                            workspace_buf.data_ptr(), _nbytes(workspace_buf),
                             _config(config), s))
     return out
 
@@ -539,9 +629,9 @@ def reduce_segmented(handle: Kernel, combine_op, neutral, offsets, total_n, args
     handle.check_lengths(int(total_n), args)
     keep, ptrs = handle.marshal(args)
     _check(lib().hipmr_reduce_segmented(handle.handle, combine_op.encode(), neutral.encode(), nseg,
-                                        ctypes.c_void_p(offsets.data_ptr()), int(total_n), ptrs,
-                                        ctypes.c_void_p(out.data_ptr()),
-                                        ctypes.c_void_p(workspace_buf.data_ptr()),
+                                        offsets.data_ptr(), int(total_n), ptrs,
+                                        out.data_ptr(),
+                                        workspace_buf.data_ptr(),
                                         _nbytes(workspace_buf), _config(config), s))
     return out
 
@@ -562,8 +652,8 @@ def reduce_segmented_noalloc(handle: Kernel, combine_op, neutral, offsets, total
     handle.check_lengths(int(total_n), args)
     keep, ptrs = handle.marshal(args)
     _check(lib().hipmr_reduce_segmented_noalloc(handle.handle, combine_op.encode(), neutral.encode(),
-                                                nseg, ctypes.c_void_p(offsets.data_ptr()),
-                                                int(total_n), ptrs, ctypes.c_void_p(out.data_ptr()),
+                                                nseg, offsets.data_ptr(),
+                                                int(total_n), ptrs, out.data_ptr(),
                                                 _config(config), _stream_ptr(stream)))
     return out
 
@@ -582,9 +672,9 @@ def autotune_segmented(handle: Kernel, combine_op, neutral, offsets, total_n, ar
     keep, ptrs = handle.marshal(args)
     best = LaunchConfig()
     _check(lib().hipmr_autotune_segmented(handle.handle, combine_op.encode(), neutral.encode(), nseg,
-                                          ctypes.c_void_p(offsets.data_ptr()), int(total_n), ptrs,
-                                          ctypes.c_void_p(out.data_ptr()),
-                                          ctypes.c_void_p(workspace_buf.data_ptr()),
+                                          offsets.data_ptr(), int(total_n), ptrs,
+                                          out.data_ptr(),
+                                          workspace_buf.data_ptr(),
                                           _nbytes(workspace_buf), int(reps), ctypes.byref(best), s))
     return {f: getattr(best, f) for f, _ in LaunchConfig._fields_}
 
@@ -599,8 +689,8 @@ def autotune_reduce(handle: Kernel, combine_op, neutral, n, args, out, reps=10,
     keep, ptrs = handle.marshal(args)
     best = LaunchConfig()
     _check(lib().hipmr_autotune_reduce(handle.handle, combine_op.encode(), neutral.encode(), int(n),
-                                       ptrs, ctypes.c_void_p(out.data_ptr()),
-                                       ctypes.c_void_p(workspace_buf.data_ptr()),
+                                       ptrs, out.data_ptr(),
+                                       workspace_buf.data_ptr(),
                                        _nbytes(workspace_buf), int(reps), ctypes.byref(best), s))
     return {f: getattr(best, f) for f, _ in LaunchConfig._fields_}
 
