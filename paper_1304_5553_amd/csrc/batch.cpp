@@ -34,9 +34,24 @@ namespace hipmr {
 
 namespace {
 
-constexpr int kSegBlock = 256, kSegIpt = 4, kSegBlocksPerCu = 8;
-constexpr int kPlanBlock = 1024;
-constexpr int kMaxLdsSegs = 8192;   // tile-start table in LDS up to this many entries
+// Default geometry by the number of segments.  Every block plans the tile table
+// in its own LDS, so few large blocks pay: sum of 68 M floats in 4096 segments
+// 54.5 us with 256 threads x 8 blocks per CU, 48.5 with 512 x 2 (48.7 with
+// 1024 x 1); in 16384 segments 58.5 with 1024 x 1 and the table in LDS (17 MB:
+// 24.7), 66.5 (26.6) with a planning launch.  Larger tables are planned by a
+// launch of their own.
+constexpr int kSegIpt = 4;
+constexpr int kSeg2Block = 256, kPlanBlock = 1024;
+constexpr int kLdsSegsMid = 8191, kLdsSegsMax = 32768;
+struct SegShape {
+    int block, blocks_per_cu, lds_limit;
+};
+constexpr SegShape kSegOwnShape = {256, 8, kLdsSegsMid};   // what a call with a geometry of its own leaves open
+SegShape default_shape(int32_t nseg) {
+    if (nseg <= kLdsSegsMid) return {512, 2, kLdsSegsMid};
+    if (nseg <= kLdsSegsMax) return {1024, 1, kLdsSegsMax};
+    return {256, 8, 0};
+}
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
@@ -56,11 +71,14 @@ std::string tune_key(const char* op, const char* combine, const char* neutral) {
     return std::string(op) + "\x1f" + (combine ? combine : "") + "\x1f" + (neutral ? neutral : "");
 }
 
-int lds_capacity(int32_t nseg) {
-    if (nseg + 1 > kMaxLdsSegs) return 0;
+// Segments the kernel's LDS table is built for (a power of two, less one
+// entry, up to kLdsSegsMid; one size above), 0 above limit.
+int lds_capacity(int32_t nseg, int limit) {
+    if (nseg > limit) return 0;
+    if (nseg > kLdsSegsMid) return kLdsSegsMax;
     int cap = 256;
     while (cap < nseg + 1) cap *= 2;
-    return cap;
+    return cap - 1;
 }
 
 struct SegLaunch {
@@ -91,7 +109,7 @@ KernelSpec seg_spec(KernelKind kind, const LaunchCfg& cfg, bool idx64, const cha
         s.unaligned = cfg.unaligned;
     }
     if (kind == KernelKind::SegS2) {
-        s.block = kSegBlock;
+        s.block = kSeg2Block;
         s.ipt = 1;
         s.vec = 1;
         s.nt_loads = s.nt_stores = true;
@@ -101,7 +119,7 @@ KernelSpec seg_spec(KernelKind kind, const LaunchCfg& cfg, bool idx64, const cha
 }
 
 hipmr_status seg_prepare(hipmr_kernel* h, const char* combine, const char* neutral, int32_t nseg,
-                         int64_t total_n, void* const* args, const LaunchCfg& cfg_in,
+                         int64_t total_n, void* const* args, const LaunchCfg& cfg_in, bool own_shape,
                          CallKernels* used, SegLaunch* out) {
     LaunchCfg cfg = cfg_in;
     long long head = vector_head(h, args, &cfg);
@@ -110,9 +128,25 @@ hipmr_status seg_prepare(hipmr_kernel* h, const char* combine, const char* neutr
         head = 0;
     }
     bool idx64 = total_n >= (int64_t(1) << 31);
-    int lds = cfg.seg_global ? 0 : lds_capacity(nseg);
+    int lds = cfg.seg_global ? 0 : lds_capacity(nseg, (own_shape ? kSegOwnShape : default_shape(nseg)).lds_limit);
     hipmr_status st = HIPMR_OK;
     out->plan = nullptr;
+    if (!own_shape && nseg > kLdsSegsMid) {       // both forms above it, for a capture of the other's size
+        LaunchCfg c = cfg;
+        c.block = c.blocks_per_cu = 0;            // not part of the key: the shapes below are
+        st = load_family(h, 'g', cfg.vec > 1, idx64, c, combine, neutral, [&] {
+            std::vector<KernelSpec> v;
+            for (int32_t ns : {kLdsSegsMax, kLdsSegsMax + 1}) {
+                c.block = default_shape(ns).block;
+                const int l = cfg.seg_global ? 0 : lds_capacity(ns, default_shape(ns).lds_limit);
+                v.push_back(seg_spec(KernelKind::SegS1, c, idx64, combine, neutral, l));
+            }
+            v.push_back(seg_spec(KernelKind::SegPlan, c, idx64, combine, neutral, 0));
+            v.push_back(seg_spec(KernelKind::SegS2, c, idx64, combine, neutral, 0));
+            return v;
+        });
+        if (st != HIPMR_OK) return st;
+    }
     if (lds == 0) {       // the table does not fit LDS: a planning launch writes it to global memory
         st = variant_function(h, seg_spec(KernelKind::SegPlan, cfg, idx64, combine, neutral, lds),
                               &out->plan, used);
@@ -160,8 +194,8 @@ hipmr_status seg_launch(hipmr_kernel* h, const SegLaunch& L, int32_t nseg, const
     st = launch(L.s1, (unsigned)L.grid1, (unsigned)L.cfg.block, p1.data(), stream);
     if (st != HIPMR_OK) return st;
     void* p2[5] = {&tile_start, &ns, &tpart, &d_out, &cap};
-    unsigned grid2 = (unsigned)((nseg + kSegBlock / 64 - 1) / (kSegBlock / 64));
-    return launch(L.s2, grid2, kSegBlock, p2, stream);
+    unsigned grid2 = (unsigned)((nseg + kSeg2Block / 64 - 1) / (kSeg2Block / 64));
+    return launch(L.s2, grid2, kSeg2Block, p2, stream);
 }
 
 hipmr_status seg_checks(hipmr_kernel* h, const char* combine, const char* neutral, int32_t nseg,
@@ -327,12 +361,14 @@ hipmr_status reduce_segmented_on(hipmr_kernel* h, const char* combine, const cha
     if (nseg == 0) return HIPMR_OK;
     hipmr_launch_config tuned{};
     cfgp = apply_tuned(h, "seg", combine, neutral, total_n, cfgp, &tuned);
+    const bool own_shape = cfgp && (cfgp->block || cfgp->grid || cfgp->blocks_per_cu);
+    const SegShape shape = own_shape ? kSegOwnShape : default_shape(nseg);
     LaunchCfg cfg;
-    st = resolve_cfg(cfgp, kSegBlock, kSegIpt, h->default_vec, kSegBlocksPerCu, &cfg);
+    st = resolve_cfg(cfgp, shape.block, kSegIpt, h->default_vec, shape.blocks_per_cu, &cfg);
     if (st != HIPMR_OK) return st;
     CallKernels used;
     SegLaunch L;
-    st = seg_prepare(h, combine, neutral, nseg, total_n, args, cfg, &used, &L);
+    st = seg_prepare(h, combine, neutral, nseg, total_n, args, cfg, own_shape, &used, &L);
     if (st != HIPMR_OK) return st;
     set_last_kernels(h, used);
     return seg_launch(h, L, nseg, d_offsets, total_n, args, d_out, workspace, stream);
@@ -397,12 +433,12 @@ hipmr_status hipmr_autotune_segmented(hipmr_handle h, const char* combine, const
     for (size_t c = 0; c < cands.size(); ++c)
         jobs.push_back([&, c] {
             LaunchCfg cfg;
-            hipmr_status s2 = resolve_cfg(&cands[c], kSegBlock, kSegIpt, h->default_vec, kSegBlocksPerCu, &cfg);
+            hipmr_status s2 = resolve_cfg(&cands[c], kSegOwnShape.block, kSegIpt, h->default_vec, kSegOwnShape.blocks_per_cu, &cfg);
             if (s2 != HIPMR_OK) return s2;
             // compile only: building variants never touches the GPU
             if (vector_head(h, args, &cfg) < 0) cfg.vec = 1;
             bool idx64 = total_n >= (int64_t(1) << 31);
-            int lds = lds_capacity(nseg);
+            int lds = lds_capacity(nseg, kLdsSegsMid);
             std::shared_ptr<CodeObject> co;
             for (KernelKind k : {KernelKind::SegPlan, KernelKind::SegS1, KernelKind::SegS2}) {
                 s2 = get_variant(h, seg_spec(k, cfg, idx64, combine, neutral, lds), &co);
@@ -416,11 +452,11 @@ hipmr_status hipmr_autotune_segmented(hipmr_handle h, const char* combine, const
     hipmr_launch_config best_cfg{};
     for (size_t c = 0; c < cands.size(); ++c) {
         LaunchCfg cfg;
-        st = resolve_cfg(&cands[c], kSegBlock, kSegIpt, h->default_vec, kSegBlocksPerCu, &cfg);
+        st = resolve_cfg(&cands[c], kSegOwnShape.block, kSegIpt, h->default_vec, kSegOwnShape.blocks_per_cu, &cfg);
         if (st != HIPMR_OK) return st;
         CallKernels used;
         SegLaunch L;
-        st = seg_prepare(h, combine, neutral, nseg, total_n, args, cfg, &used, &L);
+        st = seg_prepare(h, combine, neutral, nseg, total_n, args, cfg, true, &used, &L);
         if (st != HIPMR_OK) return st;
         float ms = 0;
         st = time_config([&] { return seg_launch(h, L, nseg, d_offsets, total_n, args, d_out, workspace, stream); },

@@ -1009,65 +1009,61 @@ __device__ __forceinline__ int hipmr_seg_tiles(long long a, long long b, long lo
 }
 
 // The tile table: tiles per segment and their exclusive prefix, by one block
-// of B threads.  Each thread takes R consecutive segments per round of
-// B * R (all offset loads issued before any is used).  Counts are summed in
-// 64 bits and every entry is capped at the tile capacity of the workspace,
-// so offsets that describe more tiles than it holds (overlapping segments)
-// can never send a later kernel past it.  The table goes to `lds` and / or
-// `glob` (either may be null); it is complete when this returns.
-template <int B, int R = 4>
+// of B threads, in rounds of B * R segments: a wave takes 64 R consecutive
+// ones, 64 per step (coalesced; all of a round's offsets are loaded before any
+// is used), so a round costs one trip to memory and two barriers.  Counts are
+// summed in 64 bits and every entry is capped at the tile capacity of the
+// workspace, so offsets that describe more tiles than it holds (overlapping
+// segments) can never send a later kernel past it.  The table goes to `lds`
+// and / or `glob` (either may be null); it is complete when this returns.
+template <int B, int R>
 __device__ void hipmr_seg_plan(const long long* __restrict__ off, int nseg, long long total,
                                long long head, int V, long long T, long long cap,
                                int* lds, int* __restrict__ glob) {
   __shared__ long long hipmr_wsum[B / 64];
-  __shared__ long long hipmr_carry;
   const auto hipmr_plus = [](long long p, long long q) { return p + q; };
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  if (threadIdx.x == 0) hipmr_carry = 0;
-  __syncthreads();
+  long long carry = 0;                           // tiles of the earlier rounds, in every thread
   for (int base = 0; base < nseg; base += B * R) {
-    const int s0 = base + threadIdx.x * R;
-    long long o[R + 1];
-#pragma unroll
-    for (int j = 0; j <= R; ++j) o[j] = s0 + j <= nseg ? off[s0 + j] : 0;
-    long long t[R], tsum = 0;
+    const int s0 = base + w * (64 * R) + l;
+    long long o0[R], o1[R];
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-      t[j] = 0;
-      if (s0 + j < nseg) {
+      o0[j] = s0 + 64 * j < nseg ? off[s0 + 64 * j] : 0;
+      o1[j] = s0 + 64 * j < nseg ? off[s0 + 64 * j + 1] : 0;
+    }
+    long long x[R], sum = 0;                     // exclusive in the wave's run
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      long long t = 0;
+      if (s0 + 64 * j < nseg) {
         long long a, b, ab;
-        hipmr_seg_clamp(o[j], o[j + 1], total, head, V, a, b, ab);
-        t[j] = hipmr_seg_tiles(a, b, ab, T);
+        hipmr_seg_clamp(o0[j], o1[j], total, head, V, a, b, ab);
+        t = hipmr_seg_tiles(a, b, ab, T);
       }
-      tsum += t[j];
+      const long long incl = hipmr_dpp_scan(t, 0LL, hipmr_plus);
+      x[j] = sum + incl - t;
+      sum += __shfl(incl, 63, 64);
     }
-    const long long x = hipmr_dpp_scan(tsum, 0LL, hipmr_plus);   // inclusive scan in the wave
-    if (l == 63) hipmr_wsum[w] = x;
+    if (l == 0) hipmr_wsum[w] = sum;
     __syncthreads();
-    if (w == 0) {                                // scan of the wave totals
-      const long long v = hipmr_dpp_scan(l < B / 64 ? hipmr_wsum[l] : 0LL, 0LL, hipmr_plus);
-      if (l < B / 64) hipmr_wsum[l] = v;
-    }
-    __syncthreads();
-    const long long excl = hipmr_carry + (w > 0 ? hipmr_wsum[w - 1] : 0) + x - tsum;
-    long long run = excl;
+    const long long v = hipmr_dpp_scan(l < B / 64 ? hipmr_wsum[l] : 0LL, 0LL, hipmr_plus);
+    const long long before = carry + (w > 0 ? __shfl(v, w - 1, 64) : 0LL);
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-      if (s0 + j < nseg) {
-        const int v = (int)(run < cap ? run : cap);
-        if (lds) lds[s0 + j] = v;
-        if (glob) glob[s0 + j] = v;
+      if (s0 + 64 * j < nseg) {
+        const int e = (int)(before + x[j] < cap ? before + x[j] : cap);
+        if (lds) lds[s0 + 64 * j] = e;
+        if (glob) glob[s0 + 64 * j] = e;
       }
-      run += t[j];
     }
-    __syncthreads();
-    if (threadIdx.x == B - 1) hipmr_carry = excl + tsum < cap ? excl + tsum : cap;
-    __syncthreads();
+    carry += __shfl(v, B / 64 - 1, 64);
+    __syncthreads();                             // hipmr_wsum is written again; the table is read next
   }
   if (threadIdx.x == 0) {
-    const int v = (int)hipmr_carry;
-    if (lds) lds[nseg] = v;
-    if (glob) glob[nseg] = v;
+    const int e = (int)(carry < cap ? carry : cap);
+    if (lds) lds[nseg] = e;
+    if (glob) glob[nseg] = e;
   }
   __syncthreads();
 }
@@ -1080,7 +1076,7 @@ extern "C" __global__ void __launch_bounds__(1024)
 @@KNAME@@(const long long* __restrict__ hipmr_off, int hipmr_nseg, long long hipmr_total,
           long long hipmr_head, int* __restrict__ hipmr_tile_start, long long hipmr_cap)
 {
-  hipmr_seg_plan<1024>(hipmr_off, hipmr_nseg, hipmr_total, hipmr_head, @@VEC@@,
+  hipmr_seg_plan<1024, 8>(hipmr_off, hipmr_nseg, hipmr_total, hipmr_head, @@VEC@@,
                        64LL * @@VEC@@ * @@IPT@@, hipmr_cap, nullptr, hipmr_tile_start);
 }
 )HIP";
@@ -1124,9 +1120,10 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   // memory.  (The host picks the LDS variant only when the table fits.)
   const int* hipmr_tab;
   if constexpr (HIPMR_LDS_SEGS > 0) {
-    __shared__ int hipmr_ts_lds[HIPMR_LDS_SEGS > 0 ? HIPMR_LDS_SEGS : 1];
-    if (hipmr_nseg >= HIPMR_LDS_SEGS) return;
-    hipmr_seg_plan<HIPMR_B>(hipmr_offsets, hipmr_nseg, hipmr_total, hipmr_head, HIPMR_V, HIPMR_T,
+    __shared__ int hipmr_ts_lds[HIPMR_LDS_SEGS + 1];
+    if (hipmr_nseg > HIPMR_LDS_SEGS) return;
+    constexpr int HIPMR_R = HIPMR_LDS_SEGS < HIPMR_B ? 1 : HIPMR_LDS_SEGS >= 8 * HIPMR_B ? 8 : (HIPMR_LDS_SEGS + 1) / HIPMR_B;
+    hipmr_seg_plan<HIPMR_B, HIPMR_R>(hipmr_offsets, hipmr_nseg, hipmr_total, hipmr_head, HIPMR_V, HIPMR_T,
                             hipmr_cap, hipmr_ts_lds, blockIdx.x == 0 ? hipmr_tile_start : nullptr);
     hipmr_tab = hipmr_ts_lds;
   } else {

@@ -147,7 +147,7 @@ struct KernelSpec {
     bool norm = false;        // CompS2: finish as sqrt(sum) / scale
     // batching extension
     int scan_mode = 0;        // Scan: 0 one tile, 1 tile totals, 2 from totals, 3 one pass
-    int lds_segs = 0;         // SegS1: tile-start table held in LDS (capacity), 0 = global
+    int lds_segs = 0;         // SegS1: segments its LDS tile table holds, 0 = table in global memory
 };
 inline auto spec_fields(const KernelSpec& s) {
     return std::tie(s.kind, s.idx64, s.block, s.ipt, s.vec, s.nt_loads, s.nt_stores, s.unaligned, s.square,
