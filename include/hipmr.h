@@ -257,8 +257,8 @@ hipmr_status hipmr_reduce_compensated(hipmr_handle h, int64_t n, void *const *ar
  *     [2^-40, 2^40] no square leaves the float range and pass 2 ends at once;
  *     else every block of it (same grid) derives from the maxima the power of
  *     two s that puts the largest in [1, 2) (exponent clamped to [-126, 126])
- *     and accumulates (map(i) * s)^2 instead.  The final FP64 step returns
- *     post_scale * sqrt(sum) / s.  Three launches; the data are read once, or
+ *     and accumulates (map(i) * s)^2 instead.  Its last FP64 step returns
+ *     post_scale * sqrt(sum) / s.  Two launches; the data are read once, or
  *     twice where pass 2 is needed.
  *   passes == 1: no scaling, one read; the squares must stay inside the float
  *     range (true for every half or FP8 load: their squares are below 2^32).

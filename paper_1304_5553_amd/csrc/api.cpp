@@ -413,7 +413,7 @@ struct Stage1 {
 };
 
 hipmr_status stage1_launch(hipmr_kernel* h, KernelSpec spec, LaunchCfg cfg,
-                           int64_t n, void* const* args, void* partial, void* extra,
+                           int64_t n, void* const* args, void* partial, void* amax, double post, void* out_p,
                            void* stream, CallKernels* used, Stage1* out) {
     const long long head = vector_head(h, args, &cfg);
     const bool vector = head >= 0;
@@ -437,7 +437,9 @@ hipmr_status stage1_launch(hipmr_kernel* h, KernelSpec spec, LaunchCfg cfg,
     params.push_back(&n64);
     params.push_back(&head64);
     params.push_back(&partial);
-    params.push_back(&extra);
+    params.push_back(&amax);
+    params.push_back(&post);
+    params.push_back(&out_p);
     return launch(out->fn, (unsigned)out->grid, (unsigned)cfg.block, params.data(), stream);
 }
 
@@ -495,7 +497,7 @@ hipmr_status hipmr_reduce_compensated(hipmr_handle h, int64_t n, void* const* ar
     s1.exact_runs = single_fp8_load(h) && cfg.vec * cfg.ipt <= 64;
     CallKernels used;
     Stage1 r;
-    st = stage1_launch(h, s1, cfg, n, args, workspace, nullptr, stream, &used, &r);
+    st = stage1_launch(h, s1, cfg, n, args, workspace, nullptr, post_scale, out, stream, &used, &r);
     if (st != HIPMR_OK) return st;
     KernelSpec s2 = comp_spec(KernelKind::CompS2, cfg);
     s2.block = kStage2Block;
@@ -504,8 +506,7 @@ hipmr_status hipmr_reduce_compensated(hipmr_handle h, int64_t n, void* const* ar
     st = variant_function(h, s2, &fn2, &used);
     if (st != HIPMR_OK) return st;
     set_last_kernels(h, used);
-    void* scale64 = (char*)workspace + kScaleOffset + 8;
-    void* params2[5] = {&workspace, &r.grid, &post_scale, &scale64, &out};
+    void* params2[4] = {&workspace, &r.grid, &post_scale, &out};
     return launch(fn2, 1, kStage2Block, params2, stream);
 }
 
@@ -520,7 +521,6 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
     st = resolve_cfg(cfgp, kRedBlock, kRedIpt, h->default_vec, kRedBlocksPerCu, &cfg);
     if (st != HIPMR_OK) return st;
     void* amax = (char*)workspace + kAmaxOffset;
-    void* scale_d = (char*)workspace + kScaleOffset + 8;
     CallKernels used;
     const bool two = passes == 2 && n > 0;     // an empty norm is 0 either way
     if (two) {
@@ -528,29 +528,32 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
         KernelSpec a1 = comp_spec(KernelKind::CompS1Vector, cfg);
         a1.square = a1.track = true;
         Stage1 r1;
-        st = stage1_launch(h, a1, cfg, n, args, workspace, amax, stream, &used, &r1);
+        st = stage1_launch(h, a1, cfg, n, args, workspace, amax, post_scale, out, stream, &used, &r1);
         if (st != HIPMR_OK) return st;
     }
     // pass 2 (or the only pass): compensated sum of (map * scale)^2; with two
     // passes every block first derives the power-of-two scale from the pass-1
-    // maxima (block 0 also stores it for the final fold) and ends there if
-    // pass 1's sums stand
+    // maxima; if pass 1's sums stand its block 0 only folds them, else its last
+    // block folds its own
     KernelSpec q1 = comp_spec(KernelKind::CompS1Vector, cfg);
     q1.square = true;
     q1.scaled = two;
     Stage1 r2;
-    st = stage1_launch(h, q1, cfg, n, args, workspace, amax, stream, &used, &r2);
+    st = stage1_launch(h, q1, cfg, n, args, workspace, amax, post_scale, out, stream, &used, &r2);
     if (st != HIPMR_OK) return st;
+    if (two) {
+        set_last_kernels(h, used);
+        return HIPMR_OK;
+    }
     KernelSpec q2 = comp_spec(KernelKind::CompS2, cfg);
     q2.block = kStage2Block;
     q2.ipt = q2.vec = 1;
     q2.norm = true;
-    q2.scaled = two;
     void* fn2 = nullptr;
     st = variant_function(h, q2, &fn2, &used);
     if (st != HIPMR_OK) return st;
     set_last_kernels(h, used);
-    void* params2[5] = {&workspace, &r2.grid, &post_scale, &scale_d, &out};
+    void* params2[4] = {&workspace, &r2.grid, &post_scale, &out};
     return launch(fn2, 1, kStage2Block, params2, stream);
 }
 
@@ -938,12 +941,11 @@ hipmr_status hipmr_selftest_compile(int32_t* count) {
                         specs.push_back(q);
                     }
                 }
-                for (int variant = 0; variant < 3; ++variant) {
+                for (int variant = 0; variant < 2; ++variant) {
                     KernelSpec q = comp_spec(KernelKind::CompS2, cfg);
                     q.block = kStage2Block;
                     q.ipt = q.vec = 1;
                     q.norm = variant > 0;
-                    q.scaled = variant == 2;
                     specs.push_back(q);
                 }
                 for (const KernelSpec& q : specs) {

@@ -721,17 +721,14 @@ __device__ __forceinline__ float hipmr_block_amax(float m) {
 // The norm's power-of-two scale from its first pass: the max |map| over
 // that pass's block partials (one per block of this grid: both passes use
 // the same geometry).  Where that maximum is 0 or lies in [2^-40, 2^40] the
-// first pass's own sums of unscaled squares stand (0 is returned, the stored
-// scale is 1): n < 2^47 such squares stay below 2^127, and what a square
+// first pass's own sums of unscaled squares stand (0 is returned): n < 2^47 such squares stay below 2^127, and what a square
 // loses below 2^-149 is at most 2^-70 of the largest one.  Scaling by a power
 // of two changes no bit of a product or sum that stays in range, so the
 // result is the one the scaled pass would give.  Else s = 2^-e, e the
 // exponent of the max clamped to [-126, 126], so the largest scaled
-// magnitude lies in [1, 2).  Every block computes it; block 0 also stores it
-// (float, then double) for the final fold.
+// magnitude lies in [1, 2).  Every block computes it.
 template <int B>
-__device__ __forceinline__ float hipmr_norm_scale(const float* __restrict__ amax,
-                                                  float* __restrict__ store) {
+__device__ __forceinline__ float hipmr_norm_scale(const float* __restrict__ amax) {
   float m = 0.0f;
   for (int k = threadIdx.x; k < (int)gridDim.x; k += B) m = __builtin_elementwise_maximum(m, amax[k]);
   m = hipmr_block_amax<B>(m);
@@ -741,10 +738,6 @@ __device__ __forceinline__ float hipmr_norm_scale(const float* __restrict__ amax
     int e = (int)((__float_as_uint(m) >> 23) & 0xffu) - 127;
     e = e < -126 ? -126 : (e > 126 ? 126 : e);
     s = __uint_as_float((unsigned int)(127 - e) << 23);
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    store[0] = s;
-    *(double*)(store + 2) = (double)s;
   }
   return stands ? 0.0f : s;
 }
@@ -803,18 +796,62 @@ __device__ __forceinline__ P hipmr_block_reduce_pair(P v, F add) {
   }
   return v;
 }
+
+// The end of a sum or norm, by one block: the FP64 block partials folded
+// (Neumaier per thread, double-double tree), times the per-tensor post scale;
+// a norm is the root, over the data's scale.  The partials may be other
+// blocks' of the same launch: they are read with device-scope loads.
+template <int B, bool NORM>
+__device__ __forceinline__ void hipmr_comp_fold(const double* partial, int g, double post, double scale,
+                                                double* __restrict__ out) {
+  double s = 0.0, c = 0.0;
+  for (int k = threadIdx.x; k < g; k += B) {
+    const double v = __builtin_bit_cast(double, __hip_atomic_load((const unsigned long long*)partial + k,
+                                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const double t = s + v;
+    if (__builtin_isfinite(t)) c += fabs(s) >= fabs(v) ? (s - t) + v : (v - t) + s;
+    s = t;
+  }
+  hipmr_dd r = hipmr_two_sum_d(s, c);
+  r = hipmr_block_reduce_pair<B>(r, [](hipmr_dd a, hipmr_dd b) { return hipmr_dd_add(a, b); });
+  if (threadIdx.x == 0) {
+    const double total = __builtin_isfinite(r.hi) ? r.hi + r.lo : r.hi;
+    if constexpr (NORM) *out = post * (sqrt(total) / scale);
+    else *out = post * total;
+  }
+}
+
+// The second pass's end: every block publishes its partial and counts itself
+// in; the last one folds.  (The first pass's block 0 zeroes the count.)
+template <int B>
+__device__ __forceinline__ void hipmr_norm_finish(double v, double* partial, unsigned* count, double post,
+                                                  double scale, double* __restrict__ out) {
+  __shared__ bool hipmr_last;
+  if (threadIdx.x == 0) {
+    __hip_atomic_store((unsigned long long*)partial + blockIdx.x, __builtin_bit_cast(unsigned long long, v),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0);                 // the partial is written before the count says so
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    hipmr_last = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+  }
+  __syncthreads();
+  if (hipmr_last) hipmr_comp_fold<B, true>(partial, (int)gridDim.x, post, scale, out);
+}
 )HIP";
 
 // Stage 1 of a compensated sum, or of the norm's sum of squares: its first
 // pass (nrm1) sums the unscaled squares and keeps each block's max |map|, its
 // second (nrm2) rescales and sums again only where those squares could have
-// left the float range, and otherwise ends at once.  Bound: HBM, one read
-// (a pass for the maximum and always a second one for the sum took 81.6 us for
-// 2^27 bfloat16 values, 45.0 now).
+// left the float range, and otherwise one block of it folds the first pass's
+// partials.  Bound: HBM, one read (a pass for the maximum, always a second one
+// for the sum and a fold launch took 81.6 us for 2^27 bfloat16 values, the sums
+// beside the maximum 45.0, without the fold launch 43.4).
 const char* kCompS1Vector = R"HIP(
 extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 @@KNAME@@(@@PARAMS@@, long long hipmr_n, long long hipmr_head,
-          double* __restrict__ hipmr_partial, float* __restrict__ hipmr_scale_p)
+          double* __restrict__ hipmr_partial, float* __restrict__ hipmr_scale_p,
+          double hipmr_post, double* __restrict__ hipmr_out)
 {
   typedef @@IDX@@ hipmr_idx;
   constexpr int HIPMR_B = @@BLOCK@@, HIPMR_U = @@IPT@@, HIPMR_V = @@VEC@@;
@@ -823,8 +860,11 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   const hipmr_idx n = (hipmr_idx)hipmr_n;
   float hipmr_sc = 1.0f, hipmr_m = 0.0f;
   if constexpr (HIPMR_SCALED) {
-    hipmr_sc = hipmr_norm_scale<HIPMR_B>(hipmr_scale_p, (float*)((char*)hipmr_scale_p + @@SCALE_GAP@@));
-    if (hipmr_sc == 0.0f) return;               // the first pass's sums stand
+    hipmr_sc = hipmr_norm_scale<HIPMR_B>(hipmr_scale_p);
+    if (hipmr_sc == 0.0f) {                     // the first pass's sums stand
+      if (blockIdx.x == 0) hipmr_comp_fold<HIPMR_B, true>(hipmr_partial, (int)gridDim.x, hipmr_post, 1.0, hipmr_out);
+      return;
+    }
   }
   float hipmr_s[HIPMR_U], hipmr_e[HIPMR_U];
 #pragma unroll
@@ -908,12 +948,18 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 #pragma unroll
   for (int u = 1; u < HIPMR_U; ++u) hipmr_r = hipmr_ff_add(hipmr_r, hipmr_ff{hipmr_s[u], -hipmr_e[u]});
   hipmr_r = hipmr_block_reduce_pair<HIPMR_B>(hipmr_r, [](hipmr_ff a, hipmr_ff b) { return hipmr_ff_add(a, b); });
-  if (threadIdx.x == 0)
-    hipmr_partial[blockIdx.x] = __builtin_isfinite(hipmr_r.hi) ? (double)hipmr_r.hi + (double)hipmr_r.lo
-                                                               : (double)hipmr_r.hi;
+  const double hipmr_v = __builtin_isfinite(hipmr_r.hi) ? (double)hipmr_r.hi + (double)hipmr_r.lo
+                                                        : (double)hipmr_r.hi;
+  unsigned* const hipmr_count = (unsigned*)((char*)hipmr_scale_p + @@COUNT_GAP@@);
+  if constexpr (HIPMR_SCALED) {
+    hipmr_norm_finish<@@BLOCK@@>(hipmr_v, hipmr_partial, hipmr_count, hipmr_post, (double)hipmr_sc, hipmr_out);
+  } else if (threadIdx.x == 0) {
+    hipmr_partial[blockIdx.x] = hipmr_v;
+  }
   if constexpr (HIPMR_TRACK) {
     hipmr_m = hipmr_block_amax<@@BLOCK@@>(hipmr_m);
     if (threadIdx.x == 0) hipmr_scale_p[blockIdx.x] = hipmr_m;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *hipmr_count = 0;
   }
 }
 )HIP";
@@ -921,15 +967,19 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 const char* kCompS1Scalar = R"HIP(
 extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 @@KNAME@@(@@PARAMS@@, long long hipmr_n, long long hipmr_head,
-          double* __restrict__ hipmr_partial, float* __restrict__ hipmr_scale_p)
+          double* __restrict__ hipmr_partial, float* __restrict__ hipmr_scale_p,
+          double hipmr_post, double* __restrict__ hipmr_out)
 {
   typedef @@IDX@@ hipmr_idx;
   constexpr bool HIPMR_SQ = @@SQUARE@@, HIPMR_SCALED = @@SCALED@@, HIPMR_TRACK = @@TRACK@@;
   const hipmr_idx n = (hipmr_idx)hipmr_n;
   float hipmr_sc = 1.0f, hipmr_m = 0.0f;
   if constexpr (HIPMR_SCALED) {
-    hipmr_sc = hipmr_norm_scale<@@BLOCK@@>(hipmr_scale_p, (float*)((char*)hipmr_scale_p + @@SCALE_GAP@@));
-    if (hipmr_sc == 0.0f) return;               // the first pass's sums stand
+    hipmr_sc = hipmr_norm_scale<@@BLOCK@@>(hipmr_scale_p);
+    if (hipmr_sc == 0.0f) {                     // the first pass's sums stand
+      if (blockIdx.x == 0) hipmr_comp_fold<@@BLOCK@@, true>(hipmr_partial, (int)gridDim.x, hipmr_post, 1.0, hipmr_out);
+      return;
+    }
   }
   float hipmr_s = 0.0f, hipmr_cc = 0.0f;
   const long long hipmr_step = (long long)gridDim.x * @@BLOCK@@;
@@ -940,39 +990,29 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   }
   hipmr_ff hipmr_r = {hipmr_s, -hipmr_cc};
   hipmr_r = hipmr_block_reduce_pair<@@BLOCK@@>(hipmr_r, [](hipmr_ff a, hipmr_ff b) { return hipmr_ff_add(a, b); });
-  if (threadIdx.x == 0)
-    hipmr_partial[blockIdx.x] = __builtin_isfinite(hipmr_r.hi) ? (double)hipmr_r.hi + (double)hipmr_r.lo
-                                                               : (double)hipmr_r.hi;
+  const double hipmr_v = __builtin_isfinite(hipmr_r.hi) ? (double)hipmr_r.hi + (double)hipmr_r.lo
+                                                        : (double)hipmr_r.hi;
+  unsigned* const hipmr_count = (unsigned*)((char*)hipmr_scale_p + @@COUNT_GAP@@);
+  if constexpr (HIPMR_SCALED) {
+    hipmr_norm_finish<@@BLOCK@@>(hipmr_v, hipmr_partial, hipmr_count, hipmr_post, (double)hipmr_sc, hipmr_out);
+  } else if (threadIdx.x == 0) {
+    hipmr_partial[blockIdx.x] = hipmr_v;
+  }
   if constexpr (HIPMR_TRACK) {
     hipmr_m = hipmr_block_amax<@@BLOCK@@>(hipmr_m);
     if (threadIdx.x == 0) hipmr_scale_p[blockIdx.x] = hipmr_m;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *hipmr_count = 0;
   }
 }
 )HIP";
 
-// Final fold of the FP64 block partials (Neumaier per thread, double-double
-// tree), times the per-tensor post scale; the norm finishes as sqrt / scale.
+// Final fold of a compensated sum, or of a norm whose only pass was unscaled.
 const char* kCompS2 = R"HIP(
 extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 @@KNAME@@(const double* __restrict__ hipmr_partial, int hipmr_g, double hipmr_post,
-          const double* __restrict__ hipmr_scale64, double* __restrict__ hipmr_out)
+          double* __restrict__ hipmr_out)
 {
-  constexpr bool NORM = @@NORM@@, SCALED = @@SCALED@@;
-  double s = 0.0, c = 0.0;
-  for (int k = threadIdx.x; k < hipmr_g; k += @@BLOCK@@) {
-    const double v = hipmr_partial[k];
-    const double t = s + v;
-    if (__builtin_isfinite(t)) c += fabs(s) >= fabs(v) ? (s - t) + v : (v - t) + s;
-    s = t;
-  }
-  hipmr_dd r = hipmr_two_sum_d(s, c);
-  r = hipmr_block_reduce_pair<@@BLOCK@@>(r, [](hipmr_dd a, hipmr_dd b) { return hipmr_dd_add(a, b); });
-  if (threadIdx.x == 0) {
-    const double total = __builtin_isfinite(r.hi) ? r.hi + r.lo : r.hi;
-    if constexpr (NORM && SCALED) *hipmr_out = hipmr_post * (sqrt(total) / *hipmr_scale64);
-    else if constexpr (NORM) *hipmr_out = hipmr_post * sqrt(total);
-    else *hipmr_out = hipmr_post * total;
-  }
+  hipmr_comp_fold<@@BLOCK@@, @@NORM@@>(hipmr_partial, hipmr_g, hipmr_post, 1.0, hipmr_out);
 }
 )HIP";
 
@@ -1712,7 +1752,7 @@ std::string render(const Program& prog, const KernelSpec& spec, std::string* sym
     replace_all(body, "@@NORM@@", spec.norm ? "true" : "false");
     replace_all(body, "@@SCALED@@", spec.scaled ? "true" : "false");
     replace_all(body, "@@TRACK@@", spec.track ? "true" : "false");
-    replace_all(body, "@@SCALE_GAP@@", std::to_string(kScaleOffset - kAmaxOffset));
+    replace_all(body, "@@COUNT_GAP@@", std::to_string(kCountOffset - kAmaxOffset));
     replace_all(body, "@@LDS_SEGS@@", std::to_string(spec.lds_segs));
     replace_all(body, "@@IDX@@", spec.idx64 ? "long long" : "int");
     replace_all(body, "@@BLOCK@@", std::to_string(spec.block));

@@ -4,7 +4,7 @@ unscaled sums stand (max |x| = 0 or in [2^-40, 2^40])."""
 import numpy as np
 import pytest
 
-from gpu_util import dev_array, need_gpu
+from gpu_util import dev_array, need_gpu, torch
 import oracle
 import paper_1304_5553_amd as hm
 
@@ -31,8 +31,33 @@ def test_norm_is_the_same_at_every_scale(fmt, flags, n):
         bits = (shifted.view(np.uint32) >> 16).astype(np.uint16)
         xd = dev_array(bits, "bfloat16") if fmt == "bfloat16" else dev_array(shifted)
         g = hm.norm2(k, n, [xd], config=cfg).item()
+        assert hm.norm2(k, n, [xd], config=cfg).item() == g          # the blocks' count starts over
         if base is None:
             base = g
             o = oracle.norm2(vals.astype(np.float64))
             assert abs(g - o) <= 1e-6 * o
         assert g == base * 2.0 ** e, e
+
+
+def test_replays_switch_between_the_passes():
+    """One captured norm over data that need the second pass and data that do not."""
+    dev = need_gpu()
+    n = 300007
+    base = np.random.default_rng(5).uniform(0.5, 1.0, n).astype(np.float32)
+    st = torch.cuda.Stream()
+    k = hm.compile("x[i]", "float: const float *x")
+    x, out = dev_array(base), torch.empty((), dtype=torch.float64, device=dev)
+    ws = torch.empty(hm.reduce_workspace_bytes(k, n), dtype=torch.uint8, device=dev)
+    torch.cuda.synchronize()
+    hm.norm2(k, n, [x], out=out, workspace_buf=ws, stream=st)
+    st.synchronize()
+    want = out.item()
+    g = hm.Graph()
+    with g.capture(st):
+        hm.norm2(k, n, [x], out=out, workspace_buf=ws, stream=st)
+    for e in (0, 60, 60, -60, 0, 100):
+        x.copy_(torch.from_numpy((base * np.float32(2.0) ** e).astype(np.float32)))
+        torch.cuda.synchronize()
+        g.launch(st)
+        torch.cuda.synchronize()
+        assert out.item() == want * 2.0 ** e, e
