@@ -104,8 +104,8 @@ typedef struct hipmr_launch_config {
     int32_t grid;             /* blocks; 0: min(needed, blocks_per_cu * CU count)       */
     int32_t blocks_per_cu;    /* cap used when grid == 0                                */
     int32_t vec;              /* elements per vector chunk: 0 = 16 bytes of the narrowest
-                                 array (elementwise over arrays of several element
-                                 sizes: of the widest); power of two 1..16             */
+                                 array (elementwise and reduce over arrays of
+                                 several element sizes: of the widest); power of two 1..16             */
     int32_t flags;            /* HIPMR_CFG_* bits                                       */
 } hipmr_launch_config;
 

@@ -50,20 +50,23 @@ long long one_block_elements(const hipmr_kernel* h) {
 }
 
 // Elements per chunk: 16 bytes of the narrowest array, but 16 bytes of the
-// widest where elementwise kernels mix element sizes.  There a wider chunk moves in several
+// widest where elementwise kernels and plain reductions mix element sizes.
+// There a wider chunk moves in several
 // instructions of which each covers every other 16 bytes of its lines, which
 // costs more than the narrow arrays' short accesses do (two chunks per thread
 // keep enough of those in flight).  Measured, 419 MB per call, inputs rotated,
 // against 16 bytes of the narrowest: FP8 -> bfloat16 80.9 -> 65.9 us, FP8 ->
 // float 115.1 -> 70.8, bfloat16 -> double 108.8 -> 69.6, float -> FP8 96.5 ->
 // 67.6, bfloat16 -> FP8 69.2 -> 66.6, float -> bfloat16 68.6 -> 66.0; one chunk
-// per thread of those widths: 75.9, 77.6, 77.7, 76.7, 74.9, 73.8.
+// per thread of those widths: 75.9, 77.6, 77.7, 76.7, 74.9, 73.8.  Dots of 2^26
+// elements (four chunks per thread): FP8 x float 88.1 -> 52.7, bfloat16 x float
+// 68.3 -> 61.4, FP8 x bfloat16 34.4 -> 33.1, float x double 126.2 -> 119.9.
 int default_vec_for(const Signature& sig) {
     int narrow, wide;
     chunk_sizes(sig, &narrow, &wide);
     return narrow == 0 ? 4 : 16 / narrow;
 }
-void default_ew_shape(const Signature& sig, int* vec, int* ipt) {
+void default_stream_shape(const Signature& sig, int* vec, int* ipt) {
     int narrow, wide;
     chunk_sizes(sig, &narrow, &wide);
     *vec = wide == 0 ? 4 : 16 / wide;
@@ -356,14 +359,14 @@ hipmr_status build_handle(const char* expr, const char* dtypes, const std::strin
                                              "unsigned, a 64-bit integer or complex64");
     }
     h->default_vec = default_vec_for(h->prog.sig);
-    default_ew_shape(h->prog.sig, &h->ew_vec, &h->ew_ipt);
+    default_stream_shape(h->prog.sig, &h->stream_vec, &h->ew_ipt);
     if (!h->prog.sig.is_reduce) {
         // build the default variant now so that errors surface at compile time
         KernelSpec spec;
         spec.kind = h->prog.info.vectorizable ? KernelKind::EwVector : KernelKind::EwScalar;
         spec.block = kEwBlock;
         spec.ipt = h->ew_ipt;
-        spec.vec = h->ew_vec;
+        spec.vec = h->stream_vec;
         std::shared_ptr<CodeObject> co;
         st = get_variant(h.get(), spec, &co);
         if (st != HIPMR_OK) return st;
@@ -491,7 +494,7 @@ hipmr_status hipmr_reduce_compensated(hipmr_handle h, int64_t n, void* const* ar
     hipmr_status st = precision_checks(h, n, args, out, workspace, workspace_bytes);
     if (st != HIPMR_OK) return st;
     LaunchCfg cfg;
-    st = resolve_cfg(cfgp, kRedBlock, kRedIpt, h->default_vec, kRedBlocksPerCu, &cfg);
+    st = resolve_cfg(cfgp, kRedBlock, kRedIpt, h->stream_vec, kRedBlocksPerCu, &cfg);
     if (st != HIPMR_OK) return st;
     KernelSpec s1 = comp_spec(KernelKind::CompS1Vector, cfg);
     s1.exact_runs = single_fp8_load(h) && cfg.vec * cfg.ipt <= 64;
@@ -518,7 +521,7 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
     if (st != HIPMR_OK) return st;
     if (passes != 1 && passes != 2) return fail(HIPMR_E_INVALID, "passes must be 1 or 2");
     LaunchCfg cfg;
-    st = resolve_cfg(cfgp, kRedBlock, kRedIpt, h->default_vec, kRedBlocksPerCu, &cfg);
+    st = resolve_cfg(cfgp, kRedBlock, kRedIpt, h->stream_vec, kRedBlocksPerCu, &cfg);
     if (st != HIPMR_OK) return st;
     void* amax = (char*)workspace + kAmaxOffset;
     CallKernels used;
@@ -579,7 +582,7 @@ hipmr_status hipmr_elementwise_ex(hipmr_handle h, int64_t n, void* const* args,
     if (st != HIPMR_OK) return st;
     if (h->prog.sig.is_reduce) return fail(HIPMR_E_MISMATCH, "map-reduce handle passed to hipmr_elementwise");
     LaunchCfg cfg;
-    st = resolve_cfg(cfgp, kEwBlock, h->ew_ipt, h->ew_vec, kEwBlocksPerCu, &cfg);
+    st = resolve_cfg(cfgp, kEwBlock, h->ew_ipt, h->stream_vec, kEwBlocksPerCu, &cfg);
     if (st != HIPMR_OK) return st;
     if (n == 0) return HIPMR_OK;
     const long long head = vector_head(h, args, &cfg);
@@ -629,7 +632,7 @@ hipmr_status hipmr_prepare_reduce_ex(hipmr_handle h, const char* combine, const 
     if (!h || !combine || !neutral) return fail(HIPMR_E_INVALID, "NULL argument");
     if (!h->prog.sig.is_reduce) return fail(HIPMR_E_MISMATCH, "elementwise handle");
     LaunchCfg cfg;
-    hipmr_status rs = resolve_cfg(cfgp, kRedBlock, kRedIpt, h->default_vec, kRedBlocksPerCu, &cfg);
+    hipmr_status rs = resolve_cfg(cfgp, kRedBlock, kRedIpt, h->stream_vec, kRedBlocksPerCu, &cfg);
     if (rs != HIPMR_OK) return rs;
     std::vector<KernelSpec> specs = {s1_spec(h, h->prog.info.vectorizable, cfg, false, combine, neutral),
                                      s2_spec(combine, neutral)};
@@ -662,7 +665,7 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
     hipmr_launch_config tuned{};
     cfgp = apply_tuned(h, "reduce", combine, neutral, n, cfgp, &tuned);
     LaunchCfg cfg;
-    st = resolve_cfg(cfgp, kRedBlock, kRedIpt, h->default_vec, kRedBlocksPerCu, &cfg);
+    st = resolve_cfg(cfgp, kRedBlock, kRedIpt, h->stream_vec, kRedBlocksPerCu, &cfg);
     if (st != HIPMR_OK) return st;
 
     // one block, unless the call chose a geometry
@@ -778,7 +781,7 @@ hipmr_status hipmr_get_kernel_source(hipmr_handle h, int32_t kind, const char* c
     if (red != (bool)h->prog.sig.is_reduce) return fail(HIPMR_E_MISMATCH, "kind does not match the handle");
     if (red && (!combine || !neutral)) return fail(HIPMR_E_INVALID, "combine_op and neutral are required");
     LaunchCfg cfg;
-    resolve_cfg(nullptr, red ? kRedBlock : kEwBlock, red ? kRedIpt : h->ew_ipt, red ? h->default_vec : h->ew_vec,
+    resolve_cfg(nullptr, red ? kRedBlock : kEwBlock, red ? kRedIpt : h->ew_ipt, h->stream_vec,
                 red ? kRedBlocksPerCu : kEwBlocksPerCu, &cfg);
     KernelSpec spec;
     if (kind == 4) {
@@ -874,7 +877,7 @@ hipmr_status hipmr_selftest_compile(int32_t* count) {
         std::shared_ptr<CodeObject> co;
         if (h->prog.sig.is_reduce) {
             LaunchCfg cfg;
-            resolve_cfg(nullptr, kRedBlock, kRedIpt, h->default_vec, kRedBlocksPerCu, &cfg);
+            resolve_cfg(nullptr, kRedBlock, kRedIpt, h->stream_vec, kRedBlocksPerCu, &cfg);
             for (bool vector : {true, false}) {
                 if (vector && !h->prog.info.vectorizable) continue;
                 for (bool idx64 : {false, true}) {

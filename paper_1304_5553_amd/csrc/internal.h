@@ -23,8 +23,9 @@ struct hipmr_kernel {
     bool cached = false;          // listed in the handle cache under cache_key
     std::string cache_key;
     hipmr::Program prog;
-    int default_vec = 4;          // elements per chunk, and of the elementwise kernels
-    int ew_vec = 4, ew_ipt = 1;   // (with the chunks per thread)
+    int default_vec = 4;          // elements per chunk,
+    int stream_vec = 4;           // and of the elementwise kernels and plain reductions
+    int ew_ipt = 1;               // elementwise chunks per thread
     std::mutex mu;
     std::unordered_map<hipmr::KernelSpec, std::shared_ptr<hipmr::CodeObject>, hipmr::KernelSpecHash> variants;
     hipmr::CallKernels last;                         // kernels of the most recent call
@@ -50,7 +51,7 @@ constexpr size_t kWorkspaceBytes = kCountOffset + 256;
 // in flight per thread and array); elementwise kernels, which mix reads and
 // writes, do best as one pass over a full grid (one chunk per thread).
 constexpr int kEwBlock = 256, kEwIpt = 1, kEwBlocksPerCu = 1 << 20;
-constexpr int kEwMixedIpt = 2;               // arrays of different element sizes (see default_ew_shape)
+constexpr int kEwMixedIpt = 2;               // arrays of different element sizes (see default_stream_shape)
 constexpr int kEwScalarBlocksPerCu = 32;     // one-element elementwise kernels
 constexpr int kRedBlock = 256, kRedIpt = 4, kRedBlocksPerCu = 2;
 // A reduction over at most this many bytes is one block's work, in one launch:
