@@ -44,7 +44,7 @@ struct Slots {
 };
 
 // kinds, one letter per argument: A array of at least n elements, a array of
-// any length, f / d float / double, i / l 32- / 64-bit integer; anything else
+// any length, f / d float / double, c complex64, i / l 32- / 64-bit integer; anything else
 // is left to the general path.  Values go to the thread's buffer (slot k is
 // what the k-th pointer points at).
 bool fill(const char* kinds, Py_ssize_t nk, PyObject* args, long long n, const Slots& out) {
@@ -71,6 +71,14 @@ bool fill(const char* kinds, Py_ssize_t nk, PyObject* args, long long n, const S
                 if (!PyFloat_CheckExact(v)) return false;
                 const double d = PyFloat_AS_DOUBLE(v);
                 std::memcpy(&bits, &d, 8);
+                break;
+            }
+            case 'c': {
+                if (!PyComplex_CheckExact(v)) return false;
+                const Py_complex z = ((PyComplexObject*)v)->cval;
+                const float re = (float)z.real, im = (float)z.imag;
+                std::memcpy(&bits, &re, 4);
+                std::memcpy((char*)&bits + 4, &im, 4);
                 break;
             }
             case 'i':

@@ -277,7 +277,7 @@ def _lowp_bits(code, value):
     return int(t.to(torch_dtype(code)).view(torch.int16).item()) & 0xFFFF
 
 
-_KINDS = {F32: "f", F64: "d", I32: "i", U32: "i", I64: "l"}
+_KINDS = {F32: "f", F64: "d", I32: "i", U32: "i", I64: "l", C64: "c"}
 
 
 class Arg:
@@ -323,6 +323,7 @@ class Kernel:
         self._kinds = bytes(              # (as the marshalling extension names them)
             ord(("A" if k in self._sized else "a") if a.pointer else _KINDS.get(a.dtype, "?"))
             for k, a in enumerate(self.args))
+        self._ordinary = b"?" not in self._kinds
         self._ws_bytes = None             # of a reduction (the same for every n), asked for once
         self._tls = None                  # per-thread argument buffers, made by the first marshal
 
@@ -472,7 +473,7 @@ def compile(expr, dtypes, name=None) -> Kernel:   # noqa: A001 - the C ABI's nam
 
 
 def elementwise(handle: Kernel, n, args, stream=None, config=None):
-    if config is None:
+    if config is None and handle._ordinary:
         fast = _fast or _load_fast()
         keep, _, base = handle._buffers()
         st = fast.elementwise(_FN["hipmr_elementwise_ex"], handle._hv, handle._kinds, args, n, base,
@@ -523,7 +524,7 @@ def reduce(handle: Kernel, map_expr, combine_op, neutral, n, args, out, workspac
     s = _stream_ptr(stream)
     if workspace_buf is None:
         workspace_buf = workspace(reduce_workspace_bytes(handle, n), out.device, s)
-    if config is None:
+    if config is None and handle._ordinary:
         st = fast.reduce(_FN["hipmr_reduce_ex"], handle._hv, handle._kinds, args, n, handle._buffers()[2], s,
                          _enc(map_expr), _enc(combine_op), _enc(neutral), ptr, workspace_buf)
         if st is not None:
@@ -596,7 +597,7 @@ def scan(handle: Kernel, combine_op, neutral, n, args, out, exclusive=False, wor
     s = _stream_ptr(stream)
     if workspace_buf is None:
         workspace_buf = workspace(scan_workspace_bytes(handle, n), out.device, s)
-    if config is None:
+    if config is None and handle._ordinary:
         st = fast.scan(_FN["hipmr_scan"], handle._hv, handle._kinds, args, n, handle._buffers()[2], s,
                        combine_op.encode(), neutral.encode(), ptr, bool(exclusive), workspace_buf)
         if st is not None:

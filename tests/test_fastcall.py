@@ -47,6 +47,18 @@ def test_values_equal_the_general_marshalling(fast):
         assert seen.pop()[2] == want
 
 
+def test_complex_scalars(fast):
+    k = hm.compile("z[i] = a*z[i] + b", "complex64 *z, complex64 a, complex64 b")
+    z = torch.zeros(8, dtype=torch.complex64)
+    seen = []
+    cb = EW(lambda h, n, ptrs, cfg, stream: seen.append(slots(ptrs, 3)) or 0)
+    args = [z, 0.75 - 1.25j, complex(float("inf"), 1e300)]
+    want = list(k.marshal(args)[0])
+    assert fast.elementwise(ctypes.cast(cb, VP).value, k._hv, k._kinds, args, 8, k._buffers()[2], 0) == 0
+    assert seen == [want]
+    assert fast.elementwise(ctypes.cast(cb, VP).value, k._hv, k._kinds, [z, 1.0, 2j], 8, k._buffers()[2], 0) is None
+
+
 def test_the_unusual_is_left_to_the_general_path(fast):
     k = hm.compile("z[i] = a*x[i]", "float *z, float a, const float *x")
     z, x = torch.zeros(8), torch.zeros(8)
@@ -60,9 +72,10 @@ def test_the_unusual_is_left_to_the_general_path(fast):
                     ([z, 1.0, sparse], 8), ([z, 1.0, x], np.int64(8)), ([z, 1.0, x], 2 ** 70),
                     (iter([z, 1.0, x]), 8)):
         assert fast.elementwise(addr, k._hv, k._kinds, args, n, k._buffers()[2], 0) is None
-    for dtype in ("bfloat16", "half", "fp8_e4m3", "complex64", "char"):
+    for dtype in ("bfloat16", "half", "fp8_e4m3", "char"):
         kk = hm.compile("z[i] = x[i]", f"float *z, {dtype} a, const float *x")
         assert fast.elementwise(addr, kk._hv, kk._kinds, [z, 1.0, x], 8, kk._buffers()[2], 0) is None
+        assert not kk._ordinary
     assert not called
     # outputs: dtype, length, layout, type
     f32 = torch.float32
