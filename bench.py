@@ -650,31 +650,31 @@ def bench_precision(torch, hm, workloads, dev, stream, checks, reps=10, copies=4
             out.setdefault(case, {})[fmt] = {
                 "sum_ms": round(t_sum, 4), "sum_GB/s": round(nbytes / t_sum / 1e6, 1),
                 "sum_frac_of_peak": round(nbytes / t_sum / 1e6 / HBM_PEAK_GBS, 4),
-                "norm2_ms": round(t_nrm, 4), "norm2_GB/s": round(2 * nbytes / t_nrm / 1e6, 1),
-                "norm2_frac_of_peak": round(2 * nbytes / t_nrm / 1e6 / HBM_PEAK_GBS, 4),
+                "norm2_ms": round(t_nrm, 4), "norm2_GB/s": round(nbytes / t_nrm / 1e6, 1),
+                "norm2_frac_of_peak": round(nbytes / t_nrm / 1e6 / HBM_PEAK_GBS, 4),
                 "sum_symbols": sum_symbols, "norm2_symbols": k.last_symbols()}
             del bufs
             torch.cuda.empty_cache()
         del v64
     return {"n": n, "workload": "lognormal(0,3) x random sign, and the cancellation case "
                                 "[x; -x (1 + eps)]; per-tensor power-of-two scale",
-            "bytes_note": "sum reads n*size once; the scaled norm reads it twice",
+            "bytes_note": "sum and scaled norm read n*size once (the norm's second pass ends at once here)",
             "inputs": f"{copies} rotated copies (out of the 256 MB last-level cache)",
             "cases": out}
 
 
 def bench_scan(torch, hm, workloads, dev, stream, reps=10):
     """Prefix scans at n = 2^28 (the plain workload's arrays): inclusive float
-    sum of x (4 B read twice + 4 B written = 12 B/element) and inclusive
-    int64 sum of the int32 k (4 + 4 + 8 = 16 B/element)."""
+    sum of x (4 B read + 4 B written = 8 B/element) and inclusive int64 sum of
+    the int32 k (4 + 8 = 12 B/element)."""
     n = workloads.N_PLAIN
     x, _ = workloads.plain_xy(n)
     xd = torch.from_numpy(x).to(dev)
     kd = torch.from_numpy(workloads.plain_k(n)).to(dev)
     res = {"n": n}
     for name, expr, sig, src, out_dt, per in (
-            ("sum_f32", "x[i]", "float: const float *x", xd, torch.float32, 12),
-            ("sum_i32_to_i64", "k[i]", "long: const int *k", kd, torch.int64, 16)):
+            ("sum_f32", "x[i]", "float: const float *x", xd, torch.float32, 8),
+            ("sum_i32_to_i64", "k[i]", "long: const int *k", kd, torch.int64, 12)):
         k = hm.compile(expr, sig, name=f"scan_{name}")
         out = torch.empty(n, dtype=out_dt, device=dev)
         ws = hm.hipmr.workspace(hm.scan_workspace_bytes(k, n), dev, stream.cuda_stream)
@@ -691,11 +691,12 @@ def bench_scan(torch, hm, workloads, dev, stream, reps=10):
 
 def bench_cg(torch, hm, dev):
     """Conjugate gradients on the five-point model problem: time per
-    iteration, eager (nine launches) and replayed from a HIP graph, on a
-    4096 x 4096 grid (bandwidth-bound) and a 256 x 256 grid (launch-bound);
-    52 algorithmic bytes per unknown and iteration."""
+    iteration, eager step by step (three launches each) and replayed from a
+    HIP graph of ten iterations (two launches each inside the run), on a 4096
+    x 4096 grid (bandwidth-bound) and a 256 x 256 grid (launch-bound); GB/s of
+    the 32 bytes per unknown and iteration that the fused kernels move."""
     from paper_1304_5553_amd import cg as hcg
-    res = {"bytes_per_unknown": hcg.BYTES_PER_UNKNOWN}
+    res = {"bytes_per_unknown": hcg.FUSED_BYTES_PER_UNKNOWN}
     for nx in (4096, 256):
         n = nx * nx
         rng = np.random.default_rng(8)
@@ -721,7 +722,7 @@ def bench_cg(torch, hm, dev):
                 stream.synchronize()
                 ms = t0.elapsed_time(t1) / 50
                 row[mode] = {"ms_per_iter": round(ms, 5),
-                             "GB/s": round(hcg.BYTES_PER_UNKNOWN * n / ms / 1e6, 1)}
+                             "GB/s": round(hcg.FUSED_BYTES_PER_UNKNOWN * n / ms / 1e6, 1)}
             row["graph_speedup"] = round(row["eager"]["ms_per_iter"] / row["graph"]["ms_per_iter"], 2)
             row["rr_after_50"] = float(solver.rr.item())
         res[f"{nx}x{nx}"] = row

@@ -37,7 +37,8 @@ UPDATE = ("float *x, float *r, float *p, const float *q, const float *c, const f
           "x[i] += (c[0]/c[1])*p[i]; r[i] -= (c[0]/c[1])*q[i]; p[i] = r[i] + (d[0]/c[0])*p[i]")
 START = ("float *x, float *r, float *p, const float *b", "x[i] = 0.0f; r[i] = b[i]; p[i] = b[i]")
 
-BYTES_PER_UNKNOWN = 52       # of the four statements (the fused kernels move 32)
+BYTES_PER_UNKNOWN = 52         # per iteration, of the four statements
+FUSED_BYTES_PER_UNKNOWN = 32   # of the fused kernels: cgr 12, cgu 20
 
 # Launch configuration for the statements above when they are run one by one:
 # they reread their vectors every iteration, so temporal accesses, which keep
@@ -125,4 +126,5 @@ class PoissonCG:
         return self.x
 
 
-__all__ = ["PoissonCG", "SPMV", "DOT", "RR_NEXT", "UPDATE", "START", "BYTES_PER_UNKNOWN", "CACHED"]
+__all__ = ["PoissonCG", "SPMV", "DOT", "RR_NEXT", "UPDATE", "START", "BYTES_PER_UNKNOWN",
+           "FUSED_BYTES_PER_UNKNOWN", "CACHED"]
