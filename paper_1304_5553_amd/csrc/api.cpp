@@ -40,10 +40,9 @@ long long chunk_bytes(const Signature& sig) {
 // 65536 elements of a map of plain arithmetic (c of about 10) cost 1 us more
 // than spread over the chip; a map that calls other functions than the
 // cheapest may be thirty times as long.
-long long one_block_elements(const hipmr_kernel* h) {
+long long one_block_elements(const std::vector<Token>& t) {
     static const std::set<std::string> cheap = {"conj", "real", "imag", "fabsf", "fabs", "sqrtf",
                                                 "fmaf", "fmaxf", "fminf"};
-    const auto& t = h->prog.toks;
     for (size_t k = 0; k + 1 < t.size(); ++k)
         if (t[k].kind == Token::Ident && t[k + 1].text == "(" && !cheap.count(t[k].text)) return 4096;
     return 65536;
@@ -360,6 +359,8 @@ hipmr_status build_handle(const char* expr, const char* dtypes, const std::strin
     }
     h->default_vec = default_vec_for(h->prog.sig);
     default_stream_shape(h->prog.sig, &h->stream_vec, &h->ew_ipt);
+    h->chunk_bytes = chunk_bytes(h->prog.sig);
+    h->one_block = one_block_elements(h->prog.toks);
     if (!h->prog.sig.is_reduce) {
         // build the default variant now so that errors surface at compile time
         KernelSpec spec;
@@ -689,7 +690,7 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
                 return v;
             });
             if (st != HIPMR_OK) return st;
-            if (n <= one_block_elements(h) && n * chunk_bytes(h->prog.sig) <= kRedOneBytes) {
+            if (n <= h->one_block && n * h->chunk_bytes <= kRedOneBytes) {
                 cfg.block = kRedOneBlock;
                 cfg.grid = 1;
             }

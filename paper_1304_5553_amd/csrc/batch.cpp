@@ -138,8 +138,8 @@ hipmr_status seg_prepare(hipmr_kernel* h, const char* combine, const char* neutr
             std::vector<KernelSpec> v;
             for (int32_t ns : {kLdsSegsMax, kLdsSegsMax + 1}) {
                 c.block = default_shape(ns).block;
-                const int l = cfg.seg_global ? 0 : lds_capacity(ns, default_shape(ns).lds_limit);
-                v.push_back(seg_spec(KernelKind::SegS1, c, idx64, combine, neutral, l));
+                v.push_back(seg_spec(KernelKind::SegS1, c, idx64, combine, neutral,
+                                     lds_capacity(ns, default_shape(ns).lds_limit)));
             }
             v.push_back(seg_spec(KernelKind::SegPlan, c, idx64, combine, neutral, 0));
             v.push_back(seg_spec(KernelKind::SegS2, c, idx64, combine, neutral, 0));
@@ -319,26 +319,30 @@ thread_local bool g_no_alloc = false;
 
 // (hipRTC programs are independent; the code-object cache is thread-safe)
 hipmr_status run_concurrently(const std::vector<std::function<hipmr_status()>>& jobs) {
-    if (jobs.empty()) return HIPMR_OK;
     std::atomic<size_t> next{0};
     std::atomic<int> status{HIPMR_OK};
     std::mutex err_mu;
     std::string err;
-    unsigned nt = std::max(1u, std::min<unsigned>(std::thread::hardware_concurrency(), 16));
-    nt = (unsigned)std::min<size_t>(nt, jobs.size());
-    std::vector<std::thread> pool;
-    for (unsigned k = 0; k < nt; ++k)
-        pool.emplace_back([&] {
-            for (size_t j; (j = next++) < jobs.size();) {
-                hipmr_status st = jobs[j]();
-                if (st != HIPMR_OK) {
-                    std::lock_guard<std::mutex> lk(err_mu);
-                    if (status == HIPMR_OK) { status = st; err = last_error(); }
-                }
+    const auto work = [&] {
+        for (size_t j; (j = next++) < jobs.size();) {
+            hipmr_status st = jobs[j]();
+            if (st != HIPMR_OK) {
+                std::lock_guard<std::mutex> lk(err_mu);
+                if (status == HIPMR_OK) { status = st; err = last_error(); }
             }
-        });
+        }
+    };
+    // the calling thread takes jobs too, and all of them where no other starts
+    const size_t nt = std::min<size_t>(std::min(std::thread::hardware_concurrency(), 16u), jobs.size());
+    std::vector<std::thread> pool;
+    try {
+        pool.reserve(nt);
+        for (size_t k = 1; k < nt; ++k) pool.emplace_back(work);
+    } catch (const std::exception&) {
+    }
+    work();
     for (auto& t : pool) t.join();
-    if (status != HIPMR_OK) return fail(status, err);
+    if (status != HIPMR_OK) return fail((hipmr_status)status.load(), err);
     return HIPMR_OK;
 }
 
@@ -361,7 +365,8 @@ hipmr_status reduce_segmented_on(hipmr_kernel* h, const char* combine, const cha
     if (nseg == 0) return HIPMR_OK;
     hipmr_launch_config tuned{};
     cfgp = apply_tuned(h, "seg", combine, neutral, total_n, cfgp, &tuned);
-    const bool own_shape = cfgp && (cfgp->block || cfgp->grid || cfgp->blocks_per_cu);
+    const bool own_shape =
+        cfgp && (cfgp->block || cfgp->grid || cfgp->blocks_per_cu || (cfgp->flags & HIPMR_CFG_SEG_GLOBAL));
     const SegShape shape = own_shape ? kSegOwnShape : default_shape(nseg);
     LaunchCfg cfg;
     st = resolve_cfg(cfgp, shape.block, kSegIpt, h->default_vec, shape.blocks_per_cu, &cfg);

@@ -26,6 +26,8 @@ struct hipmr_kernel {
     int default_vec = 4;          // elements per chunk,
     int stream_vec = 4;           // and of the elementwise kernels and plain reductions
     int ew_ipt = 1;               // elementwise chunks per thread
+    long long chunk_bytes = 1;    // per index, of the arrays moved in chunks
+    long long one_block = 0;      // elements of the map that one block may take by itself
     std::mutex mu;
     std::unordered_map<hipmr::KernelSpec, std::shared_ptr<hipmr::CodeObject>, hipmr::KernelSpecHash> variants;
     hipmr::CallKernels last;                         // kernels of the most recent call
@@ -74,8 +76,6 @@ void set_last_kernels(hipmr_kernel* h, const CallKernels& used);
 hipmr_status load_family(hipmr_kernel* h, char op, bool vector, bool idx64, const LaunchCfg& cfg,
                          const char* combine, const char* neutral,
                          const std::function<std::vector<KernelSpec>()>& specs);
-// elements of the handle's map that one block may take by itself
-long long one_block_elements(const hipmr_kernel* h);
 // runs the jobs on a thread pool; the first failure's status and message
 hipmr_status run_concurrently(const std::vector<std::function<hipmr_status()>>& jobs);
 // Element offset at which the chunks start, or -1 for the one-element kernels

@@ -133,7 +133,7 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
     if (st != HIPMR_OK) return st;
     int mode = 3;
     const LaunchCfg one = with(kScanOneBlock, kScanIpt), small = with(kScanSmallBlock, kScanIpt);
-    if (tiles_of(one) == 1 && (own_block || own_ipt || n64 <= one_block_elements(h))) {
+    if (tiles_of(one) == 1 && (own_block || own_ipt || n64 <= h->one_block)) {
         mode = 0;
         cfg = one;
     } else if (tiles_of(small) <= kScanSmallTiles) {
