@@ -191,10 +191,13 @@ size_t hipmr_reduce_workspace_bytes(hipmr_handle h, int64_t n);
  *   out:        device pointer to one element of the result type.
  *   workspace:  device buffer of at least hipmr_reduce_workspace_bytes(h, n)
  *               bytes (E_WORKSPACE otherwise); it is scratch for block partials.
- * Two launches on stream (block partials, then one block folding them), or one
- * where one block takes the whole reduction (small n), no
- * atomics; for a given device, n and launch configuration the result is
- * bitwise reproducible.  n == 0 writes neutral.  The map reads arrays in
+ * One launch on stream: one block takes a small n, else the last block folds
+ * the others' partials, published in the workspace under a tag of this launch
+ * (nothing there needs clearing; the workspace belongs to one call at a time).
+ * Two launches (block partials, then one block folding them: the same bits)
+ * under capture, since a replay would repeat the tag, and with a geometry in
+ * cfg.  No read-modify-write atomics; for a given device, n and launch
+ * configuration the result is bitwise reproducible.  n == 0 writes neutral.  The map reads arrays in
  * chunks as described for hipmr_elementwise, shifted reads name[i +/- E]
  * included (every lane loads every chunk, clamped into [0, n), and chunks
  * near the ends are mapped one element at a time); the other map-reduce

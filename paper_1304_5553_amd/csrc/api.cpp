@@ -8,6 +8,7 @@
 #include <cstring>
 #include <map>
 #include <memory>
+#include <random>
 #include <unordered_map>
 
 #include "internal.h"
@@ -392,6 +393,31 @@ KernelSpec s1_spec(const hipmr_kernel* h, bool vector, const LaunchCfg& cfg, boo
     return s;
 }
 
+// The s1 kernel that finishes the reduction itself.
+KernelSpec finish_spec(KernelSpec s1) {
+    s1.finish = true;
+    return s1;
+}
+
+// A tag for one launch's partials: 48 bits, never 0, from a random start.
+uint64_t next_tag() {
+    static std::atomic<uint64_t> tag{[] {
+        std::random_device rd;
+        return (uint64_t)rd() << 32 ^ rd();
+    }()};
+    uint64_t t;
+    do t = tag.fetch_add(1) & ((1ull << 48) - 1);
+    while (t == 0);
+    return t;
+}
+
+// Whether work put on the stream now may be replayed later.
+bool may_be_replayed(void* stream) {
+    if (capturing_now()) return true;
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing((hipStream_t)stream, &s) != hipSuccess || s != hipStreamCaptureStatusNone;
+}
+
 KernelSpec s2_spec(const char* combine, const char* neutral) {
     KernelSpec s;
     s.kind = KernelKind::RedS2;
@@ -638,6 +664,7 @@ hipmr_status hipmr_prepare_reduce_ex(hipmr_handle h, const char* combine, const 
     std::vector<KernelSpec> specs = {s1_spec(h, h->prog.info.vectorizable, cfg, false, combine, neutral),
                                      s2_spec(combine, neutral)};
     if (!cfgp) {
+        specs.push_back(finish_spec(specs[0]));
         specs.push_back(specs[0]);
         specs.back().block = kRedOneBlock;
     }
@@ -685,6 +712,7 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
                 for (int block : {kRedBlock, kRedOneBlock}) {
                     c.block = block;
                     v.push_back(s1_spec(h, vector, c, idx64, combine, neutral));
+                    if (block == kRedBlock) v.push_back(finish_spec(v.back()));
                 }
                 v.push_back(s2_spec(combine, neutral));
                 return v;
@@ -696,12 +724,15 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
             }
         }
         head64 = vector ? head : 0;
-        void* fn = nullptr;
-        st = variant_function(h, s1_spec(h, vector, cfg, n >= (int64_t(1) << 31), combine, neutral), &fn,
-                              &used);
-        if (st != HIPMR_OK) return st;
         long long units = vector ? (n64 > head64 ? (n64 - head64) / cfg.vec : 0) : n64;
         grid = grid_for(units, cfg.block * (vector ? cfg.ipt : 1), cfg, kMaxPartials);
+        KernelSpec s1 = s1_spec(h, vector, cfg, n >= (int64_t(1) << 31), combine, neutral);
+        s1.finish = !own_shape && grid > 1 && cfg.block == kStage2Block &&
+                    (size_t)grid * dtype_size(h->prog.sig.result) * 4 <= kAmaxOffset && !may_be_replayed(stream);
+        void* fn = nullptr;
+        st = variant_function(h, s1, &fn, &used);
+        if (st != HIPMR_OK) return st;
+        uint64_t tag = s1.finish ? next_tag() : 0;
         std::vector<void*> params;
         if (h->prog.sig.args.empty()) params.push_back(&head64);   // hipmr_unused
         for (size_t k = 0; k < h->prog.sig.args.size(); ++k) params.push_back(args[k]);
@@ -709,9 +740,14 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
         params.push_back(&head64);
         // one block's partial is the result
         params.push_back(grid == 1 ? (void*)&out : (void*)&workspace);
-        if (grid == 1) set_last_kernels(h, used);
+        if (s1.finish) {
+            params.push_back(&out);
+            params.push_back(&tag);
+        }
+        const bool whole = grid == 1 || s1.finish;
+        if (whole) set_last_kernels(h, used);
         st = launch(fn, (unsigned)grid, (unsigned)cfg.block, params.data(), stream);
-        if (st != HIPMR_OK || grid == 1) return st;
+        if (st != HIPMR_OK || whole) return st;
     }
     void* fn2 = nullptr;
     st = variant_function(h, s2_spec(combine, neutral), &fn2, &used);
@@ -883,6 +919,9 @@ hipmr_status hipmr_selftest_compile(int32_t* count) {
                 if (vector && !h->prog.info.vectorizable) continue;
                 for (bool idx64 : {false, true}) {
                     st = get_variant(h, s1_spec(h, vector, cfg, idx64, c.combine, c.neutral), &co);
+                    if (st == HIPMR_OK)
+                        st = get_variant(h, finish_spec(s1_spec(h, vector, cfg, idx64, c.combine, c.neutral)), &co);
+                    ++built;
                     if (st != HIPMR_OK) { hipmr_release(h); return st; }
                     ++built;
                 }

@@ -146,12 +146,13 @@ struct KernelSpec {
     bool exact_runs = false;  // CompS1: map is one FP8 load; sum runs of <= 64 exactly
     bool norm = false;        // CompS2: finish as sqrt(sum) / scale
     // batching extension
+    bool finish = false;      // RedS1: fold the partials in the same launch
     int scan_mode = 0;        // Scan: 0 one tile, 1 tile totals, 2 from totals, 3 one pass
     int lds_segs = 0;         // SegS1: segments its LDS tile table holds, 0 = table in global memory
 };
 inline auto spec_fields(const KernelSpec& s) {
     return std::tie(s.kind, s.idx64, s.block, s.ipt, s.vec, s.nt_loads, s.nt_stores, s.unaligned, s.square,
-                    s.track, s.scaled, s.exact_runs, s.norm, s.scan_mode, s.lds_segs, s.combine, s.neutral);
+                    s.track, s.scaled, s.exact_runs, s.norm, s.finish, s.scan_mode, s.lds_segs, s.combine, s.neutral);
 }
 inline bool operator==(const KernelSpec& a, const KernelSpec& b) { return spec_fields(a) == spec_fields(b); }
 struct KernelSpecHash {
@@ -160,7 +161,7 @@ struct KernelSpecHash {
                                (uint64_t)s.vec << 21 | (uint64_t)s.lds_segs << 26 | (uint64_t)s.scan_mode << 40 |
                                (uint64_t)(s.idx64 | s.nt_loads << 1 | s.nt_stores << 2 | s.unaligned << 3 |
                                           s.square << 4 | s.track << 5 | s.scaled << 6 | s.exact_runs << 7 |
-                                          s.norm << 8) << 44;
+                                          s.norm << 8 | s.finish << 9) << 44;
         const std::hash<std::string> text;
         return std::hash<uint64_t>()(shape * 0x9E3779B97F4A7C15ull) ^ text(s.combine) ^ text(s.neutral) * 31;
     }

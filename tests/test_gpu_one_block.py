@@ -36,7 +36,10 @@ def test_reduce_hands_over(dev, fmt, bytes_per, limit, calls):
             out = torch.full((2,), 7.0, device=dev)
             hm.reduce(h, None, "a+b", "0", n, xs, out)
             assert out.tolist() == [float(vals[:, offset:].sum()), 7.0]
-            assert len(h.last_symbols()) == (1 if n <= limit else 2), n
+            assert len(h.last_symbols()) == 1, n
+            two = torch.empty((), device=dev)                    # the general form, partials and their fold
+            hm.reduce(h, None, "a+b", "0", n, xs, two, config={"block": 512})
+            assert two.item() == out[0].item()
 
 
 def test_maximum_of_nan_infinity_and_lowest(dev):
@@ -73,3 +76,46 @@ def test_capture_of_another_size(dev, first, then):
         torch.cuda.synchronize()
         assert out.item() == vals[:then].sum()
         assert np.array_equal(host_bits(sc[:then]), np.cumsum(vals[:then], dtype=np.int64))
+
+
+@pytest.mark.parametrize("result,ctype,tdt", [("float", "float", torch.float32), ("double", "double", torch.float64),
+                                              ("long", "int", torch.int32), ("unsigned", "int", torch.int32),
+                                              ("complex64", "complex64", torch.complex64)])
+@pytest.mark.parametrize("n", [65537, 100003, 300007, 1 << 22])
+def test_one_launch_equals_two(dev, result, ctype, tdt, n):
+    """The launch that folds its own partials against partials and fold kernel
+    (the same geometry, asked for): the same bits, from a workspace full of
+    anything, call after call, and from a capture (which takes two launches)."""
+    x = (torch.randint(-9, 9, (n,), dtype=torch.int32, device=dev) if tdt == torch.int32
+         else torch.randn(n, dtype=tdt, device=dev))
+    h = hm.compile("x[i]", f"{result}: const {ctype} *x", name="fin")
+    rdt = hm.torch_dtype(h.result_dtype)
+    out, two = torch.zeros((), dtype=rdt, device=dev), torch.zeros((), dtype=rdt, device=dev)
+    nbytes = hm.reduce_workspace_bytes(h, n)
+    cfg = {"block": 256, "items_per_thread": 4, "blocks_per_cu": 2}
+    for fill in (0, 255, 17):
+        ws = torch.full((nbytes,), fill, dtype=torch.uint8, device=dev)
+        hm.reduce(h, None, "a+b", "0", n, [x], two, workspace_buf=ws, config=cfg)
+        assert len(h.last_symbols()) == 2
+        for _ in range(3):
+            out.zero_()
+            hm.reduce(h, None, "a+b", "0", n, [x], out, workspace_buf=ws)
+            assert len(h.last_symbols()) == 1
+            assert host_bits(out).tobytes() == host_bits(two).tobytes()
+    st = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g = hm.Graph()
+    with g.capture(st):
+        hm.reduce(h, None, "a+b", "0", n, [x], out, workspace_buf=ws, stream=st)
+    assert len(h.last_symbols()) == 2
+    tg = torch.cuda.CUDAGraph()                                  # a capture the library was not told of
+    with torch.cuda.graph(tg):
+        hm.reduce(h, None, "a+b", "0", n, [x], out, workspace_buf=ws)
+    assert len(h.last_symbols()) == 2
+    for replay in (lambda: g.launch(st), tg.replay) * 3:
+        x.neg_()
+        torch.cuda.synchronize()
+        replay()
+        torch.cuda.synchronize()
+        hm.reduce(h, None, "a+b", "0", n, [x], two)
+        assert host_bits(out).tobytes() == host_bits(two).tobytes()
