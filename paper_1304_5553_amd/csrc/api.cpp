@@ -399,6 +399,11 @@ KernelSpec finish_spec(KernelSpec s1) {
     return s1;
 }
 
+// Whether the call chose a launch geometry of its own.
+bool own_shape(const hipmr_launch_config* c) {
+    return c && (c->block || c->items_per_thread || c->grid || c->blocks_per_cu);
+}
+
 // A tag for one launch's partials: 48 bits, never 0, from a random start.
 uint64_t next_tag() {
     static std::atomic<uint64_t> tag{[] {
@@ -440,11 +445,14 @@ struct Stage1 {
     void* fn = nullptr;
     int grid = 0;
     long long head = 0;
+    bool whole = false;          // the launch folded its partials itself
 };
 
+// `fold`: the kernel that would finish the call, where the stage may do so
+// itself (a default geometry, and no capture that could repeat its tag).
 hipmr_status stage1_launch(hipmr_kernel* h, KernelSpec spec, LaunchCfg cfg,
                            int64_t n, void* const* args, void* partial, void* amax, double post, void* out_p,
-                           void* stream, CallKernels* used, Stage1* out) {
+                           const KernelSpec* fold, void* stream, CallKernels* used, Stage1* out) {
     const long long head = vector_head(h, args, &cfg);
     const bool vector = head >= 0;
     spec.unaligned = cfg.unaligned;
@@ -454,22 +462,32 @@ hipmr_status stage1_launch(hipmr_kernel* h, KernelSpec spec, LaunchCfg cfg,
         spec.exact_runs = false;
     }
     spec.idx64 = n >= (int64_t(1) << 31);
-    hipmr_status st = variant_function(h, spec, &out->fn, used);
-    if (st != HIPMR_OK) return st;
     long long n64 = n, head64 = vector ? head : 0;
     long long units = vector ? (n64 > head64 ? (n64 - head64) / cfg.vec : 0) : n64;
     out->grid = n > 0 ? grid_for(units, cfg.block * (vector ? cfg.ipt : 1), cfg, kMaxPartials) : 0;
     out->head = head64;
+    hipmr_status st;
+    if (fold && n > 0) {
+        st = load_family(h, spec.square ? 'q' : 'c', vector, spec.idx64, cfg, "", "", [&] {
+            KernelSpec one = spec;
+            one.finish = true;
+            return std::vector<KernelSpec>{spec, one, *fold};
+        });
+        if (st != HIPMR_OK) return st;
+        spec.finish = cfg.block == kStage2Block && (size_t)out->grid * sizeof(double) * 4 <= kAmaxOffset &&
+                      !may_be_replayed(stream);
+    }
+    out->whole = spec.finish;
+    st = variant_function(h, spec, &out->fn, used);
+    if (st != HIPMR_OK) return st;
     if (n == 0) return HIPMR_OK;
+    uint64_t tag = spec.finish ? next_tag() : 0;
     std::vector<void*> params;
     if (h->prog.sig.args.empty()) params.push_back(&head64);   // hipmr_unused
     for (size_t k = 0; k < h->prog.sig.args.size(); ++k) params.push_back(args[k]);
-    params.push_back(&n64);
-    params.push_back(&head64);
-    params.push_back(&partial);
-    params.push_back(&amax);
-    params.push_back(&post);
-    params.push_back(&out_p);
+    for (void* p : {(void*)&n64, (void*)&head64, (void*)&partial, (void*)&amax, (void*)&post, (void*)&out_p,
+                    (void*)&tag})
+        params.push_back(p);
     return launch(out->fn, (unsigned)out->grid, (unsigned)cfg.block, params.data(), stream);
 }
 
@@ -526,12 +544,17 @@ hipmr_status hipmr_reduce_compensated(hipmr_handle h, int64_t n, void* const* ar
     KernelSpec s1 = comp_spec(KernelKind::CompS1Vector, cfg);
     s1.exact_runs = single_fp8_load(h) && cfg.vec * cfg.ipt <= 64;
     CallKernels used;
-    Stage1 r;
-    st = stage1_launch(h, s1, cfg, n, args, workspace, nullptr, post_scale, out, stream, &used, &r);
-    if (st != HIPMR_OK) return st;
     KernelSpec s2 = comp_spec(KernelKind::CompS2, cfg);
     s2.block = kStage2Block;
     s2.ipt = s2.vec = 1;
+    Stage1 r;
+    st = stage1_launch(h, s1, cfg, n, args, workspace, nullptr, post_scale, out, own_shape(cfgp) ? nullptr : &s2,
+                       stream, &used, &r);
+    if (st != HIPMR_OK) return st;
+    if (r.whole) {
+        set_last_kernels(h, used);
+        return HIPMR_OK;
+    }
     void* fn2 = nullptr;
     st = variant_function(h, s2, &fn2, &used);
     if (st != HIPMR_OK) return st;
@@ -558,7 +581,7 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
         KernelSpec a1 = comp_spec(KernelKind::CompS1Vector, cfg);
         a1.square = a1.track = true;
         Stage1 r1;
-        st = stage1_launch(h, a1, cfg, n, args, workspace, amax, post_scale, out, stream, &used, &r1);
+        st = stage1_launch(h, a1, cfg, n, args, workspace, amax, post_scale, out, nullptr, stream, &used, &r1);
         if (st != HIPMR_OK) return st;
     }
     // pass 2 (or the only pass): compensated sum of (map * scale)^2; with two
@@ -568,17 +591,18 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
     KernelSpec q1 = comp_spec(KernelKind::CompS1Vector, cfg);
     q1.square = true;
     q1.scaled = two;
-    Stage1 r2;
-    st = stage1_launch(h, q1, cfg, n, args, workspace, amax, post_scale, out, stream, &used, &r2);
-    if (st != HIPMR_OK) return st;
-    if (two) {
-        set_last_kernels(h, used);
-        return HIPMR_OK;
-    }
     KernelSpec q2 = comp_spec(KernelKind::CompS2, cfg);
     q2.block = kStage2Block;
     q2.ipt = q2.vec = 1;
     q2.norm = true;
+    Stage1 r2;
+    st = stage1_launch(h, q1, cfg, n, args, workspace, amax, post_scale, out,
+                       two || own_shape(cfgp) ? nullptr : &q2, stream, &used, &r2);
+    if (st != HIPMR_OK) return st;
+    if (two || r2.whole) {
+        set_last_kernels(h, used);
+        return HIPMR_OK;
+    }
     void* fn2 = nullptr;
     st = variant_function(h, q2, &fn2, &used);
     if (st != HIPMR_OK) return st;
@@ -697,14 +721,14 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
     if (st != HIPMR_OK) return st;
 
     // one block, unless the call chose a geometry
-    const bool own_shape = cfgp && (cfgp->block || cfgp->items_per_thread || cfgp->grid || cfgp->blocks_per_cu);
+    const bool own = own_shape(cfgp);
     long long n64 = n, head64 = 0;
     int grid = 0;
     CallKernels used;
     if (n > 0) {
         const long long head = vector_head(h, args, &cfg);
         const bool vector = head >= 0;
-        if (!own_shape) {
+        if (!own) {
             const bool idx64 = n >= (int64_t(1) << 31);
             st = load_family(h, 'r', vector, idx64, cfg, combine, neutral, [&] {
                 std::vector<KernelSpec> v;
@@ -727,7 +751,7 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
         long long units = vector ? (n64 > head64 ? (n64 - head64) / cfg.vec : 0) : n64;
         grid = grid_for(units, cfg.block * (vector ? cfg.ipt : 1), cfg, kMaxPartials);
         KernelSpec s1 = s1_spec(h, vector, cfg, n >= (int64_t(1) << 31), combine, neutral);
-        s1.finish = !own_shape && grid > 1 && cfg.block == kStage2Block &&
+        s1.finish = !own && grid > 1 && cfg.block == kStage2Block &&
                     (size_t)grid * dtype_size(h->prog.sig.result) * 4 <= kAmaxOffset && !may_be_replayed(stream);
         void* fn = nullptr;
         st = variant_function(h, s1, &fn, &used);
@@ -973,13 +997,14 @@ hipmr_status hipmr_selftest_compile(int32_t* count) {
                 // precision extension: compensated sum, norm passes, finishers
                 std::vector<KernelSpec> specs;
                 for (KernelKind k : {KernelKind::CompS1Vector, KernelKind::CompS1Scalar}) {
-                    for (int variant = 0; variant < 4; ++variant) {
+                    for (int variant = 0; variant < 6; ++variant) {
                         KernelSpec q = comp_spec(k, cfg);
+                        q.finish = variant >= 4;
                         if (k == KernelKind::CompS1Scalar) q.vec = 1;
-                        q.square = variant > 0;
+                        q.square = variant > 0 && variant != 4;
                         q.scaled = variant == 2;
                         q.track = variant == 3;
-                        q.exact_runs = variant == 0 && k == KernelKind::CompS1Vector &&
+                        q.exact_runs = !q.square && k == KernelKind::CompS1Vector &&
                                        single_fp8_load(h);
                         specs.push_back(q);
                     }

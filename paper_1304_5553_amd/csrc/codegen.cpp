@@ -282,41 +282,52 @@ __device__ __forceinline__ hipmr_acc hipmr_fold(hipmr_acc* a) {
 // Against a separate fold launch: a dot of 2 x 2^20 floats 8.5 -> 5.5 us per
 // call, of 2 x 3.1 M 8.6 -> 6.6, a sum of 18.9 M 14.0 -> 12.8, of 157 M 92.4 ->
 // 91.2 (HBM bound).
+const char* kTagged = R"HIP(
+// publishes block k's value, and waits for it
+template <typename T>
+__device__ __forceinline__ void hipmr_put_tagged(unsigned long long* part, int k, T v, unsigned long long tag) {
+  constexpr int W = (int)sizeof(T) / 2;
+  unsigned long long bits = 0;
+  __builtin_memcpy(&bits, &v, sizeof(v));
+#pragma unroll
+  for (int j = 0; j < W; ++j)
+    __hip_atomic_store(part + (long long)k * W + j, ((bits >> (16 * j)) & 0xffffull) | tag << 16,
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T hipmr_get_tagged(const unsigned long long* part, int k, unsigned long long tag,
+                                              unsigned long long t0) {
+  constexpr int W = (int)sizeof(T) / 2;
+  unsigned long long bits;
+  for (unsigned polls = 1;; ++polls) {
+    bool here = true;
+    bits = 0;
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+      const unsigned long long w = __hip_atomic_load(part + (long long)k * W + j, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+      here = here && (w >> 16) == tag;
+      bits |= (w & 0xffffull) << (16 * j);
+    }
+    if (here || ((polls & 63u) == 0 && __builtin_amdgcn_s_memrealtime() - t0 > 1000000000ull)) break;
+    __builtin_amdgcn_s_sleep(1);
+  }
+  T v;
+  __builtin_memcpy(&v, &bits, sizeof(v));
+  return v;
+}
+)HIP";
+
 const char* kRedFinish = R"HIP(
 template <int B>
 __device__ __forceinline__ void hipmr_finish(hipmr_acc r, hipmr_acc neutral, unsigned long long* part,
                                              hipmr_acc* __restrict__ out, unsigned long long tag) {
-  constexpr int W = (int)sizeof(hipmr_acc) / 2;
-  if (threadIdx.x == 0) {
-    unsigned long long bits = 0;
-    __builtin_memcpy(&bits, &r, sizeof(r));
-#pragma unroll
-    for (int j = 0; j < W; ++j)
-      __hip_atomic_store(part + (long long)blockIdx.x * W + j, ((bits >> (16 * j)) & 0xffffull) | tag << 16,
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (threadIdx.x == 0) hipmr_put_tagged(part, (int)blockIdx.x, r, tag);
   if (blockIdx.x != gridDim.x - 1) return;
   hipmr_acc v = neutral;
   const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-  for (int k = threadIdx.x; k < (int)gridDim.x; k += B) {
-    unsigned long long bits = 0;
-    for (unsigned polls = 1;; ++polls) {
-      bool here = true;
-      bits = 0;
-#pragma unroll
-      for (int j = 0; j < W; ++j) {
-        const unsigned long long w = __hip_atomic_load(part + (long long)k * W + j, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-        here = here && (w >> 16) == tag;
-        bits |= (w & 0xffffull) << (16 * j);
-      }
-      if (here || ((polls & 63u) == 0 && __builtin_amdgcn_s_memrealtime() - t0 > 1000000000ull)) break;
-      __builtin_amdgcn_s_sleep(1);
-    }
-    hipmr_acc p;
-    __builtin_memcpy(&p, &bits, sizeof(p));
-    v = hipmr_combine(v, p);
-  }
+  for (int k = threadIdx.x; k < (int)gridDim.x; k += B)
+    v = hipmr_combine(v, hipmr_get_tagged<hipmr_acc>(part, k, tag, t0));
   __syncthreads();                              // the first fold's LDS has been read
   v = hipmr_block_reduce<B>(v, neutral);
   if (threadIdx.x == 0) *out = v;
@@ -855,13 +866,12 @@ __device__ __forceinline__ P hipmr_block_reduce_pair(P v, F add) {
 // (Neumaier per thread, double-double tree), times the per-tensor post scale;
 // a norm is the root, over the data's scale.  The partials may be other
 // blocks' of the same launch: they are read with device-scope loads.
-template <int B, bool NORM>
-__device__ __forceinline__ void hipmr_comp_fold(const double* partial, int g, double post, double scale,
-                                                double* __restrict__ out) {
+template <int B, bool NORM, typename F>
+__device__ __forceinline__ void hipmr_comp_fold_of(F load, int g, double post, double scale,
+                                                   double* __restrict__ out) {
   double s = 0.0, c = 0.0;
   for (int k = threadIdx.x; k < g; k += B) {
-    const double v = __builtin_bit_cast(double, __hip_atomic_load((const unsigned long long*)partial + k,
-                                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const double v = load(k);
     const double t = s + v;
     if (__builtin_isfinite(t)) c += fabs(s) >= fabs(v) ? (s - t) + v : (v - t) + s;
     s = t;
@@ -873,6 +883,25 @@ __device__ __forceinline__ void hipmr_comp_fold(const double* partial, int g, do
     if constexpr (NORM) *out = post * (sqrt(total) / scale);
     else *out = post * total;
   }
+}
+template <int B, bool NORM>
+__device__ __forceinline__ void hipmr_comp_fold(const double* partial, int g, double post, double scale,
+                                                double* __restrict__ out) {
+  hipmr_comp_fold_of<B, NORM>([=](int k) {
+    return __builtin_bit_cast(double, __hip_atomic_load((const unsigned long long*)partial + k, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT));
+  }, g, post, scale, out);
+}
+
+// The end of a one-pass sum or norm in one launch (partials by tag).
+template <int B, bool NORM>
+__device__ __forceinline__ void hipmr_comp_finish(double v, unsigned long long* part, double post,
+                                                  unsigned long long tag, double* __restrict__ out) {
+  if (threadIdx.x == 0) hipmr_put_tagged(part, (int)blockIdx.x, v, tag);
+  if (blockIdx.x != gridDim.x - 1) return;
+  const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+  hipmr_comp_fold_of<B, NORM>([=](int k) { return hipmr_get_tagged<double>(part, k, tag, t0); },
+                              (int)gridDim.x, post, 1.0, out);
 }
 
 // The second pass's end: every block publishes its partial and counts itself
@@ -905,7 +934,7 @@ const char* kCompS1Vector = R"HIP(
 extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 @@KNAME@@(@@PARAMS@@, long long hipmr_n, long long hipmr_head,
           double* __restrict__ hipmr_partial, float* __restrict__ hipmr_scale_p,
-          double hipmr_post, double* __restrict__ hipmr_out)
+          double hipmr_post, double* __restrict__ hipmr_out, unsigned long long hipmr_tag)
 {
   typedef @@IDX@@ hipmr_idx;
   constexpr int HIPMR_B = @@BLOCK@@, HIPMR_U = @@IPT@@, HIPMR_V = @@VEC@@;
@@ -1007,6 +1036,8 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   unsigned* const hipmr_count = (unsigned*)((char*)hipmr_scale_p + @@COUNT_GAP@@);
   if constexpr (HIPMR_SCALED) {
     hipmr_norm_finish<@@BLOCK@@>(hipmr_v, hipmr_partial, hipmr_count, hipmr_post, (double)hipmr_sc, hipmr_out);
+  } else if constexpr (@@ONE@@) {
+    hipmr_comp_finish<@@BLOCK@@, HIPMR_SQ>(hipmr_v, (unsigned long long*)hipmr_partial, hipmr_post, hipmr_tag, hipmr_out);
   } else if (threadIdx.x == 0) {
     hipmr_partial[blockIdx.x] = hipmr_v;
   }
@@ -1022,7 +1053,7 @@ const char* kCompS1Scalar = R"HIP(
 extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 @@KNAME@@(@@PARAMS@@, long long hipmr_n, long long hipmr_head,
           double* __restrict__ hipmr_partial, float* __restrict__ hipmr_scale_p,
-          double hipmr_post, double* __restrict__ hipmr_out)
+          double hipmr_post, double* __restrict__ hipmr_out, unsigned long long hipmr_tag)
 {
   typedef @@IDX@@ hipmr_idx;
   constexpr bool HIPMR_SQ = @@SQUARE@@, HIPMR_SCALED = @@SCALED@@, HIPMR_TRACK = @@TRACK@@;
@@ -1049,6 +1080,8 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   unsigned* const hipmr_count = (unsigned*)((char*)hipmr_scale_p + @@COUNT_GAP@@);
   if constexpr (HIPMR_SCALED) {
     hipmr_norm_finish<@@BLOCK@@>(hipmr_v, hipmr_partial, hipmr_count, hipmr_post, (double)hipmr_sc, hipmr_out);
+  } else if constexpr (@@ONE@@) {
+    hipmr_comp_finish<@@BLOCK@@, HIPMR_SQ>(hipmr_v, (unsigned long long*)hipmr_partial, hipmr_post, hipmr_tag, hipmr_out);
   } else if (threadIdx.x == 0) {
     hipmr_partial[blockIdx.x] = hipmr_v;
   }
@@ -1796,6 +1829,7 @@ std::string render(const Program& prog, const KernelSpec& spec, std::string* sym
                 spec.finish ? "hipmr_finish<@@BLOCK@@>(hipmr_r, hipmr_neutral, (unsigned long long*)hipmr_partial, "
                               "hipmr_out, hipmr_tag);"
                             : "if (threadIdx.x == 0) hipmr_partial[blockIdx.x] = hipmr_r;");
+    replace_all(body, "@@ONE@@", spec.finish ? "true" : "false");
     replace_all(body, "@@FPARAMS@@",
                 spec.finish ? ", hipmr_acc* __restrict__ hipmr_out, unsigned long long hipmr_tag" : "");
     replace_all(body, "@@PARAMS@@", params);
@@ -1831,9 +1865,9 @@ std::string render(const Program& prog, const KernelSpec& spec, std::string* sym
         src << "__device__ __forceinline__ hipmr_acc hipmr_combine(hipmr_acc a, hipmr_acc b) "
                "{ return (hipmr_acc)(" << cbody << "); }\n";
         src << kReduceHelpers;
-        if (spec.finish) src << kRedFinish;
+        if (spec.finish) src << kTagged << kRedFinish;
     }
-    if (comp) src << kCompHelpers;
+    if (comp) src << kTagged << kCompHelpers;
     if (seg || scan) src << kDppHelpers;
     if (seg) src << kSegHelpers;
     if (scan) src << kScanHelpers;

@@ -146,7 +146,7 @@ struct KernelSpec {
     bool exact_runs = false;  // CompS1: map is one FP8 load; sum runs of <= 64 exactly
     bool norm = false;        // CompS2: finish as sqrt(sum) / scale
     // batching extension
-    bool finish = false;      // RedS1: fold the partials in the same launch
+    bool finish = false;      // RedS1, CompS1: fold the partials in the same launch
     int scan_mode = 0;        // Scan: 0 one tile, 1 tile totals, 2 from totals, 3 one pass
     int lds_segs = 0;         // SegS1: segments its LDS tile table holds, 0 = table in global memory
 };

@@ -61,3 +61,33 @@ def test_replays_switch_between_the_passes():
         g.launch(st)
         torch.cuda.synchronize()
         assert out.item() == want * 2.0 ** e, e
+
+
+@pytest.mark.parametrize("fmt,tdt", [("float", torch.float32), ("bfloat16", torch.bfloat16),
+                                     ("fp8_e4m3", torch.float8_e4m3fn)])
+@pytest.mark.parametrize("n", [1, 4097, 100003, 1 << 22])
+def test_one_launch_equals_two(fmt, tdt, n):
+    """Compensated sums and one-pass norms that fold in their own launch, and
+    the captured form that does not: the same bits, whatever the workspace holds."""
+    dev = need_gpu()
+    x = torch.randn(n + 1, device=dev).to(tdt)[1:]
+    k = hm.compile("x[i]", f"float: const {fmt} *x", name="compf")
+    st = torch.cuda.Stream()
+    for call in (hm.reduce_compensated, lambda *a, **kw: hm.norm2(*a, passes=1, **kw)):
+        out, two = (torch.zeros((), dtype=torch.float64, device=dev) for _ in range(2))
+        for fill in (0, 255):
+            ws = torch.full((hm.reduce_workspace_bytes(k, n),), fill, dtype=torch.uint8, device=dev)
+            torch.cuda.synchronize()
+            for _ in range(3):
+                out.zero_()
+                torch.cuda.synchronize()
+                call(k, n, [x], post_scale=0.5, out=out, workspace_buf=ws, stream=st)
+                assert len(k.last_symbols()) == 1
+            g = hm.Graph()
+            with g.capture(st):
+                call(k, n, [x], post_scale=0.5, out=two, workspace_buf=ws, stream=st)
+            assert len(k.last_symbols()) == 2
+            for _ in range(2):
+                g.launch(st)
+                torch.cuda.synchronize()
+                assert two.item() == out.item() and out.item() != 0.0
