@@ -120,6 +120,10 @@ typedef struct hipmr_launch_config {
                                          geometry the autotuner stored for this handle,
                                          operation and size class, when there is one (else
                                          the other fields); never applied without the flag */
+#define HIPMR_CFG_NO_WAIT        128  /* waits inside a launch (for other blocks' partials) are
+                                         given up at the first look, as they are after their
+                                         limit: what a call does then can be tried without
+                                         keeping the GPU waiting                            */
 /* Streaming stores apply to chunks of at most 16 bytes per lane; a wider
  * chunk (e.g. four 64-bit results) leaves in several instructions that each
  * fill half lines, and is stored temporally so that the L2 merges them. */
@@ -194,6 +198,8 @@ size_t hipmr_reduce_workspace_bytes(hipmr_handle h, int64_t n);
  * One launch on stream: one block takes a small n, else the last block folds
  * the others' partials, published in the workspace under a tag of this launch
  * (nothing there needs clearing; the workspace belongs to one call at a time).
+ * Its wait for them is bounded; if it runs out, that block computes all the
+ * shares itself, in the same order (the same bits).
  * Two launches (block partials, then one block folding them: the same bits)
  * under capture, since a replay would repeat the tag, and with a geometry in
  * cfg.  No read-modify-write atomics; for a given device, n and launch

@@ -108,6 +108,7 @@ hipmr_status resolve_cfg(const hipmr_launch_config* c, int block, int ipt, int v
     if (c->flags & HIPMR_CFG_TEMPORAL_STORES) out->nt_stores = false;
     out->force_scalar = (c->flags & HIPMR_CFG_FORCE_SCALAR) != 0;
     out->seg_global = (c->flags & HIPMR_CFG_SEG_GLOBAL) != 0;
+    out->no_wait = (c->flags & HIPMR_CFG_NO_WAIT) != 0;
     return HIPMR_OK;
 }
 
@@ -404,8 +405,9 @@ bool own_shape(const hipmr_launch_config* c) {
     return c && (c->block || c->items_per_thread || c->grid || c->blocks_per_cu);
 }
 
-// A tag for one launch's partials: 48 bits, never 0, from a random start.
-uint64_t next_tag() {
+// A tag for one launch's partials: 48 bits, never 0, from a random start; bit
+// 63 asks the launch not to wait.
+uint64_t next_tag(const LaunchCfg& cfg) {
     static std::atomic<uint64_t> tag{[] {
         std::random_device rd;
         return (uint64_t)rd() << 32 ^ rd();
@@ -413,7 +415,7 @@ uint64_t next_tag() {
     uint64_t t;
     do t = tag.fetch_add(1) & ((1ull << 48) - 1);
     while (t == 0);
-    return t;
+    return t | (uint64_t)cfg.no_wait << 63;
 }
 
 // Whether work put on the stream now may be replayed later.
@@ -481,7 +483,7 @@ hipmr_status stage1_launch(hipmr_kernel* h, KernelSpec spec, LaunchCfg cfg,
     st = variant_function(h, spec, &out->fn, used);
     if (st != HIPMR_OK) return st;
     if (n == 0) return HIPMR_OK;
-    uint64_t tag = spec.finish ? next_tag() : 0;
+    uint64_t tag = spec.finish ? next_tag(cfg) : 0;
     std::vector<void*> params;
     if (h->prog.sig.args.empty()) params.push_back(&head64);   // hipmr_unused
     for (size_t k = 0; k < h->prog.sig.args.size(); ++k) params.push_back(args[k]);
@@ -756,7 +758,7 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
         void* fn = nullptr;
         st = variant_function(h, s1, &fn, &used);
         if (st != HIPMR_OK) return st;
-        uint64_t tag = s1.finish ? next_tag() : 0;
+        uint64_t tag = s1.finish ? next_tag(cfg) : 0;
         std::vector<void*> params;
         if (h->prog.sig.args.empty()) params.push_back(&head64);   // hipmr_unused
         for (size_t k = 0; k < h->prog.sig.args.size(); ++k) params.push_back(args[k]);

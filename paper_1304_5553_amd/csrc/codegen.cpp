@@ -277,13 +277,16 @@ __device__ __forceinline__ hipmr_acc hipmr_fold(hipmr_acc* a) {
 // taken only with this launch's tag (a launch that may be replayed, with the
 // same tag, folds in a launch of its own).  Device-scope accesses, no counter:
 // counting 512 blocks in through one address costs more than the second launch.
-// The wait ends: the other blocks wait for nothing.  Its limit (10 s) is reached
-// only if another call uses the workspace meanwhile.
+// The wait is bounded (2^20 polls, about a second).  It can run out while the
+// others still queue behind another stream's kernel, or where another call has
+// overwritten the words; the last block then computes every share itself, in
+// the same order, so the result is the same.
 // Against a separate fold launch: a dot of 2 x 2^20 floats 8.5 -> 5.5 us per
 // call, of 2 x 3.1 M 8.6 -> 6.6, a sum of 18.9 M 14.0 -> 12.8, of 157 M 92.4 ->
 // 91.2 (HBM bound).
 const char* kTagged = R"HIP(
-// publishes block k's value, and waits for it
+// publishes block k's value (hipmr_put_tagged), and waits for it (get: false
+// if it did not come); bit 63 of the launch's tag word asks for no wait
 template <typename T>
 __device__ __forceinline__ void hipmr_put_tagged(unsigned long long* part, int k, T v, unsigned long long tag) {
   constexpr int W = (int)sizeof(T) / 2;
@@ -295,9 +298,9 @@ __device__ __forceinline__ void hipmr_put_tagged(unsigned long long* part, int k
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 template <typename T>
-__device__ __forceinline__ T hipmr_get_tagged(const unsigned long long* part, int k, unsigned long long tag,
-                                              unsigned long long t0) {
+__device__ __forceinline__ bool hipmr_get_tagged(const unsigned long long* part, int k, unsigned long long tag, T* v) {
   constexpr int W = (int)sizeof(T) / 2;
+  const unsigned limit = tag >> 63 ? 1u : 1u << 20;
   unsigned long long bits;
   for (unsigned polls = 1;; ++polls) {
     bool here = true;
@@ -306,31 +309,53 @@ __device__ __forceinline__ T hipmr_get_tagged(const unsigned long long* part, in
     for (int j = 0; j < W; ++j) {
       const unsigned long long w = __hip_atomic_load(part + (long long)k * W + j, __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT);
-      here = here && (w >> 16) == tag;
+      here = here && (w >> 16) == (tag & 0xffffffffffffull);
       bits |= (w & 0xffffull) << (16 * j);
     }
-    if (here || ((polls & 63u) == 0 && __builtin_amdgcn_s_memrealtime() - t0 > 1000000000ull)) break;
+    if (here) break;
+    if (polls >= limit) return false;
     __builtin_amdgcn_s_sleep(1);
   }
-  T v;
-  __builtin_memcpy(&v, &bits, sizeof(v));
-  return v;
+  __builtin_memcpy(v, &bits, sizeof(T));
+  return true;
 }
 )HIP";
 
+// A kernel that finishes runs its share in a loop: `b` is the share just
+// computed, the result the next one to compute, or -1 when the block is done.
 const char* kRedFinish = R"HIP(
+struct hipmr_turn { hipmr_acc v; bool alone; };   // the last block's fold; whether it computes every share
 template <int B>
-__device__ __forceinline__ void hipmr_finish(hipmr_acc r, hipmr_acc neutral, unsigned long long* part,
-                                             hipmr_acc* __restrict__ out, unsigned long long tag) {
-  if (threadIdx.x == 0) hipmr_put_tagged(part, (int)blockIdx.x, r, tag);
-  if (blockIdx.x != gridDim.x - 1) return;
-  hipmr_acc v = neutral;
-  const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-  for (int k = threadIdx.x; k < (int)gridDim.x; k += B)
-    v = hipmr_combine(v, hipmr_get_tagged<hipmr_acc>(part, k, tag, t0));
-  __syncthreads();                              // the first fold's LDS has been read
-  v = hipmr_block_reduce<B>(v, neutral);
-  if (threadIdx.x == 0) *out = v;
+__device__ __forceinline__ int hipmr_finish(hipmr_acc r, hipmr_acc neutral, unsigned long long* part,
+                                            hipmr_acc* __restrict__ out, unsigned long long tag, int b,
+                                            hipmr_turn& f) {
+  const int g = (int)gridDim.x;
+  if (!f.alone) {
+    if (threadIdx.x == 0) hipmr_put_tagged(part, b, r, tag);
+    if ((int)blockIdx.x != g - 1) return -1;
+    f.v = neutral;
+    bool here = true;
+    for (int k = threadIdx.x; here && k < g; k += B) {
+      hipmr_acc p;
+      here = hipmr_get_tagged(part, k, tag, &p);
+      if (here) f.v = hipmr_combine(f.v, p);
+    }
+    if (__syncthreads_or(!here)) {
+      f.v = neutral;
+      f.alone = true;
+      return 0;
+    }
+  } else {
+    __shared__ hipmr_acc hipmr_share;
+    if (threadIdx.x == 0) hipmr_share = r;
+    __syncthreads();
+    if ((int)threadIdx.x == b % B) f.v = hipmr_combine(f.v, hipmr_share);
+    __syncthreads();
+    if (b + 1 < g) return b + 1;
+  }
+  f.v = hipmr_block_reduce<B>(f.v, neutral);     // the share's fold has been read: barriers above
+  if (threadIdx.x == 0) *out = f.v;
+  return -1;
 }
 )HIP";
 
@@ -434,9 +459,9 @@ __device__ __forceinline__ long long hipmr_clampv(long long off, long long s, lo
   return s < -off ? 0 : (s > hi - off ? hi : off + s);
 }
 
-__device__ __forceinline__ unsigned hipmr_xcd_block() {
-  const unsigned x = blockIdx.x % 8u, q = gridDim.x / 8u, r = gridDim.x % 8u;
-  return x * q + (x < r ? x : r) + blockIdx.x / 8u;
+__device__ __forceinline__ unsigned hipmr_xcd_block(unsigned b) {
+  const unsigned x = b % 8u, q = gridDim.x / 8u, r = gridDim.x % 8u;
+  return x * q + (x < r ? x : r) + b / 8u;
 }
 )HIP";
 
@@ -492,7 +517,7 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
     }
   }
   const long long hipmr_step = (long long)gridDim.x * (HIPMR_B * HIPMR_U);
-  for (long long hipmr_c0 = (long long)hipmr_xcd_block() * (HIPMR_B * HIPMR_U) + threadIdx.x;
+  for (long long hipmr_c0 = (long long)hipmr_xcd_block(blockIdx.x) * (HIPMR_B * HIPMR_U) + threadIdx.x;
        hipmr_c0 < hipmr_nc; hipmr_c0 += hipmr_step) {
     @@DECL_PACKS@@
     @@SHIFT_PACKS@@
@@ -556,13 +581,14 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   constexpr bool HIPMR_NTL = @@NTL@@, HIPMR_NTS = @@NTS@@;
   const hipmr_idx n = (hipmr_idx)hipmr_n;
   const hipmr_acc hipmr_neutral = (hipmr_acc)(@@NEUTRAL@@);
+  @@SHARES@@
   hipmr_acc hipmr_a[HIPMR_U];
 #pragma unroll
   for (int u = 0; u < HIPMR_U; ++u) hipmr_a[u] = hipmr_neutral;
   const long long hipmr_h = hipmr_head < hipmr_n ? hipmr_head : hipmr_n;
   const long long hipmr_nc = (hipmr_n - hipmr_h) / HIPMR_V;
   const long long hipmr_t0 = hipmr_h + hipmr_nc * HIPMR_V;
-  if (blockIdx.x == 0) {
+  if (hipmr_b == 0) {
     if ((long long)threadIdx.x < hipmr_h) {
       const hipmr_idx i = (hipmr_idx)threadIdx.x;
       hipmr_a[0] = hipmr_combine(hipmr_a[0], (hipmr_acc)(@@MAP@@));
@@ -573,7 +599,7 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
     }
   }
   const long long hipmr_step = (long long)gridDim.x * (HIPMR_B * HIPMR_U);
-  long long hipmr_c0 = (long long)blockIdx.x * (HIPMR_B * HIPMR_U) + threadIdx.x;
+  long long hipmr_c0 = (long long)hipmr_b * (HIPMR_B * HIPMR_U) + threadIdx.x;
   for (; hipmr_c0 + (HIPMR_U - 1) * HIPMR_B < hipmr_nc; hipmr_c0 += hipmr_step) {
     @@DECL_PACKS@@
 #pragma unroll
@@ -628,10 +654,11 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   typedef @@IDX@@ hipmr_idx;
   const hipmr_idx n = (hipmr_idx)hipmr_n;
   const hipmr_acc hipmr_neutral = (hipmr_acc)(@@NEUTRAL@@);
+  @@SHARES@@
   hipmr_acc hipmr_r = hipmr_neutral;
   const long long hipmr_step = (long long)gridDim.x * @@BLOCK@@;
 #pragma unroll @@IPT@@
-  for (long long hipmr_k = (long long)blockIdx.x * @@BLOCK@@ + threadIdx.x; hipmr_k < hipmr_n;
+  for (long long hipmr_k = (long long)hipmr_b * @@BLOCK@@ + threadIdx.x; hipmr_k < hipmr_n;
        hipmr_k += hipmr_step) {
     const hipmr_idx i = (hipmr_idx)hipmr_k;
     hipmr_r = hipmr_combine(hipmr_r, (hipmr_acc)(@@MAP@@));
@@ -657,13 +684,14 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   const hipmr_idx n = (hipmr_idx)hipmr_n;
   @@SHIFT_INIT@@
   const hipmr_acc hipmr_neutral = (hipmr_acc)(@@NEUTRAL@@);
+  @@SHARES@@
   hipmr_acc hipmr_a[HIPMR_U];
 #pragma unroll
   for (int u = 0; u < HIPMR_U; ++u) hipmr_a[u] = hipmr_neutral;
   const long long hipmr_h = hipmr_head < hipmr_n ? hipmr_head : hipmr_n;
   const long long hipmr_nc = (hipmr_n - hipmr_h) / HIPMR_V;
   const long long hipmr_t0 = hipmr_h + hipmr_nc * HIPMR_V;
-  if (blockIdx.x == 0) {
+  if (hipmr_b == 0) {
     if ((long long)threadIdx.x < hipmr_h) {
       const hipmr_idx i = (hipmr_idx)threadIdx.x;
       hipmr_a[0] = hipmr_combine(hipmr_a[0], (hipmr_acc)(@@MAP@@));
@@ -674,7 +702,7 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
     }
   }
   const long long hipmr_step = (long long)gridDim.x * (HIPMR_B * HIPMR_U);
-  for (long long hipmr_c0 = (long long)hipmr_xcd_block() * (HIPMR_B * HIPMR_U) + threadIdx.x;
+  for (long long hipmr_c0 = (long long)hipmr_xcd_block(hipmr_b) * (HIPMR_B * HIPMR_U) + threadIdx.x;
        hipmr_c0 < hipmr_nc; hipmr_c0 += hipmr_step) {
     @@DECL_PACKS@@
     @@SHIFT_PACKS@@
@@ -866,17 +894,17 @@ __device__ __forceinline__ P hipmr_block_reduce_pair(P v, F add) {
 // (Neumaier per thread, double-double tree), times the per-tensor post scale;
 // a norm is the root, over the data's scale.  The partials may be other
 // blocks' of the same launch: they are read with device-scope loads.
-template <int B, bool NORM, typename F>
-__device__ __forceinline__ void hipmr_comp_fold_of(F load, int g, double post, double scale,
-                                                   double* __restrict__ out) {
-  double s = 0.0, c = 0.0;
-  for (int k = threadIdx.x; k < g; k += B) {
-    const double v = load(k);
+struct hipmr_neumaier {
+  double s, c;
+  __device__ __forceinline__ void add(double v) {
     const double t = s + v;
     if (__builtin_isfinite(t)) c += fabs(s) >= fabs(v) ? (s - t) + v : (v - t) + s;
     s = t;
   }
-  hipmr_dd r = hipmr_two_sum_d(s, c);
+};
+template <int B, bool NORM>
+__device__ __forceinline__ void hipmr_comp_end(hipmr_neumaier f, double post, double scale, double* __restrict__ out) {
+  hipmr_dd r = hipmr_two_sum_d(f.s, f.c);
   r = hipmr_block_reduce_pair<B>(r, [](hipmr_dd a, hipmr_dd b) { return hipmr_dd_add(a, b); });
   if (threadIdx.x == 0) {
     const double total = __builtin_isfinite(r.hi) ? r.hi + r.lo : r.hi;
@@ -887,21 +915,46 @@ __device__ __forceinline__ void hipmr_comp_fold_of(F load, int g, double post, d
 template <int B, bool NORM>
 __device__ __forceinline__ void hipmr_comp_fold(const double* partial, int g, double post, double scale,
                                                 double* __restrict__ out) {
-  hipmr_comp_fold_of<B, NORM>([=](int k) {
-    return __builtin_bit_cast(double, __hip_atomic_load((const unsigned long long*)partial + k, __ATOMIC_RELAXED,
-                                                        __HIP_MEMORY_SCOPE_AGENT));
-  }, g, post, scale, out);
+  hipmr_neumaier f = {0.0, 0.0};
+  for (int k = threadIdx.x; k < g; k += B)
+    f.add(__builtin_bit_cast(double, __hip_atomic_load((const unsigned long long*)partial + k, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT)));
+  hipmr_comp_end<B, NORM>(f, post, scale, out);
 }
 
-// The end of a one-pass sum or norm in one launch (partials by tag).
+// The end of a one-pass sum or norm in one launch (partials by tag): the next
+// share to compute, or -1.
+struct hipmr_turn { hipmr_neumaier f; bool alone; };
 template <int B, bool NORM>
-__device__ __forceinline__ void hipmr_comp_finish(double v, unsigned long long* part, double post,
-                                                  unsigned long long tag, double* __restrict__ out) {
-  if (threadIdx.x == 0) hipmr_put_tagged(part, (int)blockIdx.x, v, tag);
-  if (blockIdx.x != gridDim.x - 1) return;
-  const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-  hipmr_comp_fold_of<B, NORM>([=](int k) { return hipmr_get_tagged<double>(part, k, tag, t0); },
-                              (int)gridDim.x, post, 1.0, out);
+__device__ __forceinline__ int hipmr_comp_finish(double v, unsigned long long* part, double post, double scale,
+                                                 unsigned long long tag, double* __restrict__ out, int b,
+                                                 hipmr_turn& h) {
+  const int g = (int)gridDim.x;
+  if (!h.alone) {
+    if (threadIdx.x == 0) hipmr_put_tagged(part, b, v, tag);
+    if ((int)blockIdx.x != g - 1) return -1;
+    h.f = {0.0, 0.0};
+    bool here = true;
+    for (int k = threadIdx.x; here && k < g; k += B) {
+      double p;
+      here = hipmr_get_tagged(part, k, tag, &p);
+      if (here) h.f.add(p);
+    }
+    if (__syncthreads_or(!here)) {
+      h.f = {0.0, 0.0};
+      h.alone = true;
+      return 0;
+    }
+  } else {
+    __shared__ double hipmr_share;
+    if (threadIdx.x == 0) hipmr_share = v;
+    __syncthreads();
+    if ((int)threadIdx.x == b % B) h.f.add(hipmr_share);
+    __syncthreads();
+    if (b + 1 < g) return b + 1;
+  }
+  hipmr_comp_end<B, NORM>(h.f, post, scale, out);
+  return -1;
 }
 
 // The second pass's end: every block publishes its partial and counts itself
@@ -949,13 +1002,14 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
       return;
     }
   }
+  @@SHARES@@
   float hipmr_s[HIPMR_U], hipmr_e[HIPMR_U];
 #pragma unroll
   for (int u = 0; u < HIPMR_U; ++u) { hipmr_s[u] = 0.0f; hipmr_e[u] = 0.0f; }
   const long long hipmr_h = hipmr_head < hipmr_n ? hipmr_head : hipmr_n;
   const long long hipmr_nc = (hipmr_n - hipmr_h) / HIPMR_V;
   const long long hipmr_t0 = hipmr_h + hipmr_nc * HIPMR_V;
-  if (blockIdx.x == 0) {
+  if (hipmr_b == 0) {
     if ((long long)threadIdx.x < hipmr_h) {
       const hipmr_idx i = (hipmr_idx)threadIdx.x;
       hipmr_kahan_add(hipmr_s[0], hipmr_e[0], hipmr_term<HIPMR_SQ, HIPMR_TRACK>((float)(@@MAP@@), hipmr_sc, hipmr_m));
@@ -966,7 +1020,7 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
     }
   }
   const long long hipmr_step = (long long)gridDim.x * (HIPMR_B * HIPMR_U);
-  long long hipmr_c0 = (long long)blockIdx.x * (HIPMR_B * HIPMR_U) + threadIdx.x;
+  long long hipmr_c0 = (long long)hipmr_b * (HIPMR_B * HIPMR_U) + threadIdx.x;
   for (; hipmr_c0 + (HIPMR_U - 1) * HIPMR_B < hipmr_nc; hipmr_c0 += hipmr_step) {
     @@DECL_PACKS@@
 #pragma unroll
@@ -1036,16 +1090,15 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   unsigned* const hipmr_count = (unsigned*)((char*)hipmr_scale_p + @@COUNT_GAP@@);
   if constexpr (HIPMR_SCALED) {
     hipmr_norm_finish<@@BLOCK@@>(hipmr_v, hipmr_partial, hipmr_count, hipmr_post, (double)hipmr_sc, hipmr_out);
-  } else if constexpr (@@ONE@@) {
-    hipmr_comp_finish<@@BLOCK@@, HIPMR_SQ>(hipmr_v, (unsigned long long*)hipmr_partial, hipmr_post, hipmr_tag, hipmr_out);
-  } else if (threadIdx.x == 0) {
-    hipmr_partial[blockIdx.x] = hipmr_v;
+  } else {
+    @@FINISH@@
   }
   if constexpr (HIPMR_TRACK) {
     hipmr_m = hipmr_block_amax<@@BLOCK@@>(hipmr_m);
     if (threadIdx.x == 0) hipmr_scale_p[blockIdx.x] = hipmr_m;
     if (blockIdx.x == 0 && threadIdx.x == 0) *hipmr_count = 0;
   }
+  @@END@@
 }
 )HIP";
 
@@ -1066,9 +1119,10 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
       return;
     }
   }
+  @@SHARES@@
   float hipmr_s = 0.0f, hipmr_cc = 0.0f;
   const long long hipmr_step = (long long)gridDim.x * @@BLOCK@@;
-  for (long long hipmr_k = (long long)blockIdx.x * @@BLOCK@@ + threadIdx.x; hipmr_k < hipmr_n;
+  for (long long hipmr_k = (long long)hipmr_b * @@BLOCK@@ + threadIdx.x; hipmr_k < hipmr_n;
        hipmr_k += hipmr_step) {
     const hipmr_idx i = (hipmr_idx)hipmr_k;
     hipmr_kahan_add(hipmr_s, hipmr_cc, hipmr_term<HIPMR_SQ, HIPMR_TRACK>((float)(@@MAP@@), hipmr_sc, hipmr_m));
@@ -1080,16 +1134,15 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   unsigned* const hipmr_count = (unsigned*)((char*)hipmr_scale_p + @@COUNT_GAP@@);
   if constexpr (HIPMR_SCALED) {
     hipmr_norm_finish<@@BLOCK@@>(hipmr_v, hipmr_partial, hipmr_count, hipmr_post, (double)hipmr_sc, hipmr_out);
-  } else if constexpr (@@ONE@@) {
-    hipmr_comp_finish<@@BLOCK@@, HIPMR_SQ>(hipmr_v, (unsigned long long*)hipmr_partial, hipmr_post, hipmr_tag, hipmr_out);
-  } else if (threadIdx.x == 0) {
-    hipmr_partial[blockIdx.x] = hipmr_v;
+  } else {
+    @@FINISH@@
   }
   if constexpr (HIPMR_TRACK) {
     hipmr_m = hipmr_block_amax<@@BLOCK@@>(hipmr_m);
     if (threadIdx.x == 0) hipmr_scale_p[blockIdx.x] = hipmr_m;
     if (blockIdx.x == 0 && threadIdx.x == 0) *hipmr_count = 0;
   }
+  @@END@@
 }
 )HIP";
 
@@ -1825,11 +1878,22 @@ std::string render(const Program& prog, const KernelSpec& spec, std::string* sym
     }
     replace_all(body, "@@VMAPX@@", vector_text);
     replace_all(body, "@@MODE@@", std::to_string(spec.scan_mode));
-    replace_all(body, "@@FINISH@@",
-                spec.finish ? "hipmr_finish<@@BLOCK@@>(hipmr_r, hipmr_neutral, (unsigned long long*)hipmr_partial, "
-                              "hipmr_out, hipmr_tag);"
-                            : "if (threadIdx.x == 0) hipmr_partial[blockIdx.x] = hipmr_r;");
-    replace_all(body, "@@ONE@@", spec.finish ? "true" : "false");
+    // a kernel that finishes computes its share in a loop (its last block may have to compute them all)
+    replace_all(body, "@@SHARES@@",
+                spec.finish ? "hipmr_turn hipmr_f; hipmr_f.alone = false;\n  for (int hipmr_b = (int)blockIdx.x;;) {"
+                            : "const unsigned hipmr_b = blockIdx.x;");
+    if (comp) {
+        replace_all(body, "@@FINISH@@",
+                    spec.finish ? "hipmr_b = hipmr_comp_finish<@@BLOCK@@, HIPMR_SQ>(hipmr_v, (unsigned long long*)hipmr_partial, "
+                                  "hipmr_post, 1.0, hipmr_tag, hipmr_out, hipmr_b, hipmr_f);\n    if (hipmr_b < 0) return;"
+                                : "if (threadIdx.x == 0) hipmr_partial[blockIdx.x] = hipmr_v;");
+        replace_all(body, "@@END@@", spec.finish ? "}" : "");
+    } else {
+        replace_all(body, "@@FINISH@@",
+                    spec.finish ? "hipmr_b = hipmr_finish<@@BLOCK@@>(hipmr_r, hipmr_neutral, (unsigned long long*)hipmr_partial, "
+                                  "hipmr_out, hipmr_tag, hipmr_b, hipmr_f);\n  if (hipmr_b < 0) return;\n  }"
+                                : "if (threadIdx.x == 0) hipmr_partial[blockIdx.x] = hipmr_r;");
+    }
     replace_all(body, "@@FPARAMS@@",
                 spec.finish ? ", hipmr_acc* __restrict__ hipmr_out, unsigned long long hipmr_tag" : "");
     replace_all(body, "@@PARAMS@@", params);

@@ -116,6 +116,7 @@ struct LaunchCfg {
     bool nt_loads = true;   // streaming (non-temporal) loads
     bool nt_stores = true;  // streaming (non-temporal) stores
     bool force_scalar = false;
+    bool no_wait = false;     // give up waits inside a launch at the first look
     bool unaligned = false;   // some arrays are read at element alignment (set by vector_head)
     bool seg_global = false;  // segmented: tile table in global memory
 };

@@ -34,7 +34,7 @@ DTYPE_NAMES = {F32: "float", F64: "double", I8: "int8_t", U8: "uint8_t", I16: "i
                BF16: "bfloat16", F16: "half", FP8: "fp8_e4m3", C64: "complex64"}
 
 CFG_NONTEMPORAL, CFG_FORCE_SCALAR, CFG_TEMPORAL = 1, 2, 4
-CFG_TEMPORAL_LOADS, CFG_TEMPORAL_STORES, CFG_SEG_GLOBAL, CFG_TUNED = 8, 16, 32, 64
+CFG_TEMPORAL_LOADS, CFG_TEMPORAL_STORES, CFG_SEG_GLOBAL, CFG_TUNED, CFG_NO_WAIT = 8, 16, 32, 64, 128
 ACCESS_INDEX, ACCESS_SHIFTED, ACCESS_FIXED, ACCESS_OTHER = 1, 2, 4, 8
 
 
