@@ -297,7 +297,9 @@ size_t hipmr_scan_workspace_bytes(hipmr_handle h, int64_t n);
  * At most two launches on `stream`, by size: one tile alone; tile totals and
  * a rescan from them; or a clear of the workspace's counters and one pass in
  * which tiles publish their totals and wait for their predecessors'.  The
- * workspace belongs to one call at a time.  The order of combination depends
+ * workspace belongs to one call at a time; if another writes it meanwhile a
+ * bounded wait may run out: the outputs whose sums are then not known are NaN
+ * (0 for whole numbers), and the next hipmr_scan on the device returns E_HIP.  The order of combination depends
  * only on n, alignment and geometry (bitwise repeatable).  Chunked accesses
  * when the map reads arrays as the vector kernels can (by default 16 bytes of
  * the narrowest input, but at most 16 bytes of output, per lane; out aligned,

@@ -239,6 +239,12 @@ long long vector_head(const hipmr_kernel* h, void* const* args, LaunchCfg* cfg, 
     return best;
 }
 
+bool may_be_replayed(void* stream) {
+    if (capturing_now()) return true;
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing((hipStream_t)stream, &s) != hipSuccess || s != hipStreamCaptureStatusNone;
+}
+
 hipmr_status check_args(hipmr_kernel* h, int64_t n, void* const* args) {
     if (!h) return fail(HIPMR_E_INVALID, "NULL handle");
     if (n < 0) return fail(HIPMR_E_INVALID, "n must be >= 0");
@@ -416,13 +422,6 @@ uint64_t next_tag(const LaunchCfg& cfg) {
     do t = tag.fetch_add(1) & ((1ull << 48) - 1);
     while (t == 0);
     return t | (uint64_t)cfg.no_wait << 63;
-}
-
-// Whether work put on the stream now may be replayed later.
-bool may_be_replayed(void* stream) {
-    if (capturing_now()) return true;
-    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing((hipStream_t)stream, &s) != hipSuccess || s != hipStreamCaptureStatusNone;
 }
 
 KernelSpec s2_spec(const char* combine, const char* neutral) {

@@ -1512,9 +1512,10 @@ __device__ __forceinline__ hipmr_acc hipmr_lane_value(hipmr_acc v, int l) {
   return hipmr_from_bits<hipmr_acc>(r);
 }
 
-// Published totals (MODE 3).  A 4-byte total is one 64-bit word, value | 1 << 32;
-// an 8-byte total two such words, so a single 64-bit load tells both whether
-// a word is there and what it holds, and no fence is needed.  Accesses are
+// Published totals (MODE 3).  A 4-byte total is one 64-bit word, value | 1 << 32
+// (3 << 32: built on a total that never came); an 8-byte total two such words,
+// so a single 64-bit load tells whether a word is there and what it holds, and
+// no fence is needed.  Accesses are
 // device-scope (the L2s of the eight dies are not coherent otherwise).  Word 0
 // counts tickets, word 1 is set when a wait has been given up.
 constexpr int HIPMR_S = (int)sizeof(hipmr_acc) / 4, HIPMR_STATE0 = 16;
@@ -1522,11 +1523,11 @@ constexpr int HIPMR_S = (int)sizeof(hipmr_acc) / 4, HIPMR_STATE0 = 16;
 __device__ __forceinline__ hipmr_u64 hipmr_peek(const hipmr_u64* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void hipmr_publish(hipmr_u64* p, hipmr_acc v) {
-  const hipmr_u64 a = hipmr_to_bits(v);
-  __hip_atomic_store(p, (1ull << 32) | (unsigned)a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void hipmr_publish(hipmr_u64* p, hipmr_acc v, bool lost) {
+  const hipmr_u64 a = hipmr_to_bits(v), there = (lost ? 3ull : 1ull) << 32;
+  __hip_atomic_store(p, there | (unsigned)a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if constexpr (HIPMR_S == 2)
-    __hip_atomic_store(p + 1, (1ull << 32) | (a >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p + 1, there | (a >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 struct hipmr_slot { hipmr_u64 w0, w1; };
 __device__ __forceinline__ hipmr_slot hipmr_first_look(const hipmr_u64* p, bool mine) {
@@ -1540,24 +1541,26 @@ __device__ __forceinline__ hipmr_slot hipmr_first_look(const hipmr_u64* p, bool 
 // The fold, in lane order, of the totals the lanes wait for (lanes with
 // mine = false hold the neutral element); every lane receives it.  The waits
 // end: a total is published by a tile with an earlier ticket, whose block is
-// already running and itself waits for still earlier ones only.  The limit
-// below (10 s, or another wave's expiry) is reached only if something else
-// writes the workspace while the scan runs; the scan then ends with wrong
-// sums instead of hanging the GPU.
+// already running and itself waits for still earlier ones only.  So the limit
+// (a number of polls, some seconds of them, or another wave's expiry) is
+// reached only if something else writes the workspace while the scan runs, or
+// if the call asked for no wait; `lost` then tells the tile and, through the
+// totals built on it, all later ones that their sums are not known.
+struct hipmr_wait { hipmr_u64* state; unsigned limit; bool lost; };
 __device__ __forceinline__ hipmr_acc hipmr_await_fold(const hipmr_u64* p, bool mine, hipmr_slot s,
-                                                      hipmr_acc e, hipmr_u64* state) {
+                                                      hipmr_acc e, hipmr_wait& wait) {
   unsigned polls = 0;
-  const hipmr_u64 t0 = __builtin_amdgcn_s_memrealtime();
   while (__ballot(!((s.w0 >> 32) && (s.w1 >> 32)))) {
-    if ((++polls & 63u) == 0 &&
-        (hipmr_peek(state + 1) || __builtin_amdgcn_s_memrealtime() - t0 > 1000000000ull)) {
-      __hip_atomic_store(state + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (++polls >= wait.limit || ((polls & 63u) == 0 && hipmr_peek(wait.state + 1))) {
+      __hip_atomic_store(wait.state + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      wait.lost = true;
       break;
     }
     __builtin_amdgcn_s_sleep(16);                    // 1024 clocks: fewer polls beside the ticket atomics
     if (!(s.w0 >> 32)) s.w0 = hipmr_peek(p);
     if constexpr (HIPMR_S == 2) { if (!(s.w1 >> 32)) s.w1 = hipmr_peek(p + 1); }
   }
+  if (__ballot((s.w0 >> 33) || (s.w1 >> 33))) wait.lost = true;
   hipmr_acc v = e;
   if (mine) v = hipmr_from_bits<hipmr_acc>(HIPMR_S == 1 ? s.w0 & 0xffffffffull : (s.w1 << 32) | (s.w0 & 0xffffffffull));
   return hipmr_lane_value(hipmr_wave_scan(v, e), 63);
@@ -1569,31 +1572,40 @@ __device__ __forceinline__ hipmr_acc hipmr_await_fold(const hipmr_u64* p, bool m
 // of a supergroup that one's, so three short folds reach any distance:
 // earlier tiles of the group, earlier groups of the supergroup, earlier
 // supergroups (64 per round).
-__device__ __forceinline__ hipmr_acc hipmr_before(int tile, int tiles, hipmr_acc own, hipmr_u64* state,
+__device__ __forceinline__ hipmr_acc hipmr_before(int tile, int tiles, hipmr_acc own, hipmr_wait& wait,
                                                   hipmr_acc e, int lane) {
+  hipmr_u64* const state = wait.state;
   const int g = tile >> 6, r = tile & 63, h = g >> 6, q = g & 63;
   hipmr_u64* const pt = state + HIPMR_STATE0;
   hipmr_u64* const pg = pt + (long long)tiles * HIPMR_S;
   hipmr_u64* const ph = pg + (long long)((tiles + 63) >> 6) * HIPMR_S;
-  if (lane == 0) hipmr_publish(pt + (long long)tile * HIPMR_S, own);
+  if (lane == 0) hipmr_publish(pt + (long long)tile * HIPMR_S, own, false);
   const hipmr_u64* const at = pt + ((long long)(tile - r) + lane) * HIPMR_S;
   const hipmr_u64* const ag = pg + ((long long)(g - q) + lane) * HIPMR_S;
   const hipmr_u64* ah = ph + (long long)lane * HIPMR_S;
   const hipmr_slot st = hipmr_first_look(at, lane < r);
   const hipmr_slot sg = hipmr_first_look(ag, lane < q);
   hipmr_slot sh = hipmr_first_look(ah, lane < h);
-  const hipmr_acc ft = hipmr_await_fold(at, lane < r, st, e, state);
-  if (r == 63 && lane == 0) hipmr_publish(pg + (long long)g * HIPMR_S, hipmr_combine(ft, own));
-  const hipmr_acc fg = hipmr_await_fold(ag, lane < q, sg, e, state);
+  const hipmr_acc ft = hipmr_await_fold(at, lane < r, st, e, wait);
+  if (r == 63 && lane == 0) hipmr_publish(pg + (long long)g * HIPMR_S, hipmr_combine(ft, own), wait.lost);
+  const hipmr_acc fg = hipmr_await_fold(ag, lane < q, sg, e, wait);
   if (r == 63 && q == 63 && lane == 0)
-    hipmr_publish(ph + (long long)h * HIPMR_S, hipmr_combine(fg, hipmr_combine(ft, own)));
-  hipmr_acc fh = hipmr_await_fold(ah, lane < h, sh, e, state);
+    hipmr_publish(ph + (long long)h * HIPMR_S, hipmr_combine(fg, hipmr_combine(ft, own)), wait.lost);
+  hipmr_acc fh = hipmr_await_fold(ah, lane < h, sh, e, wait);
   for (int k = 64; k < h; k += 64) {
     ah += 64 * HIPMR_S;
     sh = hipmr_first_look(ah, lane < h - k);
-    fh = hipmr_combine(fh, hipmr_await_fold(ah, lane < h - k, sh, e, state));
+    fh = hipmr_combine(fh, hipmr_await_fold(ah, lane < h - k, sh, e, wait));
   }
   return hipmr_combine(fh, hipmr_combine(fg, ft));
+}
+
+// what an output whose sum is not known holds: NaN where the type has one
+template <typename T> __device__ __forceinline__ T hipmr_unknown() {
+  if constexpr (__is_same(T, float)) return __builtin_nanf("");
+  else if constexpr (__is_same(T, double)) return __builtin_nan("");
+  else if constexpr (__is_same(T, hipmr_c64)) return T(__builtin_nanf(""), __builtin_nanf(""));
+  else return T(0);
 }
 )HIP";
 
@@ -1610,8 +1622,10 @@ extern "C" __global__ void __launch_bounds__(256)
 const char* kScanTile = R"HIP(
 extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 @@KNAME@@(@@PARAMS@@, long long hipmr_n, long long hipmr_base, int hipmr_tiles,
-          void* __restrict__ hipmr_state, hipmr_acc* __restrict__ hipmr_out, int hipmr_exclusive)
+          void* __restrict__ hipmr_state, hipmr_acc* __restrict__ hipmr_out, int hipmr_flags,
+          unsigned* __restrict__ hipmr_gave_up)
 {
+  const bool hipmr_exclusive = hipmr_flags & 1;      // bit 1: no wait
   typedef @@IDX@@ hipmr_idx;
   constexpr int HIPMR_B = @@BLOCK@@, HIPMR_U = @@IPT@@, HIPMR_V = @@VEC@@, HIPMR_MODE = @@MODE@@;
   constexpr int HIPMR_W = HIPMR_B / 64;
@@ -1702,6 +1716,7 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   }
   // across the block's waves: every wave scans the wave totals itself
   __shared__ hipmr_acc hipmr_wt[HIPMR_W], hipmr_wp[HIPMR_W], hipmr_pre_lds;
+  __shared__ bool hipmr_lost_lds;
   if (hipmr_lane == 63) {
     hipmr_wt[hipmr_w] = hipmr_carry;
     hipmr_wp[hipmr_w] = hipmr_pp;
@@ -1718,12 +1733,23 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
                                                  hipmr_neutral), 63);
   if constexpr (HIPMR_MODE == 3) {
     if (hipmr_w == 0) {
+      hipmr_wait hipmr_wt8 = {(hipmr_u64*)hipmr_state, hipmr_flags & 2 ? 1u : 1u << 22, false};
       const hipmr_acc hipmr_b = hipmr_before(hipmr_tile, hipmr_tiles, hipmr_lane_value(hipmr_ws, HIPMR_W - 1),
-                                             (hipmr_u64*)hipmr_state, hipmr_neutral, hipmr_lane);
-      if (hipmr_lane == 0) hipmr_pre_lds = hipmr_b;
+                                             hipmr_wt8, hipmr_neutral, hipmr_lane);
+      if (hipmr_lane == 0) {
+        hipmr_pre_lds = hipmr_b;
+        hipmr_lost_lds = hipmr_wt8.lost;
+      }
     }
     __syncthreads();
     hipmr_pre = hipmr_pre_lds;
+    if (hipmr_lost_lds) {                            // said in the outputs and to the host
+      if (threadIdx.x == 0 && hipmr_gave_up)
+        __hip_atomic_store(hipmr_gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      for (int k = threadIdx.x; k < (int)HIPMR_TILE; k += HIPMR_B)
+        if (hipmr_b0 + k >= 0 && hipmr_b0 + k < hipmr_n) hipmr_out[hipmr_b0 + k] = hipmr_unknown<hipmr_acc>();
+      return;
+    }
   }
   const hipmr_acc hipmr_wpre = hipmr_w == 0 ? hipmr_neutral : hipmr_lane_value(hipmr_ws, hipmr_w - 1);
 #pragma unroll

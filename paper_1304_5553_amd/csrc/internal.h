@@ -87,6 +87,8 @@ hipmr_status run_concurrently(const std::vector<std::function<hipmr_status()>>& 
 long long vector_head(const hipmr_kernel* h, void* const* args, LaunchCfg* cfg,
                       const void* out = nullptr, int out_size = 0);
 hipmr_status check_args(hipmr_kernel* h, int64_t n, void* const* args);
+// Whether work put on the stream now may be replayed later.
+bool may_be_replayed(void* stream);
 int grid_for(long long work_units, int per_block, const LaunchCfg& cfg, int cap);
 // geometry stored by the autotuner for (op, combine, neutral, size class of n)
 bool tuned_config(hipmr_kernel* h, const char* op, const char* combine, const char* neutral,

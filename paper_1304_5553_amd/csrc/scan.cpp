@@ -16,6 +16,9 @@
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
+#include <atomic>
+#include <mutex>
+#include <new>
 #include <vector>
 
 #include "internal.h"
@@ -68,6 +71,27 @@ KernelSpec scan_spec(bool vector, int mode, const LaunchCfg& cfg, bool idx64, co
 long long state_words(long long tiles, size_t rs) {
     const long long groups = (tiles + 63) / 64, supers = (groups + 63) / 64;
     return 16 + (tiles + groups + supers) * (long long)(rs / 4);
+}
+
+// The current device's word that a scan sets when it gives up a wait: pinned
+// host memory, kept for the life of the process.  Null until a scan that may
+// wait has allocated it outside a capture (`allocate`).
+std::atomic<unsigned>* gave_up_word(bool allocate, void* stream) {
+    constexpr int kDevices = 64;
+    static std::mutex mu;
+    static std::atomic<std::atomic<unsigned>*> words[kDevices];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return nullptr;
+    std::atomic<unsigned>* w = words[dev].load(std::memory_order_acquire);
+    if (w || !allocate || may_be_replayed(stream)) return w;
+    std::lock_guard<std::mutex> lk(mu);
+    if ((w = words[dev].load())) return w;
+    void* p = nullptr;
+    if (hipHostMalloc(&p, sizeof(std::atomic<unsigned>), hipHostMallocDefault) == hipSuccess)
+        words[dev].store(w = new (p) std::atomic<unsigned>(0), std::memory_order_release);
+    else
+        (void)hipGetLastError();
+    return w;
 }
 
 }  // namespace
@@ -131,6 +155,10 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
         return v;
     });
     if (st != HIPMR_OK) return st;
+    std::atomic<unsigned>* gave_up = gave_up_word(false, stream);
+    if (gave_up && gave_up->load(std::memory_order_relaxed) && gave_up->exchange(0))
+        return fail(HIPMR_E_HIP, "an earlier scan on this device gave up waiting for a tile's total: its workspace "
+                                 "was written by another call meanwhile, and its outputs are not the scan");
     int mode = 3;
     const LaunchCfg one = with(kScanOneBlock, kScanIpt), small = with(kScanSmallBlock, kScanIpt);
     if (tiles_of(one) == 1 && (own_block || own_ipt || n64 <= h->one_block)) {
@@ -149,8 +177,9 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
         while (!fits() && cfg.block < 1024) cfg.block = std::min(1024, 2 * cfg.block);
         if (!fits()) return fail(HIPMR_E_WORKSPACE, "workspace too small for the scan's tile totals");
     }
+    if (mode == 3 && !gave_up) gave_up = gave_up_word(true, stream);
     const long long tiles64 = tiles_of(cfg);
-    int tiles = (int)tiles64, excl = exclusive, words = (int)state_words(tiles64, rs);
+    int tiles = (int)tiles64, flags = exclusive | (cfg.no_wait ? 2 : 0), words = (int)state_words(tiles64, rs);
 
     CallKernels used;
     void *f_first = nullptr, *f_scan = nullptr;
@@ -168,7 +197,7 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
     if (h->prog.sig.args.empty()) p.push_back(&base);       // hipmr_unused
     for (size_t k = 0; k < h->prog.sig.args.size(); ++k) p.push_back(args[k]);
     long long n_arg = n64;
-    p.insert(p.end(), {(void*)&n_arg, (void*)&base, (void*)&tiles, (void*)&workspace, (void*)&out, (void*)&excl});
+    p.insert(p.end(), {(void*)&n_arg, (void*)&base, (void*)&tiles, (void*)&workspace, (void*)&out, (void*)&flags, (void*)&gave_up});
     if (mode == 2) {
         st = launch(f_first, (unsigned)tiles, (unsigned)cfg.block, p.data(), stream);
     } else if (mode == 3) {

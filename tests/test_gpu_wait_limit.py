@@ -57,3 +57,25 @@ def test_compensated_without_waiting(dev, n, fmt):
                     lambda *a, **k: hm.norm2(*a, passes=2, **k)):
             want = run(h, n, [x], config={"flags": flags}).item()
             assert run(h, n, [x], config={"flags": flags | hm.hipmr.CFG_NO_WAIT}).item() == want
+
+
+@pytest.mark.parametrize("result,ctype,tdt", [("float", "float", torch.float32), ("double", "double", torch.float64),
+                                              ("complex64", "complex64", torch.complex64), ("long", "int", torch.int32)])
+@pytest.mark.parametrize("exclusive", [False, True])
+def test_scan_without_waiting_says_so(dev, result, ctype, tdt, exclusive):
+    """Every output is the scan's or NaN (0), and the next scan reports it, once."""
+    n = (1 << 25) + 3
+    x = (torch.randint(1, 9, (n,), dtype=tdt, device=dev) if tdt == torch.int32 else torch.randn(n, dtype=tdt, device=dev))
+    h = hm.compile("x[i]", f"{result}: const {ctype} *x", name="nowait")
+    rdt = hm.torch_dtype(h.result_dtype)
+    want, out = torch.zeros(n, dtype=rdt, device=dev), torch.zeros(n, dtype=rdt, device=dev)
+    hm.scan(h, "a+b", "0", n, [x], want, exclusive=exclusive)
+    hm.scan(h, "a+b", "0", n, [x], out, exclusive=exclusive, config=NO_WAIT)
+    torch.cuda.synchronize()
+    unknown = out == 0 if rdt == torch.int64 else torch.isnan(out)
+    assert torch.equal(out[~unknown], want[~unknown])
+    assert 0 < unknown.sum().item() < n
+    with pytest.raises(hm.HipError, match="gave up"):
+        hm.scan(h, "a+b", "0", n, [x], out, exclusive=exclusive)
+    hm.scan(h, "a+b", "0", n, [x], out, exclusive=exclusive)
+    assert torch.equal(out, want)
