@@ -194,7 +194,8 @@ size_t hipmr_reduce_workspace_bytes(hipmr_handle h, int64_t n);
  *   neutral:    C expression converted to the result type.
  *   out:        device pointer to one element of the result type.
  *   workspace:  device buffer of at least hipmr_reduce_workspace_bytes(h, n)
- *               bytes (E_WORKSPACE otherwise); it is scratch for block partials.
+ *               bytes (E_WORKSPACE otherwise); it is scratch for block partials,
+ *               at any alignment.
  * One launch on stream: one block takes a small n, else the last block folds
  * the others' partials, published in the workspace under a tag of this launch
  * (nothing there needs clearing; the workspace belongs to one call at a time).
@@ -327,6 +328,8 @@ size_t hipmr_poisson_cg_workspace_bytes(int64_t nx, int64_t ny);
  *   s:       four device floats, two (r . r, p . A p) pairs: iteration k reads
  *            r . r from pair (parity + k) mod 2, writes its p . A p there and
  *            the next r . r into the other pair.
+ *   workspace: at least hipmr_poisson_cg_workspace_bytes(nx, ny) bytes, aligned
+ *            to 8.
  * 2 iters + 1 launches (one more with b), asynchronous on `stream`, nothing
  * allocated.  Sums in FP64; the result depends only on the arguments (not on
  * how a run of iterations is divided into calls).  iters == 0: only the

@@ -539,6 +539,7 @@ hipmr_status hipmr_reduce_compensated(hipmr_handle h, int64_t n, void* const* ar
     clear_error();
     hipmr_status st = precision_checks(h, n, args, out, workspace, workspace_bytes);
     if (st != HIPMR_OK) return st;
+    workspace = align_words(workspace);
     LaunchCfg cfg;
     st = resolve_cfg(cfgp, kRedBlock, kRedIpt, h->stream_vec, kRedBlocksPerCu, &cfg);
     if (st != HIPMR_OK) return st;
@@ -571,6 +572,7 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
     hipmr_status st = precision_checks(h, n, args, out, workspace, workspace_bytes);
     if (st != HIPMR_OK) return st;
     if (passes != 1 && passes != 2) return fail(HIPMR_E_INVALID, "passes must be 1 or 2");
+    workspace = align_words(workspace);
     LaunchCfg cfg;
     st = resolve_cfg(cfgp, kRedBlock, kRedIpt, h->stream_vec, kRedBlocksPerCu, &cfg);
     if (st != HIPMR_OK) return st;
@@ -721,6 +723,7 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
     st = resolve_cfg(cfgp, kRedBlock, kRedIpt, h->stream_vec, kRedBlocksPerCu, &cfg);
     if (st != HIPMR_OK) return st;
 
+    workspace = align_words(workspace);
     // one block, unless the call chose a geometry
     const bool own = own_shape(cfgp);
     long long n64 = n, head64 = 0;

@@ -390,6 +390,7 @@ hipmr_status hipmr_poisson_cg(int64_t nx, int64_t ny, const void* b, int32_t ite
     if (!x || !r || !p || !q || !s) return fail(HIPMR_E_INVALID, "NULL array");
     if (!workspace || workspace_bytes < hipmr_poisson_cg_workspace_bytes(nx, ny))
         return fail(HIPMR_E_WORKSPACE, "workspace smaller than hipmr_poisson_cg_workspace_bytes()");
+    if ((uintptr_t)workspace % 8) return fail(HIPMR_E_WORKSPACE, "workspace off its 8-byte alignment");
     for (const void* a : {b, (const void*)x, (const void*)r, (const void*)p, (const void*)q, (const void*)s})
         if ((uintptr_t)a % 4) return fail(HIPMR_E_INVALID, "array off its element alignment");
     const long long n = nx * ny;

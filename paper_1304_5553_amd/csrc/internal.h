@@ -47,6 +47,11 @@ constexpr size_t kAmaxOffset = (size_t)kMaxPartials * 8;
 constexpr size_t kCountOffset = kAmaxOffset + (size_t)kMaxPartials * 4;
 constexpr size_t kWorkspaceBytes = kCountOffset + 256;
 
+// Words that blocks of one launch exchange are 64 bits, accessed atomically:
+// a workspace that starts off their alignment is used from the next multiple
+// of 8 (the reduce workspace's last 256 bytes leave room for that).
+inline char* align_words(void* workspace) { return (char*)(((uintptr_t)workspace + 7) & ~(uintptr_t)7); }
+
 // Default geometry (overridable per call through hipmr_launch_config), from
 // sweeps on MI355X at n = 2^28: streaming reads reach their best rate with a
 // small resident grid (2 blocks of 256 threads per CU, 4 chunks of 16 bytes

@@ -117,6 +117,8 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
     if (!out) return fail(HIPMR_E_INVALID, "out is NULL");
     if (!workspace || workspace_bytes < hipmr_scan_workspace_bytes(h, n))
         return fail(HIPMR_E_WORKSPACE, "workspace smaller than hipmr_scan_workspace_bytes()");
+    workspace_bytes -= align_words(workspace) - (char*)workspace;
+    workspace = align_words(workspace);
     // Default chunk: 16 bytes of the narrowest input, but at most 16 bytes of
     // output per lane, so that each store instruction of a wave writes one
     // contiguous run.
