@@ -494,16 +494,26 @@ _ws_lock = threading.Lock()
 
 
 def workspace(nbytes, device, stream_ptr):
-    """A device workspace of at least nbytes, cached per (device, stream)."""
-    key = (device if isinstance(device, str) else (device.type, device.index), stream_ptr)
+    """A device workspace of at least nbytes, cached per (device, stream) and
+    calling thread: a call's launches on it may interleave with another
+    thread's on the same stream, and a workspace belongs to one call at a
+    time.  A thread that has none yet takes over one of a thread that has
+    ended, so there are no more than threads alive at once."""
+    key = (device if isinstance(device, str) else (device.type, device.index), stream_ptr, threading.get_ident())
     buf = _ws_cache.get(key)
     if buf is not None and buf.numel() >= nbytes:
         return buf
     import torch
     with _ws_lock:
         buf = _ws_cache.get(key)
+        if buf is None:
+            threading.current_thread()               # lists this thread, whoever started it
+            alive = {t.ident for t in threading.enumerate()}
+            left = next((k for k in _ws_cache if k[:2] == key[:2] and k[2] not in alive), None)
+            if left is not None:
+                buf = _ws_cache[key] = _ws_cache.pop(left)
         if buf is None or buf.numel() < nbytes:
-            buf = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=device)
+            buf = torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device=device)
             _ws_cache[key] = buf
         return buf
 

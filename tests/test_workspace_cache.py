@@ -1,0 +1,33 @@
+"""The binding's cached workspaces (host side; no GPU)."""
+
+import threading
+
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1304_5553_amd import hipmr  # noqa: E402
+
+
+def test_each_thread_has_its_own():
+    """Two threads that launch on one stream at a time must not share one."""
+    got, both = {}, threading.Barrier(2)
+
+    def take(k):
+        both.wait()
+        got[k] = [hipmr.workspace(1000, "cpu", 0x51) for _ in range(2)]
+        both.wait()                                  # both alive until both have theirs
+    threads = [threading.Thread(target=take, args=(k,)) for k in range(2)]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    assert got[0][0] is got[0][1] and got[1][0] is got[1][1]
+    assert got[0][0].data_ptr() != got[1][0].data_ptr()
+
+
+def test_ended_threads_leave_theirs_to_the_next():
+    before = len(hipmr._ws_cache)
+    for _ in range(20):
+        t = threading.Thread(target=hipmr.workspace, args=(1000, "cpu", 0x52))
+        t.start()
+        t.join()
+    assert len(hipmr._ws_cache) == before + 1
