@@ -520,10 +520,8 @@ def workspace(nbytes, device, stream_ptr):
 
 def reduce_workspace_bytes(handle: Kernel, n):
     need = handle._ws_bytes
-    if need is None or n < 0:
-        need = lib().hipmr_reduce_workspace_bytes(handle.handle, int(n))
-        if need:                          # 0: not a size of a reduction (a negative n, an elementwise handle)
-            handle._ws_bytes = need
+    if need is None:
+        need = handle._ws_bytes = lib().hipmr_reduce_workspace_bytes(handle.handle, int(n))
     return need
 
 

@@ -31,12 +31,3 @@ def test_ended_threads_leave_theirs_to_the_next():
         t.start()
         t.join()
     assert len(hipmr._ws_cache) == before + 1
-
-
-def test_a_refused_size_is_not_remembered():
-    h = hipmr.compile("x[i]", "float: const float *x", name="wsbytes")
-    assert hipmr.reduce_workspace_bytes(h, -1) == 0
-    need = hipmr.reduce_workspace_bytes(h, 1000)
-    assert need > 0
-    assert hipmr.reduce_workspace_bytes(h, -1) == 0
-    assert hipmr.reduce_workspace_bytes(h, 1 << 40) == need
