@@ -499,11 +499,13 @@ def workspace(nbytes, device, stream_ptr):
     thread's on the same stream, and a workspace belongs to one call at a
     time.  A thread that has none yet takes over one of a thread that has
     ended, so there are no more than threads alive at once."""
-    key = (device if isinstance(device, str) else (device.type, device.index), stream_ptr, threading.get_ident())
+    key = (device, stream_ptr, threading.get_ident())
     buf = _ws_cache.get(key)
     if buf is not None and buf.numel() >= nbytes:
         return buf
     import torch
+    given = key
+    key = (str(device), stream_ptr, key[2])          # one for every form the device is named in
     with _ws_lock:
         buf = _ws_cache.get(key)
         if buf is None:
@@ -515,6 +517,7 @@ def workspace(nbytes, device, stream_ptr):
         if buf is None or buf.numel() < nbytes:
             buf = torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device=device)
             _ws_cache[key] = buf
+        _ws_cache[given] = buf
         return buf
 
 

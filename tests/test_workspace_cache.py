@@ -31,3 +31,14 @@ def test_ended_threads_leave_theirs_to_the_next():
         t.start()
         t.join()
     assert len(hipmr._ws_cache) == before + 1
+
+
+def test_every_form_of_a_device():
+    """A string, a torch.device, or whatever else torch takes (an index), as
+    before: one buffer for the forms that read alike."""
+    class Named:                                     # any object that torch.empty would take
+        def __str__(self):
+            return "cpu"
+    a = hipmr.workspace(100, "cpu", 0x53)
+    assert hipmr.workspace(100, torch.device("cpu"), 0x53) is a
+    assert hipmr.workspace(100, Named(), 0x53) is a
