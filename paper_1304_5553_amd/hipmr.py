@@ -513,7 +513,10 @@ def workspace(nbytes, device, stream_ptr):
             alive = {t.ident for t in threading.enumerate()}
             left = next((k for k in _ws_cache if k[:2] == key[:2] and k[2] not in alive), None)
             if left is not None:
-                buf = _ws_cache[key] = _ws_cache.pop(left)
+                buf = _ws_cache[left]
+                for k in [k for k in _ws_cache if k[1:] == left[1:]]:      # under any name of the device
+                    del _ws_cache[k]
+                _ws_cache[key] = buf
         if buf is None or buf.numel() < nbytes:
             buf = torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device=device)
             _ws_cache[key] = buf

@@ -42,3 +42,13 @@ def test_every_form_of_a_device():
     a = hipmr.workspace(100, "cpu", 0x53)
     assert hipmr.workspace(100, torch.device("cpu"), 0x53) is a
     assert hipmr.workspace(100, Named(), 0x53) is a
+
+
+def test_a_workspace_taken_over_has_one_owner():
+    """However the ended thread named the device."""
+    t = threading.Thread(target=hipmr.workspace, args=(1000, torch.device("cpu"), 0x54))
+    t.start()
+    t.join()
+    buf = hipmr.workspace(1000, torch.device("cpu"), 0x54)
+    owners = {k[2] for k, v in hipmr._ws_cache.items() if v is buf}
+    assert owners == {threading.get_ident()}
