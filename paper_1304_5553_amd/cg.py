@@ -79,14 +79,19 @@ class PoissonCG:
         """This iteration's r . r (a one-element device tensor)."""
         return self._pairs()[0][0:1]
 
+    def _start(self, b, iters):
+        """A run from the right-hand side b (a tensor or a device address)."""
+        if hasattr(b, "numel") and b.numel() < self.n:
+            raise _hm.InvalidError(f"array 'b' has {b.numel()} elements, fewer than n = {self.n}")
+        b = b if isinstance(b, int) else 0 if b is None else b.data_ptr()
+        if self.n > 0 and b == 0:
+            raise _hm.InvalidError("array argument 'b' is NULL")
+        self.parity = 0
+        if self.n == 0:
+            self.s[0:1].zero_()
+        self._run(b, iters)
+
     def _run(self, b, iters):
-        if b is not None:
-            if hasattr(b, "numel") and b.numel() < self.n:
-                raise _hm.InvalidError(f"array 'b' has {b.numel()} elements, fewer than n = {self.n}")
-            self.parity = 0
-            b = b if isinstance(b, int) else b.data_ptr()
-            if self.n == 0:
-                self.s[0:1].zero_()
         iters = max(0, int(iters))
         _hm._check(_hm.lib().hipmr_poisson_cg(
             self.nx, self.ny, b, iters, self.x.data_ptr(), self.r.data_ptr(), self.p.data_ptr(),
@@ -96,7 +101,7 @@ class PoissonCG:
 
     def start(self, b):
         """x = 0, r = p = b, r . r = b . b."""
-        self._run(b, 0)
+        self._start(b, 0)
 
     def step(self):
         """One CG iteration (three launches, no host sync)."""
@@ -122,7 +127,7 @@ class PoissonCG:
 
     def solve(self, b, iters):
         """start(b), then `iters` iterations in one native call (2 iters + 2 launches)."""
-        self._run(b, iters)
+        self._start(b, iters)
         return self.x
 
 
