@@ -63,6 +63,10 @@ class PoissonCG:
         # block partials and a second buffer of p, this solver's own
         nbytes = _hm.lib().hipmr_poisson_cg_workspace_bytes(self.nx, self.ny)
         self._ws = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=dev)
+        if stream is not None and self._ws.is_cuda:   # a run may outlive the solver on that stream
+            on = torch.cuda.ExternalStream(stream, self._ws.device) if isinstance(stream, int) else stream
+            for t in (self.x, self.r, self.p, self.q, self.s, self._ws):
+                t.record_stream(on)
 
     @property
     def k(self):
