@@ -5,11 +5,13 @@
 #include <algorithm>
 #include <atomic>
 #include <cctype>
+#include <chrono>
 #include <cstring>
 #include <map>
 #include <memory>
-#include <random>
 #include <unordered_map>
+
+#include <unistd.h>
 
 #include "internal.h"
 
@@ -411,12 +413,15 @@ bool own_shape(const hipmr_launch_config* c) {
     return c && (c->block || c->items_per_thread || c->grid || c->blocks_per_cu);
 }
 
-// A tag for one launch's partials: 48 bits, never 0, from a random start; bit
-// 63 asks the launch not to wait.
+// A tag for one launch's partials: 48 bits, never 0, from a start that differs
+// from process to process (time, process, address; nothing here can throw);
+// bit 63 asks the launch not to wait.
 uint64_t next_tag(const LaunchCfg& cfg) {
     static std::atomic<uint64_t> tag{[] {
-        std::random_device rd;
-        return (uint64_t)rd() << 32 ^ rd();
+        uint64_t z = (uint64_t)std::chrono::system_clock::now().time_since_epoch().count() ^
+                     (uint64_t)getpid() << 40 ^ (uint64_t)(uintptr_t)&no_alloc_now;
+        for (uint64_t m : {0xBF58476D1CE4E5B9ull, 0x94D049BB133111EBull}) z = (z ^ z >> 30) * m;   // spread the bits
+        return z ^ z >> 31;
     }()};
     uint64_t t;
     do t = tag.fetch_add(1) & ((1ull << 48) - 1);
