@@ -268,8 +268,9 @@ hipmr_status hipmr_reduce_compensated(hipmr_handle h, int64_t n, void *const *ar
  *     else every block of it (same grid) derives from the maxima the power of
  *     two s that puts the largest in [1, 2) (exponent clamped to [-126, 126])
  *     and accumulates (map(i) * s)^2 instead.  Its last FP64 step returns
- *     post_scale * sqrt(sum) / s.  Two launches; the data are read once, or
- *     twice where pass 2 is needed.
+ *     post_scale * sqrt(sum) / s.  Two launches (a third folds for more than
+ *     1024 blocks, which only a geometry in cfg asks for); the data are read
+ *     once, or twice where pass 2 is needed.
  *   passes == 1: no scaling, one read; the squares must stay inside the float
  *     range (true for every half or FP8 load: their squares are below 2^32).
  * The first pass's maxima and the scale are kept in the workspace.  Errors:

@@ -483,11 +483,12 @@ hipmr_status stage1_launch(hipmr_kernel* h, KernelSpec spec, LaunchCfg cfg,
         spec.finish = cfg.block == kStage2Block && (size_t)out->grid * sizeof(double) * 4 <= kAmaxOffset &&
                       !may_be_replayed(stream);
     }
+    if (spec.scaled) spec.finish = out->grid <= kNormWordsBlocks;
     out->whole = spec.finish;
     st = variant_function(h, spec, &out->fn, used);
     if (st != HIPMR_OK) return st;
     if (n == 0) return HIPMR_OK;
-    uint64_t tag = spec.finish ? next_tag(cfg) : 0;
+    uint64_t tag = spec.scaled ? 1 | (uint64_t)cfg.no_wait << 63 : spec.finish ? next_tag(cfg) : 0;
     std::vector<void*> params;
     if (h->prog.sig.args.empty()) params.push_back(&head64);   // hipmr_unused
     for (size_t k = 0; k < h->prog.sig.args.size(); ++k) params.push_back(args[k]);
@@ -566,7 +567,8 @@ hipmr_status hipmr_reduce_compensated(hipmr_handle h, int64_t n, void* const* ar
     st = variant_function(h, s2, &fn2, &used);
     if (st != HIPMR_OK) return st;
     set_last_kernels(h, used);
-    void* params2[4] = {&workspace, &r.grid, &post_scale, &out};
+    void* amax = nullptr;
+    void* params2[5] = {&workspace, &r.grid, &post_scale, &amax, &out};
     return launch(fn2, 1, kStage2Block, params2, stream);
 }
 
@@ -595,7 +597,7 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
     // pass 2 (or the only pass): compensated sum of (map * scale)^2; with two
     // passes every block first derives the power-of-two scale from the pass-1
     // maxima; if pass 1's sums stand its block 0 only folds them, else its last
-    // block folds its own
+    // block folds its own (grids too large for that: a third launch folds)
     KernelSpec q1 = comp_spec(KernelKind::CompS1Vector, cfg);
     q1.square = true;
     q1.scaled = two;
@@ -603,11 +605,12 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
     q2.block = kStage2Block;
     q2.ipt = q2.vec = 1;
     q2.norm = true;
+    q2.scaled = two;
     Stage1 r2;
     st = stage1_launch(h, q1, cfg, n, args, workspace, amax, post_scale, out,
                        two || own_shape(cfgp) ? nullptr : &q2, stream, &used, &r2);
     if (st != HIPMR_OK) return st;
-    if (two || r2.whole) {
+    if (r2.whole) {
         set_last_kernels(h, used);
         return HIPMR_OK;
     }
@@ -615,7 +618,7 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
     st = variant_function(h, q2, &fn2, &used);
     if (st != HIPMR_OK) return st;
     set_last_kernels(h, used);
-    void* params2[4] = {&workspace, &r2.grid, &post_scale, &out};
+    void* params2[5] = {&workspace, &r2.grid, &post_scale, &amax, &out};
     return launch(fn2, 1, kStage2Block, params2, stream);
 }
 
@@ -1006,23 +1009,24 @@ hipmr_status hipmr_selftest_compile(int32_t* count) {
                 // precision extension: compensated sum, norm passes, finishers
                 std::vector<KernelSpec> specs;
                 for (KernelKind k : {KernelKind::CompS1Vector, KernelKind::CompS1Scalar}) {
-                    for (int variant = 0; variant < 6; ++variant) {
+                    for (int variant = 0; variant < 7; ++variant) {
                         KernelSpec q = comp_spec(k, cfg);
                         q.finish = variant >= 4;
                         if (k == KernelKind::CompS1Scalar) q.vec = 1;
                         q.square = variant > 0 && variant != 4;
-                        q.scaled = variant == 2;
+                        q.scaled = variant == 2 || variant == 6;
                         q.track = variant == 3;
                         q.exact_runs = !q.square && k == KernelKind::CompS1Vector &&
                                        single_fp8_load(h);
                         specs.push_back(q);
                     }
                 }
-                for (int variant = 0; variant < 2; ++variant) {
+                for (int variant = 0; variant < 3; ++variant) {
                     KernelSpec q = comp_spec(KernelKind::CompS2, cfg);
                     q.block = kStage2Block;
                     q.ipt = q.vec = 1;
                     q.norm = variant > 0;
+                    q.scaled = variant > 1;
                     specs.push_back(q);
                 }
                 for (const KernelSpec& q : specs) {

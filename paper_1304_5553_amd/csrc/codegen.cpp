@@ -821,9 +821,9 @@ __device__ __forceinline__ float hipmr_block_amax(float m) {
 // exponent of the max clamped to [-126, 126], so the largest scaled
 // magnitude lies in [1, 2).  Every block computes it.
 template <int B>
-__device__ __forceinline__ float hipmr_norm_scale(const float* __restrict__ amax) {
+__device__ __forceinline__ float hipmr_norm_scale(const float* __restrict__ amax, int g) {
   float m = 0.0f;
-  for (int k = threadIdx.x; k < (int)gridDim.x; k += B) m = __builtin_elementwise_maximum(m, amax[k]);
+  for (int k = threadIdx.x; k < g; k += B) m = __builtin_elementwise_maximum(m, amax[k]);
   m = hipmr_block_amax<B>(m);
   const bool stands = m == 0.0f || (m >= 0x1p-40f && m <= 0x1p40f);
   float s = 1.0f;
@@ -956,30 +956,14 @@ __device__ __forceinline__ int hipmr_comp_finish(double v, unsigned long long* p
   hipmr_comp_end<B, NORM>(h.f, post, scale, out);
   return -1;
 }
-
-// The second pass's end: every block publishes its partial and counts itself
-// in; the last one folds.  (The first pass's block 0 zeroes the count.)
-template <int B>
-__device__ __forceinline__ void hipmr_norm_finish(double v, double* partial, unsigned* count, double post,
-                                                  double scale, double* __restrict__ out) {
-  __shared__ bool hipmr_last;
-  if (threadIdx.x == 0) {
-    __hip_atomic_store((unsigned long long*)partial + blockIdx.x, __builtin_bit_cast(unsigned long long, v),
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_waitcnt(0);                 // the partial is written before the count says so
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    hipmr_last = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
-  }
-  __syncthreads();
-  if (hipmr_last) hipmr_comp_fold<B, true>(partial, (int)gridDim.x, post, scale, out);
-}
 )HIP";
 
 // Stage 1 of a compensated sum, or of the norm's sum of squares: its first
 // pass (nrm1) sums the unscaled squares and keeps each block's max |map|, its
 // second (nrm2) rescales and sums again only where those squares could have
-// left the float range, and otherwise one block of it folds the first pass's
+// left the float range, its last block folding the partials (the words they
+// travel in are cleared by the first pass, so their tag is a constant, also in
+// a replay), and otherwise one block of it folds the first pass's
 // partials.  Bound: HBM, one read (a pass for the maximum, always a second one
 // for the sum and a fold launch took 81.6 us for 2^27 bfloat16 values, the sums
 // beside the maximum 45.0, without the fold launch 43.4).
@@ -996,9 +980,11 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   const hipmr_idx n = (hipmr_idx)hipmr_n;
   float hipmr_sc = 1.0f, hipmr_m = 0.0f;
   if constexpr (HIPMR_SCALED) {
-    hipmr_sc = hipmr_norm_scale<HIPMR_B>(hipmr_scale_p);
+    hipmr_sc = hipmr_norm_scale<HIPMR_B>(hipmr_scale_p, (int)gridDim.x);
+    if (!@@ONE@@ && blockIdx.x == 0 && threadIdx.x == 0) hipmr_scale_p[@@SCALE_AT@@] = hipmr_sc;   // for the fold
     if (hipmr_sc == 0.0f) {                     // the first pass's sums stand
-      if (blockIdx.x == 0) hipmr_comp_fold<HIPMR_B, true>(hipmr_partial, (int)gridDim.x, hipmr_post, 1.0, hipmr_out);
+      if (@@ONE@@ && blockIdx.x == 0)
+        hipmr_comp_fold<HIPMR_B, true>(hipmr_partial, (int)gridDim.x, hipmr_post, 1.0, hipmr_out);
       return;
     }
   }
@@ -1087,16 +1073,12 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   hipmr_r = hipmr_block_reduce_pair<HIPMR_B>(hipmr_r, [](hipmr_ff a, hipmr_ff b) { return hipmr_ff_add(a, b); });
   const double hipmr_v = __builtin_isfinite(hipmr_r.hi) ? (double)hipmr_r.hi + (double)hipmr_r.lo
                                                         : (double)hipmr_r.hi;
-  unsigned* const hipmr_count = (unsigned*)((char*)hipmr_scale_p + @@COUNT_GAP@@);
-  if constexpr (HIPMR_SCALED) {
-    hipmr_norm_finish<@@BLOCK@@>(hipmr_v, hipmr_partial, hipmr_count, hipmr_post, (double)hipmr_sc, hipmr_out);
-  } else {
-    @@FINISH@@
-  }
+  unsigned long long* const hipmr_words = (unsigned long long*)hipmr_partial + (HIPMR_SCALED || HIPMR_TRACK ? @@WORDS_AT@@ : 0);
+  @@FINISH@@
   if constexpr (HIPMR_TRACK) {
     hipmr_m = hipmr_block_amax<@@BLOCK@@>(hipmr_m);
     if (threadIdx.x == 0) hipmr_scale_p[blockIdx.x] = hipmr_m;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *hipmr_count = 0;
+    if (threadIdx.x < 4 && gridDim.x <= @@WORDS_FOR@@) hipmr_words[blockIdx.x * 4 + threadIdx.x] = 0;
   }
   @@END@@
 }
@@ -1113,9 +1095,11 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   const hipmr_idx n = (hipmr_idx)hipmr_n;
   float hipmr_sc = 1.0f, hipmr_m = 0.0f;
   if constexpr (HIPMR_SCALED) {
-    hipmr_sc = hipmr_norm_scale<@@BLOCK@@>(hipmr_scale_p);
+    hipmr_sc = hipmr_norm_scale<@@BLOCK@@>(hipmr_scale_p, (int)gridDim.x);
+    if (!@@ONE@@ && blockIdx.x == 0 && threadIdx.x == 0) hipmr_scale_p[@@SCALE_AT@@] = hipmr_sc;   // for the fold
     if (hipmr_sc == 0.0f) {                     // the first pass's sums stand
-      if (blockIdx.x == 0) hipmr_comp_fold<@@BLOCK@@, true>(hipmr_partial, (int)gridDim.x, hipmr_post, 1.0, hipmr_out);
+      if (@@ONE@@ && blockIdx.x == 0)
+        hipmr_comp_fold<@@BLOCK@@, true>(hipmr_partial, (int)gridDim.x, hipmr_post, 1.0, hipmr_out);
       return;
     }
   }
@@ -1131,28 +1115,28 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   hipmr_r = hipmr_block_reduce_pair<@@BLOCK@@>(hipmr_r, [](hipmr_ff a, hipmr_ff b) { return hipmr_ff_add(a, b); });
   const double hipmr_v = __builtin_isfinite(hipmr_r.hi) ? (double)hipmr_r.hi + (double)hipmr_r.lo
                                                         : (double)hipmr_r.hi;
-  unsigned* const hipmr_count = (unsigned*)((char*)hipmr_scale_p + @@COUNT_GAP@@);
-  if constexpr (HIPMR_SCALED) {
-    hipmr_norm_finish<@@BLOCK@@>(hipmr_v, hipmr_partial, hipmr_count, hipmr_post, (double)hipmr_sc, hipmr_out);
-  } else {
-    @@FINISH@@
-  }
+  unsigned long long* const hipmr_words = (unsigned long long*)hipmr_partial + (HIPMR_SCALED || HIPMR_TRACK ? @@WORDS_AT@@ : 0);
+  @@FINISH@@
   if constexpr (HIPMR_TRACK) {
     hipmr_m = hipmr_block_amax<@@BLOCK@@>(hipmr_m);
     if (threadIdx.x == 0) hipmr_scale_p[blockIdx.x] = hipmr_m;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *hipmr_count = 0;
+    if (threadIdx.x < 4 && gridDim.x <= @@WORDS_FOR@@) hipmr_words[blockIdx.x * 4 + threadIdx.x] = 0;
   }
   @@END@@
 }
 )HIP";
 
-// Final fold of a compensated sum, or of a norm whose only pass was unscaled.
+// Final fold of a compensated sum or a norm in a launch of its own; after two
+// passes the partials are the second's if there was a scale, else the first's.
 const char* kCompS2 = R"HIP(
 extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 @@KNAME@@(const double* __restrict__ hipmr_partial, int hipmr_g, double hipmr_post,
-          double* __restrict__ hipmr_out)
+          const float* __restrict__ hipmr_scale_p, double* __restrict__ hipmr_out)
 {
-  hipmr_comp_fold<@@BLOCK@@, @@NORM@@>(hipmr_partial, hipmr_g, hipmr_post, 1.0, hipmr_out);
+  float hipmr_sc = 1.0f;
+  if constexpr (@@SCALED@@) hipmr_sc = hipmr_scale_p[@@SCALE_AT@@];
+  hipmr_comp_fold<@@BLOCK@@, @@NORM@@>(hipmr_partial, hipmr_g, hipmr_post, hipmr_sc == 0.0f ? 1.0 : (double)hipmr_sc,
+                                       hipmr_out);
 }
 )HIP";
 
@@ -1910,8 +1894,8 @@ std::string render(const Program& prog, const KernelSpec& spec, std::string* sym
                             : "const unsigned hipmr_b = blockIdx.x;");
     if (comp) {
         replace_all(body, "@@FINISH@@",
-                    spec.finish ? "hipmr_b = hipmr_comp_finish<@@BLOCK@@, HIPMR_SQ>(hipmr_v, (unsigned long long*)hipmr_partial, "
-                                  "hipmr_post, 1.0, hipmr_tag, hipmr_out, hipmr_b, hipmr_f);\n    if (hipmr_b < 0) return;"
+                    spec.finish ? "hipmr_b = hipmr_comp_finish<@@BLOCK@@, HIPMR_SQ>(hipmr_v, hipmr_words, "
+                                  "hipmr_post, (double)hipmr_sc, hipmr_tag, hipmr_out, hipmr_b, hipmr_f);\n    if (hipmr_b < 0) return;"
                                 : "if (threadIdx.x == 0) hipmr_partial[blockIdx.x] = hipmr_v;");
         replace_all(body, "@@END@@", spec.finish ? "}" : "");
     } else {
@@ -1920,6 +1904,7 @@ std::string render(const Program& prog, const KernelSpec& spec, std::string* sym
                                   "hipmr_out, hipmr_tag, hipmr_b, hipmr_f);\n  if (hipmr_b < 0) return;\n  }"
                                 : "if (threadIdx.x == 0) hipmr_partial[blockIdx.x] = hipmr_r;");
     }
+    replace_all(body, "@@ONE@@", spec.finish ? "true" : "false");
     replace_all(body, "@@FPARAMS@@",
                 spec.finish ? ", hipmr_acc* __restrict__ hipmr_out, unsigned long long hipmr_tag" : "");
     replace_all(body, "@@PARAMS@@", params);
@@ -1936,7 +1921,9 @@ std::string render(const Program& prog, const KernelSpec& spec, std::string* sym
     replace_all(body, "@@NORM@@", spec.norm ? "true" : "false");
     replace_all(body, "@@SCALED@@", spec.scaled ? "true" : "false");
     replace_all(body, "@@TRACK@@", spec.track ? "true" : "false");
-    replace_all(body, "@@COUNT_GAP@@", std::to_string(kCountOffset - kAmaxOffset));
+    replace_all(body, "@@WORDS_AT@@", std::to_string(kNormWordsOffset / 8));
+    replace_all(body, "@@SCALE_AT@@", std::to_string(kMaxPartials));
+    replace_all(body, "@@WORDS_FOR@@", std::to_string(kNormWordsBlocks));
     replace_all(body, "@@LDS_SEGS@@", std::to_string(spec.lds_segs));
     replace_all(body, "@@IDX@@", spec.idx64 ? "long long" : "int");
     replace_all(body, "@@BLOCK@@", std::to_string(spec.block));

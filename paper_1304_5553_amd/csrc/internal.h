@@ -42,10 +42,16 @@ constexpr int kStage2Block = 256;
 // reduce workspace layout: [0, 64 KiB) block partials (FP64 or the
 // reduction's type); [64 KiB, 96 KiB) the norm's first-pass partials (max
 // |map| per block, float), kept apart so the second pass can read them while
-// it writes its own; then the count of the second pass's blocks
+// it writes its own; then its scale, and room to spare.  The norm's second pass exchanges its
+// partials within its launch in the upper half of the first 64 KiB, which up
+// to 1024 blocks' first-pass partials leave free (32 bytes per block); larger
+// grids fold in a launch of their own.
 constexpr size_t kAmaxOffset = (size_t)kMaxPartials * 8;
-constexpr size_t kCountOffset = kAmaxOffset + (size_t)kMaxPartials * 4;
-constexpr size_t kWorkspaceBytes = kCountOffset + 256;
+constexpr size_t kNormWordsOffset = kAmaxOffset / 2;
+constexpr int kNormWordsBlocks = 1024;
+constexpr size_t kWorkspaceBytes = kAmaxOffset + (size_t)kMaxPartials * 4 + 256;
+static_assert(kNormWordsBlocks * 8 <= kNormWordsOffset &&
+              kNormWordsOffset + kNormWordsBlocks * 32 <= kAmaxOffset, "the norm's words overlap");
 
 // Words that blocks of one launch exchange are 64 bits, accessed atomically:
 // a workspace that starts off their alignment is used from the next multiple

@@ -91,3 +91,23 @@ def test_one_launch_equals_two(fmt, tdt, n):
                 g.launch(st)
                 torch.cuda.synchronize()
                 assert two.item() == out.item() and out.item() != 0.0
+
+
+@pytest.mark.parametrize("grid", [1, 2, 1024, 1025, 3000])
+@pytest.mark.parametrize("flags", [0, hm.CFG_FORCE_SCALAR, hm.hipmr.CFG_NO_WAIT])
+def test_second_pass_of_any_grid(grid, flags):
+    """Either side of the largest grid that folds in its own launch, from a
+    workspace full of anything, and with the pass needed or not in turn."""
+    dev = need_gpu()
+    n = 1 << 22
+    base = np.random.default_rng(9).uniform(0.5, 1.0, n).astype(np.float32)
+    o = oracle.norm2(base.astype(np.float64))
+    k = hm.compile("x[i]", "float: const float *x")
+    ws = torch.full((hm.reduce_workspace_bytes(k, n),), 255, dtype=torch.uint8, device=dev)
+    first = None
+    for e in (0, 60, 60, -60, 0, 100):
+        x = dev_array((base * np.float32(2.0) ** e).astype(np.float32))
+        g = hm.norm2(k, n, [x], workspace_buf=ws, config={"grid": grid, "block": 64, "flags": flags}).item() / 2.0 ** e
+        assert len(k.last_symbols()) == (2 if grid <= 1024 else 3)
+        first = g if first is None else first
+        assert g == first and abs(g - o) <= 1e-6 * o
