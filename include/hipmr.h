@@ -196,8 +196,8 @@ size_t hipmr_reduce_workspace_bytes(hipmr_handle h, int64_t n);
  *   workspace:  device buffer of at least hipmr_reduce_workspace_bytes(h, n)
  *               bytes (E_WORKSPACE otherwise); it is scratch for block partials,
  *               at any alignment.
- * One launch on stream: one block takes a small n, else the last block folds
- * the others' partials, published in the workspace under a tag of this launch
+ * One launch on stream: the last of its blocks (one takes an n up to its
+ * share) folds the others' partials, published in the workspace under a tag of this launch
  * (nothing there needs clearing; the workspace belongs to one call at a time).
  * Its wait for them is bounded; if it runs out, that block computes all the
  * shares itself, in the same order (the same bits).

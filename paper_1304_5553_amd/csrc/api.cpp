@@ -30,15 +30,7 @@ void chunk_sizes(const Signature& sig, int* narrow, int* wide) {
         }
 }
 
-// Bytes per index of the arrays moved in chunks (at least 1).
-long long chunk_bytes(const Signature& sig) {
-    long long b = 0;
-    for (auto& a : sig.args)
-        if (chunked(a) || a.shifted) b += dtype_size(a.dtype);
-    return std::max(b, 1LL);
-}
-
-// Elements one block may take by itself where that saves a launch: its 16
+// Elements a scan's one tile may take where that saves a launch: its 16
 // waves evaluate a map of c instructions on n elements in n c / 256 clocks, so
 // 65536 elements of a map of plain arithmetic (c of about 10) cost 1 us more
 // than spread over the chip; a map that calls other functions than the
@@ -369,7 +361,6 @@ hipmr_status build_handle(const char* expr, const char* dtypes, const std::strin
     }
     h->default_vec = default_vec_for(h->prog.sig);
     default_stream_shape(h->prog.sig, &h->stream_vec, &h->ew_ipt);
-    h->chunk_bytes = chunk_bytes(h->prog.sig);
     h->one_block = one_block_elements(h->prog.toks);
     if (!h->prog.sig.is_reduce) {
         // build the default variant now so that errors surface at compile time
@@ -698,11 +689,7 @@ hipmr_status hipmr_prepare_reduce_ex(hipmr_handle h, const char* combine, const 
     if (rs != HIPMR_OK) return rs;
     std::vector<KernelSpec> specs = {s1_spec(h, h->prog.info.vectorizable, cfg, false, combine, neutral),
                                      s2_spec(combine, neutral)};
-    if (!cfgp) {
-        specs.push_back(finish_spec(specs[0]));
-        specs.push_back(specs[0]);
-        specs.back().block = kRedOneBlock;
-    }
+    if (!cfgp) specs.push_back(finish_spec(specs[0]));
     std::vector<std::shared_ptr<CodeObject>> built;
     return build_variants(h, specs, &built);
 }
@@ -732,7 +719,6 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
     if (st != HIPMR_OK) return st;
 
     workspace = align_words(workspace);
-    // one block, unless the call chose a geometry
     const bool own = own_shape(cfgp);
     long long n64 = n, head64 = 0;
     int grid = 0;
@@ -743,21 +729,10 @@ hipmr_status hipmr_reduce_ex(hipmr_handle h, const char* map_expr, const char* c
         if (!own) {
             const bool idx64 = n >= (int64_t(1) << 31);
             st = load_family(h, 'r', vector, idx64, cfg, combine, neutral, [&] {
-                std::vector<KernelSpec> v;
-                LaunchCfg c = cfg;
-                for (int block : {kRedBlock, kRedOneBlock}) {
-                    c.block = block;
-                    v.push_back(s1_spec(h, vector, c, idx64, combine, neutral));
-                    if (block == kRedBlock) v.push_back(finish_spec(v.back()));
-                }
-                v.push_back(s2_spec(combine, neutral));
-                return v;
+                const KernelSpec s1 = s1_spec(h, vector, cfg, idx64, combine, neutral);
+                return std::vector<KernelSpec>{s1, finish_spec(s1), s2_spec(combine, neutral)};
             });
             if (st != HIPMR_OK) return st;
-            if (n <= h->one_block && n * h->chunk_bytes <= kRedOneBytes) {
-                cfg.block = kRedOneBlock;
-                cfg.grid = 1;
-            }
         }
         head64 = vector ? head : 0;
         long long units = vector ? (n64 > head64 ? (n64 - head64) / cfg.vec : 0) : n64;

@@ -26,8 +26,7 @@ struct hipmr_kernel {
     int default_vec = 4;          // elements per chunk,
     int stream_vec = 4;           // and of the elementwise kernels and plain reductions
     int ew_ipt = 1;               // elementwise chunks per thread
-    long long chunk_bytes = 1;    // per index, of the arrays moved in chunks
-    long long one_block = 0;      // elements of the map that one block may take by itself
+    long long one_block = 0;      // elements of the map that a scan's one tile may take
     std::mutex mu;
     std::unordered_map<hipmr::KernelSpec, std::shared_ptr<hipmr::CodeObject>, hipmr::KernelSpecHash> variants;
     hipmr::CallKernels last;                         // kernels of the most recent call
@@ -67,13 +66,6 @@ constexpr int kEwBlock = 256, kEwIpt = 1, kEwBlocksPerCu = 1 << 20;
 constexpr int kEwMixedIpt = 2;               // arrays of different element sizes (see default_stream_shape)
 constexpr int kEwScalarBlocksPerCu = 32;     // one-element elementwise kernels
 constexpr int kRedBlock = 256, kRedIpt = 4, kRedBlocksPerCu = 2;
-// A reduction over at most this many bytes is one block's work, in one launch:
-// a dot of 2 x 4096 floats takes 7.8 us per call and 18.0 waited for, against
-// 10.7 and 21.5 in two launches (3.3 us of host time each); of 2 x 65536 floats
-// 8.0 and 20.4 against 10.5 and 20.6; of twice that 9.0 and 23.8 against 10.7
-// and 20.6.
-constexpr int kRedOneBlock = 1024;
-constexpr long long kRedOneBytes = 512 << 10;
 
 hipmr_status resolve_cfg(const hipmr_launch_config* c, int block, int ipt, int vec,
                          int blocks_per_cu, LaunchCfg* out);
