@@ -30,17 +30,13 @@ void chunk_sizes(const Signature& sig, int* narrow, int* wide) {
         }
 }
 
-// Elements a scan's one tile may take where that saves a launch: its 16
-// waves evaluate a map of c instructions on n elements in n c / 256 clocks, so
-// 65536 elements of a map of plain arithmetic (c of about 10) cost 1 us more
-// than spread over the chip; a map that calls other functions than the
-// cheapest may be thirty times as long.
-long long one_block_elements(const std::vector<Token>& t) {
+// Whether a map calls functions other than the cheapest.
+bool calls_functions(const std::vector<Token>& t) {
     static const std::set<std::string> cheap = {"conj", "real", "imag", "fabsf", "fabs", "sqrtf",
                                                 "fmaf", "fmaxf", "fminf"};
     for (size_t k = 0; k + 1 < t.size(); ++k)
-        if (t[k].kind == Token::Ident && t[k + 1].text == "(" && !cheap.count(t[k].text)) return 4096;
-    return 65536;
+        if (t[k].kind == Token::Ident && t[k + 1].text == "(" && !cheap.count(t[k].text)) return true;
+    return false;
 }
 
 // Elements per chunk: 16 bytes of the narrowest array, but 16 bytes of the
@@ -361,7 +357,7 @@ hipmr_status build_handle(const char* expr, const char* dtypes, const std::strin
     }
     h->default_vec = default_vec_for(h->prog.sig);
     default_stream_shape(h->prog.sig, &h->stream_vec, &h->ew_ipt);
-    h->one_block = one_block_elements(h->prog.toks);
+    h->map_calls = calls_functions(h->prog.toks);
     if (!h->prog.sig.is_reduce) {
         // build the default variant now so that errors surface at compile time
         KernelSpec spec;

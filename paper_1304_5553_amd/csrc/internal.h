@@ -26,7 +26,7 @@ struct hipmr_kernel {
     int default_vec = 4;          // elements per chunk,
     int stream_vec = 4;           // and of the elementwise kernels and plain reductions
     int ew_ipt = 1;               // elementwise chunks per thread
-    long long one_block = 0;      // elements of the map that a scan's one tile may take
+    bool map_calls = false;       // the map calls functions other than the cheapest
     std::mutex mu;
     std::unordered_map<hipmr::KernelSpec, std::shared_ptr<hipmr::CodeObject>, hipmr::KernelSpecHash> variants;
     hipmr::CallKernels last;                         // kernels of the most recent call

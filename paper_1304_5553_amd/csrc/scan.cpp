@@ -17,8 +17,11 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cctype>
 #include <mutex>
 #include <new>
+#include <set>
+#include <string>
 #include <vector>
 
 #include "internal.h"
@@ -29,7 +32,8 @@ namespace {
 
 // Tiles and forms by size, from sweeps on MI355X (us per call; float, and
 // int32 -> int64 with half the elements per tile):
-// - one tile of 1024 threads x 8 sub-tiles: one launch instead of two;
+// - one tile of 1024 threads x 8 sub-tiles where it holds all: one launch
+//   instead of two;
 // - totals then rescan while a pass over the tiles is short and the second
 //   read comes out of the caches: 512 x 8 takes 16.0 / 24.7 at n = 2^23 and
 //   34.3 / 49.0 at 2^24, the one-pass form 17.2 / 27.6 and 30.9 / 50.1; every
@@ -41,13 +45,56 @@ namespace {
 //   blocks of 512 threads x 16 sub-tiles (126 registers) fill a compute unit:
 //   0.365 ms at n = 2^28 float and 0.302 ms at 2^27 int64, against 0.384 and
 //   0.328 for 1024 x 8 and 0.398 / 0.364 for 256 x 16 or 512 x 8.
-constexpr int kScanOneBlock = 1024, kScanSmallBlock = 256, kScanBlock = 512;
-constexpr int kScanIpt = 8, kScanPassIpt = 16;
+// A thread holds `per` 32-bit words per sub-tile (its elements of every array
+// and of the result); `most` bounds them where spilling costs more than smaller
+// tiles do: twelve float arrays of 16384 took 134 us in one tile of 1024 x 8,
+// 8.7 in tiles that fit; four arrays 23 and 7.  (Not in the one-pass form,
+// where large tiles are the better ones even so: twelve arrays of 2^24 143 us
+// against 153 with 8 sub-tiles, 156 with 4.)
+struct ScanShape {
+    int block, ipt, most;
+};
+constexpr ScanShape kScanOne = {1024, 8, 80}, kScanSmall = {256, 8, 256}, kScanMid = {512, 8, 128},
+                    kScanPass = {512, 16, 0};
+// A map or a combine that calls functions is expanded for every element of a
+// thread's run: short runs, or the code leaves the instruction cache and the
+// functions' temporaries spill.  expf * sinf of 2^26 floats 153 us with these
+// against 338; powf of 2^17 9.4 against 24.2; a logarithm of a sum of
+// exponentials as the combine, 2^14 floats, 10.5 against 32.5.
+constexpr ScanShape kCallsOne = {512, 2, 0}, kCallsSmall = {256, 2, 0}, kCallsMid = {512, 4, 0},
+                    kCallsPass = {1024, 4, 0};
+constexpr int kScanOwnWords = 128;           // of a geometry the call chose
 constexpr long long kScanSmallTiles = 512, kScanFoldTiles = 768;
 constexpr long long kScanMinTiles = 64000;   // the workspace holds at least this many totals
 constexpr long long kScanBigTile = 16384;    // elements of the largest one-element tile (1024 threads, 16 each)
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
+
+// Bytes per index of the arrays moved in chunks.
+int chunk_bytes(const Signature& sig) {
+    int b = 0;
+    for (auto& a : sig.args)
+        if (chunked(a) || a.shifted) b += dtype_size(a.dtype);
+    return b;
+}
+
+// Whether a combine calls functions that take more than an instruction or two.
+bool combine_calls(const char* combine) {
+    if (canonical_combine(combine) != Combine::Generic) return false;
+    static const std::set<std::string> cheap = {"fabsf", "fabs", "fmaf", "fma", "fmaxf", "fminf", "fmax", "fmin", "max", "min"};
+    std::string word;
+    for (const char* c = combine; *c; ++c) {
+        if (std::isalnum((unsigned char)*c) || *c == '_') {
+            word += *c;
+        } else if (*c == '(' && !word.empty()) {
+            if (!cheap.count(word)) return true;
+            word.clear();
+        } else if (!std::isspace((unsigned char)*c)) {
+            word.clear();
+        }
+    }
+    return false;
+}
 
 KernelSpec scan_spec(bool vector, int mode, const LaunchCfg& cfg, bool idx64, const char* combine,
                      const char* neutral) {
@@ -125,7 +172,10 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
     const size_t rs = (size_t)dtype_size(h->prog.sig.result);
     const int dvec = std::min(h->default_vec, std::max(1, 16 / (int)rs));
     LaunchCfg cfg;
-    st = resolve_cfg(cfgp, kScanBlock, kScanIpt, dvec, 1, &cfg);
+    const bool calls = h->map_calls || combine_calls(combine);
+    const ScanShape &mid_shape = calls ? kCallsMid : kScanMid, &one_shape = calls ? kCallsOne : kScanOne,
+                    &small_shape = calls ? kCallsSmall : kScanSmall, &pass_shape = calls ? kCallsPass : kScanPass;
+    st = resolve_cfg(cfgp, mid_shape.block, mid_shape.ipt, dvec, 1, &cfg);
     if (st != HIPMR_OK) return st;
 
     const long long n64 = n;
@@ -138,22 +188,35 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
         return (n64 - base + tile - 1) / tile;
     };
     const bool own_block = cfgp && cfgp->block, own_ipt = cfgp && cfgp->items_per_thread;
-    auto with = [&](int block, int ipt) {
-        LaunchCfg c = cfg;
-        if (!own_block) c.block = block;
-        if (!own_ipt) c.ipt = ipt;
+    const int per = std::max(1, cfg.vec * ((int)rs + chunk_bytes(h->prog.sig)) / 4);
+    const auto fit = [&](LaunchCfg c, int most) {
+        if (own_block || own_ipt) most = kScanOwnWords;
+        while (most && c.ipt > 1 && c.ipt * per > most) c.ipt /= 2;
         return c;
+    };
+    const auto with = [&](const ScanShape& s) {
+        LaunchCfg c = cfg;
+        if (!own_block) c.block = s.block;
+        if (!own_ipt) c.ipt = s.ipt;
+        return fit(c, s.most);
+    };
+    // the one-pass form's tiles are no smaller than its own, whatever the call
+    // asked for: every tile costs a ticket (12 ns; 2^26 floats in tiles of
+    // 256 x 4 took 219 us, in 64 x 1 772, against 136 in waves of those shapes)
+    const auto with_pass = [&] {
+        LaunchCfg c = with(pass_shape);
+        c.block = std::max(c.block, pass_shape.block);
+        c.ipt = std::max(c.ipt, pass_shape.ipt);
+        return fit(c, pass_shape.most);
     };
     const bool idx64 = n64 >= (int64_t(1) << 31);
     KernelSpec clear;
     clear.kind = KernelKind::ScanClear;
     st = load_family(h, 's', vector, idx64, cfg, combine, neutral, [&] {
-        const LaunchCfg one = with(kScanOneBlock, kScanIpt), small = with(kScanSmallBlock, kScanIpt);
-        const LaunchCfg pass = with(kScanBlock, kScanPassIpt);
-        std::vector<KernelSpec> v = {scan_spec(vector, 0, one, idx64, combine, neutral),
-                                     scan_spec(vector, 3, pass, idx64, combine, neutral), clear};
+        std::vector<KernelSpec> v = {scan_spec(vector, 0, with(one_shape), idx64, combine, neutral),
+                                     scan_spec(vector, 3, with_pass(), idx64, combine, neutral), clear};
         for (int mode : {1, 2})
-            for (const LaunchCfg& c : {small, cfg}) v.push_back(scan_spec(vector, mode, c, idx64, combine, neutral));
+            for (const LaunchCfg& c : {with(small_shape), with(mid_shape)}) v.push_back(scan_spec(vector, mode, c, idx64, combine, neutral));
         return v;
     });
     if (st != HIPMR_OK) return st;
@@ -162,17 +225,18 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
         return fail(HIPMR_E_HIP, "an earlier scan on this device gave up waiting for a tile's total: its workspace "
                                  "was written by another call meanwhile, and its outputs are not the scan");
     int mode = 3;
-    const LaunchCfg one = with(kScanOneBlock, kScanIpt), small = with(kScanSmallBlock, kScanIpt);
-    if (tiles_of(one) == 1 && (own_block || own_ipt || n64 <= h->one_block)) {
+    const LaunchCfg one = with(one_shape), small = with(small_shape), mid = with(mid_shape);
+    if (tiles_of(one) == 1) {
         mode = 0;
         cfg = one;
     } else if (tiles_of(small) <= kScanSmallTiles) {
         mode = 2;
         cfg = small;
-    } else if (tiles_of(cfg) <= kScanFoldTiles) {
+    } else if (tiles_of(mid) <= kScanFoldTiles) {
         mode = 2;
+        cfg = mid;
     } else {
-        cfg = with(kScanBlock, kScanPassIpt);
+        cfg = with_pass();
         // larger tiles where the workspace could not hold every tile's total
         const auto fits = [&] { return state_words(tiles_of(cfg), rs) * 8 <= (long long)workspace_bytes; };
         while (!fits() && cfg.ipt < 16) cfg.ipt = std::min(16, 2 * cfg.ipt);
