@@ -281,8 +281,8 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void *const *args, double po
 
 /* ------------------------------------------------------------------ prefix scan */
 
-/* Bytes of device workspace hipmr_scan needs (the totals of at least 64000
- * tiles, more above 2^30 elements); 0 for an elementwise or invalid handle. */
+/* Bytes of device workspace hipmr_scan needs (the totals of 64000 tiles, the
+ * same for every n); 0 for an elementwise or invalid handle. */
 size_t hipmr_scan_workspace_bytes(hipmr_handle h, int64_t n);
 
 /* Prefix scan of a map: the parallel prefix sums of section "Further
@@ -298,7 +298,9 @@ size_t hipmr_scan_workspace_bytes(hipmr_handle h, int64_t n);
  *   cfg:        NULL or a geometry (block, items_per_thread, vec, flags).
  * At most two launches on `stream`, by size: one tile alone; tile totals and
  * a rescan from them; or a clear of the workspace's counters and one pass in
- * which tiles publish their totals and wait for their predecessors'.  The
+ * which tiles publish their totals and wait for their predecessors' (again for
+ * every further part, where the workspace holds the totals of a part of the
+ * tiles: 64000, by default 2^31 floats).  The
  * workspace belongs to one call at a time; if another writes it meanwhile a
  * bounded wait may run out: the outputs whose sums are then not known are NaN
  * (0 for whole numbers), and the next hipmr_scan on the device returns E_HIP.  The order of combination depends

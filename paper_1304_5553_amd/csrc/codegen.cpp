@@ -1501,7 +1501,10 @@ __device__ __forceinline__ hipmr_acc hipmr_lane_value(hipmr_acc v, int l) {
 // so a single 64-bit load tells whether a word is there and what it holds, and
 // no fence is needed.  Accesses are
 // device-scope (the L2s of the eight dies are not coherent otherwise).  Word 0
-// counts tickets, word 1 is set when a wait has been given up.
+// counts tickets, word 1 is set when a wait has been given up; words 2 and 3
+// carry the fold of all before from one launch to the next where a workspace
+// holds the totals of a part of the tiles at a time (the launches take turns),
+// word 4 whether it is known.
 constexpr int HIPMR_S = (int)sizeof(hipmr_acc) / 4, HIPMR_STATE0 = 16;
 
 __device__ __forceinline__ hipmr_u64 hipmr_peek(const hipmr_u64* p) {
@@ -1593,13 +1596,14 @@ template <typename T> __device__ __forceinline__ T hipmr_unknown() {
 }
 )HIP";
 
-// Clears the ticket counter and the published totals of a MODE 3 launch.
+// Clears the ticket counter and the published totals of a MODE 3 launch (not
+// what the launch before it handed on).
 const char* kScanClear = R"HIP(
 extern "C" __global__ void __launch_bounds__(256)
 @@KNAME@@(unsigned long long* __restrict__ hipmr_state, int hipmr_words)
 {
   const int k = blockIdx.x * 256 + threadIdx.x;
-  if (k < hipmr_words) hipmr_state[k] = 0ull;
+  if (k < hipmr_words && (k < 2 || k > 4)) hipmr_state[k] = 0ull;
 }
 )HIP";
 
@@ -1609,7 +1613,8 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
           void* __restrict__ hipmr_state, hipmr_acc* __restrict__ hipmr_out, int hipmr_flags,
           unsigned* __restrict__ hipmr_gave_up)
 {
-  const bool hipmr_exclusive = hipmr_flags & 1;      // bit 1: no wait
+  // bit 1: no wait; bits 2 and 3: a launch went before, one comes after; bit 4: its turn
+  const bool hipmr_exclusive = hipmr_flags & 1;
   typedef @@IDX@@ hipmr_idx;
   constexpr int HIPMR_B = @@BLOCK@@, HIPMR_U = @@IPT@@, HIPMR_V = @@VEC@@, HIPMR_MODE = @@MODE@@;
   constexpr int HIPMR_W = HIPMR_B / 64;
@@ -1718,8 +1723,17 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   if constexpr (HIPMR_MODE == 3) {
     if (hipmr_w == 0) {
       hipmr_wait hipmr_wt8 = {(hipmr_u64*)hipmr_state, hipmr_flags & 2 ? 1u : 1u << 22, false};
-      const hipmr_acc hipmr_b = hipmr_before(hipmr_tile, hipmr_tiles, hipmr_lane_value(hipmr_ws, HIPMR_W - 1),
-                                             hipmr_wt8, hipmr_neutral, hipmr_lane);
+      const hipmr_acc hipmr_own = hipmr_lane_value(hipmr_ws, HIPMR_W - 1);
+      hipmr_acc hipmr_b = hipmr_before(hipmr_tile, hipmr_tiles, hipmr_own, hipmr_wt8, hipmr_neutral, hipmr_lane);
+      const int hipmr_turn = hipmr_flags >> 4 & 1;
+      if (hipmr_flags & 4) {
+        hipmr_b = hipmr_combine(hipmr_from_bits<hipmr_acc>(hipmr_wt8.state[3 - hipmr_turn]), hipmr_b);
+        if (hipmr_wt8.state[4]) hipmr_wt8.lost = true;
+      }
+      if ((hipmr_flags & 8) && hipmr_tile == hipmr_tiles - 1 && hipmr_lane == 0) {
+        hipmr_wt8.state[2 + hipmr_turn] = hipmr_to_bits(hipmr_combine(hipmr_b, hipmr_own));
+        hipmr_wt8.state[4] = hipmr_wt8.lost;
+      }
       if (hipmr_lane == 0) {
         hipmr_pre_lds = hipmr_b;
         hipmr_lost_lds = hipmr_wt8.lost;

@@ -66,7 +66,6 @@ constexpr ScanShape kCallsOne = {512, 2, 0}, kCallsSmall = {256, 2, 0}, kCallsMi
 constexpr int kScanOwnWords = 128;           // of a geometry the call chose
 constexpr long long kScanSmallTiles = 512, kScanFoldTiles = 768;
 constexpr long long kScanMinTiles = 64000;   // the workspace holds at least this many totals
-constexpr long long kScanBigTile = 16384;    // elements of the largest one-element tile (1024 threads, 16 each)
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
@@ -148,7 +147,7 @@ extern "C" {
 size_t hipmr_scan_workspace_bytes(hipmr_handle h, int64_t n) {
     if (!h || !h->prog.sig.is_reduce || n < 0) return 0;
     const size_t rs = (size_t)dtype_size(h->prog.sig.result);
-    return align256((size_t)state_words(std::max<long long>(kScanMinTiles, n / kScanBigTile + 2), rs) * 8);
+    return align256((size_t)state_words(kScanMinTiles, rs) * 8);
 }
 
 hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral, int64_t n,
@@ -237,15 +236,14 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
         cfg = mid;
     } else {
         cfg = with_pass();
-        // larger tiles where the workspace could not hold every tile's total
-        const auto fits = [&] { return state_words(tiles_of(cfg), rs) * 8 <= (long long)workspace_bytes; };
-        while (!fits() && cfg.ipt < 16) cfg.ipt = std::min(16, 2 * cfg.ipt);
-        while (!fits() && cfg.block < 1024) cfg.block = std::min(1024, 2 * cfg.block);
-        if (!fits()) return fail(HIPMR_E_WORKSPACE, "workspace too small for the scan's tile totals");
     }
     if (mode == 3 && !gave_up) gave_up = gave_up_word(true, stream);
-    const long long tiles64 = tiles_of(cfg);
-    int tiles = (int)tiles64, flags = exclusive | (cfg.no_wait ? 2 : 0), words = (int)state_words(tiles64, rs);
+    const long long all = tiles_of(cfg), tile = (long long)cfg.block * cfg.vec * cfg.ipt;
+    // tiles whose totals the workspace holds, which one launch takes (below 2^32 threads)
+    const long long room = ((long long)(workspace_bytes / 8) - 16) / (long long)(rs / 4);
+    const long long at_once = std::min(std::max(room * 4096 / (4096 + 64 + 1) - 2, 1LL), ((1LL << 32) - 1) / cfg.block);
+    int tiles = (int)std::min(all, mode == 3 ? at_once : all);
+    int flags = exclusive | (cfg.no_wait ? 2 : 0), words = 0;
 
     CallKernels used;
     void *f_first = nullptr, *f_scan = nullptr;
@@ -264,14 +262,20 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
     for (size_t k = 0; k < h->prog.sig.args.size(); ++k) p.push_back(args[k]);
     long long n_arg = n64;
     p.insert(p.end(), {(void*)&n_arg, (void*)&base, (void*)&tiles, (void*)&workspace, (void*)&out, (void*)&flags, (void*)&gave_up});
-    if (mode == 2) {
-        st = launch(f_first, (unsigned)tiles, (unsigned)cfg.block, p.data(), stream);
-    } else if (mode == 3) {
+    if (mode == 2) st = launch(f_first, (unsigned)tiles, (unsigned)cfg.block, p.data(), stream);
+    if (mode != 3) return st != HIPMR_OK ? st : launch(f_scan, (unsigned)tiles, (unsigned)cfg.block, p.data(), stream);
+    for (long long done = 0; done < all && st == HIPMR_OK; done += at_once) {
+        tiles = (int)std::min(all - done, at_once);
+        words = (int)state_words(tiles, rs);
         void* pz[2] = {&workspace, &words};
         st = launch(f_first, (unsigned)((words + 255) / 256), 256, pz, stream);
+        if (st != HIPMR_OK) break;
+        const int turn = (int)(done / at_once & 1);
+        flags = (flags & 3) | (done > 0 ? 4 : 0) | (done + tiles < all ? 8 : 0) | turn << 4;
+        st = launch(f_scan, (unsigned)tiles, (unsigned)cfg.block, p.data(), stream);
+        base += tiles * tile;
     }
-    if (st != HIPMR_OK) return st;
-    return launch(f_scan, (unsigned)tiles, (unsigned)cfg.block, p.data(), stream);
+    return st;
 }
 
 }  // extern "C"

@@ -89,3 +89,32 @@ def test_more_than_64_supergroups_of_tiles(dev):
         part = torch.cumsum(k[lo:lo + (1 << 28)], 0, dtype=torch.int32) + carry
         assert torch.equal(out[lo:lo + (1 << 28)], part), lo
         carry = part[-1].item()
+
+
+@pytest.mark.parametrize("exclusive", [False, True])
+@pytest.mark.parametrize("flags", [0, hm.hipmr.CFG_NO_WAIT])
+def test_parts_of_the_tiles_at_a_time(dev, exclusive, flags):
+    """A workspace asked for at n = 1 takes any n: three launches' worth of
+    tiles, each from what the one before handed on."""
+    n = 2 * 64000 * 8192 + 12345
+    k = torch.randint(-9, 9, (n,), dtype=torch.int8, device=dev)
+    h = hm.compile("k[i]", "int: const char *k", name="scshape")
+    ws = torch.full((hm.scan_workspace_bytes(h, 1),), 255, dtype=torch.uint8, device=dev)
+    assert hm.scan_workspace_bytes(h, n) == ws.numel()
+    out = torch.empty(n, dtype=torch.int32, device=dev)
+    hm.scan(h, "a+b", "0", n, [k], out, exclusive=exclusive, workspace_buf=ws, config={**TINY, "flags": flags})
+    torch.cuda.synchronize()
+    carry, bad = 0, 0
+    for lo in range(0, n, 1 << 28):
+        v = k[lo:lo + (1 << 28)]
+        part = torch.cumsum(v, 0, dtype=torch.int32) + carry
+        carry = part[-1].item()
+        got = out[lo:lo + (1 << 28)]
+        wrong = got != (part - v if exclusive else part)
+        bad += wrong.sum().item()
+        assert (got[wrong] == 0).all()                # only sums that are not known, and said so
+    if flags:
+        with pytest.raises(hm.HipError, match="gave up"):
+            hm.scan(h, "a+b", "0", 10, [k], out)
+    else:
+        assert bad == 0
