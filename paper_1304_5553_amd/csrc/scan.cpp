@@ -211,7 +211,8 @@ hipmr_status hipmr_scan(hipmr_handle h, const char* combine, const char* neutral
     const bool idx64 = n64 >= (int64_t(1) << 31);
     KernelSpec clear;
     clear.kind = KernelKind::ScanClear;
-    st = load_family(h, 's', vector, idx64, cfg, combine, neutral, [&] {
+    const char family = 's' + (own_block ? 1 : 0) + (own_ipt ? 2 : 0);   // the kernels depend on what is the call's own
+    st = load_family(h, family, vector, idx64, cfg, combine, neutral, [&] {
         std::vector<KernelSpec> v = {scan_spec(vector, 0, with(one_shape), idx64, combine, neutral),
                                      scan_spec(vector, 3, with_pass(), idx64, combine, neutral), clear};
         for (int mode : {1, 2})

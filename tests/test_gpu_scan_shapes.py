@@ -118,3 +118,31 @@ def test_parts_of_the_tiles_at_a_time(dev, exclusive, flags):
             hm.scan(h, "a+b", "0", 10, [k], out)
     else:
         assert bad == 0
+
+
+@pytest.mark.parametrize("first,second", [({"block": 512}, None), (None, {"block": 512}),
+                                          ({"items_per_thread": 8}, None), (None, {"items_per_thread": 8})])
+@pytest.mark.parametrize("captured", [100, 100003, 1 << 23])
+def test_capture_after_another_geometry(dev, first, second, captured):
+    """A call that names what another leaves open (512 threads, 8 runs) has
+    kernels of its own: after each has run once, at one size, a capture of the
+    second at any size finds all it needs."""
+    n = 1 << 23
+    k = torch.randint(-9, 9, (n,), dtype=torch.int32, device=dev)
+    tag = f"{'d' if first is None else list(first)[0][0]}{captured}"
+    h = hm.compile("k[i]", "long: const int *k", name=f"scfam{tag}")
+    out = torch.zeros(n, dtype=torch.int64, device=dev)
+    ws = torch.empty(hm.scan_workspace_bytes(h, n), dtype=torch.uint8, device=dev)
+    st = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for cfg in (first, second):
+        hm.scan(h, "a+b", "0", 300007, [k], out, workspace_buf=ws, stream=st, config=cfg)
+    g = hm.Graph()
+    with g.capture(st):
+        hm.scan(h, "a+b", "0", captured, [k], out, workspace_buf=ws, stream=st, config=second)
+    for _ in range(3):
+        out.zero_()
+        torch.cuda.synchronize()
+        g.launch(st)
+        torch.cuda.synchronize()
+        assert torch.equal(out[:captured], torch.cumsum(k[:captured], 0, dtype=torch.int64))
