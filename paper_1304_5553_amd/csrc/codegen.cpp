@@ -1173,9 +1173,14 @@ __device__ __forceinline__ int hipmr_seg_tiles(long long a, long long b, long lo
 }
 
 // The tile table: tiles per segment and their exclusive prefix, by one block
-// of B threads, in rounds of B * R segments: a wave takes 64 R consecutive
-// ones, 64 per step (coalesced; all of a round's offsets are loaded before any
-// is used), so a round costs one trip to memory and two barriers.  Counts are
+// of B threads, in rounds of B * R segments: a thread takes R consecutive ones
+// (all of a round's offsets are loaded before any is used), so a round costs
+// one trip to memory, two barriers and one wave scan per R segments.  Every
+// block of the tile kernel plans for itself, so the instructions count as well:
+// a scan per 64 segments over coalesced loads took 46.4 us where this takes
+// 41.1 (8191 segments of 2^24 floats, 256 threads x 8 blocks per compute unit),
+// and 21.8 against 20.8 in the default geometry; R = 8 is level there and costs
+// the planning launch 24.1 against 22.4.  Counts are
 // summed in 64 bits and every entry is capped at the tile capacity of the
 // workspace, so offsets that describe more tiles than it holds (overlapping
 // segments) can never send a later kernel past it.  The table goes to `lds`
@@ -1189,37 +1194,34 @@ __device__ void hipmr_seg_plan(const long long* __restrict__ off, int nseg, long
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   long long carry = 0;                           // tiles of the earlier rounds, in every thread
   for (int base = 0; base < nseg; base += B * R) {
-    const int s0 = base + w * (64 * R) + l;
-    long long o0[R], o1[R];
+    const int s0 = base + (int)threadIdx.x * R;
+    long long o[R + 1];
+#pragma unroll
+    for (int j = 0; j <= R; ++j) o[j] = s0 + j <= nseg ? off[s0 + j] : 0;
+    long long t[R], sum = 0;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-      o0[j] = s0 + 64 * j < nseg ? off[s0 + 64 * j] : 0;
-      o1[j] = s0 + 64 * j < nseg ? off[s0 + 64 * j + 1] : 0;
-    }
-    long long x[R], sum = 0;                     // exclusive in the wave's run
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      long long t = 0;
-      if (s0 + 64 * j < nseg) {
+      t[j] = 0;
+      if (s0 + j < nseg) {
         long long a, b, ab;
-        hipmr_seg_clamp(o0[j], o1[j], total, head, V, a, b, ab);
-        t = hipmr_seg_tiles(a, b, ab, T);
+        hipmr_seg_clamp(o[j], o[j + 1], total, head, V, a, b, ab);
+        t[j] = hipmr_seg_tiles(a, b, ab, T);
       }
-      const long long incl = hipmr_dpp_scan(t, 0LL, hipmr_plus);
-      x[j] = sum + incl - t;
-      sum += __shfl(incl, 63, 64);
+      sum += t[j];
     }
-    if (l == 0) hipmr_wsum[w] = sum;
+    const long long incl = hipmr_dpp_scan(sum, 0LL, hipmr_plus);
+    if (l == 63) hipmr_wsum[w] = incl;
     __syncthreads();
     const long long v = hipmr_dpp_scan(l < B / 64 ? hipmr_wsum[l] : 0LL, 0LL, hipmr_plus);
-    const long long before = carry + (w > 0 ? __shfl(v, w - 1, 64) : 0LL);
+    long long run = carry + (w > 0 ? __shfl(v, w - 1, 64) : 0LL) + incl - sum;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-      if (s0 + 64 * j < nseg) {
-        const int e = (int)(before + x[j] < cap ? before + x[j] : cap);
-        if (lds) lds[s0 + 64 * j] = e;
-        if (glob) glob[s0 + 64 * j] = e;
+      if (s0 + j < nseg) {
+        const int e = (int)(run < cap ? run : cap);
+        if (lds) lds[s0 + j] = e;
+        if (glob) glob[s0 + j] = e;
       }
+      run += t[j];
     }
     carry += __shfl(v, B / 64 - 1, 64);
     __syncthreads();                             // hipmr_wsum is written again; the table is read next
@@ -1240,7 +1242,7 @@ extern "C" __global__ void __launch_bounds__(1024)
 @@KNAME@@(const long long* __restrict__ hipmr_off, int hipmr_nseg, long long hipmr_total,
           long long hipmr_head, int* __restrict__ hipmr_tile_start, long long hipmr_cap)
 {
-  hipmr_seg_plan<1024, 8>(hipmr_off, hipmr_nseg, hipmr_total, hipmr_head, @@VEC@@,
+  hipmr_seg_plan<1024, 4>(hipmr_off, hipmr_nseg, hipmr_total, hipmr_head, @@VEC@@,
                        64LL * @@VEC@@ * @@IPT@@, hipmr_cap, nullptr, hipmr_tile_start);
 }
 )HIP";
@@ -1286,7 +1288,7 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
   if constexpr (HIPMR_LDS_SEGS > 0) {
     __shared__ int hipmr_ts_lds[HIPMR_LDS_SEGS + 1];
     if (hipmr_nseg > HIPMR_LDS_SEGS) return;
-    constexpr int HIPMR_R = HIPMR_LDS_SEGS < HIPMR_B ? 1 : HIPMR_LDS_SEGS >= 8 * HIPMR_B ? 8 : (HIPMR_LDS_SEGS + 1) / HIPMR_B;
+    constexpr int HIPMR_R = HIPMR_LDS_SEGS < HIPMR_B ? 1 : HIPMR_LDS_SEGS >= 4 * HIPMR_B ? 4 : (HIPMR_LDS_SEGS + 1) / HIPMR_B;
     hipmr_seg_plan<HIPMR_B, HIPMR_R>(hipmr_offsets, hipmr_nseg, hipmr_total, hipmr_head, HIPMR_V, HIPMR_T,
                             hipmr_cap, hipmr_ts_lds, blockIdx.x == 0 ? hipmr_tile_start : nullptr);
     hipmr_tab = hipmr_ts_lds;
