@@ -109,33 +109,43 @@ std::shared_ptr<CodeObject> find_variant(hipmr_kernel* h, const KernelSpec& spec
     return it == h->variants.end() ? nullptr : it->second;
 }
 
-hipmr_status get_variant(hipmr_kernel* h, const KernelSpec& spec, std::shared_ptr<CodeObject>* out) {
-    if (h->prog.sig.result == DT_C64 && !spec.combine.empty() &&
-        canonical_combine(spec.combine) != Combine::Sum && canonical_combine(spec.combine) != Combine::Generic)
-        return fail(HIPMR_E_UNSUPPORTED, "complex values have no order: reduce them with a sum");
-    if ((*out = find_variant(h, spec))) return HIPMR_OK;
+// Variants of several specs; those not built yet are built as one program.
+hipmr_status build_variants(hipmr_kernel* h, const std::vector<KernelSpec>& specs,
+                            std::vector<std::shared_ptr<CodeObject>>* out) {
+    out->assign(specs.size(), nullptr);
+    std::vector<KernelSpec> missing;
+    for (size_t k = 0; k < specs.size(); ++k) {
+        const std::string& combine = specs[k].combine;
+        if (h->prog.sig.result == DT_C64 && !combine.empty() && canonical_combine(combine) != Combine::Sum &&
+            canonical_combine(combine) != Combine::Generic)
+            return fail(HIPMR_E_UNSUPPORTED, "complex values have no order: reduce them with a sum");
+        if (!((*out)[k] = find_variant(h, specs[k])) &&
+            std::find(missing.begin(), missing.end(), specs[k]) == missing.end())
+            missing.push_back(specs[k]);
+    }
+    if (missing.empty()) return HIPMR_OK;
     if (no_alloc_now())
         return fail(HIPMR_E_INVALID, "this kernel variant has not been built for the handle: run the "
                                      "allocating entry point once with the same arguments first");
-    std::string symbol;
-    std::string src = render(h->prog, spec, &symbol);
+    std::vector<std::string> symbols;
+    const std::string src = render(h->prog, missing, &symbols);
     hipmr_status st;
-    auto co = get_or_build(src, symbol, &st);
-    if (!co) return st;
-    std::lock_guard<std::mutex> lk(h->mu);
-    *out = h->variants.emplace(spec, co).first->second;    // another thread's, if it was first
+    const auto built = get_or_build(src, symbols, &st);
+    if (built.empty()) return st;
+    {
+        std::lock_guard<std::mutex> lk(h->mu);
+        for (size_t k = 0; k < missing.size(); ++k) h->variants.emplace(missing[k], built[k]);   // or another thread's
+    }
+    for (size_t k = 0; k < specs.size(); ++k) (*out)[k] = find_variant(h, specs[k]);
     return HIPMR_OK;
 }
 
-// Variants of several specs; those not built yet are built concurrently.
-hipmr_status build_variants(hipmr_kernel* h, const std::vector<KernelSpec>& specs,
-                            std::vector<std::shared_ptr<CodeObject>>* out) {
-    out->resize(specs.size());
-    std::vector<std::function<hipmr_status()>> jobs;
-    for (size_t k = 0; k < specs.size(); ++k)
-        if (!((*out)[k] = find_variant(h, specs[k])))
-            jobs.push_back([&, k] { return get_variant(h, specs[k], &(*out)[k]); });
-    return run_concurrently(jobs);
+hipmr_status get_variant(hipmr_kernel* h, const KernelSpec& spec, std::shared_ptr<CodeObject>* out) {
+    if ((*out = find_variant(h, spec))) return HIPMR_OK;
+    std::vector<std::shared_ptr<CodeObject>> built;
+    hipmr_status st = build_variants(h, {spec}, &built);
+    if (st == HIPMR_OK) *out = built[0];
+    return st;
 }
 
 // Function of a variant on the current device; adds it to *used.
@@ -838,8 +848,8 @@ hipmr_status hipmr_get_kernel_source(hipmr_handle h, int32_t kind, const char* c
         spec.ipt = cfg.ipt;
         spec.vec = kind == 0 ? cfg.vec : 1;
     }
-    std::string sym;
-    std::string src = render(h->prog, spec, &sym);
+    std::vector<std::string> symbols;
+    std::string src = render(h->prog, {spec}, &symbols);
     if (len) *len = src.size();
     if (buf && cap) {
         size_t c = std::min(cap - 1, src.size());

@@ -21,8 +21,7 @@
 //            and an LDS tree across the block's waves -> one partial per block;
 //   rs1_sca  one element per step, same tree;
 //   rs2      one block folds the G partials in a fixed order -> *out.
-#include <cstdio>
-#include <sstream>
+#include <algorithm>
 
 #include "common.h"
 #include "internal.h"
@@ -1247,13 +1246,8 @@ extern "C" __global__ void __launch_bounds__(1024)
 }
 )HIP";
 
-// Persistent stage 1: waves take tiles t = wave, wave + nwaves, ...  (With
-// the table in LDS this is also the planner: no separate planning launch.)
-// Per tile, every load is issued before any result is used: the head and
-// tail elements, then the body chunks; the next tile's segment is found (in
-// the table) and its offsets fetched while they are in flight.  The wave's
-// fold is a DPP scan whose last lane holds the tile partial.
-const char* kSegS1 = R"HIP(
+// the fold of a wave's values, in lane order (stage 1)
+const char* kSegFold = R"HIP(
 __device__ __forceinline__ hipmr_acc hipmr_wave_total(hipmr_acc v, hipmr_acc e, int lane) {
   if constexpr (sizeof(hipmr_acc) == 4 || sizeof(hipmr_acc) == 8) {
     return hipmr_dpp_scan(v, e, [](hipmr_acc a, hipmr_acc b) { return hipmr_combine(a, b); });
@@ -1266,7 +1260,15 @@ __device__ __forceinline__ hipmr_acc hipmr_wave_total(hipmr_acc v, hipmr_acc e, 
     return v;
   }
 }
+)HIP";
 
+// Persistent stage 1: waves take tiles t = wave, wave + nwaves, ...  (With
+// the table in LDS this is also the planner: no separate planning launch.)
+// Per tile, every load is issued before any result is used: the head and
+// tail elements, then the body chunks; the next tile's segment is found (in
+// the table) and its offsets fetched while they are in flight.  The wave's
+// fold is a DPP scan whose last lane holds the tile partial.
+const char* kSegS1 = R"HIP(
 extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 @@KNAME@@(@@PARAMS@@, long long hipmr_total, long long hipmr_head,
           const long long* __restrict__ hipmr_offsets, int hipmr_nseg,
@@ -1796,11 +1798,14 @@ std::string combine_body(DType r, const KernelSpec& spec) {
     }
 }
 
-}  // namespace
+// What a kernel's source is made of: the helpers it needs, in order, and the
+// kernel itself.
+struct Source {
+    std::vector<std::string> parts;
+    std::string body, symbol;
+};
 
-const char* device_prelude() { return kPrelude; }
-
-std::string render(const Program& prog, const KernelSpec& spec, std::string* symbol) {
+Source render_parts(const Program& prog, const KernelSpec& spec) {
     const char* tmpl = nullptr;
     const char* tag = "";
     bool reduce = false;
@@ -1948,33 +1953,52 @@ std::string render(const Program& prog, const KernelSpec& spec, std::string* sym
     replace_all(body, "@@NTL@@", spec.nt_loads ? "true" : "false");
     replace_all(body, "@@NTS@@", spec.nt_stores ? "true" : "false");
 
-    std::ostringstream src;
-    src << "// generated by hipmr: " << tag << " kernel of \"" << prog.name << "\"\n";
-    src << kPrelude;
-    std::string cbody;
+    Source src;
+    std::vector<std::string>& parts = src.parts;
+    parts.push_back(kPrelude);
     if (reduce) {
-        cbody = combine_body(acc, spec);
-        src << "typedef " << dtype_device_name(acc) << " hipmr_acc;\n";
-        src << "__device__ __forceinline__ hipmr_acc hipmr_combine(hipmr_acc a, hipmr_acc b) "
-               "{ return (hipmr_acc)(" << cbody << "); }\n";
-        src << kReduceHelpers;
-        if (spec.finish) src << kTagged << kRedFinish;
+        parts.push_back(std::string("typedef ") + dtype_device_name(acc) + " hipmr_acc;\n"
+                        "__device__ __forceinline__ hipmr_acc hipmr_combine(hipmr_acc a, hipmr_acc b) "
+                        "{ return (hipmr_acc)(" + combine_body(acc, spec) + "); }\n");
+        parts.push_back(kReduceHelpers);
+        if (spec.finish) parts.insert(parts.end(), {kTagged, kRedFinish});
     }
-    if (comp) src << kTagged << kCompHelpers;
-    if (seg || scan) src << kDppHelpers;
-    if (seg) src << kSegHelpers;
-    if (scan) src << kScanHelpers;
-    if (shifts) src << kShiftHelpers;
-    if (spec.unaligned) src << kUnalignedHelpers;
+    if (comp) parts.insert(parts.end(), {kTagged, kCompHelpers});
+    if (seg || scan) parts.push_back(kDppHelpers);
+    if (seg) parts.push_back(kSegHelpers);
+    if (spec.kind == KernelKind::SegS1) parts.push_back(kSegFold);
+    if (scan) parts.push_back(kScanHelpers);
+    if (shifts) parts.push_back(kShiftHelpers);
+    if (spec.unaligned) parts.push_back(kUnalignedHelpers);
     // the symbol carries a hash of the whole source (prelude and helpers
     // included), so any change to the generated code renames the kernel
-    src << body;
-    std::string text = src.str();
-    std::string key = sha256_hex(text.data(), text.size());
-    std::string sym = prog.name + "_" + tag + "_" + key.substr(0, 8);
-    replace_all(text, "@@KNAME@@", sym);
-    if (symbol) *symbol = sym;
-    return text;
+    std::string text;
+    for (const std::string& p : parts) text += p;
+    text += body;
+    src.symbol = prog.name + "_" + tag + "_" + sha256_hex(text.data(), text.size()).substr(0, 8);
+    replace_all(body, "@@KNAME@@", src.symbol);
+    src.body = "// generated by hipmr: " + std::string(tag) + " kernel of \"" + prog.name + "\"\n" + body;
+    return src;
 }
+
+}  // namespace
+
+std::string render(const Program& prog, const std::vector<KernelSpec>& specs, std::vector<std::string>* symbols) {
+    std::vector<std::string> parts;
+    std::string bodies;
+    symbols->clear();
+    for (const KernelSpec& spec : specs) {
+        Source s = render_parts(prog, spec);
+        for (std::string& p : s.parts)       // a helper needs only helpers that every kernel with it names before it
+            if (std::find(parts.begin(), parts.end(), p) == parts.end()) parts.push_back(std::move(p));
+        symbols->push_back(s.symbol);
+        bodies += s.body;
+    }
+    std::string text;
+    for (const std::string& p : parts) text += p;
+    return text + bodies;
+}
+
+const char* device_prelude() { return kPrelude; }
 
 }  // namespace hipmr

@@ -180,14 +180,21 @@ struct Program {                 // everything codegen needs about one handle
 // loads and stores).
 const char* device_prelude();
 
-// Renders the full device source (prelude + one kernel) and its symbol name.
-std::string render(const Program& prog, const KernelSpec& spec, std::string* symbol);
+// Renders the full device source (prelude, helpers, one kernel per spec) and
+// the kernels' symbol names.
+std::string render(const Program& prog, const std::vector<KernelSpec>& specs, std::vector<std::string>* symbols);
 
 // ---------------------------------------------------------------- RTC cache
-struct CodeObject;   // opaque: compiled image + per-device modules/functions
+struct CodeObject;   // opaque: one kernel of a compiled image, its functions per device
 
-// Compiles (or loads from the memory / disk cache) a source; never touches
-// the GPU.  Returns nullptr with last_error set on failure.
+// Compiles (or loads from the memory / disk cache) a source of several kernels;
+// never touches the GPU.  Empty with last_error set on failure.  A program
+// costs its fixed 0.1 s and more once, however many kernels it holds, and
+// programs do not compile side by side.
+std::vector<std::shared_ptr<CodeObject>> get_or_build(const std::string& source,
+                                                      const std::vector<std::string>& symbols,
+                                                      hipmr_status* status);
+// the same for a source's one kernel (nullptr on failure)
 std::shared_ptr<CodeObject> get_or_build(const std::string& source, const std::string& symbol,
                                          hipmr_status* status);
 

@@ -73,7 +73,7 @@ hipmr_status get_variant(hipmr_kernel* h, const KernelSpec& spec, std::shared_pt
 hipmr_status variant_function(hipmr_kernel* h, const KernelSpec& spec, void** fn,
                               CallKernels* used);
 void set_last_kernels(hipmr_kernel* h, const CallKernels& used);
-// Builds (concurrently) and loads every kernel that `op` may use on this
+// Builds (as one program) and loads every kernel that `op` may use on this
 // device at any size, the first time it runs there, so that a later capture
 // finds them whatever its size.  Nothing is loaded during a capture.
 hipmr_status load_family(hipmr_kernel* h, char op, bool vector, bool idx64, const LaunchCfg& cfg,

@@ -34,19 +34,22 @@ namespace hipmr {
 
 constexpr int kMaxDevices = 64;
 
-struct CodeObject {
-    std::string key;
-    std::string symbol;
+// A compiled program, and one of its kernels.
+struct CodeImage {
     std::string image;
-    std::mutex mu;
+    std::mutex mu;                       // of the module and its kernels' functions
     hipModule_t module[kMaxDevices] = {};
+};
+struct CodeObject {
+    std::string symbol;
+    std::shared_ptr<CodeImage> in;
     hipFunction_t function[kMaxDevices] = {};
 };
 
 namespace {
 
 std::mutex g_mu;
-std::unordered_map<std::string, std::shared_ptr<CodeObject>> g_cache;
+std::unordered_map<std::string, std::vector<std::shared_ptr<CodeObject>>> g_cache;
 std::atomic<uint64_t> g_mem_hits{0}, g_disk_hits{0}, g_compiles{0}, g_disk_rejects{0};
 std::atomic<int64_t> g_compile_us{0};
 
@@ -160,6 +163,13 @@ hipmr_status compile_source(const std::string& source, const std::vector<std::st
 
 std::shared_ptr<CodeObject> get_or_build(const std::string& source, const std::string& symbol,
                                          hipmr_status* status) {
+    const auto all = get_or_build(source, std::vector<std::string>{symbol}, status);
+    return all.empty() ? nullptr : all[0];
+}
+
+std::vector<std::shared_ptr<CodeObject>> get_or_build(const std::string& source,
+                                                      const std::vector<std::string>& symbols,
+                                                      hipmr_status* status) {
     static const std::vector<std::string> opts = compile_options();
     static const std::string version = compiler_version();
     std::string keytext = source;
@@ -176,23 +186,27 @@ std::shared_ptr<CodeObject> get_or_build(const std::string& source, const std::s
         }
     }
     std::string key = sha256_hex(keytext.data(), keytext.size());
-    auto co = std::make_shared<CodeObject>();
-    co->key = key;
-    co->symbol = symbol;
+    auto image = std::make_shared<CodeImage>();
     std::string dir = cache_dir();
     std::string path = dir + "/" + key + ".hsaco";
-    if (read_disk(path, &co->image)) {
+    if (read_disk(path, &image->image)) {
         g_disk_hits++;
     } else {
-        hipmr_status st = compile_source(source, opts, &co->image);
+        hipmr_status st = compile_source(source, opts, &image->image);
         if (st != HIPMR_OK) {
             *status = st;
-            return nullptr;
+            return {};
         }
-        write_disk(dir, path, co->image);
+        write_disk(dir, path, image->image);
+    }
+    std::vector<std::shared_ptr<CodeObject>> all;
+    for (const std::string& symbol : symbols) {
+        all.push_back(std::make_shared<CodeObject>());
+        all.back()->symbol = symbol;
+        all.back()->in = image;
     }
     std::lock_guard<std::mutex> lk(g_mu);
-    auto ins = g_cache.emplace(std::move(keytext), co);
+    auto ins = g_cache.emplace(std::move(keytext), std::move(all));
     *status = HIPMR_OK;
     return ins.first->second;
 }
@@ -202,7 +216,7 @@ hipmr_status get_function(CodeObject& co, void** fn) {
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return fail(HIPMR_E_HIP, std::string("hipGetDevice: ") + hipGetErrorString(e));
     if (dev < 0 || dev >= kMaxDevices) return fail(HIPMR_E_HIP, "device index out of range");
-    std::lock_guard<std::mutex> lk(co.mu);
+    std::lock_guard<std::mutex> lk(co.in->mu);
     if (!co.function[dev]) {
         if (capturing_now())
             return fail(HIPMR_E_INVALID, "kernel " + co.symbol + " is not loaded on this device yet: "
@@ -210,17 +224,18 @@ hipmr_status get_function(CodeObject& co, void** fn) {
         if (no_alloc_now())
             return fail(HIPMR_E_INVALID, "kernel " + co.symbol + " is not loaded on this device yet: "
                                          "run the allocating entry point once on this device first");
-        hipModule_t m;
-        e = hipModuleLoadData(&m, co.image.data());
-        if (e != hipSuccess)
-            return fail(HIPMR_E_HIP, std::string("hipModuleLoadData: ") + hipGetErrorString(e));
+        hipModule_t& m = co.in->module[dev];
+        if (!m) {
+            hipModule_t loaded;
+            e = hipModuleLoadData(&loaded, co.in->image.data());
+            if (e != hipSuccess)
+                return fail(HIPMR_E_HIP, std::string("hipModuleLoadData: ") + hipGetErrorString(e));
+            m = loaded;
+        }
         hipFunction_t f;
         e = hipModuleGetFunction(&f, m, co.symbol.c_str());
-        if (e != hipSuccess) {
-            (void)hipModuleUnload(m);
+        if (e != hipSuccess)
             return fail(HIPMR_E_HIP, "hipModuleGetFunction(" + co.symbol + "): " + hipGetErrorString(e));
-        }
-        co.module[dev] = m;
         co.function[dev] = f;
     }
     *fn = (void*)co.function[dev];
@@ -250,7 +265,7 @@ hipmr_status launch(void* fn, unsigned grid, unsigned block, void** params, void
 }
 
 const std::string& code_object_symbol(const CodeObject& co) { return co.symbol; }
-const std::string& code_object_image(const CodeObject& co) { return co.image; }
+const std::string& code_object_image(const CodeObject& co) { return co.in->image; }
 
 void cache_stats(hipmr_cache_stats* out) {
     out->memory_hits = g_mem_hits.load();
