@@ -39,8 +39,6 @@ namespace {
 // and the scalars between kernels are float; what is computed from them in one
 // kernel (A p, alpha, the updates) is rounded once, when it is stored.
 const char* kCgCommon = R"HIP(
-constexpr int TX = 64, TY = @@TY@@, ROWS = TY / 4;
-
 // sum over the block's 256 threads, in every thread
 __device__ __forceinline__ double cg_block_sum(double v) {
   __shared__ double cg_lds[4];
@@ -73,6 +71,12 @@ __device__ __forceinline__ int cg_block() {
   const int x = blockIdx.x & 7, q = gridDim.x >> 3, r = gridDim.x & 7;
   return x * q + (x < r ? x : r) + (blockIdx.x >> 3);
 }
+
+)HIP";
+
+// The kernels below that work on tiles are in a namespace per tile height.
+const char* kCgTile = R"HIP(
+constexpr int TX = 64, TY = @@TY@@, ROWS = TY / 4;
 
 // rows [r0 - H, r0 + TY + H), columns [c0 - H, c0 + TX + H) of an nx by ny
 // grid into dst (row length TX + 2 H), zero outside the grid
@@ -314,9 +318,10 @@ extern "C" __global__ void __launch_bounds__(256)
 }
 )HIP";
 
-enum { kP, kR, kU, kF, kS, kZ, kCgKernels };
+enum { kP, kR, kU, kF, kS, kZ, kCgKernels };         // the first three work on tiles
 const char* const kCgBodies[kCgKernels] = {kCgP, kCgR, kCgU, kCgF, kCgS, kCgZ};
 const char* const kCgTags[kCgKernels] = {"cgp", "cgr", "cgu", "cgf", "cgs", "cgz"};
+constexpr int kCgRows[] = {8, 16}, kCgShapes = 2;
 // Blocks of a kernel, and so the partials its successor folds in every block:
 // eight per compute unit (at 4096^2, 98.5 us per iteration; 103 with 1536
 // blocks, 114 with 1024, 126 with 768).
@@ -327,23 +332,40 @@ void replace_key(std::string& s, const std::string& key, const std::string& val)
     for (size_t at; (at = s.find(key)) != std::string::npos;) s.replace(at, key.size(), val);
 }
 
-// The kernels are the same for every grid size: built once per tile height.
-hipmr_status cg_kernel(int which, int ty, std::shared_ptr<CodeObject>* out) {
+// The kernels of every grid size, built as one program and loaded together, so
+// that a capture of any size finds them once a run of any size went before.
+struct CgKernels {
+    std::shared_ptr<CodeObject> of[kCgShapes][kCgKernels];
+};
+hipmr_status cg_kernels(const CgKernels** out) {
     static std::mutex mu;
-    static std::map<int, std::shared_ptr<CodeObject>> built;
+    static CgKernels built;
     std::lock_guard<std::mutex> lk(mu);
-    auto& co = built[ty * kCgKernels + which];
-    if (!co) {
-        std::string text = std::string(kCgCommon) + kCgBodies[which];
-        replace_key(text, "@@TY@@", std::to_string(ty));
-        const std::string sym = std::string("hipmr_") + kCgTags[which] + "_" +
-                                sha256_hex(text.data(), text.size()).substr(0, 8);
-        replace_key(text, "@@KNAME@@", sym);
+    if (!built.of[0][0]) {
+        std::string text = kCgCommon;
+        std::vector<std::string> symbols;
+        const auto add = [&](std::string body, int which, const std::string& shape) {
+            symbols.push_back(std::string("hipmr_") + kCgTags[which] + shape + "_" +
+                              sha256_hex(body.data(), body.size()).substr(0, 8));
+            replace_key(body, "@@KNAME@@", symbols.back());
+            text += body;
+        };
+        for (int rows : kCgRows) {
+            std::string tile = kCgTile;
+            replace_key(tile, "@@TY@@", std::to_string(rows));
+            text += "namespace cg_64x" + std::to_string(rows) + " {\n" + tile;
+            for (int k : {kP, kR, kU}) add(kCgBodies[k], k, "_64x" + std::to_string(rows));
+            text += "}\n";
+        }
+        for (int k : {kF, kS, kZ}) add(kCgBodies[k], k, "");
         hipmr_status st;
-        co = get_or_build(text, sym, &st);
-        if (!co) return st;
+        const auto all = get_or_build(text, symbols, &st);
+        if (all.empty()) return st;
+        for (int s = kCgShapes - 1; s >= 0; --s)
+            for (int k = kCgKernels - 1; k >= 0; --k)
+                built.of[s][k] = k < 3 ? all[s * 3 + k] : all[kCgShapes * 3 + k - 3];
     }
-    *out = co;
+    *out = &built;
     return HIPMR_OK;
 }
 
@@ -351,8 +373,8 @@ hipmr_status cg_kernel(int which, int ty, std::shared_ptr<CodeObject>* out) {
 // latency of a small grid), else of 16 (a smaller ring, fewer partials).  Us
 // per iteration with 8 / 16 rows: 256^2 8.6 / 9.4, 333 x 777 10.4 / 11.2,
 // 1024 x 768 13.9 / 12.4, 2048^2 33.6 / 30.4, 4096^2 109 / 98.5.
-int cg_tile_rows(long long nx, long long ny) {
-    return ((nx + 63) / 64) * ((ny + 7) / 8) <= 1024 ? 8 : 16;
+int cg_shape(long long nx, long long ny) {
+    return ((nx + 63) / 64) * ((ny + 7) / 8) <= 1024 ? 0 : 1;
 }
 
 }  // namespace
@@ -360,14 +382,10 @@ int cg_tile_rows(long long nx, long long ny) {
 namespace hipmr {
 
 hipmr_status cg_selftest(int32_t* built) {
-    for (int k = 0; k < kCgKernels; ++k)
-        for (int ty : {8, 16}) {
-            std::shared_ptr<CodeObject> co;
-            hipmr_status st = cg_kernel(k, ty, &co);
-            if (st != HIPMR_OK) return st;
-            ++*built;
-        }
-    return HIPMR_OK;
+    const CgKernels* all;
+    hipmr_status st = cg_kernels(&all);
+    if (st == HIPMR_OK) *built += kCgShapes * 3 + 3;
+    return st;
 }
 
 }  // namespace hipmr
@@ -394,21 +412,23 @@ hipmr_status hipmr_poisson_cg(int64_t nx, int64_t ny, const void* b, int32_t ite
     for (const void* a : {b, (const void*)x, (const void*)r, (const void*)p, (const void*)q, (const void*)s})
         if ((uintptr_t)a % 4) return fail(HIPMR_E_INVALID, "array off its element alignment");
     const long long n = nx * ny;
-    const int ty = cg_tile_rows(nx, ny);
+    const int shape = cg_shape(nx, ny), ty = kCgRows[shape];
     const long long tiles64 = ((nx + 63) / 64) * ((ny + ty - 1) / ty);
     if (tiles64 > INT32_MAX) return fail(HIPMR_E_UNSUPPORTED, "grid too large");
-    void* fn[kCgKernels] = {};
-    // every kernel is loaded by the first call, so that a later capture of any
-    // run finds them; a kernel this call does not use may be missing
-    hipmr_status st = HIPMR_OK;
-    for (int k = 0; k < kCgKernels; ++k) {
-        const bool used = k == kS ? b != nullptr : k == kZ ? b && iters == 0 : k == kU ? iters > 1 : iters > 0;
-        std::shared_ptr<CodeObject> co;
-        st = cg_kernel(k, ty, &co);
-        if (st == HIPMR_OK) st = get_function(*co, &fn[k]);
-        if (st != HIPMR_OK && used) return st;
+    const CgKernels* all;
+    hipmr_status st = cg_kernels(&all);
+    if (st != HIPMR_OK) return st;
+    static std::atomic<uint64_t> loaded{0};            // devices on which every shape's kernels are
+    int dev = 0;
+    void* fn[kCgKernels];
+    if (hipGetDevice(&dev) == hipSuccess && dev < 64 && !(loaded.load() >> dev & 1) && !capturing_now()) {
+        for (const auto& kernels : all->of)
+            for (const auto& co : kernels)
+                if ((st = get_function(*co, &fn[0])) != HIPMR_OK) return st;
+        loaded.fetch_or(1ull << dev);
     }
-    clear_error();
+    for (int k = 0; k < kCgKernels; ++k)
+        if ((st = get_function(*all->of[shape][k], &fn[k])) != HIPMR_OK) return st;
 
     double* pq_part = (double*)workspace;
     double* rr_part = pq_part + kCgBlocks;
