@@ -34,8 +34,8 @@ using namespace hipmr;
 
 namespace {
 
-// Tiles are 64 columns (one wave) by @@TY@@ rows.  Sums are kept in FP64, in an
-// order fixed by the grid size alone, and the same in cgp and cgu.  The vectors
+// Tiles are TX columns by TY rows (the shapes below).  Sums are kept in FP64, in
+// an order fixed by the grid size alone, and the same in cgp and cgu.  The vectors
 // and the scalars between kernels are float; what is computed from them in one
 // kernel (A p, alpha, the updates) is rounded once, when it is stored.
 const char* kCgCommon = R"HIP(
@@ -74,25 +74,25 @@ __device__ __forceinline__ int cg_block() {
 
 )HIP";
 
-// The kernels below that work on tiles are in a namespace per tile height.
+// The kernels below that work on tiles are in a namespace per tile shape.  A
+// thread has one column and, of a step of RPS rows over the tile, one row.
 const char* kCgTile = R"HIP(
-constexpr int TX = 64, TY = @@TY@@, ROWS = TY / 4;
+constexpr int TX = @@TX@@, TY = @@TY@@, RPS = 256 / TX, ROWS = TY / RPS;
 
-// rows [r0 - H, r0 + TY + H), columns [c0 - H, c0 + TX + H) of an nx by ny
-// grid into dst (row length TX + 2 H), zero outside the grid
-template <int H>
+// rows [r0 - 1, r0 + TY + 1), columns [c0 - 1, c0 + TX + 1) of an nx by ny
+// grid into dst (row length TX + 2), zero outside the grid
 __device__ __forceinline__ void cg_load_tile(float* dst, const float* src, int nx, int ny, int r0, int c0) {
-  constexpr int W = TX + 2 * H, R = TY + 2 * H;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  constexpr int W = TX + 2, R = TY + 2;
+  const int lane = threadIdx.x % TX, w = threadIdx.x / TX;
 #pragma unroll
-  for (int k = 0; k < (R + 3) / 4; ++k) {
-    const int j = w + 4 * k, gr = r0 - H + j, gc = c0 + lane;
-    if (j < R) dst[j * W + H + lane] = gr >= 0 && gr < ny && gc < nx ? src[(long long)gr * nx + gc] : 0.0f;
+  for (int k = 0; k < (R + RPS - 1) / RPS; ++k) {
+    const int j = w + RPS * k, gr = r0 - 1 + j, gc = c0 + lane;
+    if (j < R) dst[j * W + 1 + lane] = gr >= 0 && gr < ny && gc < nx ? src[(long long)gr * nx + gc] : 0.0f;
   }
-  if (threadIdx.x < 2 * H * R) {
-    const int j = threadIdx.x / (2 * H), s = threadIdx.x % (2 * H);
-    const int k = s < H ? s : TX + s, gr = r0 - H + j, gc = c0 - H + k;
-    dst[j * W + k] = gr >= 0 && gr < ny && gc >= 0 && gc < nx ? src[(long long)gr * nx + gc] : 0.0f;
+#pragma unroll
+  for (int i = 0; i < (2 * R + 255) / 256; ++i) {
+    const int j = (threadIdx.x >> 1) + 128 * i, k = threadIdx.x & 1 ? TX + 1 : 0, gr = r0 - 1 + j, gc = c0 - 1 + k;
+    if (j < R) dst[j * W + k] = gr >= 0 && gr < ny && gc >= 0 && gc < nx ? src[(long long)gr * nx + gc] : 0.0f;
   }
 }
 
@@ -111,12 +111,12 @@ extern "C" __global__ void __launch_bounds__(256)
 {
   constexpr int W = TX + 2;
   __shared__ float sp[(TY + 2) * W];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, b = cg_block();
+  const int lane = threadIdx.x % TX, w = threadIdx.x / TX, b = cg_block();
   double acc = 0.0;
   for (int t = b; t < tiles; t += gridDim.x) {
     const int r0 = t / tx * TY, c0 = t % tx * TX;
     __syncthreads();
-    cg_load_tile<1>(sp, p, nx, ny, r0, c0);
+    cg_load_tile(sp, p, nx, ny, r0, c0);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < ROWS; ++k) {
@@ -141,7 +141,7 @@ extern "C" __global__ void __launch_bounds__(256)
 {
   constexpr int W = TX + 2;
   __shared__ float sp[(TY + 2) * W];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, b = cg_block();
+  const int lane = threadIdx.x % TX, w = threadIdx.x / TX, b = cg_block();
   const cg_partials parts = cg_fold_load(pq_part, pq_g);
   const float c0v = c[0];
   float rv[ROWS];
@@ -152,7 +152,7 @@ extern "C" __global__ void __launch_bounds__(256)
       const int gr = r0 + w * ROWS + k, gc = c0 + lane;
       rv[k] = gr < ny && gc < nx ? r[(long long)gr * nx + gc] : 0.0f;
     }
-    cg_load_tile<1>(sp, p, nx, ny, r0, c0);
+    cg_load_tile(sp, p, nx, ny, r0, c0);
   };
   if (b < tiles) load(b);
   const float pq = (float)cg_fold_sum(parts);
@@ -190,33 +190,32 @@ extern "C" __global__ void __launch_bounds__(256)
           float* __restrict__ p_out, int nx, int ny, int tx, int tiles, const double* __restrict__ rr_part,
           int rr_g, double* __restrict__ pq_part, const float* __restrict__ c, float* __restrict__ d)
 {
-  constexpr int W = TX + 2, R = TY + 2, K = (R + 3) / 4;
+  constexpr int W = TX + 2, R = TY + 2, K = (R + RPS - 1) / RPS, S = (2 * R + 255) / 256;
   __shared__ float sn[R * W];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, b = cg_block();
+  const int lane = threadIdx.x % TX, w = threadIdx.x / TX, b = cg_block();
   const cg_partials parts = cg_fold_load(rr_part, rr_g);
   const double c0v = c[0], c1v = c[1];
-  // rows w, w + 4, ... of the tile and the ring around it (zero outside the
-  // grid); the ring's side columns by the first 2 R threads
-  float pv[K], rv[K], xv[K], ps = 0.0f, rs = 0.0f;
+  // rows w, w + RPS, ... of the tile and the ring around it (zero outside the
+  // grid); the ring's side columns two rows' worth per pair of threads and step
+  float pv[K], rv[K], xv[K], ps[S], rs[S];
   const int sj = threadIdx.x >> 1, sk = threadIdx.x & 1 ? TX + 1 : 0;
   auto load = [&](int t) {
     const int r0 = t / tx * TY, c0 = t % tx * TX, gc = c0 + lane;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int j = w + 4 * k, gr = r0 - 1 + j;
+      const int j = w + RPS * k, gr = r0 - 1 + j;
       const bool in = j < R && gr >= 0 && gr < ny && gc < nx;
       const long long at = (long long)gr * nx + gc;
       pv[k] = in ? p[at] : 0.0f;
       rv[k] = in ? r[at] : 0.0f;
       xv[k] = in && j >= 1 && j <= TY ? x[at] : 0.0f;
     }
-    ps = rs = 0.0f;
-    if (threadIdx.x < 2 * R) {
-      const int gr = r0 - 1 + sj, gs = c0 - 1 + sk;
-      if (gr >= 0 && gr < ny && gs >= 0 && gs < nx) {
-        ps = p[(long long)gr * nx + gs];
-        rs = r[(long long)gr * nx + gs];
-      }
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+      const int j = sj + 128 * k, gr = r0 - 1 + j, gs = c0 - 1 + sk;
+      const bool in = j < R && gr >= 0 && gr < ny && gs >= 0 && gs < nx;
+      ps[k] = in ? p[(long long)gr * nx + gs] : 0.0f;
+      rs[k] = in ? r[(long long)gr * nx + gs] : 0.0f;
     }
   };
   if (b < tiles) load(b);
@@ -230,7 +229,7 @@ extern "C" __global__ void __launch_bounds__(256)
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int j = w + 4 * k, gr = r0 - 1 + j;
+      const int j = w + RPS * k, gr = r0 - 1 + j;
       if (j < R) {
         const float pn = (float)__builtin_fma(beta, (double)pv[k], (double)rv[k]);
         sn[j * W + lane + 1] = pn;
@@ -241,7 +240,9 @@ extern "C" __global__ void __launch_bounds__(256)
         }
       }
     }
-    if (threadIdx.x < 2 * R) sn[sj * W + sk] = (float)__builtin_fma(beta, (double)ps, (double)rs);
+#pragma unroll
+    for (int k = 0; k < S; ++k)
+      if (sj + 128 * k < R) sn[(sj + 128 * k) * W + sk] = (float)__builtin_fma(beta, (double)ps[k], (double)rs[k]);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < ROWS; ++k) {
@@ -321,7 +322,13 @@ extern "C" __global__ void __launch_bounds__(256)
 enum { kP, kR, kU, kF, kS, kZ, kCgKernels };         // the first three work on tiles
 const char* const kCgBodies[kCgKernels] = {kCgP, kCgR, kCgU, kCgF, kCgS, kCgZ};
 const char* const kCgTags[kCgKernels] = {"cgp", "cgr", "cgu", "cgf", "cgs", "cgz"};
-constexpr int kCgRows[] = {8, 16}, kCgShapes = 2;
+// (256 x 4 would suit flat grids better than 128 x 8, but crashes the compiler
+// that comes with PyTorch's ROCm 7.0 libraries.)
+struct CgShape {
+    int tx, ty;
+};
+constexpr CgShape kCgShape[] = {{64, 8}, {64, 16}, {128, 8}, {16, 64}, {4, 256}, {1, 1024}};
+constexpr int kCgShapes = sizeof(kCgShape) / sizeof(kCgShape[0]);
 // Blocks of a kernel, and so the partials its successor folds in every block:
 // eight per compute unit (at 4096^2, 98.5 us per iteration; 103 with 1536
 // blocks, 114 with 1024, 126 with 768).
@@ -350,11 +357,13 @@ hipmr_status cg_kernels(const CgKernels** out) {
             replace_key(body, "@@KNAME@@", symbols.back());
             text += body;
         };
-        for (int rows : kCgRows) {
+        for (const CgShape& sh : kCgShape) {
+            const std::string name = "_" + std::to_string(sh.tx) + "x" + std::to_string(sh.ty);
             std::string tile = kCgTile;
-            replace_key(tile, "@@TY@@", std::to_string(rows));
-            text += "namespace cg_64x" + std::to_string(rows) + " {\n" + tile;
-            for (int k : {kP, kR, kU}) add(kCgBodies[k], k, "_64x" + std::to_string(rows));
+            replace_key(tile, "@@TX@@", std::to_string(sh.tx));
+            replace_key(tile, "@@TY@@", std::to_string(sh.ty));
+            text += "namespace cg" + name + " {\n" + tile;
+            for (int k : {kP, kR, kU}) add(kCgBodies[k], k, name);
             text += "}\n";
         }
         for (int k : {kF, kS, kZ}) add(kCgBodies[k], k, "");
@@ -369,12 +378,23 @@ hipmr_status cg_kernels(const CgKernels** out) {
     return HIPMR_OK;
 }
 
-// Tiles of 8 rows while there are at most 1024 of them (more blocks for the
-// latency of a small grid), else of 16 (a smaller ring, fewer partials).  Us
+long long cg_tiles(const CgShape& s, long long nx, long long ny) {
+    return ((nx + s.tx - 1) / s.tx) * ((ny + s.ty - 1) / s.ty);
+}
+
+// Tiles of 64 x 8 while there are at most 1024 of them (more blocks for the
+// latency of a small grid), else of 64 x 16 (a smaller ring, fewer partials).  Us
 // per iteration with 8 / 16 rows: 256^2 8.6 / 9.4, 333 x 777 10.4 / 11.2,
-// 1024 x 768 13.9 / 12.4, 2048^2 33.6 / 30.4, 4096^2 109 / 98.5.
+// 1024 x 768 13.9 / 12.4, 2048^2 33.6 / 30.4, 4096^2 109 / 98.5.  Other shapes
+// only where 64 x 16 would work for columns or rows that a narrow grid does not
+// have: a third more elements, ring included, than the best shape.
 int cg_shape(long long nx, long long ny) {
-    return ((nx + 63) / 64) * ((ny + 7) / 8) <= 1024 ? 0 : 1;
+    if (cg_tiles(kCgShape[0], nx, ny) <= 1024) return 0;
+    const auto work = [&](int k) { return cg_tiles(kCgShape[k], nx, ny) * ((kCgShape[k].tx + 2) * (kCgShape[k].ty + 2)); };
+    int best = 1;
+    for (int k = 2; k < kCgShapes; ++k)
+        if (work(k) < work(best)) best = k;
+    return work(best) * 4 < work(1) * 3 ? best : 1;
 }
 
 }  // namespace
@@ -412,8 +432,9 @@ hipmr_status hipmr_poisson_cg(int64_t nx, int64_t ny, const void* b, int32_t ite
     for (const void* a : {b, (const void*)x, (const void*)r, (const void*)p, (const void*)q, (const void*)s})
         if ((uintptr_t)a % 4) return fail(HIPMR_E_INVALID, "array off its element alignment");
     const long long n = nx * ny;
-    const int shape = cg_shape(nx, ny), ty = kCgRows[shape];
-    const long long tiles64 = ((nx + 63) / 64) * ((ny + ty - 1) / ty);
+    if (ny == 1) std::swap(nx, ny);                  // the same unknowns and operator, one above the other
+    const int shape = cg_shape(nx, ny);
+    const long long tiles64 = cg_tiles(kCgShape[shape], nx, ny);
     if (tiles64 > INT32_MAX) return fail(HIPMR_E_UNSUPPORTED, "grid too large");
     const CgKernels* all;
     hipmr_status st = cg_kernels(&all);
@@ -433,7 +454,8 @@ hipmr_status hipmr_poisson_cg(int64_t nx, int64_t ny, const void* b, int32_t ite
     double* pq_part = (double*)workspace;
     double* rr_part = pq_part + kCgBlocks;
     float* spare = (float*)((char*)workspace + 2 * kCgPartBytes);     // the other buffer of p
-    int inx = (int)nx, iny = (int)ny, tx = (int)((nx + 63) / 64), tiles = (int)tiles64;
+    int inx = (int)nx, iny = (int)ny, tx = (int)((nx + kCgShape[shape].tx - 1) / kCgShape[shape].tx);
+    int tiles = (int)tiles64;
     int g = std::min(tiles, kCgBlocks);
     int gf = (int)std::min<long long>((n + 1023) / 1024, kCgBlocks);   // four unknowns per thread and pass
     float* c = (float*)s + 2 * parity;

@@ -46,3 +46,15 @@ def test_first_calls_build_one_program(tmp_path, monkeypatch):
         assert compiles() == before + 1
     want = sum(k % 5 + 1 for k in range(n))
     assert out.item() == want and run[-1].item() == want
+
+
+def test_the_cg_program_compiles_beside_torch(tmp_path, monkeypatch):
+    """With the compiler that the process has once torch is loaded."""
+    from paper_1304_5553_amd.cg import PoissonCG
+    if torch.cuda.is_available():
+        pytest.skip("covered by every CG test")
+    monkeypatch.setenv("HIPMR_CACHE_DIR", str(tmp_path))
+    before = compiles()
+    with pytest.raises(hm.HipError):                 # compiled; nowhere to load it
+        PoissonCG(8, 8, device="cpu", stream=0).solve(torch.zeros(64), 1)
+    assert compiles() in (before, before + 1)        # before: by an earlier call in this process
