@@ -336,8 +336,9 @@ size_t hipmr_poisson_cg_workspace_bytes(int64_t nx, int64_t ny);
  * 2 iters + 1 launches (one more with b), asynchronous on `stream`, nothing
  * allocated.  Sums in FP64; the result depends only on the arguments (not on
  * how a run of iterations is divided into calls).  iters == 0: only the
- * start runs, if b is given.  Errors: E_INVALID, E_WORKSPACE, E_UNSUPPORTED
- * (2^31 tiles), E_COMPILE, E_HIP. */
+ * start runs, if b is given.  The sides may be of any length.  Errors:
+ * E_INVALID, E_WORKSPACE, E_UNSUPPORTED (2^31 tiles of about 1024 unknowns),
+ * E_COMPILE, E_HIP. */
 hipmr_status hipmr_poisson_cg(int64_t nx, int64_t ny, const void *b, int32_t iters, void *x, void *r,
                               void *p, void *q, void *s, int32_t parity, void *workspace,
                               size_t workspace_bytes, void *stream);

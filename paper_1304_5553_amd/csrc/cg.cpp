@@ -77,21 +77,24 @@ __device__ __forceinline__ int cg_block() {
 // The kernels below that work on tiles are in a namespace per tile shape.  A
 // thread has one column and, of a step of RPS rows over the tile, one row.
 const char* kCgTile = R"HIP(
+typedef @@IDX@@ cg_idx;                          // of rows and columns
 constexpr int TX = @@TX@@, TY = @@TY@@, RPS = 256 / TX, ROWS = TY / RPS;
 
 // rows [r0 - 1, r0 + TY + 1), columns [c0 - 1, c0 + TX + 1) of an nx by ny
 // grid into dst (row length TX + 2), zero outside the grid
-__device__ __forceinline__ void cg_load_tile(float* dst, const float* src, int nx, int ny, int r0, int c0) {
+__device__ __forceinline__ void cg_load_tile(float* dst, const float* src, cg_idx nx, cg_idx ny, cg_idx r0, cg_idx c0) {
   constexpr int W = TX + 2, R = TY + 2;
   const int lane = threadIdx.x % TX, w = threadIdx.x / TX;
 #pragma unroll
   for (int k = 0; k < (R + RPS - 1) / RPS; ++k) {
-    const int j = w + RPS * k, gr = r0 - 1 + j, gc = c0 + lane;
+    const int j = w + RPS * k;
+    const cg_idx gr = r0 - 1 + j, gc = c0 + lane;
     if (j < R) dst[j * W + 1 + lane] = gr >= 0 && gr < ny && gc < nx ? src[(long long)gr * nx + gc] : 0.0f;
   }
 #pragma unroll
   for (int i = 0; i < (2 * R + 255) / 256; ++i) {
-    const int j = (threadIdx.x >> 1) + 128 * i, k = threadIdx.x & 1 ? TX + 1 : 0, gr = r0 - 1 + j, gc = c0 - 1 + k;
+    const int j = (threadIdx.x >> 1) + 128 * i, k = threadIdx.x & 1 ? TX + 1 : 0;
+    const cg_idx gr = r0 - 1 + j, gc = c0 - 1 + k;
     if (j < R) dst[j * W + k] = gr >= 0 && gr < ny && gc >= 0 && gc < nx ? src[(long long)gr * nx + gc] : 0.0f;
   }
 }
@@ -106,7 +109,7 @@ __device__ __forceinline__ double cg_apply(const float* p, int k) {
 // first p . A p of a run; after cgs also the fold of b . b
 const char* kCgP = R"HIP(
 extern "C" __global__ void __launch_bounds__(256)
-@@KNAME@@(const float* __restrict__ p, int nx, int ny, int tx, int tiles, double* __restrict__ pq_part,
+@@KNAME@@(const float* __restrict__ p, cg_idx nx, cg_idx ny, int tx, int tiles, double* __restrict__ pq_part,
           const double* __restrict__ rr_part, int rr_g, float* __restrict__ c)
 {
   constexpr int W = TX + 2;
@@ -114,7 +117,7 @@ extern "C" __global__ void __launch_bounds__(256)
   const int lane = threadIdx.x % TX, w = threadIdx.x / TX, b = cg_block();
   double acc = 0.0;
   for (int t = b; t < tiles; t += gridDim.x) {
-    const int r0 = t / tx * TY, c0 = t % tx * TX;
+    const cg_idx r0 = (cg_idx)(t / tx) * TY, c0 = (cg_idx)(t % tx) * TX;
     __syncthreads();
     cg_load_tile(sp, p, nx, ny, r0, c0);
     __syncthreads();
@@ -136,7 +139,7 @@ extern "C" __global__ void __launch_bounds__(256)
 // r -= alpha A p, r . r; stores q = A p too if asked to
 const char* kCgR = R"HIP(
 extern "C" __global__ void __launch_bounds__(256)
-@@KNAME@@(const float* __restrict__ p, float* __restrict__ r, float* __restrict__ q, int nx, int ny, int tx,
+@@KNAME@@(const float* __restrict__ p, float* __restrict__ r, float* __restrict__ q, cg_idx nx, cg_idx ny, int tx,
           int tiles, const double* __restrict__ pq_part, int pq_g, double* __restrict__ rr_part, float* c)
 {
   constexpr int W = TX + 2;
@@ -146,10 +149,10 @@ extern "C" __global__ void __launch_bounds__(256)
   const float c0v = c[0];
   float rv[ROWS];
   auto load = [&](int t) {
-    const int r0 = t / tx * TY, c0 = t % tx * TX;
+    const cg_idx r0 = (cg_idx)(t / tx) * TY, c0 = (cg_idx)(t % tx) * TX;
 #pragma unroll
     for (int k = 0; k < ROWS; ++k) {
-      const int gr = r0 + w * ROWS + k, gc = c0 + lane;
+      const cg_idx gr = r0 + w * ROWS + k, gc = c0 + lane;
       rv[k] = gr < ny && gc < nx ? r[(long long)gr * nx + gc] : 0.0f;
     }
     cg_load_tile(sp, p, nx, ny, r0, c0);
@@ -160,7 +163,7 @@ extern "C" __global__ void __launch_bounds__(256)
   if (b == 0 && threadIdx.x == 0) c[1] = pq;
   double acc = 0.0;
   for (int t = b; t < tiles; t += gridDim.x) {
-    const int r0 = t / tx * TY, c0 = t % tx * TX;
+    const cg_idx r0 = (cg_idx)(t / tx) * TY, c0 = (cg_idx)(t % tx) * TX;
     if (t != b) {
       __syncthreads();
       load(t);
@@ -168,7 +171,7 @@ extern "C" __global__ void __launch_bounds__(256)
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < ROWS; ++k) {
-      const int gr = r0 + w * ROWS + k, gc = c0 + lane;
+      const cg_idx gr = r0 + w * ROWS + k, gc = c0 + lane;
       if (gr < ny && gc < nx) {
         const double qv = cg_apply<W>(sp, (w * ROWS + k + 1) * W + lane + 1);
         const float rn = (float)__builtin_fma(-alpha, qv, (double)rv[k]);
@@ -187,7 +190,7 @@ extern "C" __global__ void __launch_bounds__(256)
 const char* kCgU = R"HIP(
 extern "C" __global__ void __launch_bounds__(256)
 @@KNAME@@(const float* __restrict__ p, const float* __restrict__ r, float* __restrict__ x,
-          float* __restrict__ p_out, int nx, int ny, int tx, int tiles, const double* __restrict__ rr_part,
+          float* __restrict__ p_out, cg_idx nx, cg_idx ny, int tx, int tiles, const double* __restrict__ rr_part,
           int rr_g, double* __restrict__ pq_part, const float* __restrict__ c, float* __restrict__ d)
 {
   constexpr int W = TX + 2, R = TY + 2, K = (R + RPS - 1) / RPS, S = (2 * R + 255) / 256;
@@ -200,10 +203,11 @@ extern "C" __global__ void __launch_bounds__(256)
   float pv[K], rv[K], xv[K], ps[S], rs[S];
   const int sj = threadIdx.x >> 1, sk = threadIdx.x & 1 ? TX + 1 : 0;
   auto load = [&](int t) {
-    const int r0 = t / tx * TY, c0 = t % tx * TX, gc = c0 + lane;
+    const cg_idx r0 = (cg_idx)(t / tx) * TY, c0 = (cg_idx)(t % tx) * TX, gc = c0 + lane;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int j = w + RPS * k, gr = r0 - 1 + j;
+      const int j = w + RPS * k;
+      const cg_idx gr = r0 - 1 + j;
       const bool in = j < R && gr >= 0 && gr < ny && gc < nx;
       const long long at = (long long)gr * nx + gc;
       pv[k] = in ? p[at] : 0.0f;
@@ -212,7 +216,8 @@ extern "C" __global__ void __launch_bounds__(256)
     }
 #pragma unroll
     for (int k = 0; k < S; ++k) {
-      const int j = sj + 128 * k, gr = r0 - 1 + j, gs = c0 - 1 + sk;
+      const int j = sj + 128 * k;
+      const cg_idx gr = r0 - 1 + j, gs = c0 - 1 + sk;
       const bool in = j < R && gr >= 0 && gr < ny && gs >= 0 && gs < nx;
       ps[k] = in ? p[(long long)gr * nx + gs] : 0.0f;
       rs[k] = in ? r[(long long)gr * nx + gs] : 0.0f;
@@ -224,12 +229,13 @@ extern "C" __global__ void __launch_bounds__(256)
   if (b == 0 && threadIdx.x == 0) d[0] = rr;
   double acc = 0.0;
   for (int t = b; t < tiles; t += gridDim.x) {
-    const int r0 = t / tx * TY, c0 = t % tx * TX, gc = c0 + lane;
+    const cg_idx r0 = (cg_idx)(t / tx) * TY, c0 = (cg_idx)(t % tx) * TX, gc = c0 + lane;
     if (t != b) load(t);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int j = w + RPS * k, gr = r0 - 1 + j;
+      const int j = w + RPS * k;
+      const cg_idx gr = r0 - 1 + j;
       if (j < R) {
         const float pn = (float)__builtin_fma(beta, (double)pv[k], (double)rv[k]);
         sn[j * W + lane + 1] = pn;
@@ -334,6 +340,7 @@ constexpr int kCgShapes = sizeof(kCgShape) / sizeof(kCgShape[0]);
 // blocks, 114 with 1024, 126 with 768).
 constexpr int kCgBlocks = 2048;
 constexpr size_t kCgPartBytes = kCgBlocks * sizeof(double);
+constexpr int64_t kCgMostUnknowns = (int64_t)1 << 48;
 
 void replace_key(std::string& s, const std::string& key, const std::string& val) {
     for (size_t at; (at = s.find(key)) != std::string::npos;) s.replace(at, key.size(), val);
@@ -344,9 +351,12 @@ void replace_key(std::string& s, const std::string& key, const std::string& val)
 struct CgKernels {
     std::shared_ptr<CodeObject> of[kCgShapes][kCgKernels];
 };
-hipmr_status cg_kernels(const CgKernels** out) {
+// (`wide`: grids with a side that 32-bit row and column numbers do not reach, a
+// program of their own.)
+hipmr_status cg_kernels(bool wide, const CgKernels** out) {
     static std::mutex mu;
-    static CgKernels built;
+    static CgKernels both[2];
+    CgKernels& built = both[wide];
     std::lock_guard<std::mutex> lk(mu);
     if (!built.of[0][0]) {
         std::string text = kCgCommon;
@@ -358,10 +368,11 @@ hipmr_status cg_kernels(const CgKernels** out) {
             text += body;
         };
         for (const CgShape& sh : kCgShape) {
-            const std::string name = "_" + std::to_string(sh.tx) + "x" + std::to_string(sh.ty);
+            const std::string name = "_" + std::to_string(sh.tx) + "x" + std::to_string(sh.ty) + (wide ? "w" : "");
             std::string tile = kCgTile;
             replace_key(tile, "@@TX@@", std::to_string(sh.tx));
             replace_key(tile, "@@TY@@", std::to_string(sh.ty));
+            replace_key(tile, "@@IDX@@", wide ? "long long" : "int");
             text += "namespace cg" + name + " {\n" + tile;
             for (int k : {kP, kR, kU}) add(kCgBodies[k], k, name);
             text += "}\n";
@@ -402,10 +413,13 @@ int cg_shape(long long nx, long long ny) {
 namespace hipmr {
 
 hipmr_status cg_selftest(int32_t* built) {
-    const CgKernels* all;
-    hipmr_status st = cg_kernels(&all);
-    if (st == HIPMR_OK) *built += kCgShapes * 3 + 3;
-    return st;
+    for (bool wide : {false, true}) {
+        const CgKernels* all;
+        hipmr_status st = cg_kernels(wide, &all);
+        if (st != HIPMR_OK) return st;
+        *built += kCgShapes * 3 + 3;
+    }
+    return HIPMR_OK;
 }
 
 }  // namespace hipmr
@@ -413,16 +427,18 @@ hipmr_status cg_selftest(int32_t* built) {
 extern "C" {
 
 size_t hipmr_poisson_cg_workspace_bytes(int64_t nx, int64_t ny) {
-    if (nx < 0 || ny < 0 || nx > INT32_MAX / 2 || ny > INT32_MAX / 2) return 0;
-    return 2 * kCgPartBytes + (size_t)nx * (size_t)ny * 4;
+    int64_t n;
+    if (nx < 0 || ny < 0 || __builtin_mul_overflow(nx, ny, &n) || n > kCgMostUnknowns) return 0;
+    return 2 * kCgPartBytes + (size_t)n * 4;
 }
 
 hipmr_status hipmr_poisson_cg(int64_t nx, int64_t ny, const void* b, int32_t iters, void* x, void* r,
                               void* p, void* q, void* s, int32_t parity, void* workspace,
                               size_t workspace_bytes, void* stream) {
     clear_error();
-    if (nx < 0 || ny < 0 || nx > INT32_MAX / 2 || ny > INT32_MAX / 2)
-        return fail(HIPMR_E_INVALID, "grid sides must be in [0, 2^30)");
+    int64_t n;
+    if (nx < 0 || ny < 0 || __builtin_mul_overflow(nx, ny, &n) || n > kCgMostUnknowns)
+        return fail(HIPMR_E_INVALID, "a grid side is negative, or the grid beyond any memory");
     if (nx == 0 || ny == 0) return HIPMR_OK;
     if (iters < 0 || (parity != 0 && parity != 1)) return fail(HIPMR_E_INVALID, "iters < 0 or parity not 0 / 1");
     if (!x || !r || !p || !q || !s) return fail(HIPMR_E_INVALID, "NULL array");
@@ -431,15 +447,16 @@ hipmr_status hipmr_poisson_cg(int64_t nx, int64_t ny, const void* b, int32_t ite
     if ((uintptr_t)workspace % 8) return fail(HIPMR_E_WORKSPACE, "workspace off its 8-byte alignment");
     for (const void* a : {b, (const void*)x, (const void*)r, (const void*)p, (const void*)q, (const void*)s})
         if ((uintptr_t)a % 4) return fail(HIPMR_E_INVALID, "array off its element alignment");
-    const long long n = nx * ny;
     if (ny == 1) std::swap(nx, ny);                  // the same unknowns and operator, one above the other
     const int shape = cg_shape(nx, ny);
     const long long tiles64 = cg_tiles(kCgShape[shape], nx, ny);
     if (tiles64 > INT32_MAX) return fail(HIPMR_E_UNSUPPORTED, "grid too large");
+    const bool wide = std::max(nx, ny) > INT32_MAX / 2;
     const CgKernels* all;
-    hipmr_status st = cg_kernels(&all);
+    hipmr_status st = cg_kernels(wide, &all);
     if (st != HIPMR_OK) return st;
-    static std::atomic<uint64_t> loaded{0};            // devices on which every shape's kernels are
+    static std::atomic<uint64_t> loaded_on[2];         // devices on which every shape's kernels are
+    std::atomic<uint64_t>& loaded = loaded_on[wide];
     int dev = 0;
     void* fn[kCgKernels];
     if (hipGetDevice(&dev) == hipSuccess && dev < 64 && !(loaded.load() >> dev & 1) && !capturing_now()) {
@@ -454,7 +471,9 @@ hipmr_status hipmr_poisson_cg(int64_t nx, int64_t ny, const void* b, int32_t ite
     double* pq_part = (double*)workspace;
     double* rr_part = pq_part + kCgBlocks;
     float* spare = (float*)((char*)workspace + 2 * kCgPartBytes);     // the other buffer of p
-    int inx = (int)nx, iny = (int)ny, tx = (int)((nx + kCgShape[shape].tx - 1) / kCgShape[shape].tx);
+    int nx32 = (int)nx, ny32 = (int)ny;
+    void *inx = wide ? (void*)&nx : &nx32, *iny = wide ? (void*)&ny : &ny32;
+    int tx = (int)((nx + kCgShape[shape].tx - 1) / kCgShape[shape].tx);
     int tiles = (int)tiles64;
     int g = std::min(tiles, kCgBlocks);
     int gf = (int)std::min<long long>((n + 1023) / 1024, kCgBlocks);   // four unknowns per thread and pass
@@ -473,13 +492,13 @@ hipmr_status hipmr_poisson_cg(int64_t nx, int64_t ny, const void* b, int32_t ite
     float* pc = (float*)p;                           // the current p
     int rr_g = b ? gf : 0;
     {
-        void* a[] = {&pc, &inx, &iny, &tx, &tiles, &pq_part, &rr_part, &rr_g, &c};
+        void* a[] = {&pc, inx, iny, &tx, &tiles, &pq_part, &rr_part, &rr_g, &c};
         st = launch(fn[kP], (unsigned)g, 256, a, stream);
     }
     for (int it = 0; it < iters && st == HIPMR_OK; ++it) {
         const bool last = it == iters - 1;
         float* qa = last ? (float*)q : nullptr;
-        void* a[] = {&pc, &r, &qa, &inx, &iny, &tx, &tiles, &pq_part, &g, &rr_part, &c};
+        void* a[] = {&pc, &r, &qa, inx, iny, &tx, &tiles, &pq_part, &g, &rr_part, &c};
         st = launch(fn[kR], (unsigned)g, 256, a, stream);
         if (st != HIPMR_OK) break;
         if (last) {
@@ -487,7 +506,7 @@ hipmr_status hipmr_poisson_cg(int64_t nx, int64_t ny, const void* b, int32_t ite
             st = launch(fn[kF], (unsigned)gf, 256, f, stream);
         } else {
             float* pn = pc == p ? spare : (float*)p;
-            void* u[] = {&pc, &r, &x, &pn, &inx, &iny, &tx, &tiles, &rr_part, &g, &pq_part, &c, &d};
+            void* u[] = {&pc, &r, &x, &pn, inx, iny, &tx, &tiles, &rr_part, &g, &pq_part, &c, &d};
             st = launch(fn[kU], (unsigned)g, 256, u, stream);
             pc = pn;
         }

@@ -44,3 +44,32 @@ def test_a_run_is_the_sum_of_its_parts(nx, ny):
     for _ in range(5):
         parts.step()
     assert torch.equal(x, parts.x) and torch.equal(whole.r, parts.r) and torch.equal(whole.p, parts.p)
+
+
+@pytest.mark.parametrize("nx,ny", [((1 << 30) + 3, 1), (1, (1 << 31) + 1001), ((1 << 30) + 77, 2)])
+def test_sides_beyond_two_to_the_30(nx, ny):
+    """One iteration, at places on both sides of each power of two and the ends."""
+    dev = need_gpu()
+    n, part = nx * ny, 1 << 28
+    b = torch.rand(n, device=dev) - 0.25
+    s = hcg.PoissonCG(nx, ny, device=dev)
+    s.solve(b, 1)
+
+    def rows(lo, hi):
+        """(A b)[lo:hi] in float64."""
+        k = torch.arange(lo, hi, device=dev)
+        g = lambda at, ok: torch.where(ok, b[at.clamp(0, n - 1)].double(), 0.0)   # noqa: E731
+        col = k % nx
+        return (4 * b[lo:hi].double() - g(k - 1, col > 0) - g(k + 1, col < nx - 1)
+                - g(k - nx, k >= nx) - g(k + nx, k < n - nx))
+    rr = sum((b[lo:lo + part].double() ** 2).sum().item() for lo in range(0, n, part))
+    pq = sum((b[lo:min(lo + part, n)].double() * rows(lo, min(lo + part, n))).sum().item() for lo in range(0, n, part))
+    alpha = rr / pq
+    at = {0, n - 4096, nx - 2048 if nx > 4096 else 0}
+    at |= {p - 2048 for p in (1 << 29, 1 << 30, 1 << 31) if p + 2048 < n}
+    for lo in sorted(at):
+        lo = min(max(0, lo), n - 4096)
+        q, v = rows(lo, lo + 4096), b[lo:lo + 4096].double()
+        assert (s.q[lo:lo + 4096].double() - q).abs().max().item() <= 4 * U24 * 8
+        assert (s.x[lo:lo + 4096].double() - alpha * v).abs().max().item() <= 4 * U24 * alpha
+        assert (s.r[lo:lo + 4096].double() - (v - alpha * q)).abs().max().item() <= 4 * U24 * (1 + 8 * alpha)
