@@ -595,7 +595,10 @@ typedef struct hipmr_handle_info {
     int32_t result_dtype;   /* HIPMR_* of the result (reduce), else 0              */
     int32_t nargs;          /* declared arguments                                  */
     int32_t vectorizable;   /* every array access is name[i]                       */
-    int32_t vec;            /* default elements per vector chunk                   */
+    int32_t vec;            /* elements per chunk of 16 bytes of the narrowest
+                               array (the default, but for elementwise calls
+                               and plain reductions over several element
+                               sizes: see hipmr_launch_config.vec)             */
     uint32_t hash;          /* first 32 bits of the expression+signature hash      */
 } hipmr_handle_info;
 

@@ -11,16 +11,27 @@
 // neutral text and the launch constants (block size, vector chunks per
 // thread, elements per chunk, index width).
 //
-// Kernel family (all wave64, no atomics, no LDS beyond the reduction tree):
-//   ew_vec   grid-stride over VEC-element chunks; each thread keeps IPT chunks
-//            of every accessed array in flight (16-byte loads/stores), runs the
-//            statement per element from registers, stores back;
-//   ew_sca   one element per step (any access pattern);
-//   rs1_vec  same loads; per-thread accumulators (one per in-flight chunk),
-//            folded pairwise, then a wave64 butterfly (cross-lane shuffles)
-//            and an LDS tree across the block's waves -> one partial per block;
-//   rs1_sca  one element per step, same tree;
-//   rs2      one block folds the G partials in a fixed order -> *out.
+// Kernel families (all wave64; LDS for the trees across a block's waves, a
+// scan's hand-over and a segmented call's tile table):
+//   ew, ews     grid-stride over VEC-element chunks, each thread with IPT chunks
+//               of every accessed array in flight (16-byte loads and stores),
+//               the statement run per element from registers; or one element
+//               per step (any access pattern);
+//   rs1, rs1s   the same loads; per-thread accumulators (one per in-flight
+//               chunk) folded pairwise, a wave64 butterfly (cross-lane
+//               shuffles) and an LDS tree across the block's waves: one partial
+//               per block.  The last block folds the others' partials in the
+//               same launch, exchanged as tagged 64-bit words (device-scope
+//               atomic loads and stores; no read-modify-write), or
+//   rs2         one block folds them in a launch of its own: the same bits;
+//   csum, nrm1, nrm2 (csums, ...), csumf, nrm2f
+//               the same for compensated sums and norms;
+//   seg1, seg2, segplan
+//               tiles of segments by a persistent kernel, their fold, the
+//               table where it does not fit LDS;
+//   sc1, scu + scd, scz + scl
+//               prefix scans: one tile, totals and rescan, one pass (tiles
+//               take tickets, publish totals and wait for earlier ones').
 #include <algorithm>
 
 #include "common.h"
@@ -813,10 +824,11 @@ __device__ __forceinline__ float hipmr_block_amax(float m) {
 // The norm's power-of-two scale from its first pass: the max |map| over
 // that pass's block partials (one per block of this grid: both passes use
 // the same geometry).  Where that maximum is 0 or lies in [2^-40, 2^40] the
-// first pass's own sums of unscaled squares stand (0 is returned): n < 2^47 such squares stay below 2^127, and what a square
-// loses below 2^-149 is at most 2^-70 of the largest one.  Scaling by a power
-// of two changes no bit of a product or sum that stays in range, so the
-// result is the one the scaled pass would give.  Else s = 2^-e, e the
+// first pass's own sums of unscaled squares stand (0 is returned): n < 2^47 such
+// squares stay below 2^127.  Scaling by a power of two changes no bit of a
+// square that is normal either way; a value below 2^-63, which the scale would
+// have raised, has a subnormal square here and loses at most 2^-150, which is
+// 2^-70 of the largest square: far below the sum's own rounding.  Else s = 2^-e, e the
 // exponent of the max clamped to [-126, 126], so the largest scaled
 // magnitude lies in [1, 2).  Every block computes it.
 template <int B>
@@ -1159,11 +1171,6 @@ __device__ __forceinline__ void hipmr_seg_clamp(long long a0, long long b0, long
   long long r = (head - a) % V;
   if (r < 0) r += V;
   ab = a + r < b ? a + r : b;
-}
-__device__ __forceinline__ void hipmr_seg_bounds(const long long* __restrict__ off, int s,
-                                                 long long total, long long head, int V,
-                                                 long long& a, long long& b, long long& ab) {
-  hipmr_seg_clamp(off[s], off[s + 1], total, head, V, a, b, ab);
 }
 __device__ __forceinline__ int hipmr_seg_tiles(long long a, long long b, long long ab, long long T) {
   if (b == a) return 0;

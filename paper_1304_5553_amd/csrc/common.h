@@ -143,11 +143,11 @@ struct KernelSpec {
     // precision extension
     bool square = false;      // CompS1: accumulate map^2 (norm)
     bool track = false;       // CompS1: also keep max |map| per block (the norm's first pass)
-    bool scaled = false;      // CompS1 / CompS2: apply the device-side power-of-two scale
+    bool scaled = false;      // CompS1: the norm's second pass (a power-of-two scale); CompS2: fold after it
     bool exact_runs = false;  // CompS1: map is one FP8 load; sum runs of <= 64 exactly
     bool norm = false;        // CompS2: finish as sqrt(sum) / scale
-    // batching extension
     bool finish = false;      // RedS1, CompS1: fold the partials in the same launch
+    // scan and batching extension
     int scan_mode = 0;        // Scan: 0 one tile, 1 tile totals, 2 from totals, 3 one pass
     int lds_segs = 0;         // SegS1: segments its LDS tile table holds, 0 = table in global memory
 };

@@ -111,3 +111,18 @@ def test_second_pass_of_any_grid(grid, flags):
         assert len(k.last_symbols()) == (2 if grid <= 1024 else 3)
         first = g if first is None else first
         assert g == first and abs(g - o) <= 1e-6 * o
+
+
+@pytest.mark.parametrize("top", [-40, -39, 0, 39])
+@pytest.mark.parametrize("span", [24, 40, 86])
+def test_magnitudes_far_below_the_largest(top, span):
+    """Values over many binades under a maximum whose unscaled squares stand:
+    those below 2^-63 have subnormal squares there.  The 1e-6 gate."""
+    need_gpu()
+    n = 1 << 20
+    rng = np.random.default_rng(span + top + 100)
+    x = (rng.uniform(1.0, 2.0, n) * 2.0 ** rng.integers(top - span, top, n)).astype(np.float32)
+    x[7] = np.float32(2.0) ** top
+    k = hm.compile("x[i]", "float: const float *x")
+    o = oracle.norm2(x.astype(np.float64))
+    assert abs(hm.norm2(k, n, [dev_array(x)]).item() - o) <= 1e-6 * o
