@@ -329,43 +329,57 @@ __device__ __forceinline__ bool hipmr_get_tagged(const unsigned long long* part,
   __builtin_memcpy(v, &bits, sizeof(T));
   return true;
 }
+// whether any thread of the block says so (a barrier)
+template <int B>
+__device__ __forceinline__ bool hipmr_any(bool says) {
+  __shared__ int hipmr_says[B / 64];
+  const bool some = __ballot(says) != 0;
+  if ((threadIdx.x & 63) == 0) hipmr_says[threadIdx.x >> 6] = some;
+  __syncthreads();
+  int any = 0;
+#pragma unroll
+  for (int w = 0; w < B / 64; ++w) any |= hipmr_says[w];
+  return any != 0;
+}
 )HIP";
 
-// A kernel that finishes runs its share in a loop: `b` is the share just
-// computed, the result the next one to compute, or -1 when the block is done.
+// hipmr_finish returns whether the block has to compute every share: a loop over
+// the shares then follows it in the kernel (the templates named ...Share below:
+// the body's order of combination, but one chunk at a time), each added by
+// hipmr_add_share.  (The body itself in a loop cost registers, and the compiler
+// then issued a compensated bfloat16 dot's loads one by one, 55 us against 40
+// at 2^26; a copy of it doubled them, 13.0 us against 11.1 for twelve arrays of
+// 2^22.)
 const char* kRedFinish = R"HIP(
-struct hipmr_turn { hipmr_acc v; bool alone; };   // the last block's fold; whether it computes every share
 template <int B>
-__device__ __forceinline__ int hipmr_finish(hipmr_acc r, hipmr_acc neutral, unsigned long long* part,
-                                            hipmr_acc* __restrict__ out, unsigned long long tag, int b,
-                                            hipmr_turn& f) {
+__device__ __forceinline__ bool hipmr_finish(hipmr_acc r, hipmr_acc neutral, unsigned long long* part,
+                                             hipmr_acc* __restrict__ out, unsigned long long tag) {
   const int g = (int)gridDim.x;
-  if (!f.alone) {
-    if (threadIdx.x == 0) hipmr_put_tagged(part, b, r, tag);
-    if ((int)blockIdx.x != g - 1) return -1;
-    f.v = neutral;
-    bool here = true;
-    for (int k = threadIdx.x; here && k < g; k += B) {
-      hipmr_acc p;
-      here = hipmr_get_tagged(part, k, tag, &p);
-      if (here) f.v = hipmr_combine(f.v, p);
-    }
-    if (__syncthreads_or(!here)) {
-      f.v = neutral;
-      f.alone = true;
-      return 0;
-    }
-  } else {
-    __shared__ hipmr_acc hipmr_share;
-    if (threadIdx.x == 0) hipmr_share = r;
-    __syncthreads();
-    if ((int)threadIdx.x == b % B) f.v = hipmr_combine(f.v, hipmr_share);
-    __syncthreads();
-    if (b + 1 < g) return b + 1;
+  if (threadIdx.x == 0) hipmr_put_tagged(part, (int)blockIdx.x, r, tag);
+  if ((int)blockIdx.x != g - 1) return false;
+  hipmr_acc v = neutral;
+  bool here = true;
+  for (int k = threadIdx.x; here && k < g; k += B) {
+    hipmr_acc p;
+    here = hipmr_get_tagged(part, k, tag, &p);
+    if (here) v = hipmr_combine(v, p);
   }
-  f.v = hipmr_block_reduce<B>(f.v, neutral);     // the share's fold has been read: barriers above
-  if (threadIdx.x == 0) *out = f.v;
-  return -1;
+  if (hipmr_any<B>(!here)) return true;          // a barrier: the share's fold has been read
+  v = hipmr_block_reduce<B>(v, neutral);
+  if (threadIdx.x == 0) *out = v;
+  return false;
+}
+template <int B>
+__device__ __forceinline__ void hipmr_add_share(hipmr_acc& v, hipmr_acc r, hipmr_acc neutral,
+                                                hipmr_acc* __restrict__ out, int b) {
+  __shared__ hipmr_acc hipmr_share;
+  if (threadIdx.x == 0) hipmr_share = r;
+  __syncthreads();
+  if ((int)threadIdx.x == b % B) v = hipmr_combine(v, hipmr_share);
+  __syncthreads();
+  if (b + 1 < (int)gridDim.x) return;
+  v = hipmr_block_reduce<B>(v, neutral);
+  if (threadIdx.x == 0) *out = v;
 }
 )HIP";
 
@@ -754,6 +768,71 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 }
 )HIP";
 
+// Share hipmr_b of a reduction, one chunk at a time: accumulator u takes the
+// chunks that the body's u takes, in the same order.
+const char* kRedShare = R"HIP(
+    hipmr_acc hipmr_c[HIPMR_U];
+#pragma unroll
+    for (int u = 0; u < HIPMR_U; ++u) hipmr_c[u] = hipmr_neutral;
+    if (hipmr_b == 0) {
+      if ((long long)threadIdx.x < hipmr_h) {
+        const hipmr_idx i = (hipmr_idx)threadIdx.x;
+        hipmr_c[0] = hipmr_combine(hipmr_c[0], (hipmr_acc)(@@MAP@@));
+      }
+      if ((long long)threadIdx.x < hipmr_n - hipmr_t0) {
+        const hipmr_idx i = (hipmr_idx)(hipmr_t0 + threadIdx.x);
+        hipmr_c[0] = hipmr_combine(hipmr_c[0], (hipmr_acc)(@@MAP@@));
+      }
+    }
+    for (long long hipmr_at = (long long)@@SHARE_BLOCK@@ * (HIPMR_B * HIPMR_U) + threadIdx.x; hipmr_at < hipmr_nc;
+         hipmr_at += hipmr_step) {
+#pragma unroll
+      for (int hipmr_w = 0; hipmr_w < HIPMR_U; ++hipmr_w) {
+        if (hipmr_at + hipmr_w * HIPMR_B < hipmr_nc) {
+          const long long hipmr_off = hipmr_h + (hipmr_at + hipmr_w * HIPMR_B) * HIPMR_V;
+          constexpr int HIPMR_U = 1, hipmr_u = 0;
+          @@DECL_PACKS@@
+          @@SHARE_CHUNK@@
+        }
+      }
+    }
+    hipmr_acc hipmr_q = hipmr_fold<HIPMR_U>(hipmr_c);
+    hipmr_q = hipmr_block_reduce<HIPMR_B>(hipmr_q, hipmr_neutral);
+)HIP";
+const char* kRedShareChunk = R"HIP(
+          @@LOADS@@
+#pragma unroll
+          for (int hipmr_j = 0; hipmr_j < HIPMR_V; ++hipmr_j) {
+            const hipmr_idx i = (hipmr_idx)(hipmr_off + hipmr_j);
+            hipmr_c[hipmr_w] = hipmr_combine(hipmr_c[hipmr_w], (hipmr_acc)(@@VMAP@@));
+          }
+)HIP";
+const char* kRedShareChunkShift = R"HIP(
+          @@SHIFT_PACKS@@
+          @@LOADS@@
+          @@SHIFT_LOADS@@
+          if (hipmr_smin >= -hipmr_off && hipmr_smax <= hipmr_n - HIPMR_V - hipmr_off) {
+#pragma unroll
+            for (int hipmr_j = 0; hipmr_j < HIPMR_V; ++hipmr_j) {
+              const hipmr_idx i = (hipmr_idx)(hipmr_off + hipmr_j);
+              hipmr_c[hipmr_w] = hipmr_combine(hipmr_c[hipmr_w], (hipmr_acc)(@@VMAP@@));
+            }
+          } else {
+            for (int hipmr_j = 0; hipmr_j < HIPMR_V; ++hipmr_j) {
+              const hipmr_idx i = (hipmr_idx)(hipmr_off + hipmr_j);
+              hipmr_c[hipmr_w] = hipmr_combine(hipmr_c[hipmr_w], (hipmr_acc)(@@MAP@@));
+            }
+          }
+)HIP";
+const char* kRedShareScalar = R"HIP(
+    hipmr_acc hipmr_q = hipmr_neutral;
+    for (long long hipmr_at = (long long)hipmr_b * @@BLOCK@@ + threadIdx.x; hipmr_at < hipmr_n; hipmr_at += hipmr_step) {
+      const hipmr_idx i = (hipmr_idx)hipmr_at;
+      hipmr_q = hipmr_combine(hipmr_q, (hipmr_acc)(@@MAP@@));
+    }
+    hipmr_q = hipmr_block_reduce<@@BLOCK@@>(hipmr_q, hipmr_neutral);
+)HIP";
+
 const char* kRedS2 = R"HIP(
 extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
 @@KNAME@@(const hipmr_acc* __restrict__ hipmr_partial, int hipmr_g,
@@ -933,39 +1012,34 @@ __device__ __forceinline__ void hipmr_comp_fold(const double* partial, int g, do
   hipmr_comp_end<B, NORM>(f, post, scale, out);
 }
 
-// The end of a one-pass sum or norm in one launch (partials by tag): the next
-// share to compute, or -1.
-struct hipmr_turn { hipmr_neumaier f; bool alone; };
+// The end of a sum or norm in its own launch (partials by tag), as hipmr_finish
+// and hipmr_add_share above.
 template <int B, bool NORM>
-__device__ __forceinline__ int hipmr_comp_finish(double v, unsigned long long* part, double post, double scale,
-                                                 unsigned long long tag, double* __restrict__ out, int b,
-                                                 hipmr_turn& h) {
+__device__ __forceinline__ bool hipmr_comp_finish(double v, unsigned long long* part, double post, double scale,
+                                                  unsigned long long tag, double* __restrict__ out) {
   const int g = (int)gridDim.x;
-  if (!h.alone) {
-    if (threadIdx.x == 0) hipmr_put_tagged(part, b, v, tag);
-    if ((int)blockIdx.x != g - 1) return -1;
-    h.f = {0.0, 0.0};
-    bool here = true;
-    for (int k = threadIdx.x; here && k < g; k += B) {
-      double p;
-      here = hipmr_get_tagged(part, k, tag, &p);
-      if (here) h.f.add(p);
-    }
-    if (__syncthreads_or(!here)) {
-      h.f = {0.0, 0.0};
-      h.alone = true;
-      return 0;
-    }
-  } else {
-    __shared__ double hipmr_share;
-    if (threadIdx.x == 0) hipmr_share = v;
-    __syncthreads();
-    if ((int)threadIdx.x == b % B) h.f.add(hipmr_share);
-    __syncthreads();
-    if (b + 1 < g) return b + 1;
+  if (threadIdx.x == 0) hipmr_put_tagged(part, (int)blockIdx.x, v, tag);
+  if ((int)blockIdx.x != g - 1) return false;
+  hipmr_neumaier f = {0.0, 0.0};
+  bool here = true;
+  for (int k = threadIdx.x; here && k < g; k += B) {
+    double p;
+    here = hipmr_get_tagged(part, k, tag, &p);
+    if (here) f.add(p);
   }
-  hipmr_comp_end<B, NORM>(h.f, post, scale, out);
-  return -1;
+  if (hipmr_any<B>(!here)) return true;
+  hipmr_comp_end<B, NORM>(f, post, scale, out);
+  return false;
+}
+template <int B, bool NORM>
+__device__ __forceinline__ void hipmr_comp_add_share(hipmr_neumaier& f, double v, double post, double scale,
+                                                     double* __restrict__ out, int b) {
+  __shared__ double hipmr_share;
+  if (threadIdx.x == 0) hipmr_share = v;
+  __syncthreads();
+  if ((int)threadIdx.x == b % B) f.add(hipmr_share);
+  __syncthreads();
+  if (b + 1 == (int)gridDim.x) hipmr_comp_end<B, NORM>(f, post, scale, out);
 }
 )HIP";
 
@@ -1091,7 +1165,6 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
     if (threadIdx.x == 0) hipmr_scale_p[blockIdx.x] = hipmr_m;
     if (threadIdx.x < 4 && gridDim.x <= @@WORDS_FOR@@) hipmr_words[blockIdx.x * 4 + threadIdx.x] = 0;
   }
-  @@END@@
 }
 )HIP";
 
@@ -1133,8 +1206,64 @@ extern "C" __global__ void __launch_bounds__(@@BLOCK@@)
     if (threadIdx.x == 0) hipmr_scale_p[blockIdx.x] = hipmr_m;
     if (threadIdx.x < 4 && gridDim.x <= @@WORDS_FOR@@) hipmr_words[blockIdx.x * 4 + threadIdx.x] = 0;
   }
-  @@END@@
 }
+)HIP";
+
+// Share hipmr_b of a compensated sum or norm, one chunk at a time.
+const char* kCompShare = R"HIP(
+    float hipmr_c[HIPMR_U], hipmr_d[HIPMR_U];
+#pragma unroll
+    for (int u = 0; u < HIPMR_U; ++u) { hipmr_c[u] = 0.0f; hipmr_d[u] = 0.0f; }
+    if (hipmr_b == 0) {
+      if ((long long)threadIdx.x < hipmr_h) {
+        const hipmr_idx i = (hipmr_idx)threadIdx.x;
+        hipmr_kahan_add(hipmr_c[0], hipmr_d[0], hipmr_term<HIPMR_SQ, HIPMR_TRACK>((float)(@@MAP@@), hipmr_sc, hipmr_m));
+      }
+      if ((long long)threadIdx.x < hipmr_n - hipmr_t0) {
+        const hipmr_idx i = (hipmr_idx)(hipmr_t0 + threadIdx.x);
+        hipmr_kahan_add(hipmr_c[0], hipmr_d[0], hipmr_term<HIPMR_SQ, HIPMR_TRACK>((float)(@@MAP@@), hipmr_sc, hipmr_m));
+      }
+    }
+    for (long long hipmr_at = (long long)hipmr_b * (HIPMR_B * HIPMR_U) + threadIdx.x; hipmr_at < hipmr_nc;
+         hipmr_at += hipmr_step) {
+      const bool hipmr_run_of_all = HIPMR_RUNS && hipmr_at + (HIPMR_U - 1) * HIPMR_B < hipmr_nc;
+      float hipmr_run = 0.0f;
+#pragma unroll
+      for (int hipmr_w = 0; hipmr_w < HIPMR_U; ++hipmr_w) {
+        if (hipmr_at + hipmr_w * HIPMR_B < hipmr_nc) {
+          const long long hipmr_off = hipmr_h + (hipmr_at + hipmr_w * HIPMR_B) * HIPMR_V;
+          constexpr int HIPMR_U = 1, hipmr_u = 0;
+          @@DECL_PACKS@@
+          @@LOADS@@
+          float hipmr_t[HIPMR_V];
+#pragma unroll
+          for (int hipmr_j = 0; hipmr_j < HIPMR_V; ++hipmr_j) {
+            const hipmr_idx i = (hipmr_idx)(hipmr_off + hipmr_j);
+            const float hipmr_x = (float)(@@VMAP@@);
+            if (hipmr_run_of_all) hipmr_run += hipmr_x;
+            hipmr_t[hipmr_j] = hipmr_term<HIPMR_SQ, HIPMR_TRACK>(hipmr_x, hipmr_sc, hipmr_m);
+          }
+          if (!hipmr_run_of_all) hipmr_kahan_add(hipmr_c[hipmr_w], hipmr_d[hipmr_w], hipmr_chunk_sum<HIPMR_V>(hipmr_t));
+        }
+      }
+      if (hipmr_run_of_all) hipmr_kahan_add(hipmr_c[0], hipmr_d[0], hipmr_run);
+    }
+    hipmr_ff hipmr_q = {hipmr_c[0], -hipmr_d[0]};
+#pragma unroll
+    for (int u = 1; u < HIPMR_U; ++u) hipmr_q = hipmr_ff_add(hipmr_q, hipmr_ff{hipmr_c[u], -hipmr_d[u]});
+)HIP";
+const char* kCompShareScalar = R"HIP(
+    float hipmr_c = 0.0f, hipmr_d = 0.0f;
+    for (long long hipmr_at = (long long)hipmr_b * @@BLOCK@@ + threadIdx.x; hipmr_at < hipmr_n; hipmr_at += hipmr_step) {
+      const hipmr_idx i = (hipmr_idx)hipmr_at;
+      hipmr_kahan_add(hipmr_c, hipmr_d, hipmr_term<HIPMR_SQ, HIPMR_TRACK>((float)(@@MAP@@), hipmr_sc, hipmr_m));
+    }
+    hipmr_ff hipmr_q = {hipmr_c, -hipmr_d};
+)HIP";
+const char* kCompShareEnd = R"HIP(
+    hipmr_q = hipmr_block_reduce_pair<@@BLOCK@@>(hipmr_q, [](hipmr_ff a, hipmr_ff b) { return hipmr_ff_add(a, b); });
+    const double hipmr_y = __builtin_isfinite(hipmr_q.hi) ? (double)hipmr_q.hi + (double)hipmr_q.lo : (double)hipmr_q.hi;
+    hipmr_comp_add_share<@@BLOCK@@, HIPMR_SQ>(hipmr_f, hipmr_y, hipmr_post, (double)hipmr_sc, hipmr_out, hipmr_b);
 )HIP";
 
 // Final fold of a compensated sum or a norm in a launch of its own; after two
@@ -1902,9 +2031,6 @@ Source render_parts(const Program& prog, const KernelSpec& spec) {
         }
         shift_init += bounds;
     }
-    replace_all(body, "@@SHIFT_INIT@@", shift_init);
-    replace_all(body, "@@SHIFT_PACKS@@", shift_packs);
-    replace_all(body, "@@SHIFT_LOADS@@", shift_loads);
 
     std::string scalar_text = join_tokens(prog.toks);
     std::string vector_text = scan_scalar ? scalar_text
@@ -1916,22 +2042,30 @@ Source render_parts(const Program& prog, const KernelSpec& spec) {
     }
     replace_all(body, "@@VMAPX@@", vector_text);
     replace_all(body, "@@MODE@@", std::to_string(spec.scan_mode));
-    // a kernel that finishes computes its share in a loop (its last block may have to compute them all)
-    replace_all(body, "@@SHARES@@",
-                spec.finish ? "hipmr_turn hipmr_f; hipmr_f.alone = false;\n  for (int hipmr_b = (int)blockIdx.x;;) {"
-                            : "const unsigned hipmr_b = blockIdx.x;");
-    if (comp) {
-        replace_all(body, "@@FINISH@@",
-                    spec.finish ? "hipmr_b = hipmr_comp_finish<@@BLOCK@@, HIPMR_SQ>(hipmr_v, hipmr_words, "
-                                  "hipmr_post, (double)hipmr_sc, hipmr_tag, hipmr_out, hipmr_b, hipmr_f);\n    if (hipmr_b < 0) return;"
-                                : "if (threadIdx.x == 0) hipmr_partial[blockIdx.x] = hipmr_v;");
-        replace_all(body, "@@END@@", spec.finish ? "}" : "");
-    } else {
-        replace_all(body, "@@FINISH@@",
-                    spec.finish ? "hipmr_b = hipmr_finish<@@BLOCK@@>(hipmr_r, hipmr_neutral, (unsigned long long*)hipmr_partial, "
-                                  "hipmr_out, hipmr_tag, hipmr_b, hipmr_f);\n  if (hipmr_b < 0) return;\n  }"
-                                : "if (threadIdx.x == 0) hipmr_partial[blockIdx.x] = hipmr_r;");
+    replace_all(body, "@@SHARES@@", "const unsigned hipmr_b = blockIdx.x;");
+    std::string finish = std::string("if (threadIdx.x == 0) hipmr_partial[blockIdx.x] = ") +
+                         (comp ? "hipmr_v;" : "hipmr_r;");
+    if (spec.finish) {
+        const bool vector = spec.kind == KernelKind::RedS1Vector || spec.kind == KernelKind::CompS1Vector;
+        const std::string loop = "#pragma clang loop unroll(disable)\n"
+                                 "  for (int hipmr_b = 0; hipmr_b < (int)gridDim.x; ++hipmr_b) {";
+        if (comp) {
+            finish = "if (!hipmr_comp_finish<@@BLOCK@@, HIPMR_SQ>(hipmr_v, hipmr_words, hipmr_post, (double)hipmr_sc, "
+                     "hipmr_tag, hipmr_out)) return;\n  hipmr_neumaier hipmr_f = {0.0, 0.0};\n" + loop +
+                     (vector ? kCompShare : kCompShareScalar) + kCompShareEnd + "  }";
+        } else {
+            finish = "if (!hipmr_finish<@@BLOCK@@>(hipmr_r, hipmr_neutral, (unsigned long long*)hipmr_partial, "
+                     "hipmr_out, hipmr_tag)) return;\n  hipmr_acc hipmr_f = hipmr_neutral;\n" + loop +
+                     (vector ? kRedShare : kRedShareScalar) +
+                     "    hipmr_add_share<@@BLOCK@@>(hipmr_f, hipmr_q, hipmr_neutral, hipmr_out, hipmr_b);\n  }";
+            replace_all(finish, "@@SHARE_CHUNK@@", shifts ? kRedShareChunkShift : kRedShareChunk);
+            replace_all(finish, "@@SHARE_BLOCK@@", shifts ? "hipmr_xcd_block(hipmr_b)" : "hipmr_b");
+        }
     }
+    replace_all(body, "@@FINISH@@", finish);
+    replace_all(body, "@@SHIFT_INIT@@", shift_init);
+    replace_all(body, "@@SHIFT_PACKS@@", shift_packs);
+    replace_all(body, "@@SHIFT_LOADS@@", shift_loads);
     replace_all(body, "@@ONE@@", spec.finish ? "true" : "false");
     replace_all(body, "@@FPARAMS@@",
                 spec.finish ? ", hipmr_acc* __restrict__ hipmr_out, unsigned long long hipmr_tag" : "");
