@@ -514,7 +514,7 @@ def workspace(nbytes, device, stream_ptr):
             left = next((k for k in _ws_cache if k[:2] == key[:2] and k[2] not in alive), None)
             if left is not None:
                 buf = _ws_cache[left]
-                for k in [k for k in _ws_cache if k[1:] == left[1:]]:      # under any name of the device
+                for k in [k for k, v in _ws_cache.items() if v is buf]:     # under any name of the device
                     del _ws_cache[k]
                 _ws_cache[key] = buf
         if buf is None or buf.numel() < nbytes:

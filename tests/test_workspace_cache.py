@@ -52,3 +52,15 @@ def test_a_workspace_taken_over_has_one_owner():
     buf = hipmr.workspace(1000, torch.device("cpu"), 0x54)
     owners = {k[2] for k, v in hipmr._ws_cache.items() if v is buf}
     assert owners == {threading.get_ident()}
+
+
+def test_taking_over_leaves_other_devices_alone():
+    """Streams of two devices may have the same number (0)."""
+    t = threading.Thread(target=lambda: (hipmr.workspace(1000, "cpu", 0x55), hipmr.workspace(1000, "meta", 0x55)))
+    t.start()
+    t.join()
+    ident = t.ident
+    other = hipmr._ws_cache[("meta", 0x55, ident)]
+    if threading.get_ident() != ident:
+        hipmr.workspace(1000, "cpu", 0x55)
+        assert hipmr._ws_cache[("meta", 0x55, ident)] is other
