@@ -64,7 +64,8 @@ class PoissonCG:
         nbytes = _hm.lib().hipmr_poisson_cg_workspace_bytes(self.nx, self.ny)
         self._ws = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=dev)
         if stream is not None and self._ws.is_cuda:   # a run may outlive the solver on that stream
-            on = torch.cuda.ExternalStream(stream, self._ws.device) if isinstance(stream, int) else stream
+            on = stream if isinstance(stream, torch.cuda.Stream) else \
+                torch.cuda.ExternalStream(_hm._stream_ptr(stream), self._ws.device)
             for t in (self.x, self.r, self.p, self.q, self.s, self._ws):
                 t.record_stream(on)
 

@@ -3,6 +3,7 @@ captured before it has run, where another size has."""
 
 import subprocess
 import sys
+import types
 
 import pytest
 
@@ -12,8 +13,10 @@ from paper_1304_5553_amd.cg import PoissonCG
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("as_int", [False, True])
-def test_arrays_stay_until_the_run_ends(as_int):
+@pytest.mark.parametrize("given", ["stream", "number", "object"])
+def test_arrays_stay_until_the_run_ends(given):
+    """The stream in each form the binding takes: torch's, its handle, or
+    whatever holds that as cuda_stream."""
     dev = need_gpu()
     nx = 1024
     st = torch.cuda.Stream()
@@ -24,7 +27,8 @@ def test_arrays_stay_until_the_run_ends(as_int):
     torch.cuda.synchronize()
     want = want.clone()
     for _ in range(5):
-        x = PoissonCG(nx, nx, stream=st.cuda_stream if as_int else st).solve(b, 100)
+        on = {"stream": st, "number": st.cuda_stream, "object": types.SimpleNamespace(cuda_stream=st.cuda_stream)}[given]
+        x = PoissonCG(nx, nx, stream=on).solve(b, 100)
         junk = [torch.full((nx * nx,), float("nan"), device=dev) for _ in range(12)]
         torch.cuda.synchronize()
         assert torch.equal(x, want)
