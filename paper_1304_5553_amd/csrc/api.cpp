@@ -451,20 +451,26 @@ struct Stage1 {
     bool whole = false;          // the launch folded its partials itself
 };
 
+// The kernel of a stage for these arguments; the chunks' first element or -1.
+long long stage1_spec(const hipmr_kernel* h, int64_t n, void* const* args, LaunchCfg* cfg, KernelSpec* spec) {
+    const long long head = vector_head(h, args, cfg);
+    spec->unaligned = cfg->unaligned;
+    if (head < 0) {
+        spec->kind = KernelKind::CompS1Scalar;
+        spec->vec = 1;
+        spec->exact_runs = false;
+    }
+    spec->idx64 = n >= (int64_t(1) << 31);
+    return head;
+}
+
 // `fold`: the kernel that would finish the call, where the stage may do so
 // itself (a default geometry, and no capture that could repeat its tag).
 hipmr_status stage1_launch(hipmr_kernel* h, KernelSpec spec, LaunchCfg cfg,
                            int64_t n, void* const* args, void* partial, void* amax, double post, void* out_p,
                            const KernelSpec* fold, void* stream, CallKernels* used, Stage1* out) {
-    const long long head = vector_head(h, args, &cfg);
+    const long long head = stage1_spec(h, n, args, &cfg, &spec);
     const bool vector = head >= 0;
-    spec.unaligned = cfg.unaligned;
-    if (!vector) {
-        spec.kind = KernelKind::CompS1Scalar;
-        spec.vec = 1;
-        spec.exact_runs = false;
-    }
-    spec.idx64 = n >= (int64_t(1) << 31);
     long long n64 = n, head64 = vector ? head : 0;
     long long units = vector ? (n64 > head64 ? (n64 - head64) / cfg.vec : 0) : n64;
     out->grid = n > 0 ? grid_for(units, cfg.block * (vector ? cfg.ipt : 1), cfg, kMaxPartials) : 0;
@@ -583,10 +589,33 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
     void* amax = (char*)workspace + kAmaxOffset;
     CallKernels used;
     const bool two = passes == 2 && n > 0;     // an empty norm is 0 either way
+    KernelSpec q2 = comp_spec(KernelKind::CompS2, cfg);
+    q2.block = kStage2Block;
+    q2.ipt = q2.vec = 1;
+    q2.norm = true;
+    q2.scaled = two;
     if (two) {
         // pass 1: sum of the unscaled squares and max |map|, per block
         KernelSpec a1 = comp_spec(KernelKind::CompS1Vector, cfg);
         a1.square = a1.track = true;
+        LaunchCfg c = cfg;
+        KernelSpec s1 = a1;
+        const bool vector = stage1_spec(h, n, args, &c, &s1) >= 0;
+        // a geometry of the call's own may give grids on both sides of what the
+        // second pass folds itself: the kernels of both are loaded
+        const bool own = own_shape(cfgp);
+        if (own || !find_variant(h, s1)) {
+            st = load_family(h, own ? 'N' : 'n', vector, s1.idx64, c, "", "", [&] {
+                KernelSpec q = s1;
+                q.track = false;
+                q.scaled = q.finish = true;
+                std::vector<KernelSpec> v = {s1, q};
+                q.finish = false;
+                if (own) v.insert(v.end(), {q, q2});
+                return v;
+            });
+            if (st != HIPMR_OK) return st;
+        }
         Stage1 r1;
         st = stage1_launch(h, a1, cfg, n, args, workspace, amax, post_scale, out, nullptr, stream, &used, &r1);
         if (st != HIPMR_OK) return st;
@@ -598,11 +627,6 @@ hipmr_status hipmr_norm2(hipmr_handle h, int64_t n, void* const* args, double po
     KernelSpec q1 = comp_spec(KernelKind::CompS1Vector, cfg);
     q1.square = true;
     q1.scaled = two;
-    KernelSpec q2 = comp_spec(KernelKind::CompS2, cfg);
-    q2.block = kStage2Block;
-    q2.ipt = q2.vec = 1;
-    q2.norm = true;
-    q2.scaled = two;
     Stage1 r2;
     st = stage1_launch(h, q1, cfg, n, args, workspace, amax, post_scale, out,
                        two || own_shape(cfgp) ? nullptr : &q2, stream, &used, &r2);

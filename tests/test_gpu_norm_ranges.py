@@ -126,3 +126,28 @@ def test_magnitudes_far_below_the_largest(top, span):
     k = hm.compile("x[i]", "float: const float *x")
     o = oracle.norm2(x.astype(np.float64))
     assert abs(hm.norm2(k, n, [dev_array(x)]).item() - o) <= 1e-6 * o
+
+
+@pytest.mark.parametrize("first,then", [(5000, 1 << 20), (1 << 20, 5000)])
+def test_capture_across_the_grids(first, then):
+    """A geometry whose grid is above 1024 blocks for one size and below for
+    the other: after a run at one, a capture of the other finds its kernels."""
+    dev = need_gpu()
+    cfg = {"block": 64, "blocks_per_cu": 32}
+    base = np.random.default_rng(11).uniform(0.5, 1.0, 1 << 20).astype(np.float32)
+    k = hm.compile("x[i]", "float: const float *x", name=f"normcap{first}")
+    x, out = dev_array(base), torch.empty((), dtype=torch.float64, device=dev)
+    ws = torch.empty(hm.reduce_workspace_bytes(k, 1 << 20), dtype=torch.uint8, device=dev)
+    st = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    hm.norm2(k, first, [x], out=out, workspace_buf=ws, stream=st, config=cfg)
+    g = hm.Graph()
+    with g.capture(st):
+        hm.norm2(k, then, [x], out=out, workspace_buf=ws, stream=st, config=cfg)
+    for e in (0, 60, 0):
+        x.copy_(torch.from_numpy((base * np.float32(2.0) ** e).astype(np.float32)))
+        torch.cuda.synchronize()
+        g.launch(st)
+        torch.cuda.synchronize()
+        o = oracle.norm2(base[:then].astype(np.float64)) * 2.0 ** e
+        assert abs(out.item() - o) <= 1e-6 * o
